@@ -14,8 +14,11 @@
 // either k-contiguous in memory (KC) or r-contiguous (!KC); no transposed copy
 // of any tensor is ever materialised.
 //
-// Structure of a workgroup (bf16: 8 waves, 2 x 4, two per SIMD; fp32: 4 waves, 2 x 2;
-// one persistent workgroup per CU):
+// Two kernels: a large-tile one for bf16 (below) and one with smaller tiles for everything
+// else (its own comment says what for); launch_gemm chooses by the number of tiles.
+//
+// Structure of a large-tile workgroup (8 waves, 2 x 4, two per SIMD; one persistent
+// workgroup per CU):
 //   * walks BM x BN output tiles.  Only tiles that hold rows exist; the expert-major
 //     tile sequence is dealt block-cyclically, a block of as many consecutive tiles
 //     as an XCD has workgroups going to one XCD (workgroup w runs on XCD w % 8), so
@@ -35,8 +38,7 @@
 //     supplies the zero fill for rows >= n_e, so the loop has no branches.  LDS tiles
 //     are unpadded and XOR-swizzled in 16-byte units (fragment reads are free of bank
 //     conflicts);
-//   * each wave accumulates (BM/2) x (BN/NWN) in 32x32 MFMA tiles
-//     (bf16: v_mfma_f32_32x32x16_bf16, fp32: v_mfma_f32_32x32x2_f32); !KC bf16
+//   * each wave accumulates (BM/2) x (BN/NWN) in 32x32 MFMA tiles; !KC
 //     operands are read from LDS with the transposing ds_read_b64_tr_b16.  A wave
 //     issues strictly in order and an MFMA holds it for the MFMA's 32 cycles, so the
 //     matrix pipe is kept busy by the SIMD's other wave; loads and fragment reads are
@@ -47,21 +49,14 @@
 //     rolled loop), and the backward epilogue only multiplies by the saved
 //     derivative, which it fetched into registers before the main loop;
 //   * the backward's four products run as two launches of two independent products
-//     each (dz with dW2, dxd with dW1): a workgroup walks its tiles of the first,
-//     then of the second.
+//     each (dz with dW2, dxd with dW1): one walk over the tiles of the first, then of
+//     the second (6 experts of 1440 rows, d = 776, f = 3080: 174 -> 143 us for the second
+//     pair against two walks that both start at the first workgroup).
 #include <math.h>
 #include "moe_common.h"
 
-// bf16 tile shape (tuning knobs; the defaults are the shipped configuration)
-#ifndef MOE_GEMM_BM
-#define MOE_GEMM_BM 256
-#endif
-#ifndef MOE_GEMM_BN
-#define MOE_GEMM_BN 256
-#endif
-#ifndef MOE_GEMM_BK
-#define MOE_GEMM_BK 64
-#endif
+// the large bf16 tile: rows, columns, slab depth, wavefronts along N
+enum { BIG_M = 256, BIG_N = 256, BIG_K = 64, BIG_WN = 4 };
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -97,15 +92,6 @@ template <> struct Mma<bf16_t> {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
     }
 };
-template <> struct Mma<float> {
-    static constexpr int FE = 1;
-    static constexpr int KSTEP = 2;
-    typedef float frag;
-    __device__ static __forceinline__ f32x16_t mma(frag a, frag b, f32x16_t c) {
-        return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-    }
-};
-
 #define OOB_OFFSET 0x80000000u  // beyond any descriptor this kernel builds (slices < 2 GiB)
 
 // LDS tile of one operand: BR rows (r) x BK reduction entries, unpadded, as
@@ -124,11 +110,13 @@ template <typename T, int BR, int BK, bool KC, int NT> struct Tile {
     static constexpr int PER_THREAD = SLOTS / NT;
     static constexpr int BYTES = SLOTS * 16;
     static constexpr int WIN = CPR >= 16 ? 1 : 16 / CPR;     // rows per 256-byte window
+    static constexpr bool IS_KC = KC;
     static_assert(SLOTS % NT == 0, "tile must be a multiple of the workgroup size in slots");
     static_assert((CPR & (CPR - 1)) == 0, "slots per row must be a power of two");
 
     __device__ static __forceinline__ int swz(int row) {
-        return KC ? (row / WIN) & (CPR - 1) : ((row & 3) << 2) & (CPR - 1);
+        if (KC) return (row / WIN) & (CPR - 1);
+        return CPR >= 16 ? ((row & 3) << 2) : ((row >> 1 & 1) << 2) & (CPR - 1);
     }
 
     // Per-thread load plan: byte offset of each of its slots at reduction offset 0
@@ -206,22 +194,14 @@ template <typename T, int BR, int BK, bool KC, int NT> struct Tile {
                 const s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 return __builtin_bit_cast(bf16x8_t, v);
             }
-        } else {
-            if constexpr (KC) {
-                const int row = rbase + l32;
-                const int slot = row * CPR + ((k / CN) ^ swz(row));
-                return *reinterpret_cast<const float*>(s + slot * 16 + (k % CN) * 4);
-            } else {
-                const int col = rbase + l32;
-                const int slot = k * CPR + ((col / CN) ^ swz(k));
-                return *reinterpret_cast<const float*>(s + slot * 16 + (col % CN) * 4);
-            }
         }
     }
 };
 
 // ---- activation in the forward epilogue ---------------------------------------
-// h = act(z) and a = act'(z) together.  fp32 tensors use the accurate erff/expf.
+// h = act(z) and a = act'(z) together.  fp32 tensors: see below; absolute error of the
+// normal cdf 1.3e-7 at most, 1.3e-8 in the mean (erff: 6e-8, 1.4e-8), relative error of its
+// left tail 1.5e-6 where 1 + erf cancels; 29 instructions against about 100.
 // bf16 tensors (8 significant bits) use the three-term rational erfc of Abramowitz &
 // Stegun 7.1.25 (absolute error of the normal cdf below 1.1e-5, i.e. 1/350 of a bf16
 // rounding step at 1) with one exponential shared with the density and all scale
@@ -236,8 +216,15 @@ __device__ __forceinline__ void act_both(float z, float& h, float& a) {
     }
     float cdf, zpdf;
     if constexpr (!FAST) {
-        cdf = 0.5f * (1.0f + erff(z * 0.70710678118654752440f));
-        zpdf = z * 0.39894228040143267794f * expf(-0.5f * z * z);
+        // Phi(-t) = phi(t) M(t) with Mills' ratio M as a (4,5) rational function of t <= 12 (beyond, phi is 0 at
+        // fp32's scale for every purpose here)
+        const float t = fminf(fabsf(z), 12.0f);
+        const float pdf = __builtin_amdgcn_exp2f(fmaf(z * z, -0.72134752044448170368f, -1.32574806473615920f));
+        const float num = fmaf(fmaf(fmaf(fmaf(0.00978147704f, t, 0.0982103422f), t, 0.448447645f), t, 1.08389807f), t, 1.25331414f);
+        const float den = fmaf(fmaf(fmaf(fmaf(fmaf(0.00978129916f, t, 0.0982190296f), t, 0.458042532f), t, 1.18445694f), t, 1.66271043f), t, 1.0f);
+        const float q = num * __builtin_amdgcn_rcpf(den) * pdf;
+        cdf = z >= 0.0f ? 1.0f - q : q;
+        zpdf = z * pdf;
     } else {
         // phi(z) = exp2(-z^2 log2(e)/2 - log2 sqrt(2 pi));  t = 1 / (1 + 0.47047 |z| / sqrt 2)
         const float pdf = __builtin_amdgcn_exp2f(fmaf(z * z, -0.72134752044448170368f, -1.32574806473615920f));
@@ -304,11 +291,8 @@ struct GemmSmem {
     typedef Tile<T, BM, BK, A_KC, NT> TA;
     typedef Tile<T, BN, BK, B_KC, NT> TB;
     static constexpr int STAGE = TA::BYTES + TB::BYTES;
-#ifndef MOE_GEMM_NS
-#define MOE_GEMM_NS 0
-#endif
     // LDS ring: 1 slab being multiplied + NSTAGE-1 in flight (as many as fit beside the epilogue strips)
-    static constexpr int NSTAGE = MOE_GEMM_NS ? MOE_GEMM_NS : (STAGE > 48 * 1024 ? 2 : (STAGE > 32 * 1024 ? 3 : 4));
+    static constexpr int NSTAGE = 2;
     static constexpr int EPI_LD = BN / NWN + 8; // floats per staged epilogue row (4 rows apart -> other bank half)
     static constexpr int EPI_ROWS = 8;          // one accumulator register quad of both lane halves
     static constexpr size_t RING = (size_t)NSTAGE * STAGE;
@@ -332,8 +316,8 @@ struct GemmSmem {
 // heavily loaded expert (long reductions in the weight-gradient GEMMs) are spread
 // over all workgroups instead of piling up on one XCD.
 #define WALK_BAND 4                     // row tiles per band of the walk inside an expert
-#define WALK_SLOTS 257                  // experts + 1
-#define WALK_BYTES (WALK_SLOTS * 4 + 12)
+#define WALK_CNT 260                    // the experts' row counts follow the 257 running tile counts
+#define WALK_BYTES ((WALK_CNT + 256) * 4)
 template <int BM, int BN>
 struct TileWalk {
     const int* tp;          // LDS: tiles before expert e (tp[256] = all tiles)
@@ -352,6 +336,7 @@ struct TileWalk {
                 const int ex = 4 * lane + i;
                 int n = ex < p.E ? p.expert_count[ex] : 0;
                 n = max(0, min(n, p.var_k ? p.K : p.M));
+                tpw[WALK_CNT + ex] = n;
                 const int tm = ex >= p.E ? 0 : (p.var_k ? p.tiles_m : (n + BM - 1) / BM);
                 a[i] = tm * p.tiles_n;
                 sa += a[i];
@@ -372,23 +357,38 @@ struct TileWalk {
         }
         __syncthreads();
     }
-    __device__ __forceinline__ void start(const GemmArgs& p, const unsigned char* lds) {
+    // `more` = tiles of the launch's later product.  A grid larger than the number of tiles still
+    // spreads them over all XCDs.
+    __device__ __forceinline__ void start(const GemmArgs& p, const unsigned char* lds, int more) {
         tp = reinterpret_cast<const int*>(lds);
-        const int S = gridDim.x >> 3;
-        step = 8 * S;
-        t = (int)(blockIdx.x & 7) * S + (int)(blockIdx.x >> 3) - step;
         t_end = __builtin_amdgcn_readfirstlane(tp[256]);
-        e = 0;
+        const int S = min((int)(gridDim.x >> 3), (t_end + more + 7) / 8);
+        const int i = (int)(blockIdx.x >> 3);
+        step = 8 * S;
+        t = i < S ? (int)(blockIdx.x & 7) * S + i - step : t_end + more;
+    }
+    // The walk over the launch's second product goes on where the first one's ended: `u` is that
+    // walk's place after its last next().
+    struct Where { int t, step; };
+    __device__ __forceinline__ Where where() const { return {t - t_end, step}; }
+    __device__ __forceinline__ void resume(Where u, const unsigned char* lds) {
+        tp = reinterpret_cast<const int*>(lds);
+        t_end = __builtin_amdgcn_readfirstlane(tp[256]);
+        step = u.step;
+        t = u.t - step;
     }
     // moves to the workgroup's next tile; false when the walk is over
     __device__ __forceinline__ bool next(const GemmArgs& p) {
         t += step;
         if (t >= t_end) return false;
-        while (t >= tp[e + 1]) ++e;          // t < tp[256]: stops at an expert that has tiles
+        // the expert that owns tile t: as many experts end at or before it (t < tp[256])
+        e = 0;
+        for (int c = 0; c < p.E; c += 64) e += __popcll(__ballot(tp[c + (threadIdx.x & 63) + 1] <= t));
         // everything here is the same in every lane; keep it in scalar registers
         e = __builtin_amdgcn_readfirstlane(e);
         const int first = __builtin_amdgcn_readfirstlane(tp[e]);
         const int count = __builtin_amdgcn_readfirstlane(tp[e + 1]) - first;
+        const int n_e = __builtin_amdgcn_readfirstlane(tp[WALK_CNT + e]);
         const int rem = t - first;
         const int tm_e = count / p.tiles_n;   // row tiles of this expert
         // Inside an expert the tiles are taken band by band: a band is WALK_BAND row tiles high
@@ -404,7 +404,6 @@ struct TileWalk {
             tn = r / rows;
             tm = band * WALK_BAND + (r - tn * rows);
         }
-        const int n_e = max(0, min(p.expert_count[e], p.var_k ? p.K : p.M));
         m0 = tm * BM; n0 = tn * BN;
         m_lim = p.var_k ? p.M : n_e;
         k_lim = p.var_k ? n_e : p.K;
@@ -417,7 +416,7 @@ struct TileWalk {
 // are already resident when the epilogue of the current one ends, and no
 // workgroup launch or cold first load sits between two tiles.
 template <typename T, int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI, int ACT, int NWN, bool KG>
-__device__ __forceinline__ void gemm_body(const GemmArgs& p) {
+__device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const GemmArgs& p, int more, typename TileWalk<BM, BN>::Where before) {
     typedef GemmSmem<T, BM, BN, BK, A_KC, B_KC, NWN> SM;
     typedef typename SM::TA TA;
     typedef typename SM::TB TB;
@@ -447,7 +446,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p) {
     unsigned char* walk_lds = smem_raw + SM::BYTES;
     TileWalk<BM, BN>::build(p, walk_lds);
     TileWalk<BM, BN> pw;       // tile whose slabs are being requested
-    pw.start(p, walk_lds);
+    if (more < 0) pw.resume(before, walk_lds); else pw.start(p, walk_lds, more);
     bool p_more = pw.next(p);
     int p_kt = 0, p_nk = 0;
     u32x4_t dsA = {0, 0, 0, 0}, dsB = {0, 0, 0, 0};
@@ -502,16 +501,13 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p) {
 
     // ---- consumer ---------------------------------------------------------------
     TileWalk<BM, BN> cw;
-    cw.start(p, walk_lds);
-    if (!cw.next(p)) return;       // nothing to do for this workgroup (uniform)
+    if (more < 0) cw.resume(before, walk_lds); else cw.start(p, walk_lds, more);
+    if (!cw.next(p)) return cw.where();    // nothing to do for this workgroup (uniform)
 #pragma unroll
     for (int s = 0; s < NS; ++s) produce(s);
     // slab 0 of the stream has landed once at most the NS-1 younger slabs are outstanding
     wait_vmcnt<(NS - 1) * SM::LOADS>();
     __syncthreads();
-#ifndef MOE_GEMM_BEARLY
-#define MOE_GEMM_BEARLY 1
-#endif
     // Two-stage ring with four k-steps per slab (the bf16 tiles): the B half of a stage is released
     // early.  A wave needs few B fragments (TN per k-step), so it reads those of all four k-steps
     // during the slab's first step; one barrier later nobody reads the B half again and it is
@@ -520,10 +516,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p) {
     // to arrive instead of one.
     // (not in the instance whose epilogue keeps saved-derivative rows in registers through the
     // main loop: the extra fragment registers would spill there)
-#ifndef MOE_GEMM_DZ_BEARLY
-#define MOE_GEMM_DZ_BEARLY 0
-#endif
-    constexpr bool BEARLY = MOE_GEMM_BEARLY && NS == 2 && KS == 4 && (EPI != EPI_MUL || MOE_GEMM_DZ_BEARLY);
+    constexpr bool BEARLY = NS == 2 && KS == 4 && EPI != EPI_MUL;
     typename Mma<T>::frag fa[2][TM], fb[BEARLY ? KS : 2][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) fa[0][i] = TA::frag(smem_raw, wm * (BM / 2) + i * 32, 0, lane);
@@ -531,8 +524,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p) {
     for (int j = 0; j < TN; ++j) fb[0][j] = TB::frag(smem_raw + TA::BYTES, wn * WCOLS + j * 32, 0, lane);
     int stage = 0;
 
-    bool more = true;
-    while (more) {
+    bool again = true;
+    while (again) {
         const int nk = (cw.k_lim + BK - 1) / BK;
         const size_t obase = (size_t)cw.e * p.strideO;
         const int ncol = cw.n0 + wn * WCOLS + ec;
@@ -542,10 +535,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p) {
         // EPI_MUL: the saved derivative does not depend on the product.  The rows of
         // the first two 32-row blocks are requested now and ride in registers through
         // the main loop; the later blocks are requested while earlier ones are written.
-#ifndef MOE_GEMM_AUXB
-#define MOE_GEMM_AUXB 2
-#endif
-        constexpr int AUXB = EPI == EPI_MUL ? (TM < MOE_GEMM_AUXB ? TM : MOE_GEMM_AUXB) : 1;
+        constexpr int AUXB = EPI == EPI_MUL ? 2 : 1;
         raw aux[AUXB][EPI == EPI_MUL ? 4 : 1][EPI == EPI_MUL ? NIT : 1];
         constexpr uint32_t OSZ = EPI == EPI_F32 ? 4u : (uint32_t)sizeof(T);   // bytes per output element
         const size_t obytes = (size_t)m_lim * p.ldo * OSZ;                    // the expert's rows in use
@@ -739,6 +729,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p) {
         // back (into the other register set) before the vectors of strip s are used:
         // the LDS round trip of every strip hides behind the previous strip's work.
         constexpr int NSTRIP = 4 * TM;
+        const int rows_left = __builtin_amdgcn_readfirstlane(m_lim - cw.m0 - wm * (BM / 2));
         auto write_strip = [&](int s_) {
             const int i = s_ >> 2, q = s_ & 3;
 #pragma unroll
@@ -758,6 +749,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p) {
         for (int s_ = 0; s_ < NSTRIP; ++s_) {
             const int i = s_ >> 2, q = s_ & 3;
             const int m_strip = mrow + i * 32 + q * 8;
+            if (ROLLED && q == 0 && i * 32 >= rows_left) break;      // no row in use from here on (uniform)
             if constexpr (ROLLED) {
                 // one copy of the activation code per strip; the next vector is read from
                 // LDS before the current one is worked on (carried in registers, no arrays)
@@ -790,16 +782,17 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p) {
                 if (q == 3 && i + AUXB < TM) fetch_aux(i % AUXB, i + AUXB);   // the buffer just used is free again
             }
         }
-        more = cw.next(p);
+        again = cw.next(p);
     }
     // the zero-fill loads requested past the end of the stream target this
     // workgroup's LDS: wait for them before the workgroup retires
     wait_vmcnt<0>();
+    return cw.where();
 }
 
 template <typename T, int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI, int ACT, int NWN, bool KG>
 __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_kernel(const GemmArgs p) {   // two waves per SIMD: at most 256 registers
-    gemm_body<T, BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, KG>(p);
+    gemm_body<T, BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, KG>(p, 0, {0, 0});
 }
 
 // Two independent grouped GEMMs in one launch: every workgroup walks its tiles of the
@@ -809,9 +802,387 @@ __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_kernel(const GemmAr
 // workgroups drift apart, which spreads the store bursts of their epilogues.
 template <typename T, int BM, int BN, int BK, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2, int NWN, bool KG>
 __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_pair_kernel(const GemmArgs p1, const GemmArgs p2) {
-    gemm_body<T, BM, BN, BK, A1, B1, EPI1, 0, NWN, KG>(p1);
+    const typename TileWalk<BM, BN>::Where w = gemm_body<T, BM, BN, BK, A1, B1, EPI1, 0, NWN, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0});
     __syncthreads();      // every wave is done with the ring and the tile table of the first product
-    gemm_body<T, BM, BN, BK, A2, B2, EPI2, 0, NWN, KG>(p2);
+    gemm_body<T, BM, BN, BK, A2, B2, EPI2, 0, NWN, KG>(p2, -1, w);
+}
+
+// ---------------------------------------------------------------------------
+// The same products on smaller tiles (64 x 64 or 128 x 128, 2 x 2 waves), several
+// workgroups per CU: for problems that give the large tile too few workgroups, for
+// experts with few rows (then the weights' stream from HBM is the bound and the
+// other workgroups of a CU keep requests in flight while one is in its prologue or
+// epilogue), and for all fp32 tensors.
+//
+// bf16: slabs of 64 through an NS-stage LDS ring, filled by loads that write LDS
+// directly; one barrier per slab.
+//
+// fp32 on the bf16 matrix pipe: every fp32 value is split into three bf16 parts
+// rounded to nearest, hi + mid + lo = value exactly (8 significant bits each and the
+// signs of the residuals), and a product is the six partial products of weight
+// above 2^-26; each is exact in fp32 and all are summed in fp32 by the MFMAs.  The
+// parts left out are below a quarter of the rounding error of one fp32 product.  Six
+// v_mfma_f32_32x32x16_bf16 (32 cycles each) replace eight v_mfma_f32_32x32x2_f32 (64
+// cycles each); results are nearer to the exact ones than the fp32 pipe's (relative
+// error of yd at d = 512, f = 2048: 3e-7 against 9e-7).  A slab is split once per
+// workgroup on its way from registers to LDS, under the MFMAs of the slab before;
+// about as much vector work as matrix work, which is what bounds it (T = 4096,
+// d = 512, f = 2048, E = 8, top-2, the four launches: 1003 -> 560 us).  An infinite
+// operand gives a non-finite result, not always the same one as the fp32 pipe.
+//
+// The products are computed with the operands exchanged (D^T), so that a lane holds four
+// consecutive columns of one output row: the epilogue's LDS strip is written and read
+// in 16-byte vectors.
+// ---------------------------------------------------------------------------
+// KW: groups of four waves that share a tile, each taking its part of every slab's k-steps (fp32)
+template <typename T, int BM, int BN, int KW, int NS, bool A_KC, bool B_KC>
+struct MidSmem {
+    static constexpr bool SPLIT = sizeof(T) == 4;
+    static constexpr int NT = 256 * KW;
+    static constexpr int BK = (SPLIT ? (BM < 128 || BN < 128 ? 32 : 16) : 64) * KW;
+    static constexpr int NP = SPLIT ? 3 : 1;               // bf16 planes per operand
+    typedef Tile<bf16_t, BM, BK, A_KC, NT> TA;
+    typedef Tile<bf16_t, BN, BK, B_KC, NT> TB;
+    static constexpr int STAGE = NP * (TA::BYTES + TB::BYTES);
+    static_assert(NS >= 2 && (!SPLIT || NS == 2) && (SPLIT || KW == 1), "ring depth and wave groups per path");
+    static constexpr int REDUCE = (KW - 1) * BM * BN * 4;
+    static constexpr int LOADS = TA::PER_THREAD + TB::PER_THREAD;
+    static constexpr int STRIP_LD = BN / 2 + 4;
+    static constexpr int STRIPS = 4 * 32 * STRIP_LD * 4;   // the epilogue's strips lie over the ring
+    static constexpr int RING = NS * STAGE;
+    static constexpr int BYTES = RING > STRIPS ? (RING > REDUCE ? RING : REDUCE) : (STRIPS > REDUCE ? STRIPS : REDUCE);
+    // workgroups per CU: what LDS holds, and registers (the fp32 form needs about 180 at 128 x 128)
+    static constexpr int FIT = 160 * 1024 / (BYTES + WALK_BYTES);
+    static constexpr int OCC = FIT >= 3 && !(SPLIT && BM * BN > 8192) ? 3 : (FIT >= 2 ? 2 : 1);
+};
+
+// 8 fp32 of one tile chunk -> three bf16 planes, rounded to nearest at every step: hi + mid + lo = w exactly
+__device__ __forceinline__ void split3_rne(const u32x4_t (&w)[2], u32x4_t& hi, u32x4_t& mid, u32x4_t& lo) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = __uint_as_float(w[i >> 1][2 * (i & 1)]), b = __uint_as_float(w[i >> 1][2 * (i & 1) + 1]);
+        const uint32_t h = pack_bf16x2(a, b);
+        const float a1 = a - __uint_as_float(h << 16), b1 = b - __uint_as_float(h & 0xffff0000u);
+        const uint32_t m = pack_bf16x2(a1, b1);
+        lo[i] = pack_bf16x2(a1 - __uint_as_float(m << 16), b1 - __uint_as_float(m & 0xffff0000u));
+        hi[i] = h;
+        mid[i] = m;
+    }
+}
+
+template <typename T, int BM, int BN, int KW, int NS, bool A_KC, bool B_KC, int EPI, int ACT, bool KG>
+__device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmArgs& p, int more, typename TileWalk<BM, BN>::Where before) {
+    typedef MidSmem<T, BM, BN, KW, NS, A_KC, B_KC> SM;
+    typedef typename SM::TA TA;
+    typedef typename SM::TB TB;
+    constexpr bool SPLIT = SM::SPLIT;
+    constexpr int BK = SM::BK, KS = BK / 16 / KW;
+    constexpr int TM = BM / 64, TN = BN / 64;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wk = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    const int l32 = lane & 31, g = lane >> 5;
+    unsigned char* walk_lds = smem_raw + SM::BYTES;
+    TileWalk<BM, BN>::build(p, walk_lds);
+    TileWalk<BM, BN> w;
+    if (more < 0) w.resume(before, walk_lds); else w.start(p, walk_lds, more);
+    while (w.next(p)) {
+        const int nk = (w.k_lim + BK - 1) / BK;
+        const T* gA = (const T*)p.A + (size_t)w.e * p.strideA;
+        const T* gB = (const T*)p.B + (size_t)w.e * p.strideB;
+        const bool live = w.m0 + wm * (BM / 2) < w.m_lim;     // does this wave hold any row in use
+        f32x16_t acc[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+        if constexpr (!SPLIT) {
+            u32x4_t dsA = TA::desc((const bf16_t*)gA, p.lda, w.m_lim, w.k_lim), dsB = TB::desc((const bf16_t*)gB, p.ldb, p.N, w.k_lim);
+            typename TA::Plan planA;
+            typename TB::Plan planB;
+            TA::plan(planA, p.lda, w.m0, w.m_lim);
+            TB::plan(planB, p.ldb, w.n0, p.N);
+            auto request = [&](int kt, int st) {
+                const int k0 = kt < nk ? kt * BK : 0;
+                u32x4_t sa = TA::slab_desc(dsA, TA::slab_shift(p.lda, k0)), sb = TB::slab_desc(dsB, TB::slab_shift(p.ldb, k0));
+                if (kt >= nk) { sa[2] = 0; sb[2] = 0; }      // past the end: zeros, so that every slab counts the same loads
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sa[i] = __builtin_amdgcn_readfirstlane(sa[i]);
+                    sb[i] = __builtin_amdgcn_readfirstlane(sb[i]);
+                }
+                const uint32_t base = lds0 + st * SM::STAGE;
+#pragma unroll
+                for (int i = 0; i < TA::PER_THREAD; ++i) TA::template issue_one<KG>(planA, sa, k0, w.k_lim, base, i);
+#pragma unroll
+                for (int i = 0; i < TB::PER_THREAD; ++i) TB::template issue_one<KG>(planB, sb, k0, w.k_lim, base + TA::BYTES, i);
+            };
+#pragma unroll
+            for (int s = 0; s < NS - 1; ++s) request(s, s);
+            int st = 0;
+            for (int kt = 0; kt < nk; ++kt) {
+                wait_vmcnt_lgkm0<(NS - 2) * SM::LOADS>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                request(kt + NS - 1, st == 0 ? NS - 1 : st - 1);
+                if (live) {
+                    const unsigned char* a_s = smem_raw + st * SM::STAGE;
+                    const unsigned char* b_s = a_s + TA::BYTES;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        bf16x8_t fa[TM], fb[TN];
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) fa[i] = TA::frag(a_s, wm * (BM / 2) + i * 32, wk * KS + ks, lane);
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) fb[j] = TB::frag(b_s, wn * (BN / 2) + j * 32, wk * KS + ks, lane);
+#pragma unroll
+                        for (int i = 0; i < TM; ++i)
+#pragma unroll
+                            for (int j = 0; j < TN; ++j) acc[i][j] = Mma<bf16_t>::mma(fb[j], fa[i], acc[i][j]);
+                    }
+                }
+                st = st == NS - 1 ? 0 : st + 1;
+            }
+            wait_vmcnt_lgkm0<0>();
+        } else {
+            constexpr int CA = TA::PER_THREAD, CB = TB::PER_THREAD;
+            uint32_t offA[CA], offB[CB], dstA[CA], dstB[CB];
+            int kcA[CA], kcB[CB];
+            auto geom = [&](auto tile, uint32_t& off, uint32_t& dst, int& kc, int i, int ld, int r0, int r_lim) {
+                typedef decltype(tile) TT;
+                const int q = threadIdx.x + i * SM::NT;
+                const int row = q / TT::CPR, c = q % TT::CPR;
+                dst = (uint32_t)((row * TT::CPR + (c ^ TT::swz(row))) * 16);
+                if (TT::IS_KC) {
+                    off = (uint32_t)((r0 + row) * ld + c * 8) * 4u;
+                    kc = c * 8;
+                } else {
+                    off = r0 + c * 8 < r_lim ? (uint32_t)(row * ld + r0 + c * 8) * 4u : BUF_OOB;
+                    kc = 0;
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < CA; ++i) geom(TA(), offA[i], dstA[i], kcA[i], i, p.lda, w.m0, w.m_lim);
+#pragma unroll
+            for (int i = 0; i < CB; ++i) geom(TB(), offB[i], dstB[i], kcB[i], i, p.ldb, w.n0, p.N);
+            const size_t rangeA = (size_t)(A_KC ? w.m_lim : w.k_lim) * p.lda * 4, rangeB = (size_t)(B_KC ? p.N : w.k_lim) * p.ldb * 4;
+            auto load8 = [&](__amdgpu_buffer_rsrc_t rs, uint32_t off, u32x4_t (&r)[2]) {
+                r[0] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+                r[1] = __builtin_amdgcn_raw_buffer_load_b128(rs, off == BUF_OOB ? BUF_OOB : off + 16, 0, 0);
+            };
+            // requests slab kt (zeros past the end) into a register set
+            struct Slab { u32x4_t a[CA][2], b[CB][2]; };
+            auto fetch = [&](int kt, Slab& r) {
+                const int k0 = kt < nk ? kt * BK : 0;
+                const size_t shA = (size_t)(A_KC ? k0 : k0 * p.lda) * 4, shB = (size_t)(B_KC ? k0 : k0 * p.ldb) * 4;
+                const __amdgpu_buffer_rsrc_t rsA = buf_rsrc((const char*)gA + shA, kt >= nk ? 0 : (A_KC ? rangeA : (rangeA > shA ? rangeA - shA : 0)));
+                const __amdgpu_buffer_rsrc_t rsB = buf_rsrc((const char*)gB + shB, kt >= nk ? 0 : (B_KC ? rangeB : (rangeB > shB ? rangeB - shB : 0)));
+#pragma unroll
+                for (int i = 0; i < CA; ++i) load8(rsA, (A_KC && KG && kcA[i] + k0 >= w.k_lim) ? BUF_OOB : offA[i], r.a[i]);
+#pragma unroll
+                for (int i = 0; i < CB; ++i) load8(rsB, (B_KC && KG && kcB[i] + k0 >= w.k_lim) ? BUF_OOB : offB[i], r.b[i]);
+            };
+            auto put = [&](unsigned char* st, const Slab& r) {      // a fetched slab, split, into a stage
+#pragma unroll
+                for (int i = 0; i < CA; ++i) {
+                    u32x4_t h, m, l;
+                    split3_rne(r.a[i], h, m, l);
+                    *reinterpret_cast<u32x4_t*>(st + dstA[i]) = h;
+                    *reinterpret_cast<u32x4_t*>(st + TA::BYTES + dstA[i]) = m;
+                    *reinterpret_cast<u32x4_t*>(st + 2 * TA::BYTES + dstA[i]) = l;
+                }
+#pragma unroll
+                for (int i = 0; i < CB; ++i) {
+                    u32x4_t h, m, l;
+                    split3_rne(r.b[i], h, m, l);
+                    unsigned char* d = st + 3 * TA::BYTES + dstB[i];
+                    *reinterpret_cast<u32x4_t*>(d) = h;
+                    *reinterpret_cast<u32x4_t*>(d + TB::BYTES) = m;
+                    *reinterpret_cast<u32x4_t*>(d + 2 * TB::BYTES) = l;
+                }
+            };
+            // One slab: its products, and under them the split of the next one (an MFMA occupies the matrix
+            // pipe for 32 cycles, in which the wave issues up to six vector instructions for nothing).
+            auto slab = [&](int kt, Slab& nxt, Slab& spare) {
+                const unsigned char* st = smem_raw + (kt & 1) * SM::STAGE;
+                fetch(kt + 2, spare);
+                bf16x8_t fa[KS][3][TM], fb[KS][3][TN];
+// in the order in which the products below need them
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                    for (int u = 0; u < 3; ++u) {
+                        constexpr int OA[3] = {2, 0, 1}, OB[3] = {0, 2, 1};
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) fa[ks][OA[u]][i] = TA::frag(st + OA[u] * TA::BYTES, wm * (BM / 2) + i * 32, wk * KS + ks, lane);
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) fb[ks][OB[u]][j] = TB::frag(st + 3 * TA::BYTES + OB[u] * TB::BYTES, wn * (BN / 2) + j * 32, wk * KS + ks, lane);
+                    }
+                put(smem_raw + ((kt + 1) & 1) * SM::STAGE, nxt);
+                // smallest products first; mid*lo, lo*mid and lo*lo (below 2^-26 of the product) are left out
+                constexpr int QA[6] = {2, 0, 1, 1, 0, 0}, QB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                    for (int q = 0; q < 6; ++q)
+#pragma unroll
+                        for (int i = 0; i < TM; ++i)
+#pragma unroll
+                            for (int j = 0; j < TN; ++j) acc[i][j] = Mma<bf16_t>::mma(fb[ks][QB[q]][j], fa[ks][QA[q]][i], acc[i][j]);
+                constexpr int NRD = 3 * (TM * (A_KC ? 1 : 2) + TN * (B_KC ? 1 : 2)), NMF = 6 * TM * TN;
+                constexpr int NV = (44 * (CA + CB) + KS * NMF - 1) / (KS * NMF);
+                __builtin_amdgcn_sched_group_barrier(0x020, 2 * (CA + CB), 0);       // the loads of the slab after next
+                __builtin_amdgcn_sched_group_barrier(0x100, NRD, 0);                 // fragments of the first k-step
+#pragma unroll
+                for (int m = 0; m < KS * NMF; ++m) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, NV, 0);
+                    if (m < NMF * (KS - 1)) __builtin_amdgcn_sched_group_barrier(0x100, (NRD + NMF - 1) / NMF, 0);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x200, 3 * (CA + CB), 0);
+                __builtin_amdgcn_sched_barrier(0);
+                // LDS writes of this wave are done and the workgroup meets; loads stay in flight
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            };
+            Slab s0, s1;
+            fetch(0, s0);
+            fetch(1, s1);
+            put(smem_raw, s0);
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            for (int kt = 0; kt < nk; kt += 2) {
+                slab(kt, s1, s0);
+                if (kt + 1 < nk) slab(kt + 1, s0, s1);
+            }
+        }
+        __syncthreads();             // the strips lie over the ring
+        if constexpr (KW > 1) {      // the groups' partial sums, added in group order
+            float4* red = reinterpret_cast<float4*>(smem_raw);
+            constexpr int PW = TM * TN * 4 * 64;     // float4 per wave
+            if (wk > 0) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            red[(wave - 4) * PW + ((i * TN + j) * 4 + q) * 64 + lane] =
+                                make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+            }
+            __syncthreads();
+            if (wk == 0) {
+#pragma unroll
+                for (int k_ = 1; k_ < KW; ++k_)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const float4 x4 = red[(wave + 4 * (k_ - 1)) * PW + ((i * TN + j) * 4 + q) * 64 + lane];
+                                acc[i][j][4 * q] += x4.x; acc[i][j][4 * q + 1] += x4.y;
+                                acc[i][j][4 * q + 2] += x4.z; acc[i][j][4 * q + 3] += x4.w;
+                            }
+            }
+            __syncthreads();
+        }
+
+        // ---- epilogue: lane holds row l32 of a 32x32 tile, columns 8q + 4g + 0..3 in registers 4q..4q+3
+        constexpr int V = EPI == EPI_F32 ? 4 : 16 / (int)sizeof(T);      // elements per lane and store
+        constexpr int WC = BN / 2, LPR = WC / V, RPI = 64 / LPR, NIT = 32 / RPI;
+        constexpr uint32_t OSZ = EPI == EPI_F32 ? 4u : (uint32_t)sizeof(T);
+        if (live && wk == 0) {
+            float* strip = reinterpret_cast<float*>(smem_raw) + wave * 32 * SM::STRIP_LD;
+            const int er = lane / LPR, ec = (lane - er * LPR) * V;
+            const int ncol = w.n0 + wn * WC + ec;
+            const bool col_ok = ncol < p.N;
+            const size_t obase = (size_t)w.e * p.strideO, obytes = (size_t)w.m_lim * p.ldo * OSZ;
+            const __amdgpu_buffer_rsrc_t o0 = buf_rsrc((const char*)p.out0 + obase * OSZ, obytes);
+            const __amdgpu_buffer_rsrc_t o1 = buf_rsrc(EPI == EPI_H_DACT ? (const char*)p.out1 + obase * OSZ : nullptr, EPI == EPI_H_DACT ? obytes : 0);
+            const __amdgpu_buffer_rsrc_t ax = buf_rsrc(EPI == EPI_MUL ? (const char*)p.aux + obase * OSZ : nullptr, EPI == EPI_MUL ? obytes : 0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int mb = w.m0 + wm * (BM / 2) + i * 32;
+                if (mb >= w.m_lim) break;
+                auto out_off = [&](int it) { return col_ok ? (uint32_t)(((size_t)(mb + er + it * RPI) * p.ldo + ncol) * OSZ) : BUF_OOB; };
+                float aux[EPI == EPI_MUL ? NIT : 1][V];
+                if constexpr (EPI == EPI_MUL) {
+#pragma unroll
+                    for (int it = 0; it < NIT; ++it) BufChunk<T>::load(ax, out_off(it), aux[it]);
+                }
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<float4*>(strip + l32 * SM::STRIP_LD + j * 32 + 8 * q + 4 * g) =
+                            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+                auto vec = [&](int it) {
+                    float v[V];
+#pragma unroll
+                    for (int c = 0; c < V / 4; ++c) {
+                        const float4 x4 = *reinterpret_cast<const float4*>(strip + (er + it * RPI) * SM::STRIP_LD + ec + 4 * c);
+                        v[4 * c] = x4.x; v[4 * c + 1] = x4.y; v[4 * c + 2] = x4.z; v[4 * c + 3] = x4.w;
+                    }
+                    const uint32_t off = out_off(it);
+                    if constexpr (EPI == EPI_F32) {
+                        BufChunk<float>::store(o0, off, v);
+                    } else if constexpr (EPI == EPI_STORE) {
+                        BufChunk<T>::store(o0, off, v);
+                    } else if constexpr (EPI == EPI_MUL) {
+#pragma unroll
+                        for (int c = 0; c < V; ++c) v[c] *= aux[it][c];
+                        BufChunk<T>::store(o0, off, v);
+                    } else {
+                        float a[V], h[V];
+#pragma unroll
+                        for (int c = 0; c < V; ++c) act_both<sizeof(T) == 2, ACT>(v[c], h[c], a[c]);
+                        if constexpr (EPI == EPI_H_DACT) {
+                            if (p.drop_thr) {
+#pragma unroll
+                                for (int c4 = 0; c4 < V / 4; ++c4) {
+                                    uint32_t nw[4];
+                                    noise_words(obase + (size_t)(mb + er + it * RPI) * p.ldo + ncol + 4 * c4, MOE_STREAM_DROPOUT, p.seed, nw);
+#pragma unroll
+                                    for (int c = 0; c < 4; ++c) {
+                                        const float sc = nw[c] >= p.drop_thr ? p.drop_scale : 0.0f;
+                                        h[4 * c4 + c] *= sc;
+                                        a[4 * c4 + c] *= sc;
+                                    }
+                                }
+                            }
+                            BufChunk<T>::store(o0, off, a);
+                            BufChunk<T>::store(o1, off, h);
+                        } else {
+                            BufChunk<T>::store(o0, off, h);
+                        }
+                    }
+                };
+                if constexpr (EPI == EPI_H_DACT || EPI == EPI_H) {
+#pragma unroll 1
+                    for (int it = 0; it < NIT; ++it) vec(it);
+                } else {
+#pragma unroll
+                    for (int it = 0; it < NIT; ++it) vec(it);
+                }
+            }
+        }
+        __syncthreads();             // the next tile's slabs overwrite the strips
+    }
+    return w.where();
+}
+
+template <typename T, int BM, int BN, int KW, int NS, bool A_KC, bool B_KC, int EPI, int ACT, bool KG>
+__global__ __launch_bounds__(256 * KW, (KW * MidSmem<T, BM, BN, KW, NS, A_KC, B_KC>::OCC)) void mid_gemm_kernel(const GemmArgs p) {
+    mid_body<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, KG>(p, 0, {0, 0});
+}
+template <typename T, int BM, int BN, int KW, int NS, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2, bool KG>
+__global__ __launch_bounds__(256 * KW, (KW * MidSmem<T, BM, BN, KW, NS, A1, B1>::OCC)) void mid_gemm_pair_kernel(const GemmArgs p1, const GemmArgs p2) {
+    const typename TileWalk<BM, BN>::Where w = mid_body<T, BM, BN, KW, NS, A1, B1, EPI1, 0, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0});
+    __syncthreads();      // every wave is done with the tile table of the first product
+    mid_body<T, BM, BN, KW, NS, A2, B2, EPI2, 0, KG>(p2, -1, w);
 }
 
 // Number of compute units of the current device (looked up once per device).
@@ -828,9 +1199,6 @@ static int num_cus() {
     return n;
 }
 
-#ifndef MOE_GEMM_NWN
-#define MOE_GEMM_NWN 4
-#endif
 // one persistent workgroup per CU (its LDS footprint allows no second one), in groups of 8 so
 // that every XCD gets the same number; never more than there could be tiles
 static int gemm_grid(long long tiles) {
@@ -841,53 +1209,136 @@ static int gemm_grid(long long tiles) {
     return per_xcd * 8;
 }
 
-template <typename T, int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI, int ACT = 0>
-static bool launch_gemm(GemmArgs p, int E, hipStream_t st) {
-    constexpr int NWN = sizeof(T) == 2 ? MOE_GEMM_NWN : 2;
-    typedef GemmSmem<T, BM, BN, BK, A_KC, B_KC, NWN> SM;
+static int mid_grid(long long tiles, int occ) {
+    const long long most = (tiles + 7) / 8;
+    long long per_xcd = (long long)num_cus() / 8 * occ;
+    if (per_xcd < 1) per_xcd = 1;
+    if (per_xcd > most) per_xcd = most;
+    return (int)per_xcd * 8;
+}
+
+static void set_tiles(GemmArgs& p, int BM, int BN, int E) {
     p.tiles_m = ceil_div(p.M, BM);
     p.tiles_n = ceil_div(p.N, BN);
     p.E = E;
+}
+static long long all_tiles(const GemmArgs& p) { return (long long)p.E * p.tiles_m * p.tiles_n; }
+
+template <typename T, int BM, int BN, int KW, int NS, bool A_KC, bool B_KC, int EPI, int ACT>
+static bool launch_mid(GemmArgs p, int E, hipStream_t st) {
+    typedef MidSmem<T, BM, BN, KW, NS, A_KC, B_KC> SM;
+    set_tiles(p, BM, BN, E);
     const size_t smem = SM::BYTES + WALK_BYTES;
-    const int grid = gemm_grid((long long)E * p.tiles_m * p.tiles_n);
-    // a k-contiguous operand whose reduction length is not a multiple of BK needs the guarded instance
-    const bool kg = (A_KC || B_KC) && !p.var_k && p.K % BK != 0;
+    // a k-contiguous operand whose reduction length is not a multiple of the slab needs the guarded instance
+    const bool kg = (A_KC || B_KC) && !p.var_k && p.K % SM::BK != 0;
     static unsigned long long opted[2] = {0, 0};
-    if (kg) {
-        auto kern = grouped_gemm_kernel<T, BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, true>;
-        if (!lds_opt_in((const void*)kern, smem, &opted[1])) return false;
-        kern<<<grid, SM::NT, smem, st>>>(p);
-    } else {
-        auto kern = grouped_gemm_kernel<T, BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, false>;
-        if (!lds_opt_in((const void*)kern, smem, &opted[0])) return false;
-        kern<<<grid, SM::NT, smem, st>>>(p);
-    }
+    auto kern = kg ? mid_gemm_kernel<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, true> : mid_gemm_kernel<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, false>;
+    if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
+    kern<<<mid_grid(all_tiles(p), SM::OCC), SM::NT, smem, st>>>(p);
     return true;
 }
 
-template <typename T, int BM, int BN, int BK, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
-static bool launch_gemm_pair(GemmArgs p1, GemmArgs p2, int E, hipStream_t st) {
-    constexpr int NWN = sizeof(T) == 2 ? MOE_GEMM_NWN : 2;
-    typedef GemmSmem<T, BM, BN, BK, A1, B1, NWN> SM1;
-    typedef GemmSmem<T, BM, BN, BK, A2, B2, NWN> SM2;
-    static_assert(SM1::NT == SM2::NT, "one workgroup shape");
-    p1.tiles_m = ceil_div(p1.M, BM); p1.tiles_n = ceil_div(p1.N, BN); p1.E = E;
-    p2.tiles_m = ceil_div(p2.M, BM); p2.tiles_n = ceil_div(p2.N, BN); p2.E = E;
-    const size_t smem = (SM1::BYTES > SM2::BYTES ? SM1::BYTES : SM2::BYTES) + WALK_BYTES;
-    const long long t1 = (long long)E * p1.tiles_m * p1.tiles_n, t2 = (long long)E * p2.tiles_m * p2.tiles_n;
-    const int grid = gemm_grid(t1 > t2 ? t1 : t2);
-    const bool kg = ((A1 || B1) && !p1.var_k && p1.K % BK != 0) || ((A2 || B2) && !p2.var_k && p2.K % BK != 0);
+template <typename T, int BM, int BN, int KW, int NS, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
+static bool launch_mid_pair(GemmArgs p1, GemmArgs p2, int E, hipStream_t st) {
+    typedef MidSmem<T, BM, BN, KW, NS, A1, B1> SM;
+    set_tiles(p1, BM, BN, E);
+    set_tiles(p2, BM, BN, E);
+    const size_t smem = SM::BYTES + WALK_BYTES;
+    const bool kg = ((A1 || B1) && !p1.var_k && p1.K % SM::BK != 0) || ((A2 || B2) && !p2.var_k && p2.K % SM::BK != 0);
     static unsigned long long opted[2] = {0, 0};
-    if (kg) {
-        auto kern = grouped_gemm_pair_kernel<T, BM, BN, BK, A1, B1, EPI1, A2, B2, EPI2, NWN, true>;
-        if (!lds_opt_in((const void*)kern, smem, &opted[1])) return false;
-        kern<<<grid, SM1::NT, smem, st>>>(p1, p2);
-    } else {
-        auto kern = grouped_gemm_pair_kernel<T, BM, BN, BK, A1, B1, EPI1, A2, B2, EPI2, NWN, false>;
-        if (!lds_opt_in((const void*)kern, smem, &opted[0])) return false;
-        kern<<<grid, SM1::NT, smem, st>>>(p1, p2);
-    }
+    auto kern = kg ? mid_gemm_pair_kernel<T, BM, BN, KW, NS, A1, B1, EPI1, A2, B2, EPI2, true> : mid_gemm_pair_kernel<T, BM, BN, KW, NS, A1, B1, EPI1, A2, B2, EPI2, false>;
+    if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
+    kern<<<mid_grid(all_tiles(p1) + all_tiles(p2), SM::OCC), SM::NT, smem, st>>>(p1, p2);
     return true;
+}
+
+template <bool A_KC, bool B_KC, int EPI, int ACT>
+static bool launch_big(GemmArgs p, int E, hipStream_t st) {
+    typedef GemmSmem<bf16_t, BIG_M, BIG_N, BIG_K, A_KC, B_KC, BIG_WN> SM;
+    set_tiles(p, BIG_M, BIG_N, E);
+    const size_t smem = SM::BYTES + WALK_BYTES;
+    const bool kg = (A_KC || B_KC) && !p.var_k && p.K % BIG_K != 0;
+    static unsigned long long opted[2] = {0, 0};
+    auto kern = kg ? grouped_gemm_kernel<bf16_t, BIG_M, BIG_N, BIG_K, A_KC, B_KC, EPI, ACT, BIG_WN, true>
+                   : grouped_gemm_kernel<bf16_t, BIG_M, BIG_N, BIG_K, A_KC, B_KC, EPI, ACT, BIG_WN, false>;
+    if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
+    kern<<<gemm_grid(all_tiles(p)), SM::NT, smem, st>>>(p);
+    return true;
+}
+
+template <bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
+static bool launch_big_pair(GemmArgs p1, GemmArgs p2, int E, hipStream_t st) {
+    typedef GemmSmem<bf16_t, BIG_M, BIG_N, BIG_K, A1, B1, BIG_WN> SM1;
+    typedef GemmSmem<bf16_t, BIG_M, BIG_N, BIG_K, A2, B2, BIG_WN> SM2;
+    static_assert(SM1::NT == SM2::NT, "one workgroup shape");
+    set_tiles(p1, BIG_M, BIG_N, E);
+    set_tiles(p2, BIG_M, BIG_N, E);
+    const size_t smem = (SM1::BYTES > SM2::BYTES ? SM1::BYTES : SM2::BYTES) + WALK_BYTES;
+    const bool kg = ((A1 || B1) && !p1.var_k && p1.K % BIG_K != 0) || ((A2 || B2) && !p2.var_k && p2.K % BIG_K != 0);
+    static unsigned long long opted[2] = {0, 0};
+    auto kern = kg ? grouped_gemm_pair_kernel<bf16_t, BIG_M, BIG_N, BIG_K, A1, B1, EPI1, A2, B2, EPI2, BIG_WN, true>
+                   : grouped_gemm_pair_kernel<bf16_t, BIG_M, BIG_N, BIG_K, A1, B1, EPI1, A2, B2, EPI2, BIG_WN, false>;
+    if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
+    kern<<<gemm_grid(all_tiles(p1) + all_tiles(p2)), SM1::NT, smem, st>>>(p1, p2);
+    return true;
+}
+
+// ---- which tile ------------------------------------------------------------------
+// The expert counts are on the device; the host knows the mean demand T k / E and the
+// capacity, so rows = the smaller of the two is what an expert holds at most on average.
+// Tiles expected with a given tile side:
+static double tiles_expected(const GemmArgs& p, int rows, int side, int E) {
+    return (double)E * ceil_div(p.var_k ? p.M : rows, side) * ceil_div(p.N, side);
+}
+// bf16, experts with more than 128 rows: time goes with the number of whole rounds.  The 256 x 256
+// kernel runs one tile per CU and round; the 128 x 128 one runs two per CU, each a quarter of the
+// work at 0.78 of the rate (0.74 - 0.87 over the six products at 32 experts of 1024 rows, d = 1024,
+// f = 4096).  h W2 with six experts of 1440 rows, d = 776, f = 3080 (144 large tiles, 504 small ones):
+// 65 us against 80; with 16 experts of 1024 rows, d = 768, f = 3072 (192 and 768): 118 against 90.
+static bool prefer_mid(double t256, double t128) {
+    const double cus = num_cus();
+    return ceil(t128 / (2 * cus)) * (cus / 2) / 0.78 < ceil(t256 / cus) * cus;
+}
+
+// fp32: 64 x 64 tiles as long as 128 x 128 ones would leave much of the chip idle (five experts of 280
+// rows, d = 136, f = 328: 10 us per product against 17 - 23); 128 x 128 with two wave groups that
+// share a tile's slabs while there are few tiles per CU (248 tiles, f = 2048: 89 us against 124 with
+// one group), with one group otherwise (992 tiles, d = 512: 105 against 117).
+// bf16: the same order.  64 x 64 (8 experts of 64 rows, d = 512, f = 2048: 7 and 11 us against 10 and
+// 22 with 128 x 128, 17 and 39 with 256 x 256); with few rows per expert the weights' stream is the
+// bound and two 128 x 128 workgroups per CU keep more of it in flight than one large one (107 experts
+// of 7 rows, d = 1024, f = 4096: 169 us = 5.3 TB/s against 203).
+template <typename T, bool A_KC, bool B_KC, int EPI, int ACT = 0>
+static bool launch_gemm(const GemmArgs& p, int rows, int E, hipStream_t st) {
+    const double cus = num_cus(), t128 = tiles_expected(p, rows, 128, E);
+    if constexpr (sizeof(T) == 4) {
+        if (t128 <= 0.6 * cus) return launch_mid<T, 64, 64, 2, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
+        if (t128 <= 1.5 * cus) return launch_mid<T, 128, 128, 2, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
+        return launch_mid<T, 128, 128, 1, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
+    } else {
+        if (t128 <= (rows <= 128 ? 1.0 : 0.5) * cus) return launch_mid<T, 64, 64, 1, 3, A_KC, B_KC, EPI, ACT>(p, E, st);
+        if (rows <= 128 || prefer_mid(tiles_expected(p, rows, 256, E), t128))
+            return launch_mid<T, 128, 128, 1, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
+        return launch_big<A_KC, B_KC, EPI, ACT>(p, E, st);
+    }
+}
+
+// Two products: the same lines at higher tile counts, because the tiles of both are in the launch
+// (fp32, 248 + 512 tiles: 185 us with two wave groups, 250 with one; 992 + 512: 197 and 179.  bf16,
+// 8 experts of 64 rows, 32 + 512 tiles: 26 us with 64 x 64, 30 with 128 x 128, 41 with 256 x 256).
+template <typename T, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
+static bool launch_gemm_pair(const GemmArgs& p1, const GemmArgs& p2, int rows, int E, hipStream_t st) {
+    const double cus = num_cus(), t128 = tiles_expected(p1, rows, 128, E) + tiles_expected(p2, rows, 128, E);
+    if constexpr (sizeof(T) == 4) {
+        if (t128 <= 0.75 * cus) return launch_mid_pair<T, 64, 64, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        if (t128 <= 4.0 * cus) return launch_mid_pair<T, 128, 128, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        return launch_mid_pair<T, 128, 128, 1, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+    } else {
+        if (t128 <= (rows <= 128 ? 3.0 : 1.0) * cus) return launch_mid_pair<T, 64, 64, 1, 3, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        if (prefer_mid(tiles_expected(p1, rows, 256, E) + tiles_expected(p2, rows, 256, E), t128))
+            return launch_mid_pair<T, 128, 128, 1, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        return launch_big_pair<A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+    }
 }
 
 size_t ffn_bwd_ws_bytes(const moe_shape* s) {
@@ -902,10 +1353,16 @@ static int check_slice_limits(const moe_shape* s) {
     return MOE_OK;
 }
 
-template <typename T, int BM, int BN, int BK>
+static int expected_rows(const moe_shape* s) {
+    const int mean = ceil_div(s->T * s->k, s->E);
+    return mean < s->capacity ? mean : s->capacity;
+}
+
+template <typename T>
 static bool ffn_fwd(const moe_shape* s, const void* xd, const int32_t* cnt, const void* W1,
                     const void* W2, void* h, void* a, void* yd, float drop_p, uint64_t seed, hipStream_t st) {
     const int E = s->E, C = s->capacity, d = s->d_model, f = s->d_ff;
+    const int rows = expected_rows(s);
     GemmArgs p = {};
     p.expert_count = cnt; p.var_k = 0;
     if (drop_p > 0.0f) {
@@ -921,10 +1378,10 @@ static bool ffn_fwd(const moe_shape* s, const void* xd, const int32_t* cnt, cons
     bool ok;
     if (!a) {   // forward-only: the derivative is neither computed nor stored
         p.out0 = h; p.out1 = nullptr;
-        if (s->act == MOE_RELU) ok = launch_gemm<T, BM, BN, BK, true, false, EPI_H, MOE_RELU>(p, E, st);
-        else ok = launch_gemm<T, BM, BN, BK, true, false, EPI_H, MOE_GELU>(p, E, st);
-    } else if (s->act == MOE_RELU) ok = launch_gemm<T, BM, BN, BK, true, false, EPI_H_DACT, MOE_RELU>(p, E, st);
-    else ok = launch_gemm<T, BM, BN, BK, true, false, EPI_H_DACT, MOE_GELU>(p, E, st);
+        if (s->act == MOE_RELU) ok = launch_gemm<T, true, false, EPI_H, MOE_RELU>(p, rows, E, st);
+        else ok = launch_gemm<T, true, false, EPI_H, MOE_GELU>(p, rows, E, st);
+    } else if (s->act == MOE_RELU) ok = launch_gemm<T, true, false, EPI_H_DACT, MOE_RELU>(p, rows, E, st);
+    else ok = launch_gemm<T, true, false, EPI_H_DACT, MOE_GELU>(p, rows, E, st);
     if (!ok) return false;
     // yd = h W2
     p.A = h; p.lda = f; p.strideA = (long long)C * f;
@@ -932,14 +1389,15 @@ static bool ffn_fwd(const moe_shape* s, const void* xd, const int32_t* cnt, cons
     p.out0 = yd; p.out1 = nullptr; p.ldo = d; p.strideO = (long long)C * d;
     p.M = C; p.N = d; p.K = f;
     p.drop_thr = 0;
-    return launch_gemm<T, BM, BN, BK, true, false, EPI_STORE>(p, E, st);
+    return launch_gemm<T, true, false, EPI_STORE>(p, rows, E, st);
 }
 
-template <typename T, int BM, int BN, int BK>
+template <typename T>
 static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const void* h,
                     const void* a, const int32_t* cnt, const void* W1, const void* W2, void* dxd,
                     float* dW1, float* dW2, void* dz, hipStream_t st) {
     const int E = s->E, C = s->capacity, d = s->d_model, f = s->d_ff;
+    const int rows = expected_rows(s);
     // Four products in two launches.  dW2 needs only h and dyd, so it shares a launch with dz;
     // dxd and dW1 both need dz and share the second one.
     GemmArgs p = {}, q = {};
@@ -956,7 +1414,7 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     q.B = dyd; q.ldb = d; q.strideB = (long long)C * d;
     q.out0 = dW2; q.ldo = d; q.strideO = (long long)f * d;
     q.M = f; q.N = d; q.K = C;
-    if (!launch_gemm_pair<T, BM, BN, BK, true, true, EPI_MUL, false, false, EPI_F32>(p, q, E, st)) return false;
+    if (!launch_gemm_pair<T, true, true, EPI_MUL, false, false, EPI_F32>(p, q, rows, E, st)) return false;
     // dxd = dz W1^T:  B(r = n in d, k in f) = W1[n*f + k]
     p.A = dz; p.lda = f; p.strideA = (long long)C * f;
     p.B = W1; p.ldb = f; p.strideB = (long long)d * f;
@@ -967,7 +1425,7 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     q.B = dz; q.ldb = f; q.strideB = (long long)C * f;
     q.out0 = dW1; q.ldo = f; q.strideO = (long long)d * f;
     q.M = d; q.N = f; q.K = C;
-    return launch_gemm_pair<T, BM, BN, BK, true, true, EPI_STORE, false, false, EPI_F32>(p, q, E, st);
+    return launch_gemm_pair<T, true, true, EPI_STORE, false, false, EPI_F32>(p, q, rows, E, st);
 }
 
 static int ffn_fwd_impl(const moe_shape* shape, const void* xd, const int32_t* expert_count,
@@ -982,8 +1440,8 @@ static int ffn_fwd_impl(const moe_shape* shape, const void* xd, const int32_t* e
     if (drop_p > 0.0f && floor((double)drop_p * 4294967296.0) < 1.0) drop_p = 0.0f;   // below one part in 2^32
     hipStream_t st = (hipStream_t)stream;
     const bool ok = shape->dtype == MOE_BF16
-        ? ffn_fwd<bf16_t, MOE_GEMM_BM, MOE_GEMM_BN, MOE_GEMM_BK>(shape, xd, expert_count, W1, W2, h_saved, dact_saved, yd, drop_p, seed, st)
-        : ffn_fwd<float, 128, 128, 16>(shape, xd, expert_count, W1, W2, h_saved, dact_saved, yd, drop_p, seed, st);
+        ? ffn_fwd<bf16_t>(shape, xd, expert_count, W1, W2, h_saved, dact_saved, yd, drop_p, seed, st)
+        : ffn_fwd<float>(shape, xd, expert_count, W1, W2, h_saved, dact_saved, yd, drop_p, seed, st);
     return ok ? launch_status() : MOE_ERR_LAUNCH;
 }
 
@@ -1013,7 +1471,7 @@ extern "C" int moe_expert_ffn_bwd(const moe_shape* shape, const void* dyd, const
     if (!ws || ((uintptr_t)ws & 255) || ws_bytes < ffn_bwd_ws_bytes(shape)) return MOE_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     const bool ok = shape->dtype == MOE_BF16
-        ? ffn_bwd<bf16_t, MOE_GEMM_BM, MOE_GEMM_BN, MOE_GEMM_BK>(shape, dyd, xd, h_saved, dact_saved, expert_count, W1, W2, dxd, dW1, dW2, ws, st)
-        : ffn_bwd<float, 128, 128, 16>(shape, dyd, xd, h_saved, dact_saved, expert_count, W1, W2, dxd, dW1, dW2, ws, st);
+        ? ffn_bwd<bf16_t>(shape, dyd, xd, h_saved, dact_saved, expert_count, W1, W2, dxd, dW1, dW2, ws, st)
+        : ffn_bwd<float>(shape, dyd, xd, h_saved, dact_saved, expert_count, W1, W2, dxd, dW1, dW2, ws, st);
     return ok ? launch_status() : MOE_ERR_LAUNCH;
 }
