@@ -155,6 +155,15 @@ int moe_gate_route_grouped(const moe_shape* shape, int32_t n_groups, const float
                            int32_t* expert_demand, int32_t* slot_src, void* ws, size_t ws_bytes,
                            void* stream);
 
+/* moe_gate_route_grouped that also counts the batch for pruning (Sec. 3.3), as
+ * moe_utilisation_accumulate does with this call's expert_demand:
+ * accum[e] += expert_demand[e].  Needs workspace. */
+int moe_gate_route_counted(const moe_shape* shape, int32_t n_groups, const float* logits,
+                           const float* rts_keys_or_null, float* probs, int32_t* expert_idx,
+                           float* gate_w, int32_t* slot, int32_t* expert_count,
+                           int32_t* expert_demand, int32_t* slot_src, int64_t* accum, void* ws,
+                           size_t ws_bytes, void* stream);
+
 /* moe_gate_route for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * inputs, outputs and results as moe_gate_route (plain routing, one group); the
@@ -243,6 +252,15 @@ int moe_combine_bwd(const moe_shape* shape, const void* dy, const void* yd,
                     const int32_t* expert_idx, const int32_t* slot, const float* gate_w,
                     void* dyd, float* dgate_w, void* stream);
 
+/* moe_combine_bwd followed by the gate's backward of the same tokens in one pass (the
+ * derivative of the combine of Sec. 3.1 and of the gate weights of Sec. 5.1): dyd and
+ * dgate_w as moe_combine_bwd, dlogits as moe_gate_bwd, or as moe_gate_bwd_aux if
+ * first_frac_or_null is given. */
+int moe_combine_gate_bwd(const moe_shape* shape, const void* dy, const void* yd,
+                         const int32_t* expert_idx, const int32_t* slot, const float* gate_w,
+                         const float* probs, const float* first_frac_or_null, float aux_coef,
+                         void* dyd, float* dgate_w, float* dlogits, void* stream);
+
 /* Expert feed-forward block, backward: the derivative of the two-matmul expert
  * of Sec. 4.2 (moe_expert_ffn_fwd) with respect to its input rows and its two
  * weight matrices; like the forward, this is where the layer's compute sits
@@ -316,6 +334,50 @@ int moe_dispatch_gate_logits_bwd(const moe_shape* shape, const void* x, const fl
                                  const float* dlogits, const void* dxd, const int32_t* expert_idx,
                                  const int32_t* slot, float jitter_eps, uint64_t seed, float* dWg,
                                  void* dx, void* ws, size_t ws_bytes, void* stream);
+
+/* One layer pass as two calls (Sec. 2.4: MoE(hidden_size, expert, num_experts)): each
+ * issues the entry points above in order on the stream, so that a training step costs the
+ * host two calls.  All buffers are the caller's; those of a part that the options leave out
+ * may be NULL.  The seed must be the same in both calls of a step. */
+typedef struct {
+    /* gate and routing */
+    float *logits, *probs;          /* [T,E] */
+    int32_t* expert_idx;            /* [T,k] */
+    float* gate_w;                  /* [T,k] */
+    int32_t *slot;                  /* [T,k] */
+    int32_t *expert_count, *expert_demand; /* [E] */
+    int32_t* slot_src;              /* [E,C] */
+    int64_t* utilisation;           /* [E], forward_only: expert_demand is added to it */
+    float *first_frac, *mean_prob, *aux_loss; /* [E], [E], [1], aux_coef != 0 */
+    /* experts and output */
+    void *xd, *h, *dact, *yd, *y;   /* dact NULL: no derivative is saved */
+    /* backward */
+    void* dyd;
+    float* dgate_w;
+    void* dxd;
+    float *dW1, *dW2, *dlogits, *dWg;
+    void* dx;
+    void* ws;                       /* moe_workspace_bytes() */
+    size_t ws_bytes;
+} moe_layer_buffers;
+
+typedef struct {
+    int32_t groups;                 /* >= 1, see moe_gate_route_grouped */
+    int32_t forward_only;           /* count utilisation; no backward will follow */
+    int32_t logits_given;           /* buffers.logits already holds the gate logits */
+    float aux_coef, jitter_eps, drop_p; /* 0 = off */
+    uint64_t seed;
+} moe_layer_options;
+
+/* gate projection (jitter), routing, utilisation, balancing loss, dispatch, experts
+ * (dropout), combine  ->  buffers.y */
+int moe_layer_fwd(const moe_shape* shape, const moe_layer_options* options, const moe_layer_buffers* buffers,
+                  const void* x, const float* Wg, const float* bias_or_null, const void* W1, const void* W2,
+                  const float* rts_keys_or_null, void* stream);
+/* combine and gate backward, experts backward, dispatch and projection backward
+ * ->  buffers.dx, dWg, dW1, dW2 */
+int moe_layer_bwd(const moe_shape* shape, const moe_layer_options* options, const moe_layer_buffers* buffers,
+                  const void* x, const float* Wg, const void* W1, const void* W2, const void* dy, void* stream);
 
 #ifdef __cplusplus
 }

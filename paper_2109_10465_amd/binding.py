@@ -21,13 +21,26 @@ EXPORTS = [
     "moe_utilisation_accumulate", "moe_gate_route_grouped",
     "moe_gate_logits_jitter", "moe_gate_logits_bwd_jitter", "moe_expert_ffn_fwd_dropout",
     "moe_dispatch_gate_logits_bwd", "moe_microbench_mfma_bf16",
-    "moe_gate_route_static", "moe_gate_route_static_max_bytes", "moe_dispatch_tokens",
+    "moe_gate_route_static", "moe_gate_route_static_max_bytes", "moe_dispatch_tokens", "moe_combine_gate_bwd",
+    "moe_gate_route_counted", "moe_layer_fwd", "moe_layer_bwd",
 ]
 
 
 class MoeShape(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in
                 ("T", "d_model", "d_ff", "E", "k", "capacity", "dtype", "act")]
+
+
+class LayerBuffers(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in
+                ("logits", "probs", "expert_idx", "gate_w", "slot", "expert_count", "expert_demand", "slot_src",
+                 "utilisation", "first_frac", "mean_prob", "aux_loss", "xd", "h", "dact", "yd", "y", "dyd", "dgate_w",
+                 "dxd", "dW1", "dW2", "dlogits", "dWg", "dx", "ws")] + [("ws_bytes", ctypes.c_size_t)]
+
+
+class LayerOptions(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_int32) for n in ("groups", "forward_only", "logits_given")]
+                + [(n, ctypes.c_float) for n in ("aux_coef", "jitter_eps", "drop_p")] + [("seed", ctypes.c_uint64)])
 
 
 class MoeError(RuntimeError):
@@ -73,6 +86,10 @@ def lib():
             "moe_gate_bwd_aux": [shp] + [vp] * 5 + [ctypes.c_float, vp, vp],
             "moe_utilisation_accumulate": [shp, vp, vp, vp],
             "moe_gate_route_grouped": [shp, i32] + [vp] * 10 + [sz, vp],
+            "moe_combine_gate_bwd": [shp] + [vp] * 7 + [ctypes.c_float] + [vp] * 4,
+            "moe_layer_fwd": [shp, ctypes.POINTER(LayerOptions), ctypes.POINTER(LayerBuffers)] + [vp] * 7,
+            "moe_layer_bwd": [shp, ctypes.POINTER(LayerOptions), ctypes.POINTER(LayerBuffers)] + [vp] * 6,
+            "moe_gate_route_counted": [shp, i32] + [vp] * 11 + [sz, vp],
             "moe_gate_logits_jitter": [shp, vp, vp, vp, ctypes.c_float, ctypes.c_uint64, vp, vp],
             "moe_gate_logits_bwd_jitter": [shp, vp, vp, vp, ctypes.c_float, ctypes.c_uint64, vp, vp, vp, sz, vp],
             "moe_expert_ffn_fwd_dropout": [shp] + [vp] * 4 + [ctypes.c_float, ctypes.c_uint64] + [vp] * 4,
@@ -153,6 +170,15 @@ def moe_gate_route_grouped(shape, n_groups, logits, rts_keys, probs, expert_idx,
                                         _stream(stream)), "moe_gate_route_grouped")
 
 
+def moe_gate_route_counted(shape, n_groups, logits, rts_keys, probs, expert_idx, gate_w, slot, expert_count,
+                           expert_demand, slot_src, accum, ws, stream=None):
+    _check(lib().moe_gate_route_counted(ctypes.byref(shape), int(n_groups), _p(logits), _p(rts_keys), _p(probs),
+                                        _p(expert_idx), _p(gate_w), _p(slot), _p(expert_count), _p(expert_demand),
+                                        _p(slot_src), _p(accum), _p(ws),
+                                        0 if ws is None else ws.numel() * ws.element_size(),
+                                        _stream(stream)), "moe_gate_route_counted")
+
+
 def moe_dispatch(shape, x, slot_src, expert_count, xd, stream=None):
     _check(lib().moe_dispatch(ctypes.byref(shape), _p(x), _p(slot_src), _p(expert_count), _p(xd),
                               _stream(stream)), "moe_dispatch")
@@ -178,6 +204,13 @@ def moe_combine_bwd(shape, dy, yd, expert_idx, slot, gate_w, dyd, dgate_w, strea
     _check(lib().moe_combine_bwd(ctypes.byref(shape), _p(dy), _p(yd), _p(expert_idx), _p(slot),
                                  _p(gate_w), _p(dyd), _p(dgate_w), _stream(stream)),
            "moe_combine_bwd")
+
+
+def moe_combine_gate_bwd(shape, dy, yd, expert_idx, slot, gate_w, probs, first_frac, aux_coef, dyd, dgate_w, dlogits,
+                         stream=None):
+    _check(lib().moe_combine_gate_bwd(ctypes.byref(shape), _p(dy), _p(yd), _p(expert_idx), _p(slot), _p(gate_w),
+                                      _p(probs), _p(first_frac), float(aux_coef), _p(dyd), _p(dgate_w), _p(dlogits),
+                                      _stream(stream)), "moe_combine_gate_bwd")
 
 
 def moe_expert_ffn_bwd(shape, dyd, xd, h_saved, dact_saved, expert_count, W1, W2, dxd, dW1, dW2, ws,
@@ -236,6 +269,16 @@ def moe_expert_ffn_fwd_dropout(shape, xd, expert_count, W1, W2, drop_p, seed, h_
     _check(lib().moe_expert_ffn_fwd_dropout(ctypes.byref(shape), _p(xd), _p(expert_count), _p(W1), _p(W2),
                                             float(drop_p), int(seed), _p(h_saved), _p(dact_saved), _p(yd),
                                             _stream(stream)), "moe_expert_ffn_fwd_dropout")
+
+
+def moe_layer_fwd(shape, options, buffers, x, Wg, bias, W1, W2, rts_keys, stream=None):
+    _check(lib().moe_layer_fwd(shape, options, buffers, _p(x), _p(Wg), _p(bias), _p(W1), _p(W2), _p(rts_keys),
+                               _stream(stream)), "moe_layer_fwd")
+
+
+def moe_layer_bwd(shape, options, buffers, x, Wg, W1, W2, dy, stream=None):
+    _check(lib().moe_layer_bwd(shape, options, buffers, _p(x), _p(Wg), _p(W1), _p(W2), _p(dy), _stream(stream)),
+           "moe_layer_bwd")
 
 
 def moe_utilisation_accumulate(shape, counts, accum, stream=None):

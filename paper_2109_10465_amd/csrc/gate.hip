@@ -398,11 +398,10 @@ static bool launch_gate_logits(const moe_shape* s, const void* x, const float* W
         if (s->E <= 32) GLM(1, true, 1); else if (s->E <= 64) GLM(2, true, 1);
         else if (s->E <= 128) GLM(4, true, 1); else GLM(8, true, 1);
     } else {
-#ifndef MOE_GATE_TT32
-#define MOE_GATE_TT32 2   // two 32-token tiles share each Wg fragment (measured: 15.7 -> 14.2 us at T = 16384, E = 32; four: slower)
-#endif
-        constexpr int TT32 = sizeof(T) == 2 ? MOE_GATE_TT32 : 1;
-        if (s->E <= 32) GLM(1, false, TT32); else if (s->E <= 64) GLM(2, false, TT2);
+        // Two 32-token tiles share each Wg fragment once that still gives most compute units a workgroup
+        // (T = 16384, E = 32: 15.7 -> 14.2 us; four tiles: slower); below, one tile's loads all fit in
+        // one round (T = 61, d = 1024, E = 32: 11.3 -> 8.0 us).
+        if (s->E <= 32) { if (ceil_div(s->T, 64) >= 192) GLM(1, false, TT2); else GLM(1, false, 1); } else if (s->E <= 64) GLM(2, false, TT2);
         else if (s->E <= 128) GLM(4, false, TT2); else GLM(8, false, 1);
     }
 #undef GLM
@@ -741,25 +740,27 @@ __device__ __forceinline__ void load_row_f32(__amdgpu_buffer_rsrc_t rs, int row_
 #define GDX_WAVES 4
 #define GDX_COLS 64     // columns per wave pass
 
+template <typename T> struct GdxSmem {
+    static constexpr int LD = GDX_COLS + 4;     // floats per staged row (16-byte aligned, rows 4 apart on other banks)
+    float stage[GDX_WAVES][32][LD];
+    int row[2][32];                             // row of dxd behind each of the token's choices (-1: dropped)
+};
 template <typename T, int EB, bool VEC, bool GATHER>   // EB = 32-expert blocks (E <= 32*EB); VEC: E % 4 == 0
-__global__ __launch_bounds__(64 * GDX_WAVES) void gate_dx_kernel(int Tn, int d, int E, int k, int C,
-                                                                 const float* __restrict__ dlogits,
-                                                                 const float* __restrict__ Wg,
-                                                                 const T* __restrict__ dxd,
-                                                                 const int32_t* __restrict__ expert_idx,
-                                                                 const int32_t* __restrict__ slot,
-                                                                 T* __restrict__ dx, float jitter_eps, uint64_t seed) {
+__device__ __forceinline__ void gate_dx_body(GdxSmem<T>& sm, int block, int Tn, int d, int E, int k, int C,
+                                             const float* __restrict__ dlogits, const float* __restrict__ Wg,
+                                             const T* __restrict__ dxd, const int32_t* __restrict__ expert_idx,
+                                             const int32_t* __restrict__ slot, T* __restrict__ dx, float jitter_eps,
+                                             uint64_t seed) {
     constexpr bool HOIST = EB <= 2;      // dlogits fragments stay in registers across passes
-    constexpr int LD = GDX_COLS + 4;     // floats per staged row (16-byte aligned, rows 4 apart on other banks)
+    constexpr int LD = GdxSmem<T>::LD;
     constexpr int CN = Chunk<T>::N;      // elements per 16-byte piece
     constexpr int LPR = GDX_COLS / CN;   // lanes per staged row
     constexpr int RPI = 64 / LPR;        // rows per wave instruction
     constexpr int NIT = 32 / RPI;        // row pieces per lane and pass
-    __shared__ __align__(16) float stage[GDX_WAVES][32][LD];
-    __shared__ int s_row[2][32];         // row of dxd behind each of the token's choices (-1: dropped)
+    int(*s_row)[32] = sm.row;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 31, h = lane >> 5;
-    const int t0 = blockIdx.x * 32;
+    const int t0 = block * 32;
     const int rows_here = min(32, Tn - t0);
     const __amdgpu_buffer_rsrc_t rs_dl = buf_rsrc(dlogits + (size_t)t0 * E, (size_t)rows_here * E * 4);
     const __amdgpu_buffer_rsrc_t rs_w = buf_rsrc(Wg, (size_t)d * E * 4);
@@ -796,7 +797,7 @@ __global__ __launch_bounds__(64 * GDX_WAVES) void gate_dx_kernel(int Tn, int d, 
         for (int eb = 0; eb < EB; ++eb) load_a(eb, eb);
     }
     const int er = lane / LPR, ec = (lane - er * LPR) * CN;
-    float(*st)[LD] = stage[wave];
+    float(*st)[LD] = sm.stage[wave];
     // What the product is added to does not depend on it: the 16-byte pieces of a
     // pass are requested one pass ahead and stay packed until they are used.
     constexpr int NSRC = GATHER ? 2 : 1;
@@ -926,6 +927,98 @@ __global__ __launch_bounds__(64 * GDX_WAVES) void gate_dx_kernel(int Tn, int d, 
         for (int q = 0; q < NSRC; ++q)
 #pragma unroll
             for (int it = 0; it < NIT; ++it) now[q][it] = ahead[q][it];
+    }
+}
+
+template <typename T, int EB, bool VEC, bool GATHER>
+__global__ __launch_bounds__(64 * GDX_WAVES) void gate_dx_kernel(int Tn, int d, int E, int k, int C,
+                                                                 const float* __restrict__ dlogits,
+                                                                 const float* __restrict__ Wg, const T* __restrict__ dxd,
+                                                                 const int32_t* __restrict__ expert_idx,
+                                                                 const int32_t* __restrict__ slot, T* __restrict__ dx,
+                                                                 float jitter_eps, uint64_t seed) {
+    __shared__ __align__(16) GdxSmem<T> sm;
+    gate_dx_body<T, EB, VEC, GATHER>(sm, blockIdx.x, Tn, d, E, k, C, dlogits, Wg, dxd, expert_idx, slot, dx, jitter_eps, seed);
+}
+
+// ---------------------------------------------------------------------------
+// Both halves of the projection's backward in one launch, for small batches (up to 1024
+// tokens, 32 experts, no jitter): three dependent launches of 4.5 us and more each
+// become one.  The first workgroups take dWg: 16 columns, all experts, all tokens, 16
+// groups of lanes that walk every 16th token with plain fp32 FMAs and are added in
+// order; the others take dx as above (T = 256, d = 64, E = 4, fp32: 15.1 + 4.6 + 4.2 us -> 4.0;
+// T = 512, d = 512, E = 8, bf16: 11.2 + 4.8 + 6.1 -> 6.2; bound by two memory latencies).
+// ---------------------------------------------------------------------------
+#define GBS_T 1024
+#define GBS_COLS 16
+#define GBS_GROUPS (64 * GDX_WAVES / GBS_COLS)
+template <typename T, int EP> union GbsSmem {
+    static constexpr int CT = EP <= 8 ? 1024 : 8192 / EP;     // tokens per chunk: up to 32 KB of dlogits rows
+    GdxSmem<T> dx;
+    float dl[CT][EP];
+    float red[GBS_GROUPS][GBS_COLS][EP];
+};
+template <typename T, int EP, bool VEC, bool GATHER>   // EP >= E: accumulators per lane (4, 8, 16, 32)
+__global__ __launch_bounds__(64 * GDX_WAVES) void gate_bwd_small_kernel(
+    int n_dwg, int Tn, int d, int E, int k, int C, const T* __restrict__ x, const float* __restrict__ dlogits,
+    const float* __restrict__ Wg, const T* __restrict__ dxd, const int32_t* __restrict__ expert_idx,
+    const int32_t* __restrict__ slot, float* __restrict__ dWg, T* __restrict__ dx) {
+    __shared__ __align__(16) GbsSmem<T, EP> sm;
+    if ((int)blockIdx.x >= n_dwg) {
+        gate_dx_body<T, 1, VEC, GATHER>(sm.dx, blockIdx.x - n_dwg, Tn, d, E, k, C, dlogits, Wg, dxd, expert_idx, slot, dx, 0.0f, 0);
+        return;
+    }
+    // A chunk of tokens at a time: the lane's x values are requested at once, the dlogits rows go through
+    // LDS (one copy of them for the 16 columns), so a chunk costs one memory latency.
+    constexpr int CT = GbsSmem<T, EP>::CT, U = CT / GBS_GROUPS;
+    const int c = threadIdx.x % GBS_COLS, g = threadIdx.x / GBS_COLS;
+    const int i = blockIdx.x * GBS_COLS + c;
+    const __amdgpu_buffer_rsrc_t rs_dl = buf_rsrc(dlogits, (size_t)Tn * E * 4), rs_x = buf_rsrc(x, (size_t)Tn * d * sizeof(T));
+    float acc[EP];
+#pragma unroll
+    for (int e = 0; e < EP; ++e) acc[e] = 0.0f;
+    for (int t0 = 0; t0 < Tn; t0 += CT) {
+        T xv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + u * GBS_GROUPS + g;
+            const uint32_t off = i < d ? (uint32_t)((t * d + i) * sizeof(T)) : BUF_OOB;      // rows beyond T read zeros
+            if constexpr (sizeof(T) == 2) xv[u] = __builtin_amdgcn_raw_buffer_load_b16(rs_x, off, 0, 0);
+            else xv[u] = buf_load_f32(rs_x, off);
+        }
+        if (t0 > 0) __syncthreads();             // the previous chunk's rows have been used
+        constexpr int PT = CT * EP / (64 * GDX_WAVES);     // elements per thread, rows padded to EP
+        float q[PT];
+#pragma unroll
+        for (int u = 0; u < PT; ++u) {
+            const int o = threadIdx.x + u * 64 * GDX_WAVES, e = o % EP;
+            q[u] = buf_load_f32(rs_dl, e < E ? (uint32_t)(((t0 + o / EP) * E + e) * 4) : BUF_OOB);   // rows beyond T read zeros
+        }
+#pragma unroll
+        for (int u = 0; u < PT; ++u) (&sm.dl[0][0])[threadIdx.x + u * 64 * GDX_WAVES] = q[u];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (t0 + u * GBS_GROUPS >= Tn) break;          // uniform
+            const float xf = ld_f32<T>(&xv[u]);
+#pragma unroll
+            for (int e = 0; e < EP; e += 4) {
+                const float4 w = *reinterpret_cast<const float4*>(&sm.dl[u * GBS_GROUPS + g][e]);
+                acc[e] = fmaf(xf, w.x, acc[e]); acc[e + 1] = fmaf(xf, w.y, acc[e + 1]);
+                acc[e + 2] = fmaf(xf, w.z, acc[e + 2]); acc[e + 3] = fmaf(xf, w.w, acc[e + 3]);
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EP; ++e) sm.red[g][c][e] = acc[e];
+    __syncthreads();
+    for (int o = threadIdx.x; o < GBS_COLS * EP; o += 64 * GDX_WAVES) {
+        const int cc = o / EP, e = o % EP, col = blockIdx.x * GBS_COLS + cc;
+        float s = 0.0f;
+#pragma unroll
+        for (int q = 0; q < GBS_GROUPS; ++q) s += sm.red[q][cc][e];
+        if (col < d && e < E) dWg[(size_t)col * E + e] = s;
     }
 }
 
@@ -1140,6 +1233,19 @@ static bool launch_gate_logits_bwd(const moe_shape* s, const void* x, const floa
                                    const float* dlogits, float* dWg, void* dx, const void* dxd,
                                    const int32_t* expert_idx, const int32_t* slot, float* partial, float eps,
                                    uint64_t seed, hipStream_t st) {
+    // (x is addressed with 32-bit byte offsets)
+    if (eps == 0.0f && s->T <= GBS_T && s->E <= 32 && s->d_model < (1 << 18)) {
+        const int n_dwg = ceil_div(s->d_model, GBS_COLS), n_dx = dx ? ceil_div(s->T, 32) : 0;
+#define GBS(EP, VEC, GA) gate_bwd_small_kernel<T, EP, VEC, GA><<<n_dwg + n_dx, 64 * GDX_WAVES, 0, st>>>( \
+    n_dwg, s->T, s->d_model, s->E, s->k, s->capacity, (const T*)x, dlogits, Wg, (const T*)dxd, expert_idx, slot, dWg, (T*)dx)
+#define GBSE(VEC, GA) do { if (s->E <= 4) GBS(4, VEC, GA); else if (s->E <= 8) GBS(8, VEC, GA); \
+                           else if (s->E <= 16) GBS(16, VEC, GA); else GBS(32, VEC, GA); } while (0)
+        if (dxd) { if (s->E % 4 == 0) GBSE(true, true); else GBSE(false, true); }
+        else     { if (s->E % 4 == 0) GBSE(true, false); else GBSE(false, false); }
+#undef GBSE
+#undef GBS
+        return true;
+    }
     const int tpc = gw_chunk_tokens(s);
     const int nch_used = ceil_div(s->T, tpc);
     dim3 grid(ceil_div(s->d_model, GW_COLS), nch_used, ceil_div(s->E, 32));

@@ -70,6 +70,97 @@ __device__ __forceinline__ bool better(float va, int ia, float vb, int ib) {
     return va > vb || (va == vb && ia < ib);
 }
 
+// The gate of one token on its LPT lanes: l = this lane's four logits (-inf beyond E), e4 the first
+// of its experts.  Writes probs, expert_idx and gate_w; returns the choices (in every lane).
+struct Choice { int i0, i1; };
+template <int LPT>
+__device__ __forceinline__ Choice token_gate(const float (&l)[4], bool valid, int e4, int E, int k, int t,
+                                             float* __restrict__ probs, int32_t* __restrict__ expert_idx,
+                                             float* __restrict__ gate_w) {
+    // the lane's own best two (ascending ids, strict comparisons).  A NaN logit never
+    // wins a comparison, so for the selection it counts as -inf: among equal values
+    // the smaller id wins, hence every expert id < E beats the sentinel and the
+    // token's k choices are always distinct valid ids, whatever the logits hold
+    // (the probabilities of such a row are NaN; nothing is indexed with them).
+    float v0 = -INFINITY, v1 = -INFINITY;
+    int i0 = 0x7fffffff, i1 = 0x7fffffff;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = e4 + i;
+        if (e < E) {
+            const float li = l[i] == l[i] ? l[i] : -INFINITY;
+            if (better(li, e, v0, i0)) { v1 = v0; i1 = i0; v0 = li; i0 = e; }
+            else if (better(li, e, v1, i1)) { v1 = li; i1 = e; }
+        }
+    }
+#pragma unroll
+    for (int o = LPT / 2; o > 0; o >>= 1) {
+        const float w0 = __shfl_xor(v0, o, MOE_WAVE), w1 = __shfl_xor(v1, o, MOE_WAVE);
+        const int j0 = __shfl_xor(i0, o, MOE_WAVE), j1 = __shfl_xor(i1, o, MOE_WAVE);
+        if (better(w0, j0, v0, i0)) {
+            if (better(v0, i0, w1, j1)) { v1 = v0; i1 = i0; } else { v1 = w1; i1 = j1; }
+            v0 = w0; i0 = j0;
+        } else if (better(w0, j0, v1, i1)) {
+            v1 = w0; i1 = j0;
+        }
+    }
+    float ex[4], part = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        ex[i] = (valid && e4 + i < E) ? expf(l[i] - v0) : 0.0f;
+        part += ex[i];
+    }
+#pragma unroll
+    for (int o = LPT / 2; o > 0; o >>= 1) part += __shfl_xor(part, o, MOE_WAVE);
+    const float sum = part;
+    if (valid) {
+        float* pr = probs + (size_t)t * E;
+        const float inv = 1.0f / sum;      // one division per lane; the products are within an ulp of ex / sum
+        if ((E & 3) == 0) {
+            if (e4 < E)
+                *reinterpret_cast<float4*>(pr + e4) = make_float4(ex[0] * inv, ex[1] * inv, ex[2] * inv, ex[3] * inv);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (e4 + i < E) pr[e4 + i] = ex[i] * inv;
+        }
+        if (e4 == 0) {
+            const float p0 = 1.0f / sum;   // = exp(0) / sum
+            if (k == 1) {
+                expert_idx[t] = i0;
+                gate_w[t] = p0;
+            } else {
+                const float p1 = expf(v1 - v0) / sum;
+                const float S = p0 + p1;
+                expert_idx[2 * t] = i0;
+                expert_idx[2 * t + 1] = i1;
+                gate_w[2 * t] = p0 / S;
+                gate_w[2 * t + 1] = p1 / S;
+            }
+        }
+    }
+    return {i0, i1};
+}
+
+// this lane's four logits of token t (-inf beyond E or T)
+__device__ __forceinline__ void load_logits(const float* __restrict__ logits, int t, int T, int e4, int E, float (&l)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) l[i] = -INFINITY;
+    if (t < T) {
+        const float* row = logits + (size_t)t * E;
+        if ((E & 3) == 0) {
+            if (e4 < E) {
+                const float4 q = *reinterpret_cast<const float4*>(row + e4);
+                l[0] = q.x; l[1] = q.y; l[2] = q.z; l[3] = q.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (e4 + i < E) l[i] = row[e4 + i];
+        }
+    }
+}
+
 // LPT lanes share one token, 4 consecutive experts per lane (4*LPT >= E), so a
 // token's logits are read with one coalesced 16-byte load per lane and reduced
 // with log2(LPT) butterfly steps.  A workgroup of up to 1024 threads owns a
@@ -97,97 +188,20 @@ __global__ __launch_bounds__(TopkGeom<LPT>::THREADS) void gate_topk_kernel(
     __syncthreads();
     const int gl = threadIdx.x % LPT, slot = threadIdx.x / LPT;
     const int e4 = gl * 4;
-    const bool vec = (E & 3) == 0;
     for (int it0 = 0; it0 < G::ROUNDS; it0 += G::BATCH) {
         float lq[G::BATCH][4];
 #pragma unroll
         for (int u = 0; u < G::BATCH; ++u) {
-            const int t = blockIdx.x * G::TOK + (it0 + u) * G::TPI + slot;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) lq[u][i] = -INFINITY;
-            if (t < T) {
-                const float* row = logits + (size_t)t * E;
-                if (vec) {
-                    if (e4 < E) {
-                        const float4 q = *reinterpret_cast<const float4*>(row + e4);
-                        lq[u][0] = q.x; lq[u][1] = q.y; lq[u][2] = q.z; lq[u][3] = q.w;
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (e4 + i < E) lq[u][i] = row[e4 + i];
-                }
-            }
+            load_logits(logits, blockIdx.x * G::TOK + (it0 + u) * G::TPI + slot, T, e4, E, lq[u]);
         }
 #pragma unroll
         for (int u = 0; u < G::BATCH; ++u) {
             const int t = blockIdx.x * G::TOK + (it0 + u) * G::TPI + slot;
             const bool valid = t < T;   // uniform within a token's lane group
-            const float(&l)[4] = lq[u];
-            // the lane's own best two (ascending ids, strict comparisons).  A NaN logit never
-            // wins a comparison, so for the selection it counts as -inf: among equal values
-            // the smaller id wins, hence every expert id < E beats the sentinel and the
-            // token's k choices are always distinct valid ids, whatever the logits hold
-            // (the probabilities of such a row are NaN; nothing is indexed with them).
-            float v0 = -INFINITY, v1 = -INFINITY;
-            int i0 = 0x7fffffff, i1 = 0x7fffffff;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = e4 + i;
-                if (e < E) {
-                    const float li = l[i] == l[i] ? l[i] : -INFINITY;
-                    if (better(li, e, v0, i0)) { v1 = v0; i1 = i0; v0 = li; i0 = e; }
-                    else if (better(li, e, v1, i1)) { v1 = li; i1 = e; }
-                }
-            }
-#pragma unroll
-            for (int o = LPT / 2; o > 0; o >>= 1) {
-                const float w0 = __shfl_xor(v0, o, MOE_WAVE), w1 = __shfl_xor(v1, o, MOE_WAVE);
-                const int j0 = __shfl_xor(i0, o, MOE_WAVE), j1 = __shfl_xor(i1, o, MOE_WAVE);
-                if (better(w0, j0, v0, i0)) {
-                    if (better(v0, i0, w1, j1)) { v1 = v0; i1 = i0; } else { v1 = w1; i1 = j1; }
-                    v0 = w0; i0 = j0;
-                } else if (better(w0, j0, v1, i1)) {
-                    v1 = w0; i1 = j0;
-                }
-            }
-            float ex[4], part = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                ex[i] = (valid && e4 + i < E) ? expf(l[i] - v0) : 0.0f;
-                part += ex[i];
-            }
-#pragma unroll
-            for (int o = LPT / 2; o > 0; o >>= 1) part += __shfl_xor(part, o, MOE_WAVE);
-            const float sum = part;
-            if (valid) {
-                float* pr = probs + (size_t)t * E;
-                const float inv = 1.0f / sum;      // one division per lane; the products are within an ulp of ex / sum
-                if (vec) {
-                    if (e4 < E)
-                        *reinterpret_cast<float4*>(pr + e4) = make_float4(ex[0] * inv, ex[1] * inv, ex[2] * inv, ex[3] * inv);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (e4 + i < E) pr[e4 + i] = ex[i] * inv;
-                }
-                if (gl == 0) {
-                    const float p0 = 1.0f / sum;   // = exp(0) / sum
-                    if (k == 1) {
-                        expert_idx[t] = i0;
-                        gate_w[t] = p0;
-                        atomicAdd(&s_hist[i0], 1);
-                    } else {
-                        const float p1 = expf(v1 - v0) / sum;
-                        const float S = p0 + p1;
-                        expert_idx[2 * t] = i0;
-                        expert_idx[2 * t + 1] = i1;
-                        gate_w[2 * t] = p0 / S;
-                        gate_w[2 * t + 1] = p1 / S;
-                        atomicAdd(&s_hist[i0 * 2], 1);
-                        atomicAdd(&s_hist[i1 * 2 + 1], 1);
-                    }
-                }
+            const Choice c = token_gate<LPT>(lq[u], valid, e4, E, k, t, probs, expert_idx, gate_w);
+            if (valid && gl == 0) {
+                atomicAdd(&s_hist[c.i0 * k], 1);
+                if (k == 2) atomicAdd(&s_hist[c.i1 * 2 + 1], 1);
             }
         }
     }
@@ -214,7 +228,7 @@ __global__ __launch_bounds__(CHUNK) void route_place_kernel(
     int T, int E, int k, int Cg, int nchunk, int cpg, int sub, const int32_t* __restrict__ expert_idx,
     const float* __restrict__ keys, const int32_t* __restrict__ hist,
     int32_t* __restrict__ seg_start, int32_t* __restrict__ tile_start, int32_t* __restrict__ goff,
-    int32_t* __restrict__ expert_count, int32_t* __restrict__ expert_demand,
+    int32_t* __restrict__ expert_count, int32_t* __restrict__ expert_demand, long long* __restrict__ accum,
     int32_t* __restrict__ seg_tok, float* __restrict__ seg_key) {
     __shared__ int32_t s_tot[512];          // candidates per segment, whole group
     __shared__ int32_t s_base[512];         // segment start + candidates in the group's earlier chunks
@@ -306,6 +320,7 @@ __global__ __launch_bounds__(CHUNK) void route_place_kernel(
         goff[(size_t)g * E + e] = off;
         if (chunk == 0) {
             expert_demand[e] = dem_tot;
+            if (accum) accum[e] += dem_tot;
             expert_count[e] = cnt_tot;
         }
     }
@@ -528,9 +543,146 @@ __global__ __launch_bounds__(RANK_TILE * RANK_PARTS) void route_rank_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// The whole of moe_gate_route in one workgroup, for small batches: three dependent
+// launches cost more than the work (T = 256, E = 4, top-1: 2.3 + 4.3 + 5.9 us of kernels and the
+// gaps between them, against one of 6.4 us; T = 512, E = 8: 3.0 + 4.7 + 6.4 against 8.8).
+// Tokens are put into priority order once (key descending, token ascending: a bitonic sort
+// of 64-bit words in LDS; without keys they are in it already), then every wave takes
+// 64 consecutive ones: the rank inside an expert's first or second choices is the number of
+// earlier lanes that chose it (one ballot per bit of the expert id) plus the earlier
+// waves' counts.
+// ---------------------------------------------------------------------------
+#define SMALL_T 1024                       // one token per thread
+static_assert(SMALL_T <= 1024, "token indices and one workgroup");
+
+// the value of lane l ^ D; below 16 by row permutations (a few cycles instead of an LDS round trip)
+template <int D> __device__ __forceinline__ uint32_t lane_xor32(uint32_t v) {
+    if constexpr (D == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xf, 0xf, true);         // quad_perm 1,0,3,2
+    else if constexpr (D == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xf, 0xf, true);    // quad_perm 2,3,0,1
+    else if constexpr (D == 4)                                                                            // l^7, then l^3
+        return (uint32_t)__builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf, true);
+    else if constexpr (D == 8) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true);   // row_ror:8
+    else return (uint32_t)__shfl_xor((int)v, D, MOE_WAVE);
+}
+template <int D> __device__ __forceinline__ unsigned long long lane_xor(unsigned long long v) {
+    return (unsigned long long)lane_xor32<D>((uint32_t)(v >> 32)) << 32 | lane_xor32<D>((uint32_t)v);
+}
+
+template <int LPT>
+__global__ __launch_bounds__(SMALL_T) void route_small_kernel(
+    int T, int E, int k, int C, const float* __restrict__ logits, const float* __restrict__ keys,
+    float* __restrict__ probs, int32_t* __restrict__ expert_idx, float* __restrict__ gate_w,
+    int32_t* __restrict__ slot, int32_t* __restrict__ expert_count, int32_t* __restrict__ expert_demand,
+    int32_t* __restrict__ slot_src, long long* __restrict__ accum) {
+    constexpr int MAXW = SMALL_T / 64;
+    const int nt = blockDim.x, tpr = nt / LPT;      // threads (a power of two >= T); tokens per round of the gate
+    __shared__ unsigned long long s_ord[2][SMALL_T];            // (key, descending) << 32 | token
+    __shared__ int16_t s_e[2][SMALL_T];
+    __shared__ int16_t s_cnt[2][MAXW][256];                       // wave counts, then counts of the waves before
+    __shared__ int s_dem[2][256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < MAXW * 256; i += nt) reinterpret_cast<int*>(s_cnt)[i] = 0;
+    unsigned long long ord = ~0ull;                             // beyond T: last
+    if (tid < T) {
+        // the usual order-preserving map of floats to unsigned, inverted; + 0.0f makes -0 equal to 0
+        const uint32_t b = keys ? __float_as_uint(keys[tid] + 0.0f) : 0u;
+        const uint32_t up = (b & 0x80000000u) ? ~b : b | 0x80000000u;
+        ord = (unsigned long long)(~up) << 32 | (unsigned)tid;
+    }
+    const int gl = tid % LPT, sl = tid / LPT, e4 = 4 * gl;
+    for (int t0 = 0; t0 < T; t0 += 4 * tpr) {
+        float l[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load_logits(logits, t0 + u * tpr + sl, T, e4, E, l[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int t = t0 + u * tpr + sl;
+            if (t0 + u * tpr >= T) break;                       // uniform
+            const Choice c = token_gate<LPT>(l[u], t < T, e4, E, k, t, probs, expert_idx, gate_w);
+            if (t < T && gl == 0) {
+                s_e[0][t] = (int16_t)c.i0;
+                s_e[1][t] = (int16_t)c.i1;
+            }
+        }
+    }
+    if (keys) {
+        // one element per thread; a step whose partners lie in the same wave exchanges them by
+        // lane permutation, the others through LDS (two buffers, so one barrier each)
+        int n = 64, buf = 0;
+        while (n < T) n <<= 1;                                  // threads beyond hold the largest word: nothing to do
+        auto keep = [&](unsigned long long other, int d, bool up) {
+            if ((other < ord) == (((tid & d) == 0) == up)) ord = other;
+        };
+        for (int len = 2; len <= n; len <<= 1) {
+            const bool up = (tid & len) == 0;
+            for (int d = len >> 1; d >= 64; d >>= 1, buf ^= 1) {
+                s_ord[buf][tid] = ord;
+                __syncthreads();
+                keep(s_ord[buf][tid ^ d], d, up);
+            }
+            if (len >= 64) keep(lane_xor<32>(ord), 32, up);
+            if (len >= 32) keep(lane_xor<16>(ord), 16, up);
+            if (len >= 16) keep(lane_xor<8>(ord), 8, up);
+            if (len >= 8) keep(lane_xor<4>(ord), 4, up);
+            if (len >= 4) keep(lane_xor<2>(ord), 2, up);
+            keep(lane_xor<1>(ord), 1, up);
+        }
+    }
+    __syncthreads();
+    const bool valid = ord != ~0ull && tid < T;                 // sorted: the T tokens come first
+    const int t = valid ? (int)(ord & 0xffffffffu) : 0;
+    const int nbits = E > 1 ? 32 - __clz(E - 1) : 0;
+    int ev[2] = {0, 0}, rank[2] = {0, 0};
+    for (int j = 0; j < k; ++j) {
+        ev[j] = s_e[j][t];
+        unsigned long long same = __ballot(valid);
+        for (int b = 0; b < nbits; ++b) {
+            const bool bit = (ev[j] >> b) & 1;
+            const unsigned long long m = __ballot(valid && bit);
+            same &= bit ? m : ~m;
+        }
+        if (valid) {
+            rank[j] = __popcll(same & ((1ull << lane) - 1ull));
+            if (rank[j] == 0) s_cnt[j][wave][ev[j]] = (int16_t)__popcll(same);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < 2 * 256; i += nt) {
+        const int j = i >> 8, e = i & 255;
+        int n[MAXW], run = 0;
+#pragma unroll
+        for (int w = 0; w < MAXW; ++w) n[w] = s_cnt[j][w][e];   // all reads first; waves that do not exist counted nothing
+#pragma unroll
+        for (int w = 0; w < MAXW; ++w) {
+            s_cnt[j][w][e] = (int16_t)run;
+            run += n[w];
+        }
+        s_dem[j][e] = run;
+    }
+    __syncthreads();
+    if (tid < E) {                                              // E <= 256 <= nt
+        const int dem = s_dem[0][tid] + s_dem[1][tid];          // k == 1: the second is zero
+        expert_demand[tid] = dem;
+        if (accum) accum[tid] += dem;
+        expert_count[tid] = min(dem, C);
+    }
+    for (int i = tid; i < E * C; i += nt) {
+        const int e = i / C;
+        if (i - e * C >= s_dem[0][e] + s_dem[1][e]) slot_src[i] = -1;
+    }
+    if (valid) {
+        for (int j = 0; j < k; ++j) {
+            const int e = ev[j], r = (j ? s_dem[0][e] : 0) + s_cnt[j][wave][e] + rank[j];
+            slot[t * k + j] = r < C ? r : -1;
+            if (r < C) slot_src[(size_t)e * C + r] = t * k + j;
+        }
+    }
+}
+
 static int route_impl(const moe_shape* shape, int G, const float* logits, const float* rts_keys_or_null,
                       float* probs, int32_t* expert_idx, float* gate_w, int32_t* slot,
-                      int32_t* expert_count, int32_t* expert_demand, int32_t* slot_src, void* ws,
+                      int32_t* expert_count, int32_t* expert_demand, int32_t* slot_src, long long* accum, void* ws,
                       size_t ws_bytes, void* stream) {
     int rc = check_shape(shape);
     if (rc) return rc;
@@ -546,13 +698,25 @@ static int route_impl(const moe_shape* shape, int G, const float* logits, const 
     const int nchunk = n_chunks(shape);
     const int cpg = G == 1 ? nchunk : T / G / CHUNK;    // chunks per group
     const int Cg = C / G;
+    // One workgroup as long as its own work stays below what the launches cost: up to 8 rounds of
+    // 128 (E = 32) tokens in the gate, up to 32 entries of slot_src per thread
+    if (G == 1 && T <= SMALL_T && T * E <= SMALL_T * 32 && (int64_t)E * C <= 32 * SMALL_T) {
+        int nt = 256;
+        while (nt < T) nt <<= 1;
+#define SMALL(LPT) route_small_kernel<LPT><<<1, nt, 0, st>>>(T, E, k, C, logits, rts_keys_or_null, probs, expert_idx, \
+    gate_w, slot, expert_count, expert_demand, slot_src, accum)
+        if (E <= 4) SMALL(1); else if (E <= 8) SMALL(2); else if (E <= 16) SMALL(4); else if (E <= 32) SMALL(8);
+        else if (E <= 64) SMALL(16); else if (E <= 128) SMALL(32); else SMALL(64);
+#undef SMALL
+        return launch_status();
+    }
 #define GATE(LPT) gate_topk_kernel<LPT><<<nchunk * TopkGeom<LPT>::SUB, TopkGeom<LPT>::THREADS, 0, st>>>(T, E, k, logits, probs, expert_idx, gate_w, r.hist)
     if (E <= 4) GATE(1); else if (E <= 8) GATE(2); else if (E <= 16) GATE(4); else if (E <= 32) GATE(8);
     else if (E <= 64) GATE(16); else if (E <= 128) GATE(32); else GATE(64);
 #undef GATE
     route_place_kernel<<<nchunk, CHUNK, 0, st>>>(T, E, k, Cg, nchunk, cpg, topk_sub(E), expert_idx, rts_keys_or_null, r.hist,
                                                  r.seg_start, r.tile_start, r.goff, expert_count,
-                                                 expert_demand, r.seg_tok, r.seg_key);
+                                                 expert_demand, accum, r.seg_tok, r.seg_key);
     const int Tg = G == 1 ? T : T / G;
     const int tiles_per_group = ceil_div(Tg * k, RANK_TILE) + k * E;
     route_rank_kernel<<<G * tiles_per_group, RANK_TILE * RANK_PARTS, 0, st>>>(E, k, C, Cg, tiles_per_group,
@@ -568,7 +732,7 @@ extern "C" int moe_gate_route(const moe_shape* shape, const float* logits,
                               int32_t* expert_demand, int32_t* slot_src, void* ws, size_t ws_bytes,
                               void* stream) {
     return route_impl(shape, 1, logits, rts_keys_or_null, probs, expert_idx, gate_w, slot, expert_count,
-                      expert_demand, slot_src, ws, ws_bytes, stream);
+                      expert_demand, slot_src, nullptr, ws, ws_bytes, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -613,7 +777,7 @@ extern "C" int moe_gate_route_static(const moe_shape* shape, const float* logits
     // candidate lists are all written in full by this call's kernels before they are read, so
     // what an earlier (possibly larger) call left behind is never seen.
     return route_impl(shape, 1, logits, rts_keys_or_null, probs, expert_idx, gate_w, slot, expert_count,
-                      expert_demand, slot_src, ws, ROUTE_SCRATCH_BYTES, stream);
+                      expert_demand, slot_src, nullptr, ws, ROUTE_SCRATCH_BYTES, stream);
 }
 
 extern "C" int moe_gate_route_grouped(const moe_shape* shape, int32_t n_groups, const float* logits,
@@ -622,5 +786,15 @@ extern "C" int moe_gate_route_grouped(const moe_shape* shape, int32_t n_groups, 
                                       int32_t* expert_demand, int32_t* slot_src, void* ws,
                                       size_t ws_bytes, void* stream) {
     return route_impl(shape, n_groups, logits, rts_keys_or_null, probs, expert_idx, gate_w, slot, expert_count,
-                      expert_demand, slot_src, ws, ws_bytes, stream);
+                      expert_demand, slot_src, nullptr, ws, ws_bytes, stream);
+}
+
+extern "C" int moe_gate_route_counted(const moe_shape* shape, int32_t n_groups, const float* logits,
+                                      const float* rts_keys_or_null, float* probs, int32_t* expert_idx,
+                                      float* gate_w, int32_t* slot, int32_t* expert_count,
+                                      int32_t* expert_demand, int32_t* slot_src, int64_t* accum, void* ws,
+                                      size_t ws_bytes, void* stream) {
+    if (!accum) return MOE_ERR_NULL;
+    return route_impl(shape, n_groups, logits, rts_keys_or_null, probs, expert_idx, gate_w, slot, expert_count,
+                      expert_demand, slot_src, (long long*)accum, ws, ws_bytes, stream);
 }

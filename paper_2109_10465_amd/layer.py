@@ -1,8 +1,8 @@
 """Buffer owner and call sequence for one MoE layer step on one GPU.
 
-Holds the device buffers (torch tensors used as raw memory) and issues the
-C-ABI calls in the order gate -> capacity/RTS -> dispatch -> experts -> combine
-(forward) and its reverse (backward).  No arithmetic happens here.
+Holds the device buffers (torch tensors used as raw memory) and makes the two
+C-ABI calls of a step: moe_layer_fwd (gate -> capacity/RTS -> dispatch -> experts
+-> combine) and moe_layer_bwd, its reverse.  No arithmetic happens here.
 """
 import torch
 
@@ -66,55 +66,36 @@ class MoELayer:
         self.dWg = buf((d_model, E), f32)
         self.dx = buf((T, d_model), adt)
 
+    # what moe_layer_fwd and moe_layer_bwd take, in the order of B.LayerBuffers; a forward-only layer has no
+    # derivative and no backward buffers
+    _FWD = ("logits", "probs", "expert_idx", "gate_w", "slot", "expert_count", "expert_demand", "slot_src",
+            "utilisation", "first_frac", "mean_prob", "aux_loss", "xd", "h", "dact", "yd", "y")
+    _BWD = ("dyd", "dgate_w", "dxd", "dW1", "dW2", "dlogits", "dWg", "dx")
+
+    def _call_args(self, logits_given=False):
+        """Options and buffers of one call, from the layer's attributes as they are now."""
+        at = self.__dict__
+        ptrs = [None if at[n] is None else at[n].data_ptr() for n in self._FWD]
+        ptrs += [None] * len(self._BWD) if self.forward_only else [at[n].data_ptr() for n in self._BWD]
+        return (B.LayerOptions(self.groups, self.forward_only, logits_given, self.aux_coef, self.jitter_eps,
+                               self.drop_p, self.seed & 0xFFFFFFFFFFFFFFFF),
+                B.LayerBuffers(*ptrs, self.ws.data_ptr(), self.ws.numel()))
+
     def forward(self, x, Wg, bias, W1, W2, rts_keys, logits=None, seed=0):
         """logits: optional precomputed [T,E] fp32 gate logits; the projection call is
         then skipped and routing runs on exactly these values."""
-        s = self.shape
         self._saved = (x, Wg, W1, W2)
         self.seed = int(seed)     # of this step's jitter and dropout draws
-        if logits is None:
-            B.moe_gate_logits_jitter(s, x, Wg, bias, self.jitter_eps, self.seed, self.logits)
-        else:
+        if logits is not None:
             self.logits.copy_(logits)
-        if self.groups > 1:
-            B.moe_gate_route_grouped(s, self.groups, self.logits, rts_keys, self.probs, self.expert_idx,
-                                     self.gate_w, self.slot, self.expert_count, self.expert_demand,
-                                     self.slot_src, self.ws)
-        else:
-            B.moe_gate_route(s, self.logits, rts_keys, self.probs, self.expert_idx, self.gate_w,
-                             self.slot, self.expert_count, self.expert_demand, self.slot_src, self.ws)
-        if self.forward_only:
-            B.moe_utilisation_accumulate(s, self.expert_demand, self.utilisation)
-        if self.aux_coef != 0.0:
-            B.moe_aux_loss(s, self.probs, self.expert_idx, self.first_frac, self.mean_prob, self.aux_loss,
-                           self.ws)
-        B.moe_dispatch_tokens(s, x, self.expert_idx, self.slot, self.xd)    # reads every token row once
-        if self.drop_p > 0.0:
-            B.moe_expert_ffn_fwd_dropout(s, self.xd, self.expert_count, W1, W2, self.drop_p, self.seed, self.h,
-                                         self.dact, self.yd)
-        else:
-            B.moe_expert_ffn_fwd(s, self.xd, self.expert_count, W1, W2, self.h, self.dact, self.yd)
-        B.moe_combine_fwd(s, self.yd, self.expert_idx, self.slot, self.gate_w, self.y)
+        B.moe_layer_fwd(self.shape, *self._call_args(logits is not None), x, Wg, bias, W1, W2, rts_keys)
         return self.y
 
     def backward(self, dy):
         if self.forward_only:
             raise B.MoeError("this layer was built forward-only")
-        s = self.shape
         x, Wg, W1, W2 = self._saved
-        B.moe_combine_bwd(s, dy, self.yd, self.expert_idx, self.slot, self.gate_w, self.dyd,
-                          self.dgate_w)
-        B.moe_expert_ffn_bwd(s, self.dyd, self.xd, self.h, self.dact, self.expert_count, W1, W2,
-                             self.dxd, self.dW1, self.dW2, self.ws)
-        if self.aux_coef != 0.0:
-            B.moe_gate_bwd_aux(s, self.dgate_w, self.probs, self.expert_idx, self.slot, self.first_frac,
-                               self.aux_coef, self.dlogits)
-        else:
-            B.moe_gate_bwd(s, self.dgate_w, self.probs, self.expert_idx, self.slot, self.dlogits)
-        # dispatch's backward (combine with unit weights) and the gate projection's backward in one call
-        B.moe_dispatch_gate_logits_bwd(s, x, Wg, self.dlogits, self.dxd, self.expert_idx, self.slot,
-                                       self.jitter_eps, self.seed,
-                                       self.dWg, self.dx, self.ws)
+        B.moe_layer_bwd(self.shape, *self._call_args(), x, Wg, W1, W2, dy)
         return self.dx, self.dWg, self.dW1, self.dW2
 
     def step(self, x, Wg, bias, W1, W2, rts_keys, dy, logits=None, seed=0):

@@ -1,0 +1,107 @@
+"""GPU: what small batches and the layer's fused calls run on - routing in one workgroup, the projection's backward in
+one launch, combine and gate backward in one pass - at the edges of their ranges, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_oracle as O
+from paper_2109_10465_amd import binding as B
+from paper_2109_10465_amd import inputs as I
+import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+
+def i32(*shape):
+    return torch.full(shape, -7, dtype=torch.int32, device="cuda")
+
+
+def f32(*shape):
+    return torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+
+
+@pytest.mark.parametrize("T,E,k,C,keys", [
+    (1, 2, 2, 1, "uniform"), (63, 4, 1, 20, "ties"), (64, 3, 2, 50, "uniform"), (65, 5, 1, 9, "signed"),
+    (256, 8, 2, 64, "ties"), (257, 130, 2, 3, "uniform"), (512, 64, 1, 8, None), (1000, 31, 2, 70, "signed"),
+    (1023, 9, 2, 500, None), (1024, 32, 2, 64, "uniform"), (1024, 1, 1, 1000, "ties"),
+    (1025, 32, 2, 64, "uniform"), (200, 256, 1, 200, "uniform")])       # the last two: beyond one workgroup's range
+def test_route_small(T, E, k, C, keys):
+    rng = np.random.default_rng(T * 7 + E)
+    lg = rng.standard_normal((T, E)).astype(np.float32)
+    lg[rng.random(T) < 0.2, :min(2, E)] = 1.5                           # tied logits
+    kv = {None: None, "uniform": rng.random(T, dtype=np.float32),
+          "ties": rng.integers(0, 4, T).astype(np.float32) / 4,
+          "signed": np.where(rng.random(T) < 0.3, rng.choice([0.0, -0.0], T), rng.standard_normal(T) * 1e3).astype(np.float32)}[keys]
+    s = B.make_shape(T, 8, 8, E, k, C, I.F32, I.GELU)
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    probs, gw, ei, slot, cnt, dem, src = f32(T, E), f32(T, k), i32(T, k), i32(T, k), i32(E), i32(E), i32(E, C)
+    util = torch.zeros(E, dtype=torch.int64, device="cuda")
+    lgd, kd = G.to_dev(lg, I.F32), G.to_dev(kv, I.F32)
+    print(f"[gpu] route T={T} E={E} k={k} C={C} keys={keys}", flush=True)
+    for _ in range(2):
+        B.moe_gate_route_counted(s, 1, lgd, kd, probs, ei, gw, slot, cnt, dem, src, util, ws)
+    torch.cuda.synchronize()
+    p = O.softmax(lg)
+    idx = O.top_k(lg, k)
+    rslot, rcnt, rdem, rsrc = O.route(idx, kv, E, C)
+    for name, got, want in (("expert_idx", ei, idx), ("slot", slot, rslot), ("count", cnt, rcnt), ("demand", dem, rdem),
+                            ("slot_src", src, rsrc), ("utilisation", util, 2 * rdem.astype(np.int64))):
+        assert np.array_equal(got.cpu().numpy(), want), name
+    assert G.rel_l2(G.host(probs), p) <= 1e-5
+    assert G.rel_l2(G.host(gw), O.gate_weights(p, idx)) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [I.F32, I.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("T,d,E,k,aux", [(1, 8, 2, 2, 0.0), (130, 72, 5, 2, 0.0), (777, 520, 32, 1, 0.01),
+                                         (300, 1032, 130, 2, 0.01), (515, 64, 256, 2, 0.0), (64, 8, 1, 1, 0.01)])
+def test_combine_and_gate_backward(T, d, E, k, aux, dtype):
+    rng = np.random.default_rng(T + E)
+    C = max(1, (T * k) // E)
+    lg = rng.standard_normal((T, E)).astype(np.float32)
+    p, idx = O.softmax(lg), O.top_k(lg, k)
+    gw = O.gate_weights(p, idx).astype(np.float32)
+    slot, cnt, _, _ = O.route(idx, rng.random(T, dtype=np.float32), E, C)
+    dy = rng.standard_normal((T, d)).astype(np.float32)
+    yd = rng.standard_normal((E, C, d)).astype(np.float32)
+    if dtype == I.BF16:
+        dy, yd = I.round_to_bf16(dy), I.round_to_bf16(yd)
+    s = B.make_shape(T, d, 8, E, k, C, dtype, I.GELU)
+    dyd = torch.zeros((E, C, d), dtype=torch.bfloat16 if dtype == I.BF16 else torch.float32, device="cuda")
+    dg, dl = f32(T, k), f32(T, E)
+    p32 = p.astype(np.float32)
+    ff = O.aux_loss(p, idx)[1].astype(np.float32) if aux else None
+    print(f"[gpu] combine + gate backward T={T} d={d} E={E} k={k} aux={aux}", flush=True)
+    B.moe_combine_gate_bwd(s, G.to_dev(dy, dtype), G.to_dev(yd, dtype), G.to_dev(idx.astype(np.int32), None),
+                           G.to_dev(slot, None), G.to_dev(gw, I.F32), G.to_dev(p32, I.F32), G.to_dev(ff, I.F32), aux,
+                           dyd, dg, dl)
+    torch.cuda.synchronize()
+    rdyd, rdg = O.combine_bwd(dy, yd, idx, slot, gw)
+    rdl = O.gate_bwd(rdg, p32, idx, slot)
+    if aux:
+        rdl = rdl + O.aux_loss_bwd(p32, ff, aux)
+    m = G.row_mask(cnt, C)
+    assert G.rel_l2(G.host(dyd)[m], rdyd[m]) <= G.TOL[dtype]
+    # fp32 sums of products of given values, whatever the activation type
+    assert G.rel_l2(G.host(dg), rdg) <= 1e-5
+    assert G.rel_l2(G.host(dl), rdl) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [I.F32, I.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("T,d,E,with_dx", [(1, 8, 1, True), (31, 24, 3, True), (33, 136, 4, False), (255, 520, 8, True),
+                                           (513, 72, 9, True), (600, 136, 17, True), (1024, 264, 32, True),
+                                           (1025, 72, 32, True)])       # the last one: three launches
+def test_projection_backward_small(T, d, E, with_dx, dtype):
+    rng = np.random.default_rng(T + d + E)
+    x, dx0 = rng.standard_normal((T, d)).astype(np.float32), rng.standard_normal((T, d)).astype(np.float32)
+    if dtype == I.BF16:
+        x, dx0 = I.round_to_bf16(x), I.round_to_bf16(dx0)
+    Wg, dl = rng.standard_normal((d, E)).astype(np.float32), rng.standard_normal((T, E)).astype(np.float32)
+    s = B.make_shape(T, d, 8, E, 1, 4, dtype, I.GELU)
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    dWg, dx = f32(d, E), G.to_dev(dx0, dtype)
+    print(f"[gpu] projection backward T={T} d={d} E={E}", flush=True)
+    B.moe_gate_logits_bwd(s, G.to_dev(x, dtype), G.to_dev(Wg, I.F32), G.to_dev(dl, I.F32), dWg, dx if with_dx else None, ws)
+    torch.cuda.synchronize()
+    rdWg, rdx = O.gate_logits_bwd(x, Wg, dl)
+    assert G.rel_l2(G.host(dWg), rdWg) <= 1e-5
+    assert G.rel_l2(G.host(dx), dx0 + (rdx if with_dx else 0.0)) <= G.TOL[dtype]
