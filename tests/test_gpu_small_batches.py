@@ -105,3 +105,24 @@ def test_projection_backward_small(T, d, E, with_dx, dtype):
     rdWg, rdx = O.gate_logits_bwd(x, Wg, dl)
     assert G.rel_l2(G.host(dWg), rdWg) <= 1e-5
     assert G.rel_l2(G.host(dx), dx0 + (rdx if with_dx else 0.0)) <= G.TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [I.F32, I.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("eps", [0.0, 0.01], ids=["plain", "jitter"])
+@pytest.mark.parametrize("T,d,E", [(1025, 72, 5), (1153, 264, 33), (2049, 520, 8), (4100, 264, 16)])
+def test_projection_backward_short_chunks(T, d, E, eps, dtype):
+    """Token chunks of one or two rounds, the last one with a few tokens."""
+    rng = np.random.default_rng(T + d)
+    x = rng.standard_normal((T, d)).astype(np.float32)
+    if dtype == I.BF16:
+        x = I.round_to_bf16(x)
+    Wg, dl = rng.standard_normal((d, E)).astype(np.float32), rng.standard_normal((T, E)).astype(np.float32)
+    s = B.make_shape(T, d, 8, E, 1, 4, dtype, I.GELU)
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    dWg = f32(d, E)
+    print(f"[gpu] projection backward T={T} d={d} E={E} eps={eps}", flush=True)
+    B.moe_gate_logits_bwd_jitter(s, G.to_dev(x, dtype), G.to_dev(Wg, I.F32), G.to_dev(dl, I.F32), eps, 11, dWg, None, ws)
+    torch.cuda.synchronize()
+    noise = O.jitter_noise(T, d, eps, 11) if eps else 1.0
+    # fp32 sums of T products: the same bound as the other projection tests
+    assert G.rel_l2(G.host(dWg), O.gate_logits_bwd(x * noise, Wg, dl)[0]) <= 1e-5
