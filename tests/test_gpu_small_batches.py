@@ -126,3 +126,24 @@ def test_projection_backward_short_chunks(T, d, E, eps, dtype):
     noise = O.jitter_noise(T, d, eps, 11) if eps else 1.0
     # fp32 sums of T products: the same bound as the other projection tests
     assert G.rel_l2(G.host(dWg), O.gate_logits_bwd(x * noise, Wg, dl)[0]) <= 1e-5
+
+
+@pytest.mark.parametrize("groups,chunks,E,k", [(2, 1, 3, 2), (17, 1, 8, 1), (3, 5, 130, 2), (5, 7, 16, 2), (2, 16, 200, 1)])
+def test_route_grouped_offsets(groups, chunks, E, k):
+    """Rows kept by earlier groups, from histogram runs that end inside, at and beyond a batch of loads."""
+    T = groups * chunks * 256
+    C = groups * max(1, T * k // (2 * E * groups))                      # half the demand fits
+    rng = np.random.default_rng(groups * 100 + chunks)
+    lg = (rng.standard_normal((T, E)) + np.linspace(0.0, 2.0, E)).astype(np.float32)
+    keys = rng.random(T, dtype=np.float32)
+    s = B.make_shape(T, 8, 8, E, k, C, I.F32, I.GELU)
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    probs, gw, ei, slot, cnt, dem, src = f32(T, E), f32(T, k), i32(T, k), i32(T, k), i32(E), i32(E), i32(E, C)
+    print(f"[gpu] grouped route T={T} groups={groups} E={E} k={k}", flush=True)
+    B.moe_gate_route_grouped(s, groups, G.to_dev(lg, I.F32), G.to_dev(keys, I.F32), probs, ei, gw, slot, cnt, dem, src, ws)
+    torch.cuda.synchronize()
+    idx = O.top_k(lg, k)
+    rslot, rcnt, rdem, rsrc = O.route_grouped(idx, keys, E, C, groups)
+    for name, got, want in (("expert_idx", ei, idx), ("slot", slot, rslot), ("count", cnt, rcnt), ("demand", dem, rdem),
+                            ("slot_src", src, rsrc)):
+        assert np.array_equal(got.cpu().numpy(), want), name
