@@ -827,8 +827,9 @@ __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_pair_kernel(const G
 // error of yd at d = 512, f = 2048: 3e-7 against 9e-7).  A slab is split once per
 // workgroup on its way from registers to LDS, under the MFMAs of the slab before;
 // about as much vector work as matrix work, which is what bounds it (T = 4096,
-// d = 512, f = 2048, E = 8, top-2, the four launches: 1003 -> 560 us).  An infinite
-// operand gives a non-finite result, not always the same one as the fp32 pipe.
+// d = 512, f = 2048, E = 8, top-2, the four launches: 1003 -> 560 us).  The parts hold a
+// value exactly from 2^-110 to 3.39e38; results that operands outside of that range, or
+// infinite or NaN ones, may have reached are formed again on the fp32 pipe (redo_f32).
 //
 // The products are computed with the operands exchanged (D^T), so that a lane holds four
 // consecutive columns of one output row: the epilogue's LDS strip is written and read
@@ -857,6 +858,8 @@ struct MidSmem {
 };
 
 // 8 fp32 of one tile chunk -> three bf16 planes, rounded to nearest at every step: hi + mid + lo = w exactly
+// for 2^-110 <= |w| <= 3.39e38.  Below, lo falls under bf16's subnormals; above, hi rounds to infinity and mid
+// is then the opposite one, as for an infinite w: every product and sum that such a w enters is NaN or infinite.
 __device__ __forceinline__ void split3_rne(const u32x4_t (&w)[2], u32x4_t& hi, u32x4_t& mid, u32x4_t& lo) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -867,6 +870,66 @@ __device__ __forceinline__ void split3_rne(const u32x4_t (&w)[2], u32x4_t& hi, u
         lo[i] = pack_bf16x2(a1 - __uint_as_float(m << 16), b1 - __uint_as_float(m & 0xffff0000u));
         hi[i] = h;
         mid[i] = m;
+    }
+}
+
+// May any of this wave's sums hold less than fp32 products would have given?  A sum that is NaN or infinite may
+// come from an operand that the split made so; one below 2^-80 that is not zero may come from operands below
+// 2^-110 (larger ones in the same sum leave the lost bits, 2^-134 per operand, far below its rounding).
+template <int TM, int TN>
+__device__ __forceinline__ bool split_in_doubt(const f32x16_t (&acc)[TM][TN]) {
+    float big[4] = {0.0f, 0.0f, 0.0f, 0.0f};           // four chains: the adds wait for each other otherwise
+    uint32_t small[4] = {~0u, ~0u, ~0u, ~0u};
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                big[v & 3] += fabsf(acc[i][j][v]);
+                small[v & 3] = min(small[v & 3], (__float_as_uint(acc[i][j][v]) << 1) - 1u);      // zeros come out largest
+            }
+    const bool finite = (big[0] + big[1]) + (big[2] + big[3]) < INFINITY;
+    return __ballot(!finite || min(min(small[0], small[1]), min(small[2], small[3])) < (127u - 80u) << 24) != 0;
+}
+
+// One wave's part of an fp32 tile of expert e on the fp32 pipe, operands straight from memory (m, n: the part's first
+// row and column): the exact fallback of the split, for waves that split_in_doubt() sends here.  `args` = which of the
+// kernel's arguments describes the product; they are read again here, so that nothing is kept in registers for this.
+template <bool A_KC, bool B_KC, int TM, int TN>
+__device__ __forceinline__ void redo_f32(f32x16_t (&acc)[TM][TN], int args, int e, int m, int m_lim, int n, int l32, int g) {
+    auto base = (const __attribute__((address_space(4))) GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm("" : "+s"(base));
+    const __attribute__((address_space(4))) GemmArgs& q = base[args];
+    const int lda = q.lda, ldb = q.ldb, N = q.N, k_lim = q.var_k ? max(0, min(q.expert_count[e], q.K)) : q.K;
+    const __amdgpu_buffer_rsrc_t rsA = buf_rsrc((const float*)q.A + (size_t)e * q.strideA, (size_t)(A_KC ? m_lim : k_lim) * lda * 4);
+    const __amdgpu_buffer_rsrc_t rsB = buf_rsrc((const float*)q.B + (size_t)e * q.strideB, (size_t)(B_KC ? N : k_lim) * ldb * 4);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    auto load = [&](bool kc, __amdgpu_buffer_rsrc_t rs, int r, int r_lim, int k, int ld) {
+        return buf_load_f32(rs, r < r_lim && k < k_lim ? (uint32_t)(kc ? r * ld + k : k * ld + r) * 4u : BUF_OOB);
+    };
+    constexpr int U = 4;
+#pragma unroll 1
+    for (int k0 = 0; k0 < k_lim; k0 += 2 * U) {
+        float fa[U][TM], fb[U][TN];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[u][i] = load(A_KC, rsA, m + i * 32 + l32, m_lim, k0 + 2 * u + g, lda);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[u][j] = load(B_KC, rsB, n + j * 32 + l32, N, k0 + 2 * u + g, ldb);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[u][j], fa[u][i], acc[i][j], 0, 0, 0);
     }
 }
 
@@ -1095,6 +1158,10 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
         constexpr int WC = BN / 2, LPR = WC / V, RPI = 64 / LPR, NIT = 32 / RPI;
         constexpr uint32_t OSZ = EPI == EPI_F32 ? 4u : (uint32_t)sizeof(T);
         if (live && wk == 0) {
+            if constexpr (SPLIT) {
+                if (__builtin_expect(split_in_doubt<TM, TN>(acc), 0))
+                    redo_f32<A_KC, B_KC, TM, TN>(acc, more < 0 ? 1 : 0, w.e, w.m0 + wm * (BM / 2), w.m_lim, w.n0 + wn * (BN / 2), l32, g);
+            }
             float* strip = reinterpret_cast<float*>(smem_raw) + wave * 32 * SM::STRIP_LD;
             const int er = lane / LPR, ec = (lane - er * LPR) * V;
             const int ncol = w.n0 + wn * WC + ec;
