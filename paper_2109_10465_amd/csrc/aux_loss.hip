@@ -116,13 +116,19 @@ __global__ __launch_bounds__(256) void aux_final_kernel(
     }
 }
 
+int aux_loss_check(const moe_shape* s, const float* probs, const int32_t* expert_idx, const float* first_frac,
+                   const float* mean_prob, const float* loss, const void* ws, size_t ws_bytes) {
+    const int rc = shape_status(s);
+    if (rc) return rc;
+    if (!probs || !expert_idx || !first_frac || !mean_prob || !loss) return MOE_ERR_NULL;
+    return ws_ok(ws, ws_bytes, aux_loss_ws_bytes(s)) ? MOE_OK : MOE_ERR_WORKSPACE;
+}
+
 extern "C" int moe_aux_loss(const moe_shape* shape, const float* probs, const int32_t* expert_idx,
                             float* first_frac, float* mean_prob, float* loss, void* ws,
                             size_t ws_bytes, void* stream) {
-    int rc = check_shape(shape);
+    const int rc = begin_call(aux_loss_check(shape, probs, expert_idx, first_frac, mean_prob, loss, ws, ws_bytes));
     if (rc) return rc;
-    if (!probs || !expert_idx || !first_frac || !mean_prob || !loss) return MOE_ERR_NULL;
-    if (!ws || ((uintptr_t)ws & 255) || ws_bytes < aux_loss_ws_bytes(shape)) return MOE_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     const int nchunk = aux_chunks(shape);
     float* part_sum = (float*)ws;

@@ -1495,15 +1495,20 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     return launch_gemm_pair<T, true, true, EPI_STORE, false, false, EPI_F32>(p, q, rows, E, st);
 }
 
+int ffn_fwd_check(const moe_shape* s, const void* xd, const int32_t* expert_count, const void* W1, const void* W2,
+                  float drop_p, const void* h_saved, const void* dact_saved, const void* yd) {
+    int rc = shape_status(s);
+    if (rc || (rc = check_slice_limits(s))) return rc;
+    if (!xd || !expert_count || !W1 || !W2 || !h_saved || !yd) return MOE_ERR_NULL;   // dact_saved may be NULL
+    if (!(drop_p >= 0.0f && drop_p < 1.0f)) return MOE_ERR_SHAPE;
+    return drop_p > 0.0f && !dact_saved ? MOE_ERR_NULL : MOE_OK;      // dropout is a training feature
+}
+
 static int ffn_fwd_impl(const moe_shape* shape, const void* xd, const int32_t* expert_count,
                         const void* W1, const void* W2, float drop_p, uint64_t seed, void* h_saved,
                         void* dact_saved, void* yd, void* stream) {
-    int rc = check_shape(shape);
+    const int rc = begin_call(ffn_fwd_check(shape, xd, expert_count, W1, W2, drop_p, h_saved, dact_saved, yd));
     if (rc) return rc;
-    if ((rc = check_slice_limits(shape))) return rc;
-    if (!xd || !expert_count || !W1 || !W2 || !h_saved || !yd) return MOE_ERR_NULL;   // dact_saved may be NULL
-    if (!(drop_p >= 0.0f && drop_p < 1.0f)) return MOE_ERR_SHAPE;
-    if (drop_p > 0.0f && !dact_saved) return MOE_ERR_NULL;      // dropout is a training feature
     if (drop_p > 0.0f && floor((double)drop_p * 4294967296.0) < 1.0) drop_p = 0.0f;   // below one part in 2^32
     hipStream_t st = (hipStream_t)stream;
     const bool ok = shape->dtype == MOE_BF16
@@ -1525,17 +1530,23 @@ extern "C" int moe_expert_ffn_fwd_dropout(const moe_shape* shape, const void* xd
     return ffn_fwd_impl(shape, xd, expert_count, W1, W2, drop_p, seed, h_saved, dact_saved, yd, stream);
 }
 
+int ffn_bwd_check(const moe_shape* s, const void* dyd, const void* xd, const void* h_saved, const void* dact_saved,
+                  const int32_t* expert_count, const void* W1, const void* W2, const void* dxd, const float* dW1,
+                  const float* dW2, const void* ws, size_t ws_bytes) {
+    int rc = shape_status(s);
+    if (rc || (rc = check_slice_limits(s))) return rc;
+    if (!dyd || !xd || !h_saved || !dact_saved || !expert_count || !W1 || !W2 || !dxd || !dW1 || !dW2)
+        return MOE_ERR_NULL;
+    return ws_ok(ws, ws_bytes, ffn_bwd_ws_bytes(s)) ? MOE_OK : MOE_ERR_WORKSPACE;
+}
+
 extern "C" int moe_expert_ffn_bwd(const moe_shape* shape, const void* dyd, const void* xd,
                                   const void* h_saved, const void* dact_saved,
                                   const int32_t* expert_count, const void* W1, const void* W2,
                                   void* dxd, float* dW1, float* dW2, void* ws, size_t ws_bytes,
                                   void* stream) {
-    int rc = check_shape(shape);
+    const int rc = begin_call(ffn_bwd_check(shape, dyd, xd, h_saved, dact_saved, expert_count, W1, W2, dxd, dW1, dW2, ws, ws_bytes));
     if (rc) return rc;
-    if ((rc = check_slice_limits(shape))) return rc;
-    if (!dyd || !xd || !h_saved || !dact_saved || !expert_count || !W1 || !W2 || !dxd || !dW1 || !dW2)
-        return MOE_ERR_NULL;
-    if (!ws || ((uintptr_t)ws & 255) || ws_bytes < ffn_bwd_ws_bytes(shape)) return MOE_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     const bool ok = shape->dtype == MOE_BF16
         ? ffn_bwd<bf16_t>(shape, dyd, xd, h_saved, dact_saved, expert_count, W1, W2, dxd, dW1, dW2, ws, st)

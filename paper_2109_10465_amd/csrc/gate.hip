@@ -408,12 +408,17 @@ static bool launch_gate_logits(const moe_shape* s, const void* x, const float* W
     return true;
 }
 
-static int gate_logits_impl(const moe_shape* shape, const void* x, const float* Wg,
-                            const float* bias_or_null, float eps, uint64_t seed, float* logits, void* stream) {
-    int rc = check_shape(shape);
+int gate_logits_check(const moe_shape* s, const void* x, const float* Wg, const float* logits, float eps) {
+    const int rc = shape_status(s);
     if (rc) return rc;
     if (!x || !Wg || !logits) return MOE_ERR_NULL;
-    if (!(eps >= 0.0f && eps < 1.0f)) return MOE_ERR_SHAPE;
+    return eps >= 0.0f && eps < 1.0f ? MOE_OK : MOE_ERR_SHAPE;
+}
+
+static int gate_logits_impl(const moe_shape* shape, const void* x, const float* Wg,
+                            const float* bias_or_null, float eps, uint64_t seed, float* logits, void* stream) {
+    const int rc = begin_call(gate_logits_check(shape, x, Wg, logits, eps));
+    if (rc) return rc;
     const bool ok = shape->dtype == MOE_BF16
         ? launch_gate_logits<bf16_t>(shape, x, Wg, bias_or_null, logits, eps, seed, (hipStream_t)stream)
         : launch_gate_logits<float>(shape, x, Wg, bias_or_null, logits, eps, seed, (hipStream_t)stream);
@@ -1302,15 +1307,21 @@ static bool launch_gate_logits_bwd(const moe_shape* s, const void* x, const floa
     return true;
 }
 
+int gate_logits_bwd_check(const moe_shape* s, const void* x, const float* Wg, const float* dlogits, float eps,
+                          const float* dWg, const void* ws, size_t ws_bytes) {
+    const int rc = shape_status(s);
+    if (rc) return rc;
+    if (!x || !Wg || !dlogits || !dWg) return MOE_ERR_NULL;
+    if (!(eps >= 0.0f && eps < 1.0f)) return MOE_ERR_SHAPE;
+    return ws_ok(ws, ws_bytes, gate_logits_bwd_ws_bytes(s)) ? MOE_OK : MOE_ERR_WORKSPACE;
+}
+
 static int gate_logits_bwd_impl(const moe_shape* shape, const void* x, const float* Wg, const float* dlogits,
                                 float eps, uint64_t seed, float* dWg, void* dx_accum, const void* dxd,
                                 const int32_t* expert_idx, const int32_t* slot, void* ws, size_t ws_bytes,
                                 void* stream) {
-    int rc = check_shape(shape);
+    const int rc = begin_call(gate_logits_bwd_check(shape, x, Wg, dlogits, eps, dWg, ws, ws_bytes));
     if (rc) return rc;
-    if (!x || !Wg || !dlogits || !dWg) return MOE_ERR_NULL;
-    if (!(eps >= 0.0f && eps < 1.0f)) return MOE_ERR_SHAPE;
-    if (!ws || ((uintptr_t)ws & 255) || ws_bytes < gate_logits_bwd_ws_bytes(shape)) return MOE_ERR_WORKSPACE;
     const bool ok = shape->dtype == MOE_BF16
         ? launch_gate_logits_bwd<bf16_t>(shape, x, Wg, dlogits, dWg, dx_accum, dxd, expert_idx, slot, (float*)ws, eps, seed, (hipStream_t)stream)
         : launch_gate_logits_bwd<float>(shape, x, Wg, dlogits, dWg, dx_accum, dxd, expert_idx, slot, (float*)ws, eps, seed, (hipStream_t)stream);

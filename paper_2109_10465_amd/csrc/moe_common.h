@@ -282,10 +282,7 @@ static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 static inline size_t elem_bytes(int dtype) { return dtype == MOE_BF16 ? 2 : 4; }
 
 // Validates the shape limits documented in moe_hip.h.
-static inline int check_shape(const moe_shape* s) {
-    // every entry point starts here: an error that an earlier, unrelated HIP call left behind is
-    // dropped now, so that launch_status() at the end reports this call's launches only
-    (void)hipGetLastError();
+static inline int shape_status(const moe_shape* s) {
     if (!s) return MOE_ERR_NULL;
     if (s->dtype != MOE_F32 && s->dtype != MOE_BF16) return MOE_ERR_DTYPE;
     if (s->act != MOE_RELU && s->act != MOE_GELU) return MOE_ERR_DTYPE;
@@ -294,6 +291,16 @@ static inline int check_shape(const moe_shape* s) {
     if (s->d_model % 8 || s->d_ff % 8) return MOE_ERR_SHAPE;
     if ((int64_t)s->T * s->k >= (1 << 30) || (int64_t)s->E * s->capacity >= (1 << 30)) return MOE_ERR_SHAPE;
     return MOE_OK;
+}
+// Every entry point starts with its check: an error that an earlier, unrelated HIP call left behind is
+// dropped now, so that launch_status() at the end reports this call's launches only
+static inline int begin_call(int check) {
+    (void)hipGetLastError();
+    return check;
+}
+static inline int check_shape(const moe_shape* s) { return begin_call(shape_status(s)); }
+static inline bool ws_ok(const void* ws, size_t ws_bytes, size_t need) {
+    return ws && !((uintptr_t)ws & 255) && ws_bytes >= need;
 }
 // A kernel that uses more than 64 KB of the CU's 160 KB LDS has to opt in, once per kernel
 // instance and device (`done` is that instance's bit mask over device ids).
@@ -317,3 +324,24 @@ size_t route_ws_bytes(const moe_shape* s);
 size_t ffn_bwd_ws_bytes(const moe_shape* s);
 size_t gate_logits_bwd_ws_bytes(const moe_shape* s);
 size_t aux_loss_ws_bytes(const moe_shape* s);
+
+// What an entry point requires of its arguments (host only, nothing is enqueued), for the calls that issue several
+// of them and have to know beforehand that none will refuse.
+int gate_logits_check(const moe_shape* s, const void* x, const float* Wg, const float* logits, float eps);
+int route_check(const moe_shape* s, int G, const float* logits, const float* probs, const int32_t* expert_idx,
+                const float* gate_w, const int32_t* slot, const int32_t* expert_count, const int32_t* expert_demand,
+                const int32_t* slot_src, const void* ws, size_t ws_bytes);
+int aux_loss_check(const moe_shape* s, const float* probs, const int32_t* expert_idx, const float* first_frac,
+                   const float* mean_prob, const float* loss, const void* ws, size_t ws_bytes);
+int dispatch_tokens_check(const moe_shape* s, const void* x, const int32_t* expert_idx, const int32_t* slot, const void* xd);
+int ffn_fwd_check(const moe_shape* s, const void* xd, const int32_t* expert_count, const void* W1, const void* W2,
+                  float drop_p, const void* h_saved, const void* dact_saved, const void* yd);
+int combine_fwd_check(const moe_shape* s, const void* yd, const int32_t* expert_idx, const int32_t* slot, const void* y);
+int combine_gate_bwd_check(const moe_shape* s, const void* dy, const void* yd, const int32_t* expert_idx,
+                           const int32_t* slot, const float* gate_w, const float* probs, const void* dyd,
+                           const float* dgate_w, const float* dlogits);
+int ffn_bwd_check(const moe_shape* s, const void* dyd, const void* xd, const void* h_saved, const void* dact_saved,
+                  const int32_t* expert_count, const void* W1, const void* W2, const void* dxd, const float* dW1,
+                  const float* dW2, const void* ws, size_t ws_bytes);
+int gate_logits_bwd_check(const moe_shape* s, const void* x, const float* Wg, const float* dlogits, float eps,
+                          const float* dWg, const void* ws, size_t ws_bytes);

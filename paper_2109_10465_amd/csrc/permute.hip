@@ -229,11 +229,15 @@ extern "C" int moe_dispatch(const moe_shape* shape, const void* x, const int32_t
     return launch_status();
 }
 
+int dispatch_tokens_check(const moe_shape* s, const void* x, const int32_t* expert_idx, const int32_t* slot, const void* xd) {
+    const int rc = shape_status(s);
+    return rc ? rc : x && expert_idx && slot && xd ? MOE_OK : MOE_ERR_NULL;
+}
+
 extern "C" int moe_dispatch_tokens(const moe_shape* shape, const void* x, const int32_t* expert_idx,
                                    const int32_t* slot, void* xd, void* stream) {
-    int rc = check_shape(shape);
+    const int rc = begin_call(dispatch_tokens_check(shape, x, expert_idx, slot, xd));
     if (rc) return rc;
-    if (!x || !expert_idx || !slot || !xd) return MOE_ERR_NULL;
     const int grid = ceil_div(shape->T, ROWS_PER_WG);
     hipStream_t st = (hipStream_t)stream;
     if (shape->dtype == MOE_BF16)
@@ -245,12 +249,16 @@ extern "C" int moe_dispatch_tokens(const moe_shape* shape, const void* x, const 
     return launch_status();
 }
 
+int combine_fwd_check(const moe_shape* s, const void* yd, const int32_t* expert_idx, const int32_t* slot, const void* y) {
+    const int rc = shape_status(s);
+    return rc ? rc : yd && expert_idx && slot && y ? MOE_OK : MOE_ERR_NULL;
+}
+
 extern "C" int moe_combine_fwd(const moe_shape* shape, const void* yd, const int32_t* expert_idx,
                                const int32_t* slot, const float* gate_w_or_null, void* y,
                                void* stream) {
-    int rc = check_shape(shape);
+    const int rc = begin_call(combine_fwd_check(shape, yd, expert_idx, slot, y));
     if (rc) return rc;
-    if (!yd || !expert_idx || !slot || !y) return MOE_ERR_NULL;
     const int grid = ceil_div(shape->T, ROWS_PER_WG);
     hipStream_t st = (hipStream_t)stream;
     if (shape->dtype == MOE_BF16)
@@ -287,13 +295,20 @@ extern "C" int moe_combine_bwd(const moe_shape* shape, const void* dy, const voi
     return launch_status();
 }
 
+int combine_gate_bwd_check(const moe_shape* s, const void* dy, const void* yd, const int32_t* expert_idx,
+                           const int32_t* slot, const float* gate_w, const float* probs, const void* dyd,
+                           const float* dgate_w, const float* dlogits) {
+    const int rc = shape_status(s);
+    if (rc) return rc;
+    return dy && yd && expert_idx && slot && gate_w && probs && dyd && dgate_w && dlogits ? MOE_OK : MOE_ERR_NULL;
+}
+
 extern "C" int moe_combine_gate_bwd(const moe_shape* shape, const void* dy, const void* yd,
                                     const int32_t* expert_idx, const int32_t* slot, const float* gate_w,
                                     const float* probs, const float* first_frac_or_null, float aux_coef,
                                     void* dyd, float* dgate_w, float* dlogits, void* stream) {
-    int rc = check_shape(shape);
+    const int rc = begin_call(combine_gate_bwd_check(shape, dy, yd, expert_idx, slot, gate_w, probs, dyd, dgate_w, dlogits));
     if (rc) return rc;
-    if (!dy || !yd || !expert_idx || !slot || !gate_w || !probs || !dyd || !dgate_w || !dlogits) return MOE_ERR_NULL;
     launch_combine_bwd<true>(shape, dy, yd, expert_idx, slot, gate_w, probs, first_frac_or_null, aux_coef, dyd, dgate_w,
                              dlogits, stream);
     return launch_status();

@@ -687,19 +687,26 @@ __global__ __launch_bounds__(SMALL_T) void route_small_kernel(
     }
 }
 
+int route_check(const moe_shape* s, int G, const float* logits, const float* probs, const int32_t* expert_idx,
+                const float* gate_w, const int32_t* slot, const int32_t* expert_count, const int32_t* expert_demand,
+                const int32_t* slot_src, const void* ws, size_t ws_bytes) {
+    const int rc = shape_status(s);
+    if (rc) return rc;
+    if (!logits || !probs || !expert_idx || !gate_w || !slot || !expert_count || !expert_demand || !slot_src)
+        return MOE_ERR_NULL;
+    if (G < 1) return MOE_ERR_SHAPE;
+    if (G > 1 && (s->T % G || (s->T / G) % CHUNK || s->capacity % G)) return MOE_ERR_SHAPE;
+    return ws_ok(ws, ws_bytes, route_ws_bytes(s)) ? MOE_OK : MOE_ERR_WORKSPACE;
+}
+
 static int route_impl(const moe_shape* shape, int G, const float* logits, const float* rts_keys_or_null,
                       float* probs, int32_t* expert_idx, float* gate_w, int32_t* slot,
                       int32_t* expert_count, int32_t* expert_demand, int32_t* slot_src, long long* accum, void* ws,
                       size_t ws_bytes, void* stream) {
-    int rc = check_shape(shape);
+    const int rc = begin_call(route_check(shape, G, logits, probs, expert_idx, gate_w, slot, expert_count, expert_demand,
+                                          slot_src, ws, ws_bytes));
     if (rc) return rc;
-    if (!logits || !probs || !expert_idx || !gate_w || !slot || !expert_count || !expert_demand ||
-        !slot_src)
-        return MOE_ERR_NULL;
     const int T = shape->T, E = shape->E, k = shape->k, C = shape->capacity;
-    if (G < 1) return MOE_ERR_SHAPE;
-    if (G > 1 && (T % G || (T / G) % CHUNK || C % G)) return MOE_ERR_SHAPE;
-    if (!ws || ((uintptr_t)ws & 255) || ws_bytes < route_ws_bytes(shape)) return MOE_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     const RouteWs r = carve(shape, ws);
     const int nchunk = n_chunks(shape);

@@ -86,6 +86,65 @@ def test_argument_errors_are_reported_before_any_launch():
         B._check(-2, "x")
 
 
+LAYER_FWD = ("logits", "probs", "expert_idx", "gate_w", "slot", "expert_count", "expert_demand", "slot_src", "xd", "h", "yd", "y")
+LAYER_BWD = ("probs", "expert_idx", "gate_w", "slot", "expert_count", "xd", "h", "dact", "yd", "dyd", "dgate_w", "dxd", "dW1",
+             "dW2", "dlogits", "dWg", "dx")
+
+
+def layer_call(backward, shape=(64, 16, 16, 4, 1, 16, 0, 0), without=(), inputs=(1, 1, 1, 1, 1), ws=None, **options):
+    """The native layer call on buffers that are never touched (each "pointer" is just not NULL): what it returns is the
+    host's verdict on the arguments."""
+    s = B.make_shape(*shape)
+    somewhere = 1 << 20
+    buffers = B.LayerBuffers()
+    for n, _ in B.LayerBuffers._fields_:
+        setattr(buffers, n, None if n in without else somewhere)
+    buffers.ws_bytes = B.moe_workspace_bytes(s) if ws is None else ws
+    o = B.LayerOptions(groups=1)
+    for n, v in options.items():
+        setattr(o, n, v)
+    x, Wg, W1, W2, dy = (somewhere if i else None for i in inputs)
+    L = B.lib()
+    if backward:
+        return L.moe_layer_bwd(ctypes.byref(s), ctypes.byref(o), ctypes.byref(buffers), x, Wg, W1, W2, dy, None)
+    return L.moe_layer_fwd(ctypes.byref(s), ctypes.byref(o), ctypes.byref(buffers), x, Wg, None, W1, W2, None, None)
+
+
+def test_layer_calls_report_every_argument_error_before_their_first_launch():
+    """An error of a late step of the pass comes back as that step's code.  Had an earlier step been issued by then, this
+    process, which has no device, would get MOE_ERR_LAUNCH from it."""
+    L = B.lib()
+    s, o, b = B.make_shape(64, 16, 16, 4, 1, 16, 0, 0), B.LayerOptions(groups=1), B.LayerBuffers()
+    for args in ((None, o, b), (s, None, b), (s, o, None)):
+        args = [a if a is None else ctypes.byref(a) for a in args]
+        assert L.moe_layer_fwd(*args, *[None] * 7) == -1
+        assert L.moe_layer_bwd(*args, *[None] * 6) == -1
+    for name in LAYER_FWD:
+        assert layer_call(False, without=(name,)) == -1, name
+    for name in LAYER_BWD:
+        assert layer_call(True, without=(name,)) == -1, name
+    for i in range(4):
+        assert layer_call(False, inputs=[j != i for j in range(5)]) == -1, i
+    for i in range(5):
+        assert layer_call(True, inputs=[j != i for j in range(5)]) == -1, i
+    assert layer_call(False, without=("utilisation",), forward_only=1) == -1
+    for name in ("first_frac", "mean_prob", "aux_loss"):
+        assert layer_call(False, without=(name,), aux_coef=0.01) == -1, name
+    assert layer_call(False, without=("dact",), drop_p=0.4) == -1
+    big = (64, 1 << 16, 1 << 14, 4, 1, 16, 0, 0)            # beyond the expert FFN's slice limits
+    small = (64, 16, 16, 4, 1, 16, 0, 0)
+    for backward in (False, True):
+        assert layer_call(backward, groups=0) == -2
+        assert layer_call(backward, jitter_eps=1.5) == -2
+        assert layer_call(backward, shape=big) == -2
+        assert layer_call(backward, ws=16) == -4
+        assert layer_call(backward, without=("ws",)) == -4
+    assert layer_call(False, shape=small, groups=3) == -2   # 64 tokens are no three groups of whole chunks
+    assert layer_call(False, drop_p=1.0) == -2
+    wide = (64, 512, 8, 32, 1, 1, 0, 0)
+    assert layer_call(True, shape=wide, ws=32 * 8 * 4) == -4        # enough for the experts' backward, not for the projection's
+
+
 def test_build_rejects_scratch_in_kernels_with_hand_issued_loads():
     """A kernel that issues loads through inline asm and waits for them by hand must not spill: the build reads the
     compiler's resource-usage remarks and fails if such a kernel reports scratch memory."""
