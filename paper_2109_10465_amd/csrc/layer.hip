@@ -32,7 +32,8 @@ static int check_bwd(const moe_shape* s, const moe_layer_options* o, const moe_l
     if (rc) return rc;
     if ((rc = combine_gate_bwd_check(s, dy, b->yd, b->expert_idx, b->slot, b->gate_w, b->probs, b->dyd, b->dgate_w, b->dlogits))) return rc;
     if ((rc = ffn_bwd_check(s, b->dyd, b->xd, b->h, b->dact, b->expert_count, W1, W2, b->dxd, b->dW1, b->dW2, b->ws, b->ws_bytes))) return rc;
-    if (!b->dx) return MOE_ERR_NULL;
+    // without first_frac moe_combine_gate_bwd would leave the balancing loss's gradient out
+    if (!b->dx || (o->aux_coef != 0.0f && !b->first_frac)) return MOE_ERR_NULL;
     return gate_logits_bwd_check(s, x, Wg, b->dlogits, o->jitter_eps, b->dWg, b->ws, b->ws_bytes);
 }
 

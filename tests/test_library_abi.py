@@ -130,6 +130,7 @@ def test_layer_calls_report_every_argument_error_before_their_first_launch():
     assert layer_call(False, without=("utilisation",), forward_only=1) == -1
     for name in ("first_frac", "mean_prob", "aux_loss"):
         assert layer_call(False, without=(name,), aux_coef=0.01) == -1, name
+    assert layer_call(True, without=("first_frac",), aux_coef=0.01) == -1
     assert layer_call(False, without=("dact",), drop_p=0.4) == -1
     big = (64, 1 << 16, 1 << 14, 4, 1, 16, 0, 0)            # beyond the expert FFN's slice limits
     small = (64, 16, 16, 4, 1, 16, 0, 0)
