@@ -1,12 +1,13 @@
 /*
  * moe_bench_aid.h - measurement aid shipped with the MoE layer library; NOT part of
- * the layer's ABI (that is moe_hip.h).  bench.py uses it to print what the chip
- * sustains on the matrix pipe beside the published peak.
+ * the layer's ABI (that is moe_hip.h): what the chip sustains on the matrix pipe, which
+ * bench.py prints beside the published peak, and which kernel a dispatch rule chooses for
+ * a shape, for the tests of the rules and for whoever times the calls.
  */
 #ifndef MOE_BENCH_AID_H
 #define MOE_BENCH_AID_H
 
-#include <stdint.h>
+#include "moe_hip.h"
 
 #ifdef __cplusplus
 extern "C" {
@@ -18,6 +19,10 @@ extern "C" {
  * out: n_workgroups * 256 floats, written once so that the loop is not dead code. */
 int moe_microbench_mfma_bf16(int32_t n_workgroups, int32_t iters, int32_t random_operands, float* out,
                              void* stream);
+
+/* Launches of one routing call (moe_gate_route, _grouped, _counted): 1 = one workgroup does it
+ * all, 3 = gate, placement and ranking.  Host function; a moe_status on an invalid shape. */
+int moe_route_launches(const moe_shape* shape, int32_t n_groups, int32_t has_keys);
 
 #ifdef __cplusplus
 }

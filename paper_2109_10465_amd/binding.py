@@ -22,7 +22,7 @@ EXPORTS = [
     "moe_gate_logits_jitter", "moe_gate_logits_bwd_jitter", "moe_expert_ffn_fwd_dropout",
     "moe_dispatch_gate_logits_bwd", "moe_microbench_mfma_bf16",
     "moe_gate_route_static", "moe_gate_route_static_max_bytes", "moe_dispatch_tokens", "moe_combine_gate_bwd",
-    "moe_gate_route_counted", "moe_layer_fwd", "moe_layer_bwd",
+    "moe_gate_route_counted", "moe_layer_fwd", "moe_layer_bwd", "moe_route_launches",
 ]
 
 
@@ -94,6 +94,7 @@ def lib():
             "moe_gate_logits_bwd_jitter": [shp, vp, vp, vp, ctypes.c_float, ctypes.c_uint64, vp, vp, vp, sz, vp],
             "moe_expert_ffn_fwd_dropout": [shp] + [vp] * 4 + [ctypes.c_float, ctypes.c_uint64] + [vp] * 4,
             "moe_dispatch_gate_logits_bwd": [shp] + [vp] * 6 + [ctypes.c_float, ctypes.c_uint64, vp, vp, vp, sz, vp],
+            "moe_route_launches": [shp, i32, i32],
             "moe_microbench_mfma_bf16": [i32, i32, i32, vp, vp],
         }
         for name, args in sigs.items():
@@ -257,6 +258,10 @@ def moe_dispatch_gate_logits_bwd(shape, x, Wg, dlogits, dxd, expert_idx, slot, j
                                               float(jitter_eps), int(seed), _p(dWg), _p(dx), _p(ws),
                                               0 if ws is None else ws.numel() * ws.element_size(),
                                               _stream(stream)), "moe_dispatch_gate_logits_bwd")
+
+
+def moe_route_launches(shape, n_groups, has_keys):
+    return lib().moe_route_launches(ctypes.byref(shape), int(n_groups), int(has_keys))
 
 
 def moe_microbench_mfma_bf16(n_workgroups, iters, random_operands, out, stream=None):

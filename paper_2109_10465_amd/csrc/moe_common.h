@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "../../include/moe_hip.h"
+#include "../../include/moe_bench_aid.h"
 
 #define MOE_WAVE 64
 

@@ -699,6 +699,41 @@ int route_check(const moe_shape* s, int G, const float* logits, const float* pro
     return ws_ok(ws, ws_bytes, route_ws_bytes(s)) ? MOE_OK : MOE_ERR_WORKSPACE;
 }
 
+// threads of route_small_kernel: a power of two, one per token
+static int small_threads(int T) {
+    int nt = 256;
+    while (nt < T) nt <<= 1;
+    return nt;
+}
+
+// Does one workgroup beat the three launches?  Its time is a start of 5 us, 1.4 us for each time that its threads go
+// round the tokens in the gate (LPT lanes per token), and 0.115 us for each entry of slot_src per thread, which is
+// the unit below; the three launches take 12 to 20 us whatever the batch, more with more experts and 2.5 us more
+// with keys (one workgroup sorts them: 1, 2.5 or 5 us at 256, 512 or 1024 threads).  Measured, one workgroup against
+// three launches, top-1 with keys unless stated, capacity T / E unless stated:
+//   E = 16: T = 512 11.4 against 14.2 us, 768 13.1 against 14.6, 900 14.6 against 14.3 (9.8 against 12.3 without keys)
+//   E = 32: T = 160 12.4 against 15.9, 384 15.0 against 16.1, 512 18.0 against 15.2 (15.0 against 12.1 without keys)
+//   E = 64: T = 90 14.2 against 19.0, 128 17.2 against 18.7, 256 30.2 against 19.3
+//   E = 128: T = 48 14.9 against 19.8, 64 18.0 against 19.9, 128 32.2 against 20.5
+//   E = 256: T = 24 15.9 against 21.5, 32 19.5 against 21.4, 64 34.5 against 22.1
+//   T = 512, E = 8: capacity 2048 11.9 against 14.2, 4096 16.0 against 14.3; T = 1024, E = 8: 13.3 and 14.0, 15.9 and 14.2
+//   T = 61, E = 32: capacity 512 14.5 against 15.4, 1024 21.8 against 15.5
+static bool one_workgroup_wins(const moe_shape* s, bool keys) {
+    if (s->T > SMALL_T) return false;
+    const int nt = small_threads(s->T), lpt = s->E <= 4 ? 1 : s->E <= 8 ? 2 : s->E <= 16 ? 4 : s->E <= 32 ? 8 : s->E <= 64 ? 16 : s->E <= 128 ? 32 : 64;
+    const int64_t work = 12 * ceil_div(s->T, nt / lpt) + (int64_t)s->E * s->capacity / nt;
+    const int sort = nt == 256 ? 0 : nt == 512 ? 12 : 36;
+    if (!keys) return work <= (s->E <= 32 ? 73 : 104);
+    return work <= (s->E <= 16 ? 80 : s->E <= 32 ? 88 : 112) - sort;
+}
+
+// measurement aid: how many launches the routing of this shape takes
+extern "C" int moe_route_launches(const moe_shape* shape, int32_t n_groups, int32_t has_keys) {
+    const int rc = shape_status(shape);
+    if (rc) return rc;
+    return n_groups == 1 && one_workgroup_wins(shape, has_keys != 0) ? 1 : 3;
+}
+
 static int route_impl(const moe_shape* shape, int G, const float* logits, const float* rts_keys_or_null,
                       float* probs, int32_t* expert_idx, float* gate_w, int32_t* slot,
                       int32_t* expert_count, int32_t* expert_demand, int32_t* slot_src, long long* accum, void* ws,
@@ -712,11 +747,8 @@ static int route_impl(const moe_shape* shape, int G, const float* logits, const 
     const int nchunk = n_chunks(shape);
     const int cpg = G == 1 ? nchunk : T / G / CHUNK;    // chunks per group
     const int Cg = C / G;
-    // One workgroup as long as its own work stays below what the launches cost: up to 8 rounds of
-    // 128 (E = 32) tokens in the gate, up to 32 entries of slot_src per thread
-    if (G == 1 && T <= SMALL_T && T * E <= SMALL_T * 32 && (int64_t)E * C <= 32 * SMALL_T) {
-        int nt = 256;
-        while (nt < T) nt <<= 1;
+    if (G == 1 && one_workgroup_wins(shape, rts_keys_or_null != nullptr)) {
+        const int nt = small_threads(T);
 #define SMALL(LPT) route_small_kernel<LPT><<<1, nt, 0, st>>>(T, E, k, C, logits, rts_keys_or_null, probs, expert_idx, \
     gate_w, slot, expert_count, expert_demand, slot_src, accum)
         if (E <= 4) SMALL(1); else if (E <= 8) SMALL(2); else if (E <= 16) SMALL(4); else if (E <= 32) SMALL(8);

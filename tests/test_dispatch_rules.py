@@ -1,0 +1,45 @@
+"""Which kernel the dispatch rules choose, at shapes where both sides have been measured (host-only queries).  The times in
+the comments are microseconds on an MI355X."""
+import pytest
+
+from paper_2109_10465_amd import binding as B
+from paper_2109_10465_amd import inputs as I
+
+
+#        T     E   k  capacity keys  launches
+ROUTE = [
+    (61, 32, 1, 128, True, 1),          # one workgroup 9.1, three launches 15.5
+    (61, 32, 1, 512, True, 1),          # 14.5, 15.4
+    (61, 32, 1, 1024, True, 3),         # 21.8, 15.5
+    (160, 32, 2, 10, True, 1),          # 13.7, 16.5
+    (384, 32, 2, 24, True, 1),          # 16.4, 17.0
+    (384, 32, 1, 12, False, 1),         # 12.1, 13.6
+    (512, 32, 1, 16, True, 3),          # 18.0, 15.2
+    (512, 32, 1, 16, False, 3),         # 15.0, 12.1
+    (1024, 32, 2, 64, True, 3),         # 26.6, 16.6
+    (512, 16, 1, 512, True, 1),         # 13.0, 14.7
+    (512, 16, 1, 2048, True, 3),        # 18.1, 14.7
+    (768, 16, 1, 48, True, 1),          # 13.1, 14.6
+    (900, 16, 2, 112, True, 3),         # 16.6, 15.1
+    (900, 16, 1, 56, False, 1),         # 9.8, 12.3
+    (1024, 8, 1, 2048, True, 1),        # 13.3, 14.0
+    (1024, 8, 1, 4096, True, 3),        # 15.9, 14.2
+    (1024, 4, 1, 8192, True, 1),        # 14.2, 15.7
+    (512, 8, 1, 4096, True, 3),         # 16.0, 14.3
+    (90, 64, 2, 2, True, 1),            # 15.6, 20.0
+    (256, 64, 1, 4, True, 3),           # 30.2, 19.3
+    (64, 128, 1, 1, True, 1),           # 18.0, 19.9
+    (64, 128, 1, 128, True, 3),         # 25.6, 20.1
+    (128, 128, 2, 2, True, 3),          # 34.9, 23.0
+    (24, 256, 1, 1, True, 1),           # 15.9, 21.5
+    (64, 256, 1, 1, True, 3),           # 34.5, 22.1
+    (1025, 4, 1, 256, True, 3),         # beyond one workgroup
+]
+
+
+@pytest.mark.parametrize("T,E,k,C,keys,launches", ROUTE)
+def test_route(T, E, k, C, keys, launches):
+    s = B.make_shape(T, 64, 64, E, k, C, I.BF16, I.GELU)
+    assert B.moe_route_launches(s, 1, keys) == launches
+    assert B.moe_route_launches(s, 2, keys) == 3            # groups are ranked on their own
+    assert B.moe_route_launches(B.make_shape(T, 60, 64, E, k, C, I.BF16, I.GELU), 1, keys) == -2

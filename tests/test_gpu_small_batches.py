@@ -24,7 +24,11 @@ def f32(*shape):
     (1, 2, 2, 1, "uniform"), (63, 4, 1, 20, "ties"), (64, 3, 2, 50, "uniform"), (65, 5, 1, 9, "signed"),
     (256, 8, 2, 64, "ties"), (257, 130, 2, 3, "uniform"), (512, 64, 1, 8, None), (1000, 31, 2, 70, "signed"),
     (1023, 9, 2, 500, None), (1024, 32, 2, 64, "uniform"), (1024, 1, 1, 1000, "ties"),
-    (1025, 32, 2, 64, "uniform"), (200, 256, 1, 200, "uniform")])       # the last two: beyond one workgroup's range
+    (1025, 32, 2, 64, "uniform"), (200, 256, 1, 200, "uniform"),        # beyond one workgroup's range, as are some above
+    # the largest batches that one workgroup takes, per number of lanes that share a token
+    (384, 32, 2, 24, "ties"), (384, 32, 1, 12, None), (768, 16, 2, 90, "signed"), (900, 16, 1, 56, None),
+    (1024, 8, 1, 2048, "signed"), (1024, 4, 2, 4096, "ties"), (96, 64, 2, 40, "ties"), (64, 128, 1, 20, "signed"),
+    (32, 256, 2, 3, "uniform"), (20, 130, 2, 1, None)])
 def test_route_small(T, E, k, C, keys):
     rng = np.random.default_rng(T * 7 + E)
     lg = rng.standard_normal((T, E)).astype(np.float32)
