@@ -24,6 +24,10 @@ int moe_microbench_mfma_bf16(int32_t n_workgroups, int32_t iters, int32_t random
  * all, 3 = gate, placement and ranking.  Host function; a moe_status on an invalid shape. */
 int moe_route_launches(const moe_shape* shape, int32_t n_groups, int32_t has_keys);
 
+/* 32-token tiles that share a workgroup of the gate projection (moe_gate_logits) of at most 32
+ * experts: 1 or 2 (1 for fp32).  Host function. */
+int moe_gate_logits_token_tiles(const moe_shape* shape);
+
 #ifdef __cplusplus
 }
 #endif

@@ -23,6 +23,7 @@ EXPORTS = [
     "moe_dispatch_gate_logits_bwd", "moe_microbench_mfma_bf16",
     "moe_gate_route_static", "moe_gate_route_static_max_bytes", "moe_dispatch_tokens", "moe_combine_gate_bwd",
     "moe_gate_route_counted", "moe_layer_fwd", "moe_layer_bwd", "moe_route_launches",
+    "moe_gate_logits_token_tiles",
 ]
 
 
@@ -95,6 +96,7 @@ def lib():
             "moe_expert_ffn_fwd_dropout": [shp] + [vp] * 4 + [ctypes.c_float, ctypes.c_uint64] + [vp] * 4,
             "moe_dispatch_gate_logits_bwd": [shp] + [vp] * 6 + [ctypes.c_float, ctypes.c_uint64, vp, vp, vp, sz, vp],
             "moe_route_launches": [shp, i32, i32],
+            "moe_gate_logits_token_tiles": [shp],
             "moe_microbench_mfma_bf16": [i32, i32, i32, vp, vp],
         }
         for name, args in sigs.items():
@@ -262,6 +264,10 @@ def moe_dispatch_gate_logits_bwd(shape, x, Wg, dlogits, dxd, expert_idx, slot, j
 
 def moe_route_launches(shape, n_groups, has_keys):
     return lib().moe_route_launches(ctypes.byref(shape), int(n_groups), int(has_keys))
+
+
+def moe_gate_logits_token_tiles(shape):
+    return lib().moe_gate_logits_token_tiles(ctypes.byref(shape))
 
 
 def moe_microbench_mfma_bf16(n_workgroups, iters, random_operands, out, stream=None):

@@ -378,6 +378,23 @@ static bool launch_gate_logits_lds(const moe_shape* s, const void* x, const floa
     return true;
 }
 
+// Up to 32 experts, bf16, no jitter: do two 32-token tiles per workgroup share each Wg fragment?  One tile is the
+// faster one beyond 512 columns (at most 512 are one round of loads for two tiles as well) as long as a workgroup per
+// tile is at most one per compute unit; two workgroups on a unit cost more than one with two tiles.  E = 32, one
+// tile against two: T = 61 5.1 against 6.8 us at d = 1024, 4.8 against 4.7 at d = 512, 4.0 against 3.5 at d = 64;
+// T = 8192 6.5 against 8.5 (d = 1024), 10.5 against 13.5 (d = 2048), 5.6 against 5.2 (d = 512); T = 8256 9.3 against 8.5
+// (d = 1024); T = 16384, d = 1024 15.7 against 14.2.  Four tiles: slower.
+static bool two_token_tiles(const moe_shape* s) { return s->d_model <= 512 || ceil_div(s->T, 32) > 256; }
+
+// measurement aid: 32-token tiles per workgroup of the gate projection without jitter, where the rule above decides
+extern "C" int moe_gate_logits_token_tiles(const moe_shape* shape) {
+    const int rc = shape_status(shape);
+    if (rc) return rc;
+    if (shape->E > 32) return MOE_ERR_SHAPE;
+    if (shape->dtype != MOE_BF16) return 1;
+    return two_token_tiles(shape) ? 2 : 1;
+}
+
 template <typename T>
 static bool launch_gate_logits(const moe_shape* s, const void* x, const float* Wg, const float* bias,
                                float* logits, float eps, uint64_t seed, hipStream_t st) {
@@ -398,10 +415,7 @@ static bool launch_gate_logits(const moe_shape* s, const void* x, const float* W
         if (s->E <= 32) GLM(1, true, 1); else if (s->E <= 64) GLM(2, true, 1);
         else if (s->E <= 128) GLM(4, true, 1); else GLM(8, true, 1);
     } else {
-        // Two 32-token tiles share each Wg fragment once that still gives most compute units a workgroup
-        // (T = 16384, E = 32: 15.7 -> 14.2 us; four tiles: slower); below, one tile's loads all fit in
-        // one round (T = 61, d = 1024, E = 32: 11.3 -> 8.0 us).
-        if (s->E <= 32) { if (ceil_div(s->T, 64) >= 192) GLM(1, false, TT2); else GLM(1, false, 1); } else if (s->E <= 64) GLM(2, false, TT2);
+        if (s->E <= 32) { if (two_token_tiles(s)) GLM(1, false, TT2); else GLM(1, false, 1); } else if (s->E <= 64) GLM(2, false, TT2);
         else if (s->E <= 128) GLM(4, false, TT2); else GLM(8, false, 1);
     }
 #undef GLM

@@ -43,3 +43,19 @@ def test_route(T, E, k, C, keys, launches):
     assert B.moe_route_launches(s, 1, keys) == launches
     assert B.moe_route_launches(s, 2, keys) == 3            # groups are ranked on their own
     assert B.moe_route_launches(B.make_shape(T, 60, 64, E, k, C, I.BF16, I.GELU), 1, keys) == -2
+
+
+@pytest.mark.parametrize("T,d,tiles", [
+    (61, 1024, 1),          # one token tile per workgroup 5.1, two 6.8
+    (61, 512, 2),           # 4.8, 4.7
+    (61, 64, 2),            # 4.0, 3.5
+    (4096, 640, 1),         # 5.5, 6.7
+    (8192, 2048, 1),        # 10.5, 13.5
+    (8256, 2048, 2),        # 16.3, 13.6
+    (12224, 768, 2),        # 8.4, 7.1
+    (12224, 256, 2),        # 8.0, 4.9
+    (16384, 1024, 2)])      # 15.7, 14.2
+def test_gate_projection(T, d, tiles):
+    for E in (2, 8, 32):
+        assert B.moe_gate_logits_token_tiles(B.make_shape(T, d, 64, E, 1, 8, I.BF16, I.GELU)) == tiles
+    assert B.moe_gate_logits_token_tiles(B.make_shape(T, d, 64, 8, 1, 8, I.F32, I.GELU)) == 1

@@ -151,3 +151,15 @@ def test_route_grouped_offsets(groups, chunks, E, k):
     for name, got, want in (("expert_idx", ei, idx), ("slot", slot, rslot), ("count", cnt, rcnt), ("demand", dem, rdem),
                             ("slot_src", src, rsrc)):
         assert np.array_equal(got.cpu().numpy(), want), name
+
+
+@pytest.mark.parametrize("T,d,E", [(1, 8, 1), (31, 72, 3), (33, 512, 8), (33, 520, 8), (65, 1032, 31), (8192, 520, 5), (8193, 520, 5)])
+def test_gate_projection_tiles(T, d, E):
+    """One and two token tiles per workgroup, at the lines between them."""
+    rng = np.random.default_rng(T + d)
+    x, Wg = I.round_to_bf16(rng.standard_normal((T, d)).astype(np.float32)), rng.standard_normal((d, E)).astype(np.float32)
+    logits = f32(T, E)
+    print(f"[gpu] gate projection T={T} d={d} E={E}", flush=True)
+    B.moe_gate_logits(B.make_shape(T, d, 8, E, 1, 4, I.BF16, I.GELU), G.to_dev(x, I.BF16), G.to_dev(Wg, I.F32), None, logits)
+    torch.cuda.synchronize()
+    assert G.rel_l2(G.host(logits), O.gate_logits(x, Wg, None)) <= 1e-5     # fp32 sums of products that the split leaves exact
