@@ -28,6 +28,10 @@ int moe_route_launches(const moe_shape* shape, int32_t n_groups, int32_t has_key
  * experts: 1 or 2 (1 for fp32).  Host function. */
 int moe_gate_logits_token_tiles(const moe_shape* shape);
 
+/* Launches of the projection's backward (moe_gate_logits_bwd and the calls built on it): 1 = dWg and
+ * dx together, else dWg in two and dx in one.  Host function. */
+int moe_gate_logits_bwd_launches(const moe_shape* shape, int32_t with_dx, float jitter_eps);
+
 #ifdef __cplusplus
 }
 #endif

@@ -1259,13 +1259,32 @@ __global__ __launch_bounds__(64 * NW, TT == 2 ? 2 : 1) void gate_dx_wide_kernel(
 #define GDW_TT 4
 #define GDW_NW 8
 #endif
+// Does the one-launch form beat the two or three launches?  Its columns of dWg are FMAs, as many as T E per column
+// and 16 columns per workgroup, where the other form has the matrix pipe: it gains as long as the launches' 5 us each
+// are what counts.  Measured, one launch against the others, with dx unless stated, bf16 unless stated:
+//   T = 512, E = 32: d = 64 9.0 against 14.2 us, d = 4096 24.6 against 36.0, d = 8192 53.6 and 57.1, d = 16384 102.5 and
+//     100.1 (fp32 144 and 146); without dx, d = 256 9.1 and 12.0
+//   T = 1024, E = 16: d = 8192 48.2 against 51.8, d = 12288 69.1 and 69.6, d = 16384 89.7 and 86.8; without dx, d = 256 8.6 and 13.1
+//   T = 1024, E = 32: d = 64 14.8 against 14.5, d = 4096 28.6 and 37.2, d = 8192 61.9 and 59.1; without dx, d = 256 15.2 and 12.4
+static bool one_launch_wins(const moe_shape* s, bool with_dx, float eps) {
+    if (eps != 0.0f || s->T > GBS_T || s->E > 32) return false;
+    if (s->T <= 512 || s->E <= 16) return s->d_model <= 12288;
+    return with_dx && s->d_model <= 4096;
+}
+
+// measurement aid: how many launches the projection's backward of this shape takes
+extern "C" int moe_gate_logits_bwd_launches(const moe_shape* shape, int32_t with_dx, float jitter_eps) {
+    const int rc = shape_status(shape);
+    if (rc) return rc;
+    return one_launch_wins(shape, with_dx != 0, jitter_eps) ? 1 : with_dx ? 3 : 2;
+}
+
 template <typename T>
 static bool launch_gate_logits_bwd(const moe_shape* s, const void* x, const float* Wg,
                                    const float* dlogits, float* dWg, void* dx, const void* dxd,
                                    const int32_t* expert_idx, const int32_t* slot, float* partial, float eps,
                                    uint64_t seed, hipStream_t st) {
-    // (x is addressed with 32-bit byte offsets)
-    if (eps == 0.0f && s->T <= GBS_T && s->E <= 32 && s->d_model < (1 << 18)) {
+    if (one_launch_wins(s, dx != nullptr, eps)) {
         const int n_dwg = ceil_div(s->d_model, GBS_COLS), n_dx = dx ? ceil_div(s->T, 32) : 0;
 #define GBS(EP, VEC, GA) gate_bwd_small_kernel<T, EP, VEC, GA><<<n_dwg + n_dx, 64 * GDX_WAVES, 0, st>>>( \
     n_dwg, s->T, s->d_model, s->E, s->k, s->capacity, (const T*)x, dlogits, Wg, (const T*)dxd, expert_idx, slot, dWg, (T*)dx)

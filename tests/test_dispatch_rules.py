@@ -59,3 +59,22 @@ def test_gate_projection(T, d, tiles):
     for E in (2, 8, 32):
         assert B.moe_gate_logits_token_tiles(B.make_shape(T, d, 64, E, 1, 8, I.BF16, I.GELU)) == tiles
     assert B.moe_gate_logits_token_tiles(B.make_shape(T, d, 64, 8, 1, 8, I.F32, I.GELU)) == 1
+
+
+@pytest.mark.parametrize("T,d,E,with_dx,launches", [
+    (1, 8, 1, True, 1),
+    (512, 256, 32, False, 1),       # one launch 9.1, two 12.0
+    (512, 8192, 32, True, 1),       # 53.6, three 57.1
+    (512, 16384, 32, True, 3),      # 102.5, 100.1
+    (1024, 256, 16, False, 1),      # 8.6, 13.1
+    (1024, 8192, 16, True, 1),      # 48.2, 51.8
+    (1024, 16384, 16, True, 3),     # 89.7, 86.8
+    (1024, 4096, 32, True, 1),      # 28.6, 37.2
+    (1024, 8192, 32, True, 3),      # 61.9, 59.1
+    (1024, 64, 17, False, 2),       # 15.4, 11.5
+    (900, 128, 32, False, 2),       # 14.3, 11.9
+    (1025, 64, 4, True, 3), (64, 64, 33, True, 3)])
+def test_projection_backward(T, d, E, with_dx, launches):
+    s = B.make_shape(T, d, 64, E, 1, 8, I.BF16, I.GELU)
+    assert B.moe_gate_logits_bwd_launches(s, with_dx, 0.0) == launches
+    assert B.moe_gate_logits_bwd_launches(s, with_dx, 0.01) == (3 if with_dx else 2)

@@ -93,7 +93,9 @@ def test_combine_and_gate_backward(T, d, E, k, aux, dtype):
 @pytest.mark.parametrize("dtype", [I.F32, I.BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("T,d,E,with_dx", [(1, 8, 1, True), (31, 24, 3, True), (33, 136, 4, False), (255, 520, 8, True),
                                            (513, 72, 9, True), (600, 136, 17, True), (1024, 264, 32, True),
-                                           (1025, 72, 32, True)])       # the last one: three launches
+                                           (1025, 72, 32, True),        # three launches
+                                           (512, 72, 32, False), (1024, 72, 16, False),     # one, without dx
+                                           (513, 72, 17, False), (700, 4104, 17, True), (7, 12296, 4, True)])   # beyond the line
 def test_projection_backward_small(T, d, E, with_dx, dtype):
     rng = np.random.default_rng(T + d + E)
     x, dx0 = rng.standard_normal((T, d)).astype(np.float32), rng.standard_normal((T, d)).astype(np.float32)
