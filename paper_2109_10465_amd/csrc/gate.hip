@@ -1259,6 +1259,10 @@ __global__ __launch_bounds__(64 * NW, TT == 2 ? 2 : 1) void gate_dx_wide_kernel(
 #define GDW_TT 4
 #define GDW_NW 8
 #endif
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    return a && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 // Does the one-launch form beat the two or three launches?  Its columns of dWg are FMAs, as many as T E per column
 // and 16 columns per workgroup, where the other form has the matrix pipe: it gains as long as the launches' 5 us each
 // are what counts.  Measured, one launch against the others, with dx unless stated, bf16 unless stated:
@@ -1284,7 +1288,12 @@ static bool launch_gate_logits_bwd(const moe_shape* s, const void* x, const floa
                                    const float* dlogits, float* dWg, void* dx, const void* dxd,
                                    const int32_t* expert_idx, const int32_t* slot, float* partial, float eps,
                                    uint64_t seed, hipStream_t st) {
-    if (one_launch_wins(s, dx != nullptr, eps)) {
+    // In one launch dWg's workgroups still read x and dlogits while others write: outputs that lie over an input
+    // (dx in place of x, say) take the launches in a row.
+    const size_t x_bytes = (size_t)s->T * s->d_model * sizeof(T), dl_bytes = (size_t)s->T * s->E * 4, dwg_bytes = (size_t)s->d_model * s->E * 4;
+    const bool in_place = overlap(dx, x_bytes, x, x_bytes) || overlap(dx, x_bytes, dlogits, dl_bytes) ||
+                          overlap(dWg, dwg_bytes, x, x_bytes) || overlap(dWg, dwg_bytes, dlogits, dl_bytes);
+    if (!in_place && one_launch_wins(s, dx != nullptr, eps)) {
         const int n_dwg = ceil_div(s->d_model, GBS_COLS), n_dx = dx ? ceil_div(s->T, 32) : 0;
 #define GBS(EP, VEC, GA) gate_bwd_small_kernel<T, EP, VEC, GA><<<n_dwg + n_dx, 64 * GDX_WAVES, 0, st>>>( \
     n_dwg, s->T, s->d_model, s->E, s->k, s->capacity, (const T*)x, dlogits, Wg, (const T*)dxd, expert_idx, slot, dWg, (T*)dx)

@@ -165,3 +165,23 @@ def test_gate_projection_tiles(T, d, E):
     B.moe_gate_logits(B.make_shape(T, d, 8, E, 1, 4, I.BF16, I.GELU), G.to_dev(x, I.BF16), G.to_dev(Wg, I.F32), None, logits)
     torch.cuda.synchronize()
     assert G.rel_l2(G.host(logits), O.gate_logits(x, Wg, None)) <= 1e-5     # fp32 sums of products that the split leaves exact
+
+
+@pytest.mark.parametrize("dtype", [I.F32, I.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("T,d,E", [(64, 72, 4), (700, 264, 8), (1024, 1032, 30)])
+def test_projection_backward_in_place_of_its_tokens(T, d, E, dtype):
+    """dx written over x: dWg is that of the tokens as they were, whatever the number of launches."""
+    rng = np.random.default_rng(T)
+    x = rng.standard_normal((T, d)).astype(np.float32)
+    if dtype == I.BF16:
+        x = I.round_to_bf16(x)
+    Wg, dl = rng.standard_normal((d, E)).astype(np.float32), rng.standard_normal((T, E)).astype(np.float32)
+    s = B.make_shape(T, d, 8, E, 1, 4, dtype, I.GELU)
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    xd, dWg = G.to_dev(x, dtype), f32(d, E)
+    print(f"[gpu] projection backward in place T={T} d={d} E={E}", flush=True)
+    B.moe_gate_logits_bwd(s, xd, G.to_dev(Wg, I.F32), G.to_dev(dl, I.F32), dWg, xd, ws)
+    torch.cuda.synchronize()
+    rdWg, rdx = O.gate_logits_bwd(x, Wg, dl)
+    assert G.rel_l2(G.host(dWg), rdWg) <= 1e-5
+    assert G.rel_l2(G.host(xd), x + rdx) <= G.TOL[dtype]
