@@ -19,6 +19,7 @@
 // and expert; an expert's kept rows of successive groups are laid end to end.
 // Work is O(T*E + sum over segments of n^2), bounded by the single-expert worst
 // case; balanced routing makes step 3 a few microseconds.
+#include <type_traits>
 #include "moe_common.h"
 
 #define CHUNK 256       // tokens per histogram chunk (= per route_place workgroup; gate_topk: see topk_sub)
@@ -294,36 +295,48 @@ __global__ __launch_bounds__(CHUNK) void route_place_kernel(
             dem_tot = s_tot[e * k] + (k == 2 ? s_tot[e * k + 1] : 0);
             cnt_tot = dem_tot < Cg ? dem_tot : Cg;
         }
-        // All groups' histogram rows as one run, 16 in flight: a load per row and group after group
-        // is a chain of memory latencies (32 chunks in 8 groups, 16 experts, top-2: this kernel
-        // 15.3 us, as one run 9.1).
-        const int rows = ngroups == 1 ? 0 : min(upto * cpg, nchunk) * sub, per_group = cpg * sub;
+        // All groups' histogram rows as one run, 16 loads in flight: a load per row and group after group is a chain
+        // of memory latencies (32 chunks in 8 groups, 16 experts, top-2: this kernel 15.3 us, as one run 9.1).  One
+        // load holds both choices of a top-2 row.  Groups of whole batches are added without a look at every row.
+        const int rows = ngroups == 1 ? 0 : upto * cpg * sub, per_group = cpg * sub;
         constexpr int HR = 16;
-        int dem = 0, gg = 0, left = per_group;         // left: rows of group gg still to come
-        for (int c0 = 0; c0 < rows; c0 += HR) {
-            int v[HR], w[HR];
+        auto add_rows = [&](auto two, auto whole) {
+            int dem = 0, gg = 0, left = per_group;     // left: rows of group gg still to come
+            auto close = [&]() {
+                const int kept = dem < Cg ? dem : Cg;
+                if (gg < g) off += kept;
+                dem_tot += dem;
+                cnt_tot += kept;
+                dem = 0;
+                left = per_group;
+                ++gg;
+            };
+            for (int c0 = 0; c0 < rows; c0 += HR) {
+                int v[HR];
 #pragma unroll
-            for (int u = 0; u < HR; ++u) {
-                const int32_t* h = hist + (size_t)min(c0 + u, rows - 1) * kE + e * k;
-                v[u] = h[0];
-                w[u] = h[k - 1];       // the same entry with k = 1: no branch between the loads
-            }
-#pragma unroll
-            for (int u = 0; u < HR; ++u) {
-                if (c0 + u < rows) {
-                    dem += k == 2 ? v[u] + w[u] : v[u];
-                    if (--left == 0 || c0 + u + 1 == rows) {       // the last group may be shorter
-                        const int kept = dem < Cg ? dem : Cg;
-                        if (gg < g) off += kept;
-                        dem_tot += dem;
-                        cnt_tot += kept;
-                        dem = 0;
-                        left = per_group;
-                        ++gg;
+                for (int u = 0; u < HR; ++u) {
+                    const int32_t* h = hist + (size_t)(whole.value ? c0 + u : min(c0 + u, rows - 1)) * kE;
+                    if constexpr (two.value) {
+                        const int2 q = reinterpret_cast<const int2*>(h)[e];
+                        v[u] = q.x + q.y;
+                    } else {
+                        v[u] = h[e];
                     }
                 }
+#pragma unroll
+                for (int u = 0; u < HR; ++u) {
+                    if (whole.value || c0 + u < rows) {
+                        dem += v[u];
+                        if (!whole.value && --left == 0) close();
+                    }
+                }
+                if (whole.value && (left -= HR) == 0) close();
             }
-        }
+        };
+        typedef std::integral_constant<bool, true> yes;
+        typedef std::integral_constant<bool, false> no;
+        if (per_group % HR == 0) { if (k == 2) add_rows(yes(), yes()); else add_rows(no(), yes()); }
+        else { if (k == 2) add_rows(yes(), no()); else add_rows(no(), no()); }
         goff[(size_t)g * E + e] = off;
         if (chunk == 0) {
             expert_demand[e] = dem_tot;

@@ -134,7 +134,8 @@ def test_projection_backward_short_chunks(T, d, E, eps, dtype):
     assert G.rel_l2(G.host(dWg), O.gate_logits_bwd(x * noise, Wg, dl)[0]) <= 1e-5
 
 
-@pytest.mark.parametrize("groups,chunks,E,k", [(2, 1, 3, 2), (17, 1, 8, 1), (3, 5, 130, 2), (5, 7, 16, 2), (2, 16, 200, 1)])
+@pytest.mark.parametrize("groups,chunks,E,k", [(2, 1, 3, 2), (17, 1, 8, 1), (3, 5, 130, 2), (5, 7, 16, 2), (2, 16, 200, 1),
+                                               (3, 16, 9, 2), (2, 32, 5, 1), (6, 17, 4, 1)])
 def test_route_grouped_offsets(groups, chunks, E, k):
     """Rows kept by earlier groups, from histogram runs that end inside, at and beyond a batch of loads."""
     T = groups * chunks * 256
