@@ -32,6 +32,9 @@ int moe_gate_logits_token_tiles(const moe_shape* shape);
  * dx together, else dWg in two and dx in one.  Host function. */
 int moe_gate_logits_bwd_launches(const moe_shape* shape, int32_t with_dx, float jitter_eps);
 
+/* Token chunks, each with a partial sum of dWg of its own, of the form with several launches. */
+int moe_gate_logits_bwd_chunks(const moe_shape* shape, float jitter_eps);
+
 #ifdef __cplusplus
 }
 #endif

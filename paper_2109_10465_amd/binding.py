@@ -23,7 +23,7 @@ EXPORTS = [
     "moe_dispatch_gate_logits_bwd", "moe_microbench_mfma_bf16",
     "moe_gate_route_static", "moe_gate_route_static_max_bytes", "moe_dispatch_tokens", "moe_combine_gate_bwd",
     "moe_gate_route_counted", "moe_layer_fwd", "moe_layer_bwd", "moe_route_launches",
-    "moe_gate_logits_token_tiles", "moe_gate_logits_bwd_launches",
+    "moe_gate_logits_token_tiles", "moe_gate_logits_bwd_launches", "moe_gate_logits_bwd_chunks",
 ]
 
 
@@ -97,6 +97,7 @@ def lib():
             "moe_dispatch_gate_logits_bwd": [shp] + [vp] * 6 + [ctypes.c_float, ctypes.c_uint64, vp, vp, vp, sz, vp],
             "moe_route_launches": [shp, i32, i32],
             "moe_gate_logits_token_tiles": [shp],
+            "moe_gate_logits_bwd_chunks": [shp, ctypes.c_float],
             "moe_gate_logits_bwd_launches": [shp, i32, ctypes.c_float],
             "moe_microbench_mfma_bf16": [i32, i32, i32, vp, vp],
         }
@@ -273,6 +274,10 @@ def moe_gate_logits_token_tiles(shape):
 
 def moe_gate_logits_bwd_launches(shape, with_dx, jitter_eps):
     return lib().moe_gate_logits_bwd_launches(ctypes.byref(shape), int(with_dx), float(jitter_eps))
+
+
+def moe_gate_logits_bwd_chunks(shape, jitter_eps):
+    return lib().moe_gate_logits_bwd_chunks(ctypes.byref(shape), float(jitter_eps))
 
 
 def moe_microbench_mfma_bf16(n_workgroups, iters, random_operands, out, stream=None):

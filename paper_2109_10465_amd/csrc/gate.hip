@@ -527,17 +527,23 @@ extern "C" int moe_gate_bwd(const moe_shape* shape, const float* dgate_w, const 
 
 // Tokens that the four waves take per round of their loops (16 each; bf16 without jitter 32).
 static inline int gw_round(const moe_shape* s) { return s->dtype == MOE_BF16 ? 128 : 64; }
-static inline int gw_chunks(const moe_shape* s) {
-    // enough workgroups to fill the chip twice, at least 256 tokens per chunk; where that leaves
-    // compute units idle, a workgroup for each as long as a chunk holds a whole round (T = 4096,
-    // d = 512, 8 experts, fp32: 16 chunks 18.9 us, 64 chunks 11.3; T = 8192, d = 768, 16 experts, bf16 with
-    // jitter: 32 chunks 37 us, 64 chunks 26)
+static inline int gw_chunks(const moe_shape* s, bool jitter) {
+    // Enough workgroups to fill the chip twice, at least 256 tokens per chunk.  Where that leaves compute units idle,
+    // a workgroup for each as long as a chunk holds a whole round, if the time that a chunk then takes less is more
+    // than the sum over more chunks costs.  Measured, us:
+    //   jitter (its Philox words are the time): T = 8192, d = 768, E = 16: 32 chunks 37, 64 chunks 26; T = 32768, d = 64,
+    //     E = 32: 128 chunks 36.7, 256 31.2
+    //   fp32: T = 4096, d = 512, E = 8: 16 chunks 18.9, 64 11.3; T = 8192, d = 64, E = 32: 32 chunks 17.9, 128 15.9; T = 16384,
+    //     d = 64, E = 16: 64 chunks 19.3, 256 21.6
+    //   bf16: T = 4096, d = 512, E = 32: 16 chunks 12.9, 32 12.1; E = 128 (8 MiB of partial sums): 13.9, 15.2; T = 6000, d = 1024,
+    //     E = 32: 24 chunks 13.9, 47 16.1
     const int tiles = ceil_div(s->d_model, GW_COLS) * ceil_div(s->E, 32);
     const int want = ceil_div(512, tiles), maxc = ceil_div(s->T, 256);
     int n = want < maxc ? want : maxc;
     if ((long long)n * tiles < 256) {
-        const int one = ceil_div(256, tiles), most = ceil_div(s->T, gw_round(s));
-        n = one < most ? one : most;
+        const int one = ceil_div(256, tiles), most = ceil_div(s->T, gw_round(s)), m = one < most ? one : most;
+        const bool bf16 = s->dtype == MOE_BF16;
+        if (jitter || (bf16 ? m <= 32 && (size_t)m * s->d_model * s->E * 4 <= 4608 * 1024 : m <= 128)) n = m;
     }
     // one chunk's rows of x are addressed with 32-bit byte offsets: keep it below 1 GiB
     const int minc = (int)(((size_t)s->T * s->d_model * 4 + ((size_t)1 << 30) - 1) >> 30);
@@ -546,13 +552,14 @@ static inline int gw_chunks(const moe_shape* s) {
 }
 // tokens per chunk: a multiple of 2 tokens per wave, of a round where chunks are short (a partial
 // round costs as much as a whole one)
-static inline int gw_chunk_tokens(const moe_shape* s) {
-    const int n = ceil_div(s->T, gw_chunks(s));
+static inline int gw_chunk_tokens(const moe_shape* s, bool jitter) {
+    const int n = ceil_div(s->T, gw_chunks(s, jitter));
     const int q = n < 256 ? gw_round(s) : 2 * GW_WAVES;
     return ceil_div(n, q) * q;
 }
-size_t gate_logits_bwd_ws_bytes(const moe_shape* s) {
-    return align_up((size_t)ceil_div(s->T, gw_chunk_tokens(s)) * s->d_model * s->E * 4, 256);
+size_t gate_logits_bwd_ws_bytes(const moe_shape* s) {    
+    const int n = ceil_div(s->T, gw_chunk_tokens(s, true)), n0 = ceil_div(s->T, gw_chunk_tokens(s, false));
+    return align_up((size_t)(n > n0 ? n : n0) * s->d_model * s->E * 4, 256);
 }
 
 #ifndef GW_MINB
@@ -1276,6 +1283,12 @@ static bool one_launch_wins(const moe_shape* s, bool with_dx, float eps) {
     return with_dx && s->d_model <= 4096;
 }
 
+// measurement aid: token chunks (partial sums) of dWg in the form with several launches
+extern "C" int moe_gate_logits_bwd_chunks(const moe_shape* shape, float jitter_eps) {
+    const int rc = shape_status(shape);
+    return rc ? rc : ceil_div(shape->T, gw_chunk_tokens(shape, jitter_eps != 0.0f));
+}
+
 // measurement aid: how many launches the projection's backward of this shape takes
 extern "C" int moe_gate_logits_bwd_launches(const moe_shape* shape, int32_t with_dx, float jitter_eps) {
     const int rc = shape_status(shape);
@@ -1305,7 +1318,7 @@ static bool launch_gate_logits_bwd(const moe_shape* s, const void* x, const floa
 #undef GBS
         return true;
     }
-    const int tpc = gw_chunk_tokens(s);
+    const int tpc = gw_chunk_tokens(s, eps != 0.0f);
     const int nch_used = ceil_div(s->T, tpc);
     dim3 grid(ceil_div(s->d_model, GW_COLS), nch_used, ceil_div(s->E, 32));
     constexpr size_t red_bytes = (size_t)2 * GW_COLS * 32 * sizeof(float);   // two staged tiles: 64 KB

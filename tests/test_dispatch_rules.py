@@ -78,3 +78,20 @@ def test_projection_backward(T, d, E, with_dx, launches):
     s = B.make_shape(T, d, 64, E, 1, 8, I.BF16, I.GELU)
     assert B.moe_gate_logits_bwd_launches(s, with_dx, 0.0) == launches
     assert B.moe_gate_logits_bwd_launches(s, with_dx, 0.01) == (3 if with_dx else 2)
+
+
+@pytest.mark.parametrize("T,d,E,dtype,eps,chunks", [
+    (4096, 512, 32, I.BF16, 0.0, 32),       # 16 chunks 12.9, 32 12.1
+    (4096, 512, 128, I.BF16, 0.0, 16),      # 13.9, 15.2 with 32
+    (6000, 1024, 32, I.BF16, 0.0, 24),      # 13.9, 16.1 with 47
+    (32768, 64, 32, I.BF16, 0.0, 128),      # 17.0, 21.1 with 256
+    (6000, 1024, 16, I.BF16, 0.01, 47),     # 24 chunks 33.3, 47 25.6
+    (32768, 64, 32, I.BF16, 0.01, 256),     # 128 chunks 36.7, 256 31.2
+    (8192, 64, 32, I.F32, 0.0, 128),        # 32 chunks 17.9, 128 15.9
+    (16384, 64, 16, I.F32, 0.0, 64),        # 19.3, 21.6 with 256
+    (65536, 1024, 32, I.BF16, 0.0, 128)])   # the chip is full twice
+def test_projection_backward_chunks(T, d, E, dtype, eps, chunks):
+    s = B.make_shape(T, d, 64, E, 1, 8, dtype, I.GELU)
+    assert B.moe_gate_logits_bwd_chunks(s, eps) == chunks
+    # the workspace that the query asks for holds every chunk's partial sums, with jitter and without
+    assert B.moe_workspace_bytes(s) >= max(B.moe_gate_logits_bwd_chunks(s, e) for e in (0.0, 0.01)) * d * E * 4
