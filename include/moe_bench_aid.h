@@ -35,6 +35,9 @@ int moe_gate_logits_bwd_launches(const moe_shape* shape, int32_t with_dx, float 
 /* Token chunks, each with a partial sum of dWg of its own, of the form with several launches. */
 int moe_gate_logits_bwd_chunks(const moe_shape* shape, float jitter_eps);
 
+/* Launches of moe_combine_gate_bwd: 1 = one pass over the tokens, 2 = combine, then gate. */
+int moe_combine_gate_bwd_launches(const moe_shape* shape);
+
 #ifdef __cplusplus
 }
 #endif

@@ -24,6 +24,7 @@ EXPORTS = [
     "moe_gate_route_static", "moe_gate_route_static_max_bytes", "moe_dispatch_tokens", "moe_combine_gate_bwd",
     "moe_gate_route_counted", "moe_layer_fwd", "moe_layer_bwd", "moe_route_launches",
     "moe_gate_logits_token_tiles", "moe_gate_logits_bwd_launches", "moe_gate_logits_bwd_chunks",
+    "moe_combine_gate_bwd_launches",
 ]
 
 
@@ -97,6 +98,7 @@ def lib():
             "moe_dispatch_gate_logits_bwd": [shp] + [vp] * 6 + [ctypes.c_float, ctypes.c_uint64, vp, vp, vp, sz, vp],
             "moe_route_launches": [shp, i32, i32],
             "moe_gate_logits_token_tiles": [shp],
+            "moe_combine_gate_bwd_launches": [shp],
             "moe_gate_logits_bwd_chunks": [shp, ctypes.c_float],
             "moe_gate_logits_bwd_launches": [shp, i32, ctypes.c_float],
             "moe_microbench_mfma_bf16": [i32, i32, i32, vp, vp],
@@ -278,6 +280,10 @@ def moe_gate_logits_bwd_launches(shape, with_dx, jitter_eps):
 
 def moe_gate_logits_bwd_chunks(shape, jitter_eps):
     return lib().moe_gate_logits_bwd_chunks(ctypes.byref(shape), float(jitter_eps))
+
+
+def moe_combine_gate_bwd_launches(shape):
+    return lib().moe_combine_gate_bwd_launches(ctypes.byref(shape))
 
 
 def moe_microbench_mfma_bf16(n_workgroups, iters, random_operands, out, stream=None):

@@ -295,6 +295,25 @@ extern "C" int moe_combine_bwd(const moe_shape* shape, const void* dy, const voi
     return launch_status();
 }
 
+// One pass for combine and gate backward, or two?  One saves a launch (5 us) and a read of dgate_w, but it has a wave
+// per token for a dlogits row that a few lanes write, which shows once there are many tokens of short rows.
+// Measured, one pass against two, us:
+//   bf16, E = 32, top-2: T = 16384, d = 64 11.2 and 11.6, T = 24576, d = 128 16.5 and 15.8, T = 32768, d = 64 20.2 and 18.2, d = 512
+//     30.9 and 31.2; T = 65536, d = 512 81.4 and 74.4; T = 131072, d = 256 132.6 and 115.3, fp32, d = 512 (2 KB rows): the same
+//   bf16, E = 16, top-1: T = 32768, d = 64 14.0 and 14.0; T = 65536, d = 128 28.2 and 25.7; E = 64: 4 % faster in one pass
+//   E = 256: one pass is the faster one throughout (T = 131072, d = 128, top-2: 6 %)
+static bool two_passes_win(const moe_shape* s) {
+    const int64_t choices = (int64_t)s->T * s->k;
+    const size_t row = s->d_model * elem_bytes(s->dtype);
+    return s->E <= 32 * s->k && (choices >= 131072 ? row <= 1024 : choices >= 49152 && row <= 512);
+}
+
+// measurement aid: passes of moe_combine_gate_bwd over the tokens
+extern "C" int moe_combine_gate_bwd_launches(const moe_shape* shape) {
+    const int rc = shape_status(shape);
+    return rc ? rc : two_passes_win(shape) ? 2 : 1;
+}
+
 int combine_gate_bwd_check(const moe_shape* s, const void* dy, const void* yd, const int32_t* expert_idx,
                            const int32_t* slot, const float* gate_w, const float* probs, const void* dyd,
                            const float* dgate_w, const float* dlogits) {
@@ -309,6 +328,12 @@ extern "C" int moe_combine_gate_bwd(const moe_shape* shape, const void* dy, cons
                                     void* dyd, float* dgate_w, float* dlogits, void* stream) {
     const int rc = begin_call(combine_gate_bwd_check(shape, dy, yd, expert_idx, slot, gate_w, probs, dyd, dgate_w, dlogits));
     if (rc) return rc;
+    if (two_passes_win(shape)) {
+        launch_combine_bwd<false>(shape, dy, yd, expert_idx, slot, gate_w, nullptr, nullptr, 0.0f, dyd, dgate_w, nullptr, stream);
+        return first_frac_or_null
+            ? moe_gate_bwd_aux(shape, dgate_w, probs, expert_idx, slot, first_frac_or_null, aux_coef, dlogits, stream)
+            : moe_gate_bwd(shape, dgate_w, probs, expert_idx, slot, dlogits, stream);
+    }
     launch_combine_bwd<true>(shape, dy, yd, expert_idx, slot, gate_w, probs, first_frac_or_null, aux_coef, dyd, dgate_w,
                              dlogits, stream);
     return launch_status();

@@ -95,3 +95,20 @@ def test_projection_backward_chunks(T, d, E, dtype, eps, chunks):
     assert B.moe_gate_logits_bwd_chunks(s, eps) == chunks
     # the workspace that the query asks for holds every chunk's partial sums, with jitter and without
     assert B.moe_workspace_bytes(s) >= max(B.moe_gate_logits_bwd_chunks(s, e) for e in (0.0, 0.01)) * d * E * 4
+
+
+@pytest.mark.parametrize("T,d,E,k,dtype,launches", [
+    (256, 64, 4, 1, I.F32, 1),
+    (16384, 64, 32, 2, I.BF16, 1),      # one pass 11.2, two 11.6
+    (24576, 128, 4, 2, I.BF16, 2),      # 16.8, 15.8
+    (32768, 64, 32, 2, I.BF16, 2),      # 20.2, 18.2
+    (32768, 512, 32, 2, I.BF16, 1),     # 30.9, 31.2
+    (65536, 512, 32, 2, I.BF16, 2),     # 81.4, 74.4
+    (65536, 512, 32, 2, I.F32, 1),      # the same
+    (32768, 64, 16, 1, I.F32, 1),       # the same
+    (65536, 128, 16, 1, I.BF16, 2),     # 28.2, 25.7
+    (65536, 64, 64, 1, I.F32, 1),       # 4 % faster in one
+    (131072, 128, 256, 2, I.BF16, 1),   # 6 % faster in one
+    (65536, 2048, 16, 2, I.BF16, 1)])
+def test_combine_and_gate_backward(T, d, E, k, dtype, launches):
+    assert B.moe_combine_gate_bwd_launches(B.make_shape(T, d, 64, E, k, max(1, T * k // E), dtype, I.GELU)) == launches

@@ -57,7 +57,9 @@ def test_route_small(T, E, k, C, keys):
 
 @pytest.mark.parametrize("dtype", [I.F32, I.BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("T,d,E,k,aux", [(1, 8, 2, 2, 0.0), (130, 72, 5, 2, 0.0), (777, 520, 32, 1, 0.01),
-                                         (300, 1032, 130, 2, 0.01), (515, 64, 256, 2, 0.0), (64, 8, 1, 1, 0.01)])
+                                         (300, 1032, 130, 2, 0.01), (515, 64, 256, 2, 0.0), (64, 8, 1, 1, 0.01),
+                                         # two passes: many tokens of short rows
+                                         (24577, 72, 6, 2, 0.0), (24577, 72, 6, 2, 0.01), (49153, 72, 7, 1, 0.0)])
 def test_combine_and_gate_backward(T, d, E, k, aux, dtype):
     rng = np.random.default_rng(T + E)
     C = max(1, (T * k) // E)
