@@ -975,6 +975,21 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
         const T* gA = (const T*)p.A + (size_t)w.e * p.strideA;
         const T* gB = (const T*)p.B + (size_t)w.e * p.strideB;
         const bool live = w.m0 + wm * (BM / 2) < w.m_lim;     // does this wave hold any row in use
+        if constexpr (EPI == EPI_F32) {
+            if (nk == 0) {
+                // An expert without rows: its zeros are stored at once.  Through the loop, loads that wait for the
+                // stores before them and the barriers would hold back the next tile's (16 empty experts, d = 408,
+                // f = 752, fp32 backward: 24.9 -> 17.0 us).
+                constexpr int CH = BN / 4;                   // 16-byte pieces of a tile row
+                const __amdgpu_buffer_rsrc_t o0 = buf_rsrc((float*)p.out0 + (size_t)w.e * p.strideO, (size_t)w.m_lim * p.ldo * 4);
+                const int col = w.n0 + (int)(threadIdx.x % CH) * 4;
+                const float zero[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+                for (int row = threadIdx.x / CH; row < BM; row += SM::NT / CH)
+                    BufChunk<float>::store(o0, col < p.N ? (uint32_t)((w.m0 + row) * p.ldo + col) * 4u : BUF_OOB, zero);
+                continue;
+            }
+        }
         f32x16_t acc[TM][TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i)

@@ -1,7 +1,10 @@
 """GPU: the expert FFN on every tile the launch rule can choose, at sizes that fall between tiles: row counts around
 a tile edge, d_model and d_ff that are no multiple of a tile or a slab, experts without rows."""
+import numpy as np
 import pytest
+import torch
 
+from paper_2109_10465_amd import binding as B
 from paper_2109_10465_amd import inputs as I
 import gpu_util as G
 
@@ -30,3 +33,29 @@ def test_ffn_tile(name, T, d, f, E, k, C, dtype, act):
     data = I.make_inputs(w, seed=3)
     _, got = G.run_layer(w, data)
     G.check_full(w, data, got)
+
+
+@pytest.mark.parametrize("dtype", [F, H], ids=["f32", "bf16"])
+@pytest.mark.parametrize("E,C,d,f", [(5, 40, 72, 136), (100, 8, 200, 520), (40, 3, 136, 2056)])
+def test_experts_without_rows_get_zero_weight_gradients(E, C, d, f, dtype):
+    rng = np.random.default_rng(E)
+    cnt = np.where(np.arange(E) % 3 == 1, rng.integers(1, C + 1, E), 0).astype(np.int32)
+    tdt = torch.bfloat16 if dtype == H else torch.float32
+    xd, h, dact, dyd = (torch.from_numpy(rng.standard_normal((E, C, n)).astype(np.float32)).cuda().to(tdt) for n in (d, f, f, d))
+    W1, W2 = (torch.from_numpy(0.05 * rng.standard_normal((E, *n)).astype(np.float32)).cuda().to(tdt) for n in ((d, f), (f, d)))
+    s = B.make_shape(E * C, d, f, E, 1, C, dtype, I.GELU)
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    dxd, dW1, dW2 = torch.empty_like(xd), torch.full((E, d, f), float("nan"), device="cuda"), torch.full((E, f, d), float("nan"), device="cuda")
+    print(f"[gpu] ffn backward with empty experts E={E} C={C} d={d} f={f} dtype={dtype}", flush=True)
+    B.moe_expert_ffn_bwd(s, dyd, xd, h, dact, G.to_dev(cnt, None), W1, W2, dxd, dW1, dW2, ws)
+    torch.cuda.synchronize()
+    dW1, dW2 = G.host(dW1), G.host(dW2)
+    for e in range(E):
+        n = cnt[e]
+        if n == 0:
+            assert not dW1[e].any() and not dW2[e].any(), e
+            continue
+        X, D, Hh, A, V2 = (G.host(t[e]).astype(np.float64) for t in (xd, dyd, h, dact, W2))
+        dz = (D[:n] @ V2.T) * A[:n]
+        assert G.rel_l2(dW2[e], Hh[:n].T @ D[:n]) <= 1e-5           # fp32 sums of products of given values
+        assert G.rel_l2(dW1[e], X[:n].T @ dz) <= G.TOL[dtype]       # dz is stored in the activation type
