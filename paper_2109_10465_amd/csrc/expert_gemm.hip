@@ -200,18 +200,18 @@ template <typename T, int BR, int BK, bool KC, int NT> struct Tile {
 
 // ---- activation in the forward epilogue ---------------------------------------
 // h = act(z) and a = act'(z) together.
-// fp32 tensors: the normal cdf Phi from two fits that meet at |z| = 1.0625, without erff and expf (about 35
-// instructions against about 100; forward pair at 8 experts of 1024 rows, d = 512, f = 2048: 202.1 us against
-// 204.5).  Inside, Phi(z) = 1/2 + z C(z^2), one rounding at the size of the result; outside, Phi(-t) = phi(t) M(t)
+// fp32 tensors: the normal cdf Phi from two fits that meet at |z| = 1.0625, without erff and expf (about 32
+// instructions against about 100; forward pair at 8 experts of 1024 rows, d = 512, f = 2048: 201.3 us against
+// 204.7).  Inside, Phi(z) = 1/2 + z C(z^2), one rounding at the size of the result; outside, Phi(-t) = phi(t) M(t)
 // with Mills' ratio M as a (3,4) rational function, small against the 1 or 0 that it is taken from.  The
-// density's exponent keeps what the roundings of t^2 and of its factor leave.
+// density's exponent keeps what its own rounding leaves.
 //   C: least squares in z^2 on Chebyshev nodes of [0, 1.129], weight |z| + 0.05, each coefficient rounded to fp32
 //      before the next ones are fitted (error of z C: 1.5e-9).
 //   M: linearised least squares on Chebyshev nodes of [1.0625, 13.5] in log t, reweighted towards equal relative
 //      errors (2.6e-8).
 // The rms errors of h and a against 64 bits are below those of erff and expf on every range of z (|z| < 1/2:
 // 3.9e-9 .. 7.1e-9 and 1.3e-8 .. 2.5e-8 against 4.4e-9 .. 7.4e-9 and 1.4e-8 .. 2.6e-8), and the left tail keeps
-// its relative accuracy (4e-7), where 1 + erf cancels.
+// its relative accuracy (1e-6 at -5), where 1 + erf cancels.
 // bf16 tensors (8 significant bits) use the three-term rational erfc of Abramowitz &
 // Stegun 7.1.25 (absolute error of the normal cdf below 1.1e-5, i.e. 1/350 of a bf16
 // rounding step at 1) with one exponential shared with the density and all scale
@@ -229,11 +229,11 @@ __device__ __forceinline__ void act_both(float z, float& h, float& a) {
         constexpr float CENTRE[6] = {0.39894229f, -0.066490486f, 0.0099737411f, -0.0011868734f, 0.00011374246f, -7.6692668e-06f};
         constexpr float MILLS_NUM[4] = {1.2527357f, 1.0029950f, 0.36051896f, 0.061547495f};
         constexpr float MILLS_DEN[5] = {1.0f, 1.5959138f, 1.0661000f, 0.36044064f, 0.061549164f};
-        constexpr float LH = -0.72134751f, LL = -9.6298150e-09f;       // -log2(e) / 2 in two parts
+        constexpr float LH = -0.72134751f;                             // -log2(e) / 2
         constexpr float PHI0 = 0.39894228f, PHI0_LN2 = 0.27652571f;    // 1 / sqrt(2 pi), times ln 2
         const float t = fminf(fabsf(z), 16.0f), s = t * t;             // phi is 0 from 16 on, also for an infinite z
         const float e = s * LH;
-        const float rest = fmaf(s, LL, fmaf(fmaf(t, t, -s), LH, fmaf(s, LH, -e)));     // exp2(e + rest) = exp2(e) (1 + rest ln 2)
+        const float rest = fmaf(s, LH, -e);                            // exp2(e + rest) = exp2(e) (1 + rest ln 2)
         const float pdf = __builtin_amdgcn_exp2f(e) * fmaf(rest, PHI0_LN2, PHI0);
         float c = CENTRE[5], num = MILLS_NUM[3], den = MILLS_DEN[4];
 #pragma unroll
@@ -898,7 +898,7 @@ __device__ __forceinline__ void split3_rne(const u32x4_t (&w)[2], u32x4_t& hi, u
 // 2^-110 (larger ones in the same sum leave the lost bits, 2^-134 per operand, far below its rounding).
 template <int TM, int TN>
 __device__ __forceinline__ bool split_in_doubt(const f32x16_t (&acc)[TM][TN]) {
-    float big[4] = {0.0f, 0.0f, 0.0f, 0.0f};           // four chains: the adds wait for each other otherwise
+    float big[4] = {0.0f, 0.0f, 0.0f, 0.0f};           // four chains: each step waits for the one before; `maximum` keeps NaN
     uint32_t small[4] = {~0u, ~0u, ~0u, ~0u};
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -906,10 +906,10 @@ __device__ __forceinline__ bool split_in_doubt(const f32x16_t (&acc)[TM][TN]) {
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                big[v & 3] += fabsf(acc[i][j][v]);
+                big[v & 3] = __builtin_elementwise_maximum(big[v & 3], fabsf(acc[i][j][v]));
                 small[v & 3] = min(small[v & 3], (__float_as_uint(acc[i][j][v]) << 1) - 1u);      // zeros come out largest
             }
-    const bool finite = (big[0] + big[1]) + (big[2] + big[3]) < INFINITY;
+    const bool finite = __builtin_elementwise_maximum(__builtin_elementwise_maximum(big[0], big[1]), __builtin_elementwise_maximum(big[2], big[3])) < INFINITY;
     return __ballot(!finite || min(min(small[0], small[1]), min(small[2], small[3])) < (127u - 80u) << 24) != 0;
 }
 

@@ -18,7 +18,7 @@ def constants():
     for name in ("CENTRE", "MILLS_NUM", "MILLS_DEN"):
         body, = re.findall(r"constexpr float %s\[\d\] = \{([^}]*)\}" % name, text)
         out[name] = [f(v.strip().rstrip("f")) for v in body.split(",")]
-    for name in ("LH", "LL", "PHI0", "PHI0_LN2"):
+    for name in ("LH", "PHI0", "PHI0_LN2"):
         v, = re.findall(r"\b%s = (-?[0-9.e+-]+)f" % name, text)
         out[name] = f(v)
     return out
@@ -40,7 +40,7 @@ def test_fits():
     mills = math.sqrt(math.pi / 2.0) * erfcx(t / math.sqrt(2.0))
     # the fit's 2.6e-8 and the roundings of the coefficients above and below, 2^-24 each at most
     assert np.abs(poly64(K["MILLS_NUM"], t) / poly64(K["MILLS_DEN"], t) / mills - 1.0).max() <= 2.6e-8 + 2 * 2.0 ** -24
-    assert abs(float(K["LH"]) + float(K["LL"]) + math.log2(math.e) / 2.0) <= 1e-15
+    assert K["LH"] == f(-math.log2(math.e) / 2.0)
     assert K["PHI0"] == f(1.0 / math.sqrt(2.0 * math.pi)) and K["PHI0_LN2"] == f(math.log(2.0) / math.sqrt(2.0 * math.pi))
 
 
@@ -59,7 +59,7 @@ def kernel_form(z):
     t = np.minimum(np.abs(z), f(16))
     s = f(t * t)
     e = f(s * K["LH"])
-    rest = fma(s, K["LL"], fma(fma(t, t, -s), K["LH"], fma(s, K["LH"], -e)))
+    rest = fma(s, K["LH"], -e)
     pdf = f(f(np.exp2(e.astype(np.float64))) * fma(rest, K["PHI0_LN2"], K["PHI0"]))
     q = f(f(horner(K["MILLS_NUM"], t) * pdf) * f(1.0 / horner(K["MILLS_DEN"], t).astype(np.float64)))
     cdf = np.where(t < f(EDGE), fma(z, horner(K["CENTRE"], s), f(0.5)), np.where(z >= 0, f(f(1) - q), q))
