@@ -1275,11 +1275,12 @@ static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 // are what counts.  Measured, one launch against the others, with dx unless stated, bf16 unless stated:
 //   T = 512, E = 32: d = 64 9.0 against 14.2 us, d = 4096 24.6 against 36.0, d = 8192 53.6 and 57.1, d = 16384 102.5 and
 //     100.1 (fp32 144 and 146); without dx, d = 256 9.1 and 12.0
+//   T = 512, E = 4: d = 16384 75.1 and 81.5
 //   T = 1024, E = 16: d = 8192 48.2 against 51.8, d = 12288 69.1 and 69.6, d = 16384 89.7 and 86.8; without dx, d = 256 8.6 and 13.1
 //   T = 1024, E = 32: d = 64 14.8 against 14.5, d = 4096 28.6 and 37.2, d = 8192 61.9 and 59.1; without dx, d = 256 15.2 and 12.4
 static bool one_launch_wins(const moe_shape* s, bool with_dx, float eps) {
     if (eps != 0.0f || s->T > GBS_T || s->E > 32) return false;
-    if (s->T <= 512 || s->E <= 16) return s->d_model <= 12288;
+    if (s->T <= 512 || s->E <= 16) return s->d_model <= (s->T <= 512 && s->E <= 16 ? 16384 : 12288);
     return with_dx && s->d_model <= 4096;
 }
 

@@ -66,6 +66,7 @@ def test_gate_projection(T, d, tiles):
     (512, 256, 32, False, 1),       # one launch 9.1, two 12.0
     (512, 8192, 32, True, 1),       # 53.6, three 57.1
     (512, 16384, 32, True, 3),      # 102.5, 100.1
+    (512, 16384, 4, True, 1),       # 75.1, 81.5
     (1024, 256, 16, False, 1),      # 8.6, 13.1
     (1024, 8192, 16, True, 1),      # 48.2, 51.8
     (1024, 16384, 16, True, 3),     # 89.7, 86.8
