@@ -551,10 +551,11 @@ static inline int gw_chunks(const moe_shape* s, bool jitter) {
     return n < 1 ? 1 : n;
 }
 // tokens per chunk: a multiple of 2 tokens per wave, of a round where chunks are short (a partial
-// round costs as much as a whole one)
+// round costs as much as a whole one) and the round does not take the chunk past 1 GiB
 static inline int gw_chunk_tokens(const moe_shape* s, bool jitter) {
     const int n = ceil_div(s->T, gw_chunks(s, jitter));
-    const int q = n < 256 ? gw_round(s) : 2 * GW_WAVES;
+    const int r = gw_round(s);
+    const int q = n < 256 && (size_t)(ceil_div(n, r) * r) * s->d_model * 4 <= (size_t)1 << 30 ? r : 2 * GW_WAVES;
     return ceil_div(n, q) * q;
 }
 size_t gate_logits_bwd_ws_bytes(const moe_shape* s) {    

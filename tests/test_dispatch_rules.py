@@ -113,3 +113,15 @@ def test_projection_backward_chunks(T, d, E, dtype, eps, chunks):
     (65536, 2048, 16, 2, I.BF16, 1)])
 def test_combine_and_gate_backward(T, d, E, k, dtype, launches):
     assert B.moe_combine_gate_bwd_launches(B.make_shape(T, d, 64, E, k, max(1, T * k // E), dtype, I.GELU)) == launches
+
+
+@pytest.mark.parametrize("dtype,d", [(I.F32, 1 << 22), (I.F32, 1 << 23), (I.F32, 1 << 24), (I.BF16, 1 << 23), (I.BF16, 1 << 24)])
+def test_projection_backward_chunks_of_very_wide_tokens_keep_32_bit_offsets(dtype, d):
+    """A chunk's rows of x are addressed with 32-bit byte offsets up to 2 GiB; rounding its tokens up must not pass that."""
+    for T in (1025, 4096, 5003):
+        s = B.make_shape(T, d, 8, 2, 1, 1, dtype, I.GELU)
+        for eps in (0.0, 0.01):
+            chunks = B.moe_gate_logits_bwd_chunks(s, eps)
+            # every chunk but the last is full, so no chunk holds fewer tokens than this
+            tokens = -(-T // chunks)
+            assert tokens * d * (4 if dtype == I.F32 else 2) < 1 << 31, (T, chunks)
