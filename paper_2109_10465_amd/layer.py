@@ -76,10 +76,11 @@ class MoELayer:
         """Options and buffers of one call, from the layer's attributes as they are now."""
         at = self.__dict__
         ptrs = [None if at[n] is None else at[n].data_ptr() for n in self._FWD]
-        ptrs += [None] * len(self._BWD) if self.forward_only else [at[n].data_ptr() for n in self._BWD]
-        return (B.LayerOptions(self.groups, self.forward_only, logits_given, self.aux_coef, self.jitter_eps,
-                               self.drop_p, self.seed & 0xFFFFFFFFFFFFFFFF),
-                B.LayerBuffers(*ptrs, self.ws.data_ptr(), self.ws.numel()))
+        ptrs += [None] * len(self._BWD) if self.forward_only else [None if at[n] is None else at[n].data_ptr() for n in self._BWD]
+        # attributes may have been set anew since: whatever is a number, and fewer than two groups is plain routing
+        return (B.LayerOptions(max(1, int(self.groups)), bool(self.forward_only), logits_given, self.aux_coef,
+                               self.jitter_eps, self.drop_p, int(self.seed) & 0xFFFFFFFFFFFFFFFF),
+                B.LayerBuffers(*ptrs, self.ws.data_ptr(), self.ws.numel() * self.ws.element_size()))
 
     def forward(self, x, Wg, bias, W1, W2, rts_keys, logits=None, seed=0):
         """logits: optional precomputed [T,E] fp32 gate logits; the projection call is
