@@ -38,6 +38,10 @@ int moe_gate_logits_bwd_chunks(const moe_shape* shape, float jitter_eps);
 /* Launches of moe_combine_gate_bwd: 1 = one pass over the tokens, 2 = combine, then gate. */
 int moe_combine_gate_bwd_launches(const moe_shape* shape);
 
+/* Tile side (64, 128 or 256) and groups of four waves that share a tile (1 or 2), for each of the
+ * expert FFN's four launches: xd W1, h W2, dz with dW2, dxd with dW1. */
+int moe_expert_ffn_tiles(const moe_shape* shape, int32_t* side, int32_t* wave_groups);
+
 #ifdef __cplusplus
 }
 #endif

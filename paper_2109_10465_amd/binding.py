@@ -24,7 +24,7 @@ EXPORTS = [
     "moe_gate_route_static", "moe_gate_route_static_max_bytes", "moe_dispatch_tokens", "moe_combine_gate_bwd",
     "moe_gate_route_counted", "moe_layer_fwd", "moe_layer_bwd", "moe_route_launches",
     "moe_gate_logits_token_tiles", "moe_gate_logits_bwd_launches", "moe_gate_logits_bwd_chunks",
-    "moe_combine_gate_bwd_launches",
+    "moe_combine_gate_bwd_launches", "moe_expert_ffn_tiles",
 ]
 
 
@@ -98,6 +98,7 @@ def lib():
             "moe_dispatch_gate_logits_bwd": [shp] + [vp] * 6 + [ctypes.c_float, ctypes.c_uint64, vp, vp, vp, sz, vp],
             "moe_route_launches": [shp, i32, i32],
             "moe_gate_logits_token_tiles": [shp],
+            "moe_expert_ffn_tiles": [shp, vp, vp],
             "moe_combine_gate_bwd_launches": [shp],
             "moe_gate_logits_bwd_chunks": [shp, ctypes.c_float],
             "moe_gate_logits_bwd_launches": [shp, i32, ctypes.c_float],
@@ -284,6 +285,13 @@ def moe_gate_logits_bwd_chunks(shape, jitter_eps):
 
 def moe_combine_gate_bwd_launches(shape):
     return lib().moe_combine_gate_bwd_launches(ctypes.byref(shape))
+
+
+def moe_expert_ffn_tiles(shape):
+    """[(tile side, wave groups)] of the four launches: xd W1, h W2, dz with dW2, dxd with dW1."""
+    side, groups = (ctypes.c_int32 * 4)(), (ctypes.c_int32 * 4)()
+    _check(lib().moe_expert_ffn_tiles(ctypes.byref(shape), side, groups), "moe_expert_ffn_tiles")
+    return list(zip(side, groups))
 
 
 def moe_microbench_mfma_bf16(n_workgroups, iters, random_operands, out, stream=None):

@@ -1386,12 +1386,13 @@ static bool launch_big_pair(GemmArgs p1, GemmArgs p2, int E, hipStream_t st) {
 }
 
 // ---- which tile ------------------------------------------------------------------
-// The expert counts are on the device; the host knows the mean demand T k / E and the
-// capacity, so rows = the smaller of the two is what an expert holds at most on average.
-// Tiles expected with a given tile side:
-static double tiles_expected(const GemmArgs& p, int rows, int side, int E) {
-    return (double)E * ceil_div(p.var_k ? p.M : rows, side) * ceil_div(p.N, side);
-}
+// The expert counts are on the device; the host knows the mean demand T k / E and the capacity and takes the smaller
+// of the two for the rows of every expert.  With a skewed gate that is more than the mean of what experts hold: those
+// above the capacity drop rows and the others have fewer.  (Six experts, T = 5003, top-2, Zipf gate: 1668 against 1392 on
+// average, so that h W2 with d = 776, f = 3080 gets the large tile where the small one measured faster.)
+enum FfnTile { TILE_64, TILE_128_PAIRED, TILE_128, TILE_256 };      // PAIRED: two wave groups share a tile
+// Tiles of a given side of one product: `rows` output rows (the expert's, or all M of a weight gradient), N columns.
+static double tiles_expected(int rows, int N, int side, int E) { return (double)E * ceil_div(rows, side) * ceil_div(N, side); }
 // bf16, experts with more than 128 rows: time goes with the number of whole rounds.  The 256 x 256
 // kernel runs one tile per CU and round; the 128 x 128 one runs two per CU, each a quarter of the
 // work at 0.78 of the rate (0.74 - 0.87 over the six products at 32 experts of 1024 rows, d = 1024,
@@ -1410,35 +1411,48 @@ static bool prefer_mid(double t256, double t128) {
 // 22 with 128 x 128, 17 and 39 with 256 x 256); with few rows per expert the weights' stream is the
 // bound and two 128 x 128 workgroups per CU keep more of it in flight than one large one (107 experts
 // of 7 rows, d = 1024, f = 4096: 169 us = 5.3 TB/s against 203).
+static FfnTile tile_for(bool f32, int rows, int N, int E) {
+    const double cus = num_cus(), t128 = tiles_expected(rows, N, 128, E);
+    if (f32) return t128 <= 0.6 * cus ? TILE_64 : t128 <= 1.5 * cus ? TILE_128_PAIRED : TILE_128;
+    if (t128 <= (rows <= 128 ? 1.0 : 0.5) * cus) return TILE_64;
+    return rows <= 128 || prefer_mid(tiles_expected(rows, N, 256, E), t128) ? TILE_128 : TILE_256;
+}
+
+// Two products, `rows` rows by N1 columns and a weight gradient of M2 by N2: the same lines at higher tile
+// counts, because the tiles of both are in the launch (fp32, 248 + 512 tiles: 185 us with two wave groups, 250 with
+// one; 992 + 512: 197 and 179.  bf16, 8 experts of 64 rows, 32 + 512 tiles: 26 us with 64 x 64, 30 with 128 x 128, 41
+// with 256 x 256).
+static FfnTile tile_for_pair(bool f32, int rows, int N1, int M2, int N2, int E) {
+    const double cus = num_cus(), t128 = tiles_expected(rows, N1, 128, E) + tiles_expected(M2, N2, 128, E);
+    if (f32) return t128 <= 0.75 * cus ? TILE_64 : t128 <= 4.0 * cus ? TILE_128_PAIRED : TILE_128;
+    if (t128 <= (rows <= 128 ? 3.0 : 1.0) * cus) return TILE_64;
+    return prefer_mid(tiles_expected(rows, N1, 256, E) + tiles_expected(M2, N2, 256, E), t128) ? TILE_128 : TILE_256;
+}
+
 template <typename T, bool A_KC, bool B_KC, int EPI, int ACT = 0>
 static bool launch_gemm(const GemmArgs& p, int rows, int E, hipStream_t st) {
-    const double cus = num_cus(), t128 = tiles_expected(p, rows, 128, E);
+    const FfnTile t = tile_for(sizeof(T) == 4, rows, p.N, E);
     if constexpr (sizeof(T) == 4) {
-        if (t128 <= 0.6 * cus) return launch_mid<T, 64, 64, 2, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
-        if (t128 <= 1.5 * cus) return launch_mid<T, 128, 128, 2, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
+        if (t == TILE_64) return launch_mid<T, 64, 64, 2, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
+        if (t == TILE_128_PAIRED) return launch_mid<T, 128, 128, 2, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
         return launch_mid<T, 128, 128, 1, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
     } else {
-        if (t128 <= (rows <= 128 ? 1.0 : 0.5) * cus) return launch_mid<T, 64, 64, 1, 3, A_KC, B_KC, EPI, ACT>(p, E, st);
-        if (rows <= 128 || prefer_mid(tiles_expected(p, rows, 256, E), t128))
-            return launch_mid<T, 128, 128, 1, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
+        if (t == TILE_64) return launch_mid<T, 64, 64, 1, 3, A_KC, B_KC, EPI, ACT>(p, E, st);
+        if (t == TILE_128) return launch_mid<T, 128, 128, 1, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
         return launch_big<A_KC, B_KC, EPI, ACT>(p, E, st);
     }
 }
 
-// Two products: the same lines at higher tile counts, because the tiles of both are in the launch
-// (fp32, 248 + 512 tiles: 185 us with two wave groups, 250 with one; 992 + 512: 197 and 179.  bf16,
-// 8 experts of 64 rows, 32 + 512 tiles: 26 us with 64 x 64, 30 with 128 x 128, 41 with 256 x 256).
 template <typename T, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
 static bool launch_gemm_pair(const GemmArgs& p1, const GemmArgs& p2, int rows, int E, hipStream_t st) {
-    const double cus = num_cus(), t128 = tiles_expected(p1, rows, 128, E) + tiles_expected(p2, rows, 128, E);
+    const FfnTile t = tile_for_pair(sizeof(T) == 4, rows, p1.N, p2.M, p2.N, E);
     if constexpr (sizeof(T) == 4) {
-        if (t128 <= 0.75 * cus) return launch_mid_pair<T, 64, 64, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
-        if (t128 <= 4.0 * cus) return launch_mid_pair<T, 128, 128, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        if (t == TILE_64) return launch_mid_pair<T, 64, 64, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        if (t == TILE_128_PAIRED) return launch_mid_pair<T, 128, 128, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
         return launch_mid_pair<T, 128, 128, 1, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
     } else {
-        if (t128 <= (rows <= 128 ? 3.0 : 1.0) * cus) return launch_mid_pair<T, 64, 64, 1, 3, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
-        if (prefer_mid(tiles_expected(p1, rows, 256, E) + tiles_expected(p2, rows, 256, E), t128))
-            return launch_mid_pair<T, 128, 128, 1, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        if (t == TILE_64) return launch_mid_pair<T, 64, 64, 1, 3, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        if (t == TILE_128) return launch_mid_pair<T, 128, 128, 1, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
         return launch_big_pair<A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
     }
 }
@@ -1528,6 +1542,21 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     q.out0 = dW1; q.ldo = f; q.strideO = (long long)d * f;
     q.M = d; q.N = f; q.K = C;
     return launch_gemm_pair<T, true, true, EPI_STORE, false, false, EPI_F32>(p, q, rows, E, st);
+}
+
+// measurement aid: the tile of each of the four launches (xd W1, h W2, dz with dW2, dxd with dW1)
+extern "C" int moe_expert_ffn_tiles(const moe_shape* shape, int32_t* side, int32_t* wave_groups) {
+    int rc = shape_status(shape);
+    if (rc || (rc = check_slice_limits(shape))) return rc;
+    if (!side || !wave_groups) return MOE_ERR_NULL;
+    const bool f32 = shape->dtype == MOE_F32;
+    const int rows = expected_rows(shape), d = shape->d_model, f = shape->d_ff, E = shape->E;
+    const FfnTile t[4] = {tile_for(f32, rows, f, E), tile_for(f32, rows, d, E), tile_for_pair(f32, rows, f, f, d, E), tile_for_pair(f32, rows, d, d, f, E)};
+    for (int i = 0; i < 4; ++i) {
+        side[i] = t[i] == TILE_64 ? 64 : t[i] == TILE_256 ? 256 : 128;
+        wave_groups[i] = f32 && t[i] != TILE_128 ? 2 : 1;
+    }
+    return MOE_OK;
 }
 
 int ffn_fwd_check(const moe_shape* s, const void* xd, const int32_t* expert_count, const void* W1, const void* W2,

@@ -26,6 +26,39 @@ CASES = [
     eval_workload("eval_bf16_top2", 1500, 264, 520, 6, 2, I.BF16, I.GELU, skew="zipf", skew_param=1.1),
     eval_workload("eval_bf16_relu", 2049, 128, 136, 9, 1, I.BF16, I.RELU, skew="hot0", skew_param=0.6),
 ]
+# the activation-only epilogue on the other tiles: name, sizes, tile side and wave groups of xd W1
+TILES = [("eval_bf16_128", 6400, 136, 1032, 64, 1, I.BF16, (128, 1)), ("eval_bf16_256", 2600, 520, 2056, 8, 2, I.BF16, (256, 1)),
+         ("eval_f32_128_groups", 1500, 136, 1032, 8, 2, I.F32, (128, 2)), ("eval_f32_128", 2200, 40, 2056, 8, 2, I.F32, (128, 1))]
+TILE_CASES = [(eval_workload(f"{n}_{a}", T, d, f, E, k, dt, act, skew="hot0", skew_param=0.3), tile)
+              for n, T, d, f, E, k, dt, tile in TILES for a, act in (("gelu", I.GELU), ("relu", I.RELU))]
+
+
+@pytest.mark.parametrize("w,tile", TILE_CASES, ids=[w.name for w, _ in TILE_CASES])
+def test_forward_only_on_every_tile(w, tile):
+    """h, yd and y of the forward-only call equal those of the training forward bit for bit, and the oracle's."""
+    assert B.moe_expert_ffn_tiles(B.make_shape(w.T, w.d_model, w.d_ff, w.E, w.k, w.capacity, w.dtype, w.act))[0] == tile
+    d = I.make_inputs(w, seed=31)
+    _, lg32 = G.oracle_logits(d)
+    ref = O.moe_layer(d["x"], d["Wg"], d["bias"], d["W1"], d["W2"], d["rts_keys"], None, w.k, w.capacity, w.act, logits=lg32)
+    train = MoELayer(w.T, w.d_model, w.d_ff, w.E, w.k, w.capacity, w.dtype, w.act)
+    ev = MoELayer(w.T, w.d_model, w.d_ff, w.E, w.k, w.capacity, w.dtype, w.act, forward_only=True)
+    args = (G.to_dev(d["x"], w.dtype), G.to_dev(d["Wg"], I.F32), G.to_dev(d["bias"], I.F32), G.to_dev(d["W1"], w.dtype),
+            G.to_dev(d["W2"], w.dtype), G.to_dev(d["rts_keys"], I.F32))
+    print(f"[gpu] {w.name} forward-only", flush=True)
+    for layer in (train, ev):
+        layer.forward(*args, logits=G.to_dev(lg32, I.F32))
+    torch.cuda.synchronize()
+    for n in G.INT_NAMES:
+        assert np.array_equal(G.host(getattr(ev, n)), ref[n]), n
+    m = G.row_mask(ref["expert_count"], w.capacity)
+    md = torch.from_numpy(m).cuda()
+    for n in ("h", "yd"):
+        assert torch.equal(getattr(train, n)[md], getattr(ev, n)[md]), n
+    assert torch.equal(train.y, ev.y)
+    tol = G.TOL[w.dtype]
+    assert G.rel_l2(G.host(ev.h)[m], ref["H"][m]) <= tol
+    assert G.rel_l2(G.host(ev.yd)[m], ref["Yd"][m]) <= tol
+    assert G.rel_l2(G.host(ev.y), ref["y"]) <= tol
 
 
 @pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)

@@ -1,5 +1,6 @@
-"""GPU: the expert FFN on every tile the launch rule can choose, at sizes that fall between tiles: row counts around
-a tile edge, d_model and d_ff that are no multiple of a tile or a slab, experts without rows."""
+"""GPU: the expert FFN on every tile the launch rule can choose, in each of its four launches, at sizes that fall between
+tiles: row counts around a tile edge, d_model and d_ff that are no multiple of a tile or a slab, experts without rows.
+The tile that the rule chooses for a shape is asserted, so that a shape cannot come to test another kernel unnoticed."""
 import numpy as np
 import pytest
 import torch
@@ -11,24 +12,37 @@ import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 F, H = I.F32, I.BF16
-#        name          T     d     f   E  k  capacity dtype
+S64, S128, S256, P64, P128 = (64, 1), (128, 1), (256, 1), (64, 2), (128, 2)      # tile side, wave groups
+#        name          T     d     f   E  k  capacity dtype, tiles of xd W1, h W2, dz with dW2, dxd with dW1
 SHAPES = [
-    ("bf16_64_one_row",    3,   72,  136,  3, 1,    1, H),     # 64 x 64, nearly every row masked
-    ("bf16_64_edge",     390,   64,  200,  3, 2,  129, H),     # rows past two 64-row tiles
-    ("bf16_64_long_k",   120,  520, 1032,  4, 1,   40, H),     # slabs beyond the ring, last one partial
-    ("bf16_128_few",    6400,  136, 1032, 64, 1,  127, H),     # 128 x 128: few rows per expert, many tiles
-    ("bf16_128_rows",   1500,  776, 2056,  4, 2,  800, H),     # 128 x 128 because the large tile leaves CUs idle
-    ("bf16_256_ragged", 2600,  520, 2056,  8, 2,  700, H),     # the large tile, both extents ragged
-    ("f32_64_edge",      390,   72,  200,  3, 2,  129, F),
-    ("f32_64_long_k",    130,  328,  520,  2, 1,   65, F),
-    ("f32_128_groups",  1500,  136, 1032,  8, 2,  380, F),     # 128 x 128, two wave groups per tile
-    ("f32_128_single",  2200,   40, 2056,  8, 2,  560, F),     # 128 x 128, one group
+    ("bf16_64_one_row",    3,   72,  136,  3, 1,    1, H, [S64, S64, S64, S64]),       # nearly every row masked
+    ("bf16_64_edge",     390,   64,  200,  3, 2,  129, H, [S64, S64, S64, S64]),       # rows past two 64-row tiles
+    ("bf16_64_long_k",   120,  520, 1032,  4, 1,   40, H, [S64, S64, S64, S64]),       # slabs beyond the ring, last one partial
+    ("bf16_128_few",    6400,  136, 1032, 64, 1,  127, H, [S128, S64, S128, S128]),    # few rows per expert, many tiles
+    ("bf16_128_rows",   1500,  776, 2056,  4, 2,  800, H, [S128, S128, S256, S256]),   # the large tile leaves CUs idle
+    ("bf16_256_ragged", 2600,  520, 2056,  8, 2,  700, H, [S256, S128, S128, S128]),   # both extents ragged
+    ("bf16_256_second", 7168,  520,  328,  8, 2, 1900, H, [S128, S256, S128, S256]),   # h W2 with a partial last slab
+    ("f32_64_edge",      390,   72,  200,  3, 2,  129, F, [P64, P64, P64, P64]),
+    ("f32_64_long_k",    130,  328,  520,  2, 1,   65, F, [P64, P64, P64, P64]),
+    ("f32_128_groups",  1500,  136, 1032,  8, 2,  380, F, [P128, P64, P128, P64]),     # two wave groups per tile
+    ("f32_128_single",  2200,   40, 2056,  8, 2,  560, F, [S128, P64, P128, P64]),
+    ("f32_128_one",     8320,  264, 1032, 32, 2,  520, F, [S128, S128, S128, S128]),   # one group, partial last slabs
+    ("f32_128_one_even", 8320, 272, 1040, 32, 2,  520, F, [S128, S128, S128, S128]),   # whole slabs
 ]
 
 
-@pytest.mark.parametrize("name,T,d,f,E,k,C,dtype", SHAPES, ids=[s[0] for s in SHAPES])
+def test_the_shapes_cover_every_tile_of_every_launch():
+    for dtype, tiles in ((H, {S64, S128, S256}), (F, {P64, P128, S128})):
+        for launch in range(4):
+            seen = {s[8][launch] for s in SHAPES if s[7] == dtype}
+            # fp32's two-group tile in h W2 and in dxd + dW1: with the accuracy of the fp32 products
+            assert seen >= tiles - ({P128} if dtype == F and launch in (1, 3) else set()), (dtype, launch, seen)
+
+
+@pytest.mark.parametrize("name,T,d,f,E,k,C,dtype,tiles", SHAPES, ids=[s[0] for s in SHAPES])
 @pytest.mark.parametrize("act", [I.GELU, I.RELU], ids=["gelu", "relu"])
-def test_ffn_tile(name, T, d, f, E, k, C, dtype, act):
+def test_ffn_tile(name, T, d, f, E, k, C, dtype, tiles, act):
+    assert B.moe_expert_ffn_tiles(B.make_shape(T, d, f, E, k, C, dtype, act)) == tiles
     w = I.small(name, T, d, f, E, k, C, dtype, act, skew="hot0" if E > 2 else "none", skew_param=0.4)
     data = I.make_inputs(w, seed=3)
     _, got = G.run_layer(w, data)
