@@ -304,14 +304,15 @@ __device__ __forceinline__ void epilogue4(const GemmArgs& p, const TileOut& to, 
     }
 }
 
-// NWN = wavefronts along N (2 or 4); always 2 along M.
-template <typename T, int BM, int BN, int BK, bool A_KC, bool B_KC, int NWN>
+// The large-tile kernel (bf16).  NWN = wavefronts along N; 2 along M.
+template <int BM, int BN, int BK, bool A_KC, bool B_KC, int NWN>
 struct GemmSmem {
+    typedef bf16_t T;
     static constexpr int NT = 128 * NWN;        // threads per workgroup
     typedef Tile<T, BM, BK, A_KC, NT> TA;
     typedef Tile<T, BN, BK, B_KC, NT> TB;
     static constexpr int STAGE = TA::BYTES + TB::BYTES;
-    // LDS ring: 1 slab being multiplied + NSTAGE-1 in flight (as many as fit beside the epilogue strips)
+    // LDS ring: one slab being multiplied, one in flight (as many as fit beside the epilogue strips)
     static constexpr int NSTAGE = 2;
     static constexpr int EPI_LD = BN / NWN + 8; // floats per staged epilogue row (4 rows apart -> other bank half)
     static constexpr int EPI_ROWS = 8;          // one accumulator register quad of both lane halves
@@ -435,9 +436,10 @@ struct TileWalk {
 // them as one stream through the LDS ring, so the first slabs of the next tile
 // are already resident when the epilogue of the current one ends, and no
 // workgroup launch or cold first load sits between two tiles.
-template <typename T, int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI, int ACT, int NWN, bool KG>
+template <int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI, int ACT, int NWN, bool KG>
 __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const GemmArgs& p, int more, typename TileWalk<BM, BN>::Where before) {
-    typedef GemmSmem<T, BM, BN, BK, A_KC, B_KC, NWN> SM;
+    typedef bf16_t T;
+    typedef GemmSmem<BM, BN, BK, A_KC, B_KC, NWN> SM;
     typedef typename SM::TA TA;
     typedef typename SM::TB TB;
     typedef typename Vec4io<T>::raw raw;
@@ -528,7 +530,7 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
     // slab 0 of the stream has landed once at most the NS-1 younger slabs are outstanding
     wait_vmcnt<(NS - 1) * SM::LOADS>();
     __syncthreads();
-    // Two-stage ring with four k-steps per slab (the bf16 tiles): the B half of a stage is released
+    // Two-stage ring with four k-steps per slab: the B half of a stage is released
     // early.  A wave needs few B fragments (TN per k-step), so it reads those of all four k-steps
     // during the slab's first step; one barrier later nobody reads the B half again and it is
     // refilled three k-steps before the A half.  The two halves of a slab are then requested at
@@ -536,7 +538,8 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
     // to arrive instead of one.
     // (not in the instance whose epilogue keeps saved-derivative rows in registers through the
     // main loop: the extra fragment registers would spill there)
-    constexpr bool BEARLY = NS == 2 && KS == 4 && EPI != EPI_MUL;
+    static_assert(NS == 2 && KS == 4, "the schedules below are laid out by hand for these");
+    constexpr bool BEARLY = EPI != EPI_MUL;
     typename Mma<T>::frag fa[2][TM], fb[BEARLY ? KS : 2][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) fa[0][i] = TA::frag(smem_raw, wm * (BM / 2) + i * 32, 0, lane);
@@ -595,7 +598,7 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
             const int next = stage == NS - 1 ? 0 : stage + 1;
             if constexpr (BEARLY) {
                 constexpr int NMMA = TM * TN;
-                static_assert(TM + TN <= NMMA && TB::PER_THREAD <= NMMA && TA::PER_THREAD <= NMMA, "one request per MFMA slot");
+                static_assert(NMMA == 2 * TM && TN <= TM && NMMA % TB::PER_THREAD == 0 && NMMA % TA::PER_THREAD == 0, "slots of the requests and fragment reads below");
                 // ---- k-step 0: MFMAs on (fa[0], fb[0]); A fragments of step 1 and B fragments of steps 1..3
 #pragma unroll
                 for (int i = 0; i < TM; ++i) fa[1][i] = TA::frag(a_s, wm * (BM / 2) + i * 32, 1, lane);
@@ -626,22 +629,16 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
                 // them in one place leaves the pipe idle whenever both waves are in such a run.)
 #pragma unroll
                 for (int q = 0; q < NMMA; ++q) {
-                    constexpr int LSTEP = NMMA / TB::PER_THREAD >= 1 ? NMMA / TB::PER_THREAD : 1;   // a request every LSTEP slots
-                    if (q % LSTEP == 0 && q / LSTEP < TB::PER_THREAD) produce_issue(TA::PER_THREAD + q / LSTEP);
-                    if (NMMA >= 2 * TM ? (q % 2 == 1 && q / 2 < TM) : q < TM) {
-                        const int i = NMMA >= 2 * TM ? q / 2 : q;
-                        fa[0][i] = TA::frag(a_s, wm * (BM / 2) + i * 32, 2, lane);
-                    }
+                    constexpr int LSTEP = NMMA / TB::PER_THREAD;   // a request every LSTEP slots
+                    if (q % LSTEP == 0) produce_issue(TA::PER_THREAD + q / LSTEP);
+                    if (q % 2 == 1) fa[0][q / 2] = TA::frag(a_s, wm * (BM / 2) + q / 2 * 32, 2, lane);
                     acc[q / TN][q % TN] = Mma<T>::mma(fa[1][q / TN], fb[1][q % TN], acc[q / TN][q % TN]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 // ---- k-step 2: MFMAs on (fa[0], fb[2]); A fragments of step 3
 #pragma unroll
                 for (int q = 0; q < NMMA; ++q) {
-                    if (NMMA >= 2 * TM ? (q % 2 == 0 && q / 2 < TM) : q < TM) {
-                        const int i = NMMA >= 2 * TM ? q / 2 : q;
-                        fa[1][i] = TA::frag(a_s, wm * (BM / 2) + i * 32, 3, lane);
-                    }
+                    if (q % 2 == 0) fa[1][q / 2] = TA::frag(a_s, wm * (BM / 2) + q / 2 * 32, 3, lane);
                     acc[q / TN][q % TN] = Mma<T>::mma(fa[0][q / TN], fb[2][q % TN], acc[q / TN][q % TN]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -662,18 +659,13 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
                 const unsigned char* a_n = smem_raw + next * SM::STAGE;
 #pragma unroll
                 for (int q = 0; q < NMMA; ++q) {
-                    constexpr int LSTEP = NMMA / TA::PER_THREAD >= 1 ? NMMA / TA::PER_THREAD : 1;
-                    if (q % LSTEP == 0 && q / LSTEP < TA::PER_THREAD) produce_issue(q / LSTEP);
-                    if (NMMA >= 2 * TM) {
-                        // odd slots: one A fragment each; the B fragments (needed first) ride with the first ones
-                        if (q % 2 == 1) {
-                            const int i = q / 2;
-                            if (i < TM) fa[0][i] = TA::frag(a_n, wm * (BM / 2) + i * 32, 0, lane);
-                            if (i < TN) fb[0][i] = TB::frag(a_n + TA::BYTES, wn * WCOLS + i * 32, 0, lane);
-                        }
-                    } else {
-                        if (q < TM) fa[0][q] = TA::frag(a_n, wm * (BM / 2) + q * 32, 0, lane);
-                        else if (q < TM + TN) fb[0][q - TM] = TB::frag(a_n + TA::BYTES, wn * WCOLS + (q - TM) * 32, 0, lane);
+                    constexpr int LSTEP = NMMA / TA::PER_THREAD;
+                    if (q % LSTEP == 0) produce_issue(q / LSTEP);
+                    // odd slots: one A fragment each; the B fragments (needed first) ride with the first ones
+                    if (q % 2 == 1) {
+                        const int i = q / 2;
+                        fa[0][i] = TA::frag(a_n, wm * (BM / 2) + i * 32, 0, lane);
+                        if (i < TN) fb[0][i] = TB::frag(a_n + TA::BYTES, wn * WCOLS + i * 32, 0, lane);
                     }
                     acc[q / TN][q % TN] = Mma<T>::mma(fa[1][q / TN], fb[3][q % TN], acc[q / TN][q % TN]);
                     __builtin_amdgcn_sched_barrier(0);
@@ -810,9 +802,9 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
     return cw.where();
 }
 
-template <typename T, int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI, int ACT, int NWN, bool KG>
+template <int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI, int ACT, int NWN, bool KG>
 __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_kernel(const GemmArgs p) {   // two waves per SIMD: at most 256 registers
-    gemm_body<T, BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, KG>(p, 0, {0, 0});
+    gemm_body<BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, KG>(p, 0, {0, 0});
 }
 
 // Two independent grouped GEMMs in one launch: every workgroup walks its tiles of the
@@ -820,16 +812,17 @@ __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_kernel(const GemmAr
 // two products must not depend on each other), so a workgroup that is done with the first
 // starts the second at once: one launch, one ramp-up and one tail instead of two, and the
 // workgroups drift apart, which spreads the store bursts of their epilogues.
-template <typename T, int BM, int BN, int BK, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2, int NWN, bool KG>
+template <int BM, int BN, int BK, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2, int NWN, bool KG>
 __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_pair_kernel(const GemmArgs p1, const GemmArgs p2) {
-    const typename TileWalk<BM, BN>::Where w = gemm_body<T, BM, BN, BK, A1, B1, EPI1, 0, NWN, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0});
+    const typename TileWalk<BM, BN>::Where w = gemm_body<BM, BN, BK, A1, B1, EPI1, 0, NWN, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0});
     __syncthreads();      // every wave is done with the ring and the tile table of the first product
-    gemm_body<T, BM, BN, BK, A2, B2, EPI2, 0, NWN, KG>(p2, -1, w);
+    gemm_body<BM, BN, BK, A2, B2, EPI2, 0, NWN, KG>(p2, -1, w);
 }
 
 // ---------------------------------------------------------------------------
-// The same products on smaller tiles (64 x 64 or 128 x 128, 2 x 2 waves), several
-// workgroups per CU: for problems that give the large tile too few workgroups, for
+// The same products on smaller tiles (64 x 64 or 128 x 128, 2 x 2 waves; fp32 with few
+// tiles: two such groups share one), two or three workgroups per CU (one for the
+// two-group forms, whose ring takes 96 KB): for problems that give the large tile too few workgroups, for
 // experts with few rows (then the weights' stream from HBM is the bound and the
 // other workgroups of a CU keep requests in flight while one is in its prologue or
 // epilogue), and for all fp32 tensors.
@@ -1356,13 +1349,13 @@ static bool launch_mid_pair(GemmArgs p1, GemmArgs p2, int E, hipStream_t st) {
 
 template <bool A_KC, bool B_KC, int EPI, int ACT>
 static bool launch_big(GemmArgs p, int E, hipStream_t st) {
-    typedef GemmSmem<bf16_t, BIG_M, BIG_N, BIG_K, A_KC, B_KC, BIG_WN> SM;
+    typedef GemmSmem<BIG_M, BIG_N, BIG_K, A_KC, B_KC, BIG_WN> SM;
     set_tiles(p, BIG_M, BIG_N, E);
     const size_t smem = SM::BYTES + WALK_BYTES;
     const bool kg = (A_KC || B_KC) && !p.var_k && p.K % BIG_K != 0;
     static unsigned long long opted[2] = {0, 0};
-    auto kern = kg ? grouped_gemm_kernel<bf16_t, BIG_M, BIG_N, BIG_K, A_KC, B_KC, EPI, ACT, BIG_WN, true>
-                   : grouped_gemm_kernel<bf16_t, BIG_M, BIG_N, BIG_K, A_KC, B_KC, EPI, ACT, BIG_WN, false>;
+    auto kern = kg ? grouped_gemm_kernel<BIG_M, BIG_N, BIG_K, A_KC, B_KC, EPI, ACT, BIG_WN, true>
+                   : grouped_gemm_kernel<BIG_M, BIG_N, BIG_K, A_KC, B_KC, EPI, ACT, BIG_WN, false>;
     if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
     kern<<<gemm_grid(all_tiles(p)), SM::NT, smem, st>>>(p);
     return true;
@@ -1370,16 +1363,16 @@ static bool launch_big(GemmArgs p, int E, hipStream_t st) {
 
 template <bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
 static bool launch_big_pair(GemmArgs p1, GemmArgs p2, int E, hipStream_t st) {
-    typedef GemmSmem<bf16_t, BIG_M, BIG_N, BIG_K, A1, B1, BIG_WN> SM1;
-    typedef GemmSmem<bf16_t, BIG_M, BIG_N, BIG_K, A2, B2, BIG_WN> SM2;
+    typedef GemmSmem<BIG_M, BIG_N, BIG_K, A1, B1, BIG_WN> SM1;
+    typedef GemmSmem<BIG_M, BIG_N, BIG_K, A2, B2, BIG_WN> SM2;
     static_assert(SM1::NT == SM2::NT, "one workgroup shape");
     set_tiles(p1, BIG_M, BIG_N, E);
     set_tiles(p2, BIG_M, BIG_N, E);
     const size_t smem = (SM1::BYTES > SM2::BYTES ? SM1::BYTES : SM2::BYTES) + WALK_BYTES;
     const bool kg = ((A1 || B1) && !p1.var_k && p1.K % BIG_K != 0) || ((A2 || B2) && !p2.var_k && p2.K % BIG_K != 0);
     static unsigned long long opted[2] = {0, 0};
-    auto kern = kg ? grouped_gemm_pair_kernel<bf16_t, BIG_M, BIG_N, BIG_K, A1, B1, EPI1, A2, B2, EPI2, BIG_WN, true>
-                   : grouped_gemm_pair_kernel<bf16_t, BIG_M, BIG_N, BIG_K, A1, B1, EPI1, A2, B2, EPI2, BIG_WN, false>;
+    auto kern = kg ? grouped_gemm_pair_kernel<BIG_M, BIG_N, BIG_K, A1, B1, EPI1, A2, B2, EPI2, BIG_WN, true>
+                   : grouped_gemm_pair_kernel<BIG_M, BIG_N, BIG_K, A1, B1, EPI1, A2, B2, EPI2, BIG_WN, false>;
     if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
     kern<<<gemm_grid(all_tiles(p1) + all_tiles(p2)), SM1::NT, smem, st>>>(p1, p2);
     return true;
