@@ -838,9 +838,11 @@ __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_pair_kernel(const G
 // v_mfma_f32_32x32x16_bf16 (32 cycles each) replace eight v_mfma_f32_32x32x2_f32 (64
 // cycles each); results are nearer to the exact ones than the fp32 pipe's (relative
 // error of yd at d = 512, f = 2048: 3e-7 against 9e-7).  A slab is split once per
-// workgroup on its way from registers to LDS, under the MFMAs of the slab before;
-// about as much vector work as matrix work, which is what bounds it (T = 4096,
-// d = 512, f = 2048, E = 8, top-2, the four launches: 1003 -> 560 us).  The parts hold a
+// workgroup on its way from registers to LDS, under the MFMAs of the slab before.  T = 4096,
+// d = 512, f = 2048, E = 8, top-2, the four launches: 1033 us on the fp32 pipe, 609 now, with the
+// matrix pipe busy in 39 - 51 % of the cycles and vector instructions issued in 28 - 37 %: the
+// split of every slab in every workgroup that reads it is what keeps the two apart from the
+// 225 us that six partial products take at the pipe's peak.  The parts hold a
 // value exactly from 2^-110 to 3.39e38; results that operands outside of that range, or
 // infinite or NaN ones, may have reached are formed again on the fp32 pipe (redo_f32).
 //
