@@ -533,17 +533,18 @@ static inline int gw_chunks(const moe_shape* s, bool jitter) {
     // than the sum over more chunks costs.  Measured, us:
     //   jitter (its Philox words are the time): T = 8192, d = 768, E = 16: 32 chunks 37, 64 chunks 26; T = 32768, d = 64,
     //     E = 32: 128 chunks 36.7, 256 31.2
-    //   fp32: T = 4096, d = 512, E = 8: 16 chunks 18.9, 64 11.3; T = 8192, d = 64, E = 32: 32 chunks 17.9, 128 15.9; T = 16384,
-    //     d = 64, E = 16: 64 chunks 19.3, 256 21.6
-    //   bf16: T = 4096, d = 512, E = 32: 16 chunks 12.9, 32 12.1; E = 128 (8 MiB of partial sums): 13.9, 15.2; T = 6000, d = 1024,
-    //     E = 32: 24 chunks 13.9, 47 16.1
+    //   fp32: T = 4096, d = 512, E = 16: 16 chunks 18.5, 64 14.2; T = 12288, d = 64, E = 16: 48 chunks 18.3, 192 17.4; T = 16384,
+    //     d = 64, E = 4: 64 chunks 18.8, 256 19.2
+    //   bf16: T = 4096, d = 512, E = 32: 16 chunks 12.7, 32 12.0; T = 6000, d = 512, E = 16: 24 chunks 13.7, 47 13.1; T = 7000,
+    //     d = 776, E = 16: 28 chunks 13.9, 55 14.5; partial sums of 3.2 MiB (T = 2100, d = 776, E = 64): 13.0 and 12.8,
+    //     of 4.3 MiB (E = 128, d = 512): 13.0 and 13.2, of 8 MiB (T = 4096, d = 1024, E = 64): 13.8 and 15.2
     const int tiles = ceil_div(s->d_model, GW_COLS) * ceil_div(s->E, 32);
     const int want = ceil_div(512, tiles), maxc = ceil_div(s->T, 256);
     int n = want < maxc ? want : maxc;
     if ((long long)n * tiles < 256) {
         const int one = ceil_div(256, tiles), most = ceil_div(s->T, gw_round(s)), m = one < most ? one : most;
         const bool bf16 = s->dtype == MOE_BF16;
-        if (jitter || (bf16 ? m <= 32 && (size_t)m * s->d_model * s->E * 4 <= 4608 * 1024 : m <= 128)) n = m;
+        if (jitter || (bf16 ? m <= 48 && (size_t)m * s->d_model * s->E * 4 <= 3584 * 1024 : m <= 192)) n = m;
     }
     // one chunk's rows of x are addressed with 32-bit byte offsets: keep it below 1 GiB
     const int minc = (int)(((size_t)s->T * s->d_model * 4 + ((size_t)1 << 30) - 1) >> 30);
@@ -729,15 +730,14 @@ __global__ __launch_bounds__(256) void gate_dwg_reduce_kernel(int n, int nchunk,
     const int idx = blockIdx.x * 256 + threadIdx.x;
     if (idx >= n) return;
     float s = 0.0f;
-    int c = 0;
-    for (; c + 8 <= nchunk; c += 8) {   // 8 independent loads in flight, added in chunk order
-        float v[8];
+    for (int c = 0; c < nchunk; c += 16) {      // 16 independent loads in flight, the last ones too, added in chunk order
+        float v[16];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)(c + u) * n + idx];
+        for (int u = 0; u < 16; ++u) v[u] = partial[(size_t)min(c + u, nchunk - 1) * n + idx];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s += v[u];
+        for (int u = 0; u < 16; ++u)
+            if (c + u < nchunk) s += v[u];
     }
-    for (; c < nchunk; ++c) s += partial[(size_t)c * n + idx];
     dWg[idx] = s;
 }
 

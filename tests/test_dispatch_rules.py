@@ -82,14 +82,16 @@ def test_projection_backward(T, d, E, with_dx, launches):
 
 
 @pytest.mark.parametrize("T,d,E,dtype,eps,chunks", [
-    (4096, 512, 32, I.BF16, 0.0, 32),       # 16 chunks 12.9, 32 12.1
-    (4096, 512, 128, I.BF16, 0.0, 16),      # 13.9, 15.2 with 32
-    (6000, 1024, 32, I.BF16, 0.0, 24),      # 13.9, 16.1 with 47
-    (32768, 64, 32, I.BF16, 0.0, 128),      # 17.0, 21.1 with 256
+    (4096, 512, 32, I.BF16, 0.0, 32),       # 16 chunks 12.7, 32 12.0
+    (4096, 1024, 64, I.BF16, 0.0, 16),      # 13.8, 15.2 with 32
+    (5003, 776, 4, I.BF16, 0.0, 40),        # 20 chunks 13.4, 40 12.6
+    (6000, 1024, 32, I.BF16, 0.0, 24),      # 14.0, 14.4 with 47
+    (7000, 776, 16, I.BF16, 0.0, 28),       # 13.9, 14.5 with 55
+    (32768, 64, 32, I.BF16, 0.0, 128),      # 16.0, 19.2 with 256
     (6000, 1024, 16, I.BF16, 0.01, 47),     # 24 chunks 33.3, 47 25.6
     (32768, 64, 32, I.BF16, 0.01, 256),     # 128 chunks 36.7, 256 31.2
-    (8192, 64, 32, I.F32, 0.0, 128),        # 32 chunks 17.9, 128 15.9
-    (16384, 64, 16, I.F32, 0.0, 64),        # 19.3, 21.6 with 256
+    (12288, 64, 16, I.F32, 0.0, 192),       # 48 chunks 18.3, 192 17.4
+    (16384, 64, 4, I.F32, 0.0, 64),         # 18.8, 19.2 with 256
     (65536, 1024, 32, I.BF16, 0.0, 128)])   # the chip is full twice
 def test_projection_backward_chunks(T, d, E, dtype, eps, chunks):
     s = B.make_shape(T, d, 64, E, 1, 8, dtype, I.GELU)
