@@ -328,7 +328,8 @@ extern "C" int moe_combine_gate_bwd(const moe_shape* shape, const void* dy, cons
                                     void* dyd, float* dgate_w, float* dlogits, void* stream) {
     const int rc = begin_call(combine_gate_bwd_check(shape, dy, yd, expert_idx, slot, gate_w, probs, dyd, dgate_w, dlogits));
     if (rc) return rc;
-    if (two_passes_win(shape)) {
+    // (in one pass every wave has its token's probabilities before it writes the row: dlogits may be probs itself)
+    if (two_passes_win(shape) && dlogits != probs) {
         launch_combine_bwd<false>(shape, dy, yd, expert_idx, slot, gate_w, nullptr, nullptr, 0.0f, dyd, dgate_w, nullptr, stream);
         return first_frac_or_null
             ? moe_gate_bwd_aux(shape, dgate_w, probs, expert_idx, slot, first_frac_or_null, aux_coef, dlogits, stream)

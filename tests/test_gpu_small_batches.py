@@ -87,6 +87,12 @@ def test_combine_and_gate_backward(T, d, E, k, aux, dtype):
         rdl = rdl + O.aux_loss_bwd(p32, ff, aux)
     m = G.row_mask(cnt, C)
     assert G.rel_l2(G.host(dyd)[m], rdyd[m]) <= G.TOL[dtype]
+    # dlogits in place of the probabilities
+    pd, dg2 = G.to_dev(p32, I.F32), f32(T, k)
+    B.moe_combine_gate_bwd(s, G.to_dev(dy, dtype), G.to_dev(yd, dtype), G.to_dev(idx.astype(np.int32), None),
+                           G.to_dev(slot, None), G.to_dev(gw, I.F32), pd, G.to_dev(ff, I.F32), aux, dyd, dg2, pd)
+    torch.cuda.synchronize()
+    assert G.rel_l2(G.host(pd), rdl) <= 1e-5
     # fp32 sums of products of given values, whatever the activation type
     assert G.rel_l2(G.host(dg), rdg) <= 1e-5
     assert G.rel_l2(G.host(dl), rdl) <= 1e-5
