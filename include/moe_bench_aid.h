@@ -42,6 +42,10 @@ int moe_combine_gate_bwd_launches(const moe_shape* shape);
  * expert FFN's four launches: xd W1, h W2, dz with dW2, dxd with dW1. */
 int moe_expert_ffn_tiles(const moe_shape* shape, int32_t* side, int32_t* wave_groups);
 
+/* For the same four launches: 1 where fp32's 64 x 64 tiles are computed as 32 x 32 parts, each by a
+ * workgroup of its own whose four waves share the reduction, 0 elsewhere. */
+int moe_expert_ffn_parts(const moe_shape* shape, int32_t* parts);
+
 #ifdef __cplusplus
 }
 #endif

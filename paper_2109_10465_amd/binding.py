@@ -24,7 +24,7 @@ EXPORTS = [
     "moe_gate_route_static", "moe_gate_route_static_max_bytes", "moe_dispatch_tokens", "moe_combine_gate_bwd",
     "moe_gate_route_counted", "moe_layer_fwd", "moe_layer_bwd", "moe_route_launches",
     "moe_gate_logits_token_tiles", "moe_gate_logits_bwd_launches", "moe_gate_logits_bwd_chunks",
-    "moe_combine_gate_bwd_launches", "moe_expert_ffn_tiles",
+    "moe_combine_gate_bwd_launches", "moe_expert_ffn_tiles", "moe_expert_ffn_parts",
 ]
 
 
@@ -99,6 +99,7 @@ def lib():
             "moe_route_launches": [shp, i32, i32],
             "moe_gate_logits_token_tiles": [shp],
             "moe_expert_ffn_tiles": [shp, vp, vp],
+            "moe_expert_ffn_parts": [shp, vp],
             "moe_combine_gate_bwd_launches": [shp],
             "moe_gate_logits_bwd_chunks": [shp, ctypes.c_float],
             "moe_gate_logits_bwd_launches": [shp, i32, ctypes.c_float],
@@ -292,6 +293,13 @@ def moe_expert_ffn_tiles(shape):
     side, groups = (ctypes.c_int32 * 4)(), (ctypes.c_int32 * 4)()
     _check(lib().moe_expert_ffn_tiles(ctypes.byref(shape), side, groups), "moe_expert_ffn_tiles")
     return list(zip(side, groups))
+
+
+def moe_expert_ffn_parts(shape):
+    """Of the same four launches: are fp32's 64 x 64 tiles computed as 32 x 32 parts."""
+    parts = (ctypes.c_int32 * 4)()
+    _check(lib().moe_expert_ffn_parts(ctypes.byref(shape), parts), "moe_expert_ffn_parts")
+    return [bool(v) for v in parts]
 
 
 def moe_microbench_mfma_bf16(n_workgroups, iters, random_operands, out, stream=None):

@@ -53,6 +53,7 @@
 //     the second (6 experts of 1440 rows, d = 776, f = 3080: 174 -> 143 us for the second
 //     pair against two walks that both start at the first workgroup).
 #include <math.h>
+#include <type_traits>
 #include "moe_common.h"
 
 // the large bf16 tile: rows, columns, slab depth, wavefronts along N
@@ -76,6 +77,10 @@ struct GemmArgs {
     int M, N, K;      // extents; the one bounded by expert_count is an upper limit
     int var_k;        // 0: rows (M) bounded by expert_count; 1: K bounded by it
     int tiles_m, tiles_n, E;
+    // smaller tiles, where all that there could be fit the chip at once: this product's are an XCD's workgroups from
+    // direct_first on, direct_count tiles in all (0: by the experts' row counts), and t / d is the upper half of t * inv
+    int direct_first, direct_count;
+    uint32_t inv_expert, inv_m;
     // expert dropout in the activation epilogue (drop_thr = 0: off): an element is dropped when its
     // noise word < drop_thr, kept ones are scaled by drop_scale = 1 / (1 - p)
     uint32_t drop_thr;
@@ -336,12 +341,26 @@ struct GemmSmem {
 // every workgroup gets the same number of tiles up to one; and the tiles of a
 // heavily loaded expert (long reductions in the weight-gradient GEMMs) are spread
 // over all workgroups instead of piling up on one XCD.
+// inclusive sums over the lanes of a wave, without LDS
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);     // row_shr 1, 2, 4, 8: inside rows of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);    // row_bcast 15: rows 0 and 2 into the next ones
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);    // row_bcast 31: the lower half into the upper
+    return v;
+}
 #define WALK_BAND 4                     // row tiles per band of the walk inside an expert
 #define WALK_CNT 260                    // the experts' row counts follow the 257 running tile counts
 #define WALK_BYTES ((WALK_CNT + 256) * 4)
 template <int BM, int BN>
 struct TileWalk {
     const int* tp;          // LDS: tiles before expert e (tp[256] = all tiles)
+    // Smaller tiles and at most 64 experts: lane e holds its expert's rows and the tiles up to its last one, and no LDS
+    // or barrier is needed (0.9 us less at the start of a launch).
+    bool in_regs = false;
+    int rn, rt;
     int t, t_end, step;
     int e, m0, n0, m_lim, k_lim;   // current tile
 
@@ -390,28 +409,88 @@ struct TileWalk {
     }
     // The walk over the launch's second product goes on where the first one's ended: `u` is that
     // walk's place after its last next().
-    struct Where { int t, step; };
-    __device__ __forceinline__ Where where() const { return {t - t_end, step}; }
+    struct Where { int t, step, total; };
+    __device__ __forceinline__ Where where() const { return {t - t_end, step, t_end}; }
     __device__ __forceinline__ void resume(Where u, const unsigned char* lds) {
         tp = reinterpret_cast<const int*>(lds);
         t_end = __builtin_amdgcn_readfirstlane(tp[256]);
         step = u.step;
         t = u.t - step;
     }
+    __device__ __forceinline__ void count(const GemmArgs& p) {
+        in_regs = true;
+        const int lane = threadIdx.x & 63;
+        rn = lane < p.E ? p.expert_count[lane] : 0;
+        rn = max(0, min(rn, p.var_k ? p.K : p.M));
+        rt = lane >= p.E ? 0 : (p.var_k ? p.tiles_m : (rn + BM - 1) / BM) * p.tiles_n;
+        rt = wave_scan(rt);
+        t_end = __builtin_amdgcn_readlane(rt, 63);
+    }
+    // The workgroup's first tile: as start(), but where the tiles of both products of a launch fit in one round, an XCD
+    // has its share of each.  `other` = tiles of the other product, `second`: this is the later one.
+    __device__ __forceinline__ void begin(int other, bool second) {
+        const int x = (int)(blockIdx.x & 7), i = (int)(blockIdx.x >> 3), G = (int)(gridDim.x >> 3);
+        const int S = (t_end + 7) >> 3, O = (other + 7) >> 3;
+        if (S + O <= G) {
+            const int j = second ? i - O : i;
+            step = 0x3fffffff;
+            t = (j >= 0 && j < S ? x * S + j : t_end) - step;
+        } else {
+            const int all = min(G, (t_end + other + 7) >> 3);
+            step = 8 * all;
+            t = (i < all ? x * all + i : t_end + other);
+            if (second) t = t >= other ? t - other : t + (other - t + step - 1) / step * step - other;      // goes on where the first product's walk ended
+            t -= step;
+        }
+    }
+    // All tiles that there could be run at once, one per workgroup, and most of them are there: nothing waits for the
+    // expert's row count but what needs it (a scalar load).  Each XCD has an eighth of each product's tiles.
+    __device__ __forceinline__ bool only(const GemmArgs& p) {
+        t = t_end = step = 0;
+        const int x = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3) - p.direct_first;
+        const int S = (p.direct_count + 7) >> 3, i = x * S + j;
+        if (j < 0 || j >= S || i >= p.direct_count) return false;
+        e = p.inv_expert ? (int)__umulhi((uint32_t)i, p.inv_expert) : i;
+        const int rem = i - e * p.tiles_m * p.tiles_n, tn = p.inv_m ? (int)__umulhi((uint32_t)rem, p.inv_m) : rem;
+        m0 = (rem - tn * p.tiles_m) * BM;
+        n0 = tn * BN;
+        const int n_e = *((const __attribute__((address_space(4))) int32_t*)(uintptr_t)p.expert_count + e);
+        m_lim = p.var_k ? p.M : n_e;
+        k_lim = p.var_k ? max(0, min(n_e, p.K)) : p.K;
+        return true;
+    }
+    // only()'s rows, now that the first loads are on their way; does the tile hold any
+    __device__ __forceinline__ bool arrived(const GemmArgs& p) {
+        asm volatile("" : "+s"(m_lim));
+        m_lim = max(0, min(m_lim, p.M));
+        return m0 < m_lim;
+    }
+    // a / d for 0 <= a < 2^22: the estimate is at most one off
+    __device__ static __forceinline__ int quotient(int a, int d) {
+        const int q = __builtin_amdgcn_readfirstlane((int)((float)a * __builtin_amdgcn_rcpf((float)d)));
+        const int r = a - q * d;
+        return q + (r >= d) - (r < 0);
+    }
     // moves to the workgroup's next tile; false when the walk is over
     __device__ __forceinline__ bool next(const GemmArgs& p) {
         t += step;
         if (t >= t_end) return false;
-        // the expert that owns tile t: as many experts end at or before it (t < tp[256])
-        e = 0;
-        for (int c = 0; c < p.E; c += 64) e += __popcll(__ballot(tp[c + (threadIdx.x & 63) + 1] <= t));
-        // everything here is the same in every lane; keep it in scalar registers
-        e = __builtin_amdgcn_readfirstlane(e);
-        const int first = __builtin_amdgcn_readfirstlane(tp[e]);
-        const int count = __builtin_amdgcn_readfirstlane(tp[e + 1]) - first;
-        const int n_e = __builtin_amdgcn_readfirstlane(tp[WALK_CNT + e]);
+        // the expert that owns tile t: as many experts end at or before it
+        int first, n_e;
+        if (in_regs) {
+            e = __popcll(__ballot(rt <= t));
+            n_e = __builtin_amdgcn_readlane(rn, e);
+            first = __builtin_amdgcn_readlane(rt, e) - (p.var_k ? p.tiles_m : (n_e + BM - 1) / BM) * p.tiles_n;
+        } else {
+            e = 0;
+            for (int c = 0; c < p.E; c += 64) e += __popcll(__ballot(tp[c + (threadIdx.x & 63) + 1] <= t));
+            // everything here is the same in every lane; keep it in scalar registers
+            e = __builtin_amdgcn_readfirstlane(e);
+            first = __builtin_amdgcn_readfirstlane(tp[e]);
+            n_e = __builtin_amdgcn_readfirstlane(tp[WALK_CNT + e]);
+        }
         const int rem = t - first;
-        const int tm_e = count / p.tiles_n;   // row tiles of this expert
+        const int tm_e = p.var_k ? p.tiles_m : (n_e + BM - 1) / BM;   // row tiles of this expert
         // Inside an expert the tiles are taken band by band: a band is WALK_BAND row tiles high
         // and all column tiles wide, and inside it the row tile varies fastest.  A run of 32
         // consecutive tiles (what one XCD works on at a time) is then a 4 x 8 block that shares
@@ -419,10 +498,10 @@ struct TileWalk {
         // column tile, or the reverse, would fetch 32 + 1 panels for the same 32 tiles).
         int tm, tn;
         {
-            const int band = rem / (WALK_BAND * p.tiles_n);
+            const int band = quotient(rem, WALK_BAND * p.tiles_n);
             const int r = rem - band * WALK_BAND * p.tiles_n;
             const int rows = min(WALK_BAND, tm_e - band * WALK_BAND);   // the last band may be lower
-            tn = r / rows;
+            tn = quotient(r, rows);
             tm = band * WALK_BAND + (r - tn * rows);
         }
         m0 = tm * BM; n0 = tn * BN;
@@ -804,7 +883,7 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
 
 template <int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI, int ACT, int NWN, bool KG>
 __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_kernel(const GemmArgs p) {   // two waves per SIMD: at most 256 registers
-    gemm_body<BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, KG>(p, 0, {0, 0});
+    gemm_body<BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, KG>(p, 0, {0, 0, 0});
 }
 
 // Two independent grouped GEMMs in one launch: every workgroup walks its tiles of the
@@ -814,14 +893,14 @@ __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_kernel(const GemmAr
 // workgroups drift apart, which spreads the store bursts of their epilogues.
 template <int BM, int BN, int BK, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2, int NWN, bool KG>
 __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_pair_kernel(const GemmArgs p1, const GemmArgs p2) {
-    const typename TileWalk<BM, BN>::Where w = gemm_body<BM, BN, BK, A1, B1, EPI1, 0, NWN, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0});
+    const typename TileWalk<BM, BN>::Where w = gemm_body<BM, BN, BK, A1, B1, EPI1, 0, NWN, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0, 0});
     __syncthreads();      // every wave is done with the ring and the tile table of the first product
     gemm_body<BM, BN, BK, A2, B2, EPI2, 0, NWN, KG>(p2, -1, w);
 }
 
 // ---------------------------------------------------------------------------
 // The same products on smaller tiles (64 x 64 or 128 x 128, 2 x 2 waves; fp32 with few
-// tiles: two such groups share one), two or three workgroups per CU (one for the
+// tiles: two such groups share one; fp32's smallest: further below), two or three workgroups per CU (one for the
 // two-group forms, whose ring takes 96 KB): for problems that give the large tile too few workgroups, for
 // experts with few rows (then the weights' stream from HBM is the bound and the
 // other workgroups of a CU keep requests in flight while one is in its prologue or
@@ -869,7 +948,7 @@ struct MidSmem {
     static constexpr int BYTES = RING > STRIPS ? (RING > REDUCE ? RING : REDUCE) : (STRIPS > REDUCE ? STRIPS : REDUCE);
     // workgroups per CU: what LDS holds, and registers (the fp32 form needs about 180 at 128 x 128)
     static constexpr int FIT = 160 * 1024 / (BYTES + WALK_BYTES);
-    static constexpr int OCC = FIT >= 3 && !(SPLIT && BM * BN > 8192) ? 3 : (FIT >= 2 ? 2 : 1);
+    static constexpr int OCC = FIT >= 3 && !SPLIT ? 3 : (FIT >= 2 ? 2 : 1);
 };
 
 // 8 fp32 of one tile chunk -> three bf16 planes, rounded to nearest at every step: hi + mid + lo = w exactly
@@ -891,12 +970,14 @@ __device__ __forceinline__ void split3_rne(const u32x4_t (&w)[2], u32x4_t& hi, u
 // May any of this wave's sums hold less than fp32 products would have given?  A sum that is NaN or infinite may
 // come from an operand that the split made so; one below 2^-80 that is not zero may come from operands below
 // 2^-110 (larger ones in the same sum leave the lost bits, 2^-134 per operand, far below its rounding).
+// Rows from `rows` on (this lane's: i * 32 + l32) are not in use and may hold anything.
 template <int TM, int TN>
-__device__ __forceinline__ bool split_in_doubt(const f32x16_t (&acc)[TM][TN]) {
-    float big[4] = {0.0f, 0.0f, 0.0f, 0.0f};           // four chains: each step waits for the one before; `maximum` keeps NaN
-    uint32_t small[4] = {~0u, ~0u, ~0u, ~0u};
+__device__ __forceinline__ bool split_in_doubt(const f32x16_t (&acc)[TM][TN], int rows, int l32) {
+    bool doubt = false;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+        float big[4] = {0.0f, 0.0f, 0.0f, 0.0f};           // four chains: each step waits for the one before; `maximum` keeps NaN
+        uint32_t small[4] = {~0u, ~0u, ~0u, ~0u};
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -904,8 +985,10 @@ __device__ __forceinline__ bool split_in_doubt(const f32x16_t (&acc)[TM][TN]) {
                 big[v & 3] = __builtin_elementwise_maximum(big[v & 3], fabsf(acc[i][j][v]));
                 small[v & 3] = min(small[v & 3], (__float_as_uint(acc[i][j][v]) << 1) - 1u);      // zeros come out largest
             }
-    const bool finite = __builtin_elementwise_maximum(__builtin_elementwise_maximum(big[0], big[1]), __builtin_elementwise_maximum(big[2], big[3])) < INFINITY;
-    return __ballot(!finite || min(min(small[0], small[1]), min(small[2], small[3])) < (127u - 80u) << 24) != 0;
+        const bool finite = __builtin_elementwise_maximum(__builtin_elementwise_maximum(big[0], big[1]), __builtin_elementwise_maximum(big[2], big[3])) < INFINITY;
+        doubt |= i * 32 + l32 < rows && (!finite || min(min(small[0], small[1]), min(small[2], small[3])) < (127u - 80u) << 24);
+    }
+    return __ballot(doubt) != 0;
 }
 
 // One wave's part of an fp32 tile of expert e on the fp32 pipe, operands straight from memory (m, n: the part's first
@@ -962,14 +1045,23 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
     const int wk = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
     const int l32 = lane & 31, g = lane >> 5;
     unsigned char* walk_lds = smem_raw + SM::BYTES;
-    TileWalk<BM, BN>::build(p, walk_lds);
     TileWalk<BM, BN> w;
-    if (more < 0) w.resume(before, walk_lds); else w.start(p, walk_lds, more);
-    while (w.next(p)) {
+    const bool direct = p.direct_count > 0;
+    if (direct) {
+        if (!w.only(p)) return w.where();
+    } else if (p.E <= MOE_WAVE) {
+        w.count(p);
+        w.begin(more < 0 ? before.total : more, more < 0);
+    } else {
+        TileWalk<BM, BN>::build(p, walk_lds);
+        if (more < 0) w.resume(before, walk_lds); else w.start(p, walk_lds, more);
+    }
+    for (bool more_tiles = direct || w.next(p); more_tiles; more_tiles = !direct && w.next(p)) {
+        // rows that loads may touch: without waiting for the expert's count, all of its buffer's
+        const int m_load = direct ? p.M : w.m_lim;
         const int nk = (w.k_lim + BK - 1) / BK;
         const T* gA = (const T*)p.A + (size_t)w.e * p.strideA;
         const T* gB = (const T*)p.B + (size_t)w.e * p.strideB;
-        const bool live = w.m0 + wm * (BM / 2) < w.m_lim;     // does this wave hold any row in use
         if constexpr (EPI == EPI_F32) {
             if (nk == 0) {
                 // An expert without rows: its zeros are stored at once.  Through the loop, loads that wait for the
@@ -993,11 +1085,12 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
+        bool live;          // does this wave hold any row in use
         if constexpr (!SPLIT) {
-            u32x4_t dsA = TA::desc((const bf16_t*)gA, p.lda, w.m_lim, w.k_lim), dsB = TB::desc((const bf16_t*)gB, p.ldb, p.N, w.k_lim);
+            u32x4_t dsA = TA::desc((const bf16_t*)gA, p.lda, m_load, w.k_lim), dsB = TB::desc((const bf16_t*)gB, p.ldb, p.N, w.k_lim);
             typename TA::Plan planA;
             typename TB::Plan planB;
-            TA::plan(planA, p.lda, w.m0, w.m_lim);
+            TA::plan(planA, p.lda, w.m0, m_load);
             TB::plan(planB, p.ldb, w.n0, p.N);
             auto request = [&](int kt, int st) {
                 const int k0 = kt < nk ? kt * BK : 0;
@@ -1016,6 +1109,11 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
             };
 #pragma unroll
             for (int s = 0; s < NS - 1; ++s) request(s, s);
+            if (direct && !w.arrived(p)) {
+                wait_vmcnt<0>();
+                continue;
+            }
+            live = w.m0 + wm * (BM / 2) < w.m_lim;
             int st = 0;
             for (int kt = 0; kt < nk; ++kt) {
                 wait_vmcnt_lgkm0<(NS - 2) * SM::LOADS>();
@@ -1059,10 +1157,10 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
                 }
             };
 #pragma unroll
-            for (int i = 0; i < CA; ++i) geom(TA(), offA[i], dstA[i], kcA[i], i, p.lda, w.m0, w.m_lim);
+            for (int i = 0; i < CA; ++i) geom(TA(), offA[i], dstA[i], kcA[i], i, p.lda, w.m0, m_load);
 #pragma unroll
             for (int i = 0; i < CB; ++i) geom(TB(), offB[i], dstB[i], kcB[i], i, p.ldb, w.n0, p.N);
-            const size_t rangeA = (size_t)(A_KC ? w.m_lim : w.k_lim) * p.lda * 4, rangeB = (size_t)(B_KC ? p.N : w.k_lim) * p.ldb * 4;
+            const size_t rangeA = (size_t)(A_KC ? m_load : w.k_lim) * p.lda * 4, rangeB = (size_t)(B_KC ? p.N : w.k_lim) * p.ldb * 4;
             auto load8 = [&](__amdgpu_buffer_rsrc_t rs, uint32_t off, u32x4_t (&r)[2]) {
                 r[0] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
                 r[1] = __builtin_amdgcn_raw_buffer_load_b128(rs, off == BUF_OOB ? BUF_OOB : off + 16, 0, 0);
@@ -1144,6 +1242,8 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
             Slab s0, s1;
             fetch(0, s0);
             fetch(1, s1);
+            if (direct && !w.arrived(p)) continue;
+            live = w.m0 + wm * (BM / 2) < w.m_lim;
             put(smem_raw, s0);
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             for (int kt = 0; kt < nk; kt += 2) {
@@ -1189,7 +1289,7 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
         constexpr uint32_t OSZ = EPI == EPI_F32 ? 4u : (uint32_t)sizeof(T);
         if (live && wk == 0) {
             if constexpr (SPLIT) {
-                if (__builtin_expect(split_in_doubt<TM, TN>(acc), 0))
+                if (__builtin_expect(split_in_doubt<TM, TN>(acc, w.m_lim - w.m0 - wm * (BM / 2), l32), 0))
                     redo_f32<A_KC, B_KC, TM, TN>(acc, more < 0 ? 1 : 0, w.e, w.m0 + wm * (BM / 2), w.m_lim, w.n0 + wn * (BN / 2), l32, g);
             }
             float* strip = reinterpret_cast<float*>(smem_raw) + wave * 32 * SM::STRIP_LD;
@@ -1273,13 +1373,181 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
 
 template <typename T, int BM, int BN, int KW, int NS, bool A_KC, bool B_KC, int EPI, int ACT, bool KG>
 __global__ __launch_bounds__(256 * KW, (KW * MidSmem<T, BM, BN, KW, NS, A_KC, B_KC>::OCC)) void mid_gemm_kernel(const GemmArgs p) {
-    mid_body<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, KG>(p, 0, {0, 0});
+    mid_body<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, KG>(p, 0, {0, 0, 0});
 }
 template <typename T, int BM, int BN, int KW, int NS, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2, bool KG>
 __global__ __launch_bounds__(256 * KW, (KW * MidSmem<T, BM, BN, KW, NS, A1, B1>::OCC)) void mid_gemm_pair_kernel(const GemmArgs p1, const GemmArgs p2) {
-    const typename TileWalk<BM, BN>::Where w = mid_body<T, BM, BN, KW, NS, A1, B1, EPI1, 0, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0});
+    const typename TileWalk<BM, BN>::Where w = mid_body<T, BM, BN, KW, NS, A1, B1, EPI1, 0, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0, 0});
     __syncthreads();      // every wave is done with the tile table of the first product
     mid_body<T, BM, BN, KW, NS, A2, B2, EPI2, 0, KG>(p2, -1, w);
+}
+
+// ---------------------------------------------------------------------------
+// The smallest fp32 products: 32 x 32 tiles, one per workgroup of four waves, which take the reduction's 32-deep
+// chunks in turn.  What bounds these launches is latency, not work: with 64 x 64 tiles, slabs staged through LDS and a
+// table of tiles, h W2 with 256 rows, d = 64, f = 256 took 8.2 us, of which 1.8 went to the table and 0.9 to each of its
+// four slabs (LDS traffic of the split planes and a barrier).  Here a wave's fragments come straight from memory into
+// registers, two chunks ahead, and are split there; nothing is shared before the four partial sums meet in LDS, and
+// each wave finishes a quarter of the columns.  Every operand element is split by each tile that needs it, so this is
+// for products whose tiles would leave much of the chip idle.  The four launches of 256 tokens, d = 64, f = 256,
+// 4 experts: 7.0, 8.1, 7.7, 9.5 -> 4.8, 5.2, 4.6, 5.8 us; of 777 tokens, d = 136, f = 328, 5 experts, top-2:
+// 12.4, 11.1, 14.3, 12.9 -> 7.4, 6.4, 12.6, 9.0.  Three waves per SIMD: with four (128 registers) 10 - 24 of them spill.
+// ---------------------------------------------------------------------------
+enum { THIN = 32, THIN_WAVES = 4, THIN_OCC = 3, THIN_GRID = 8 };      // waves per SIMD; most workgroups per CU of a launch
+
+template <bool A_KC, bool B_KC, int EPI, int ACT>
+__device__ __forceinline__ typename TileWalk<THIN, THIN>::Where thin_body(const GemmArgs& p, int more, typename TileWalk<THIN, THIN>::Where before) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    constexpr int SUMS = THIN_WAVES * THIN * THIN * 4;
+    float4* red = reinterpret_cast<float4*>(smem_raw);
+    TileWalk<THIN, THIN> w;
+    const bool direct = p.direct_count > 0;
+    if (direct) {
+        if (!w.only(p)) return w.where();
+    } else if (p.E <= MOE_WAVE) {
+        w.count(p);
+        w.begin(more < 0 ? before.total : more, more < 0);
+    } else {
+        TileWalk<THIN, THIN>::build(p, smem_raw + SUMS);
+        if (more < 0) w.resume(before, smem_raw + SUMS); else w.start(p, smem_raw + SUMS, more);
+    }
+    for (bool more_tiles = direct || w.next(p); more_tiles; more_tiles = !direct && w.next(p)) {
+        const int m_load = direct ? p.M : w.m_lim;      // rows that loads may touch, without waiting for the expert's count
+        const int nc = (w.k_lim + 31) >> 5;
+        // A chunk's element (r, k0 + 16g + 8s + j) is entry j of k-step s: the order of a reduction is free, and so a
+        // lane of a k-contiguous operand reads 64 consecutive bytes and its two lanes a whole line.
+        struct Chunk { u32x4_t q[4]; };
+        const __amdgpu_buffer_rsrc_t rsA = buf_rsrc((const float*)p.A + (size_t)w.e * p.strideA, (size_t)(A_KC ? m_load : w.k_lim) * p.lda * 4);
+        const __amdgpu_buffer_rsrc_t rsB = buf_rsrc((const float*)p.B + (size_t)w.e * p.strideB, (size_t)(B_KC ? p.N : w.k_lim) * p.ldb * 4);
+        const int rA = w.m0 + l32, rB = w.n0 + l32;
+        auto load = [&](auto kc, __amdgpu_buffer_rsrc_t rs, int r, int r_lim, int ld, int c) {
+            Chunk v;
+            const int k = 32 * c + 16 * g;
+            if constexpr (decltype(kc)::value) {
+                const uint32_t off = (uint32_t)(r * ld + k) * 4u;        // rows >= r_lim lie beyond the range
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v.q[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, k + 4 * i < w.k_lim ? off + 16 * i : BUF_OOB, 0, 0);
+            } else {
+                const uint32_t off = r < r_lim ? (uint32_t)(k * ld + r) * 4u : BUF_OOB;     // k >= k_lim lies beyond it
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v.q[i >> 2][i & 3] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + (uint32_t)(i * ld) * 4u, 0, 0);
+            }
+            return v;
+        };
+        struct Both { Chunk a, b; };
+        auto fetch = [&](int c) {
+            Both v;
+            v.b = load(std::integral_constant<bool, B_KC>(), rsB, rB, p.N, p.ldb, c);
+            v.a = load(std::integral_constant<bool, A_KC>(), rsA, rA, m_load, p.lda, c);
+            return v;
+        };
+        // The products of the leading parts are summed apart from the five corrections (2^-8 of them and less): one
+        // rounding at the size of the sum per 16 products instead of six, and two chains of MFMAs instead of one.
+        f32x16_t acc, fine;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = fine[v] = 0.0f;
+        auto multiply = [&](const Both& v) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const u32x4_t wa[2] = {v.a.q[2 * s], v.a.q[2 * s + 1]}, wb[2] = {v.b.q[2 * s], v.b.q[2 * s + 1]};
+                u32x4_t fa[3], fb[3];
+                split3_rne(wa, fa[0], fa[1], fa[2]);
+                split3_rne(wb, fb[0], fb[1], fb[2]);
+                auto mma = [&](int qa, int qb, f32x16_t c) { return Mma<bf16_t>::mma(__builtin_bit_cast(bf16x8_t, fb[qb]), __builtin_bit_cast(bf16x8_t, fa[qa]), c); };
+                acc = mma(0, 0, acc);
+                constexpr int QA[5] = {2, 0, 1, 1, 0}, QB[5] = {0, 2, 1, 0, 1};    // smallest products first
+#pragma unroll
+                for (int q = 0; q < 5; ++q) fine = mma(QA[q], QB[q], fine);
+            }
+        };
+        // issued in this order and not rearranged: the waits in the loop count on it
+        Both v0 = fetch(wave);
+        __builtin_amdgcn_sched_barrier(0);
+        Both v1 = fetch(wave + THIN_WAVES);
+        __builtin_amdgcn_sched_barrier(0);
+        // this wave's share of the result: row l32, columns 8 wave + 4g + 0..3 of the tile
+        const int row = w.m0 + l32, col = w.n0 + 8 * wave + 4 * g;
+        const uint32_t off = col < p.N ? (uint32_t)((size_t)row * p.ldo + col) * 4u : BUF_OOB;
+        const size_t obase = (size_t)w.e * p.strideO;
+        if (direct && !w.arrived(p)) continue;
+        const size_t obytes = (size_t)w.m_lim * p.ldo * 4;       // the expert's rows in use
+        float aux[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (EPI == EPI_MUL) BufChunk<float>::load(buf_rsrc((const float*)p.aux + obase, obytes), off, aux);
+        for (int c = wave; c < nc; c += 2 * THIN_WAVES) {
+            multiply(v0);
+            __builtin_amdgcn_sched_barrier(0);
+            v0 = fetch(c + 2 * THIN_WAVES);
+            __builtin_amdgcn_sched_barrier(0);
+            if (c + THIN_WAVES >= nc) break;
+            multiply(v1);
+            __builtin_amdgcn_sched_barrier(0);
+            v1 = fetch(c + 3 * THIN_WAVES);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] += fine[v];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[(wave * 4 + q) * 64 + lane] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+        __syncthreads();
+        f32x16_t sum[1][1];
+#pragma unroll
+        for (int v = 4; v < 16; ++v) sum[0][0][v] = 0.0f;
+        static_assert(THIN_WAVES == 4, "the sum below");
+        float4 part[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[i] = red[(i * 4 + wave) * 64 + lane];
+        sum[0][0][0] = (part[0].x + part[1].x) + (part[2].x + part[3].x);
+        sum[0][0][1] = (part[0].y + part[1].y) + (part[2].y + part[3].y);
+        sum[0][0][2] = (part[0].z + part[1].z) + (part[2].z + part[3].z);
+        sum[0][0][3] = (part[0].w + part[1].w) + (part[2].w + part[3].w);
+        if (!direct) __syncthreads();      // the next tile's sums go to the same place
+        float z[4] = {sum[0][0][0], sum[0][0][1], sum[0][0][2], sum[0][0][3]};
+        if (__builtin_expect(split_in_doubt<1, 1>(sum, w.m_lim - w.m0, l32), 0)) {
+            redo_f32<A_KC, B_KC, 1, 1>(sum, more < 0 ? 1 : 0, w.e, w.m0, w.m_lim, w.n0, l32, g);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[r] = wave == 0 ? sum[0][0][r] : wave == 1 ? sum[0][0][4 + r] : wave == 2 ? sum[0][0][8 + r] : sum[0][0][12 + r];
+        }
+        const __amdgpu_buffer_rsrc_t o0 = buf_rsrc((const float*)p.out0 + obase, obytes);
+        if constexpr (EPI == EPI_H_DACT || EPI == EPI_H) {
+            float h[4], a[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) act_both<false, ACT>(z[r], h[r], a[r]);
+            if constexpr (EPI == EPI_H_DACT) {
+                if (p.drop_thr) {
+                    uint32_t nw[4];
+                    noise_words(obase + (size_t)row * p.ldo + col, MOE_STREAM_DROPOUT, p.seed, nw);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float sc = nw[r] >= p.drop_thr ? p.drop_scale : 0.0f;
+                        h[r] *= sc;
+                        a[r] *= sc;
+                    }
+                }
+                BufChunk<float>::store(o0, off, a);
+                BufChunk<float>::store(buf_rsrc((const float*)p.out1 + obase, obytes), off, h);
+            } else {
+                BufChunk<float>::store(o0, off, h);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[r] = EPI == EPI_MUL ? z[r] * aux[r] : z[r];
+            BufChunk<float>::store(o0, off, z);
+        }
+    }
+    return w.where();
+}
+
+template <bool A_KC, bool B_KC, int EPI, int ACT>
+__global__ __launch_bounds__(64 * THIN_WAVES, THIN_OCC) void thin_gemm_kernel(const GemmArgs p) {
+    thin_body<A_KC, B_KC, EPI, ACT>(p, 0, {0, 0, 0});
+}
+template <bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
+__global__ __launch_bounds__(64 * THIN_WAVES, THIN_OCC) void thin_gemm_pair_kernel(const GemmArgs p1, const GemmArgs p2) {
+    const typename TileWalk<THIN, THIN>::Where w = thin_body<A1, B1, EPI1, 0>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0, 0});
+    __syncthreads();      // every wave is done with the sums and the tile table of the first product
+    thin_body<A2, B2, EPI2, 0>(p2, -1, w);
 }
 
 // Number of compute units of the current device (looked up once per device).
@@ -1321,31 +1589,69 @@ static void set_tiles(GemmArgs& p, int BM, int BN, int E) {
 }
 static long long all_tiles(const GemmArgs& p) { return (long long)p.E * p.tiles_m * p.tiles_n; }
 
+// One tile per workgroup, addressed without the experts' row counts, where the chip holds all tiles that there could be
+// and at least four of five of them are expected to hold rows (otherwise the others crowd some of the CUs).
+// p2: the launch's second product or null.  Returns the workgroups per XCD, 0 where the tiles are walked instead.
+static int set_direct(GemmArgs& p, GemmArgs* p2, int rows, int side, long long per_xcd) {
+    const long long s1 = (all_tiles(p) + 7) / 8, s2 = p2 ? (all_tiles(*p2) + 7) / 8 : 0;
+    if (4 * p.tiles_m > 5 * ceil_div(rows, side) || s1 + s2 > per_xcd) return 0;
+    for (GemmArgs* q : {&p, p2}) {
+        if (!q) continue;
+        const int per_e = q->tiles_m * q->tiles_n;
+        q->direct_first = q == &p ? 0 : (int)s1;
+        q->direct_count = (int)all_tiles(*q);
+        q->inv_expert = per_e > 1 ? (uint32_t)((1ull << 32) / per_e + 1) : 0;       // exact for t d < 2^32; 0: d = 1
+        q->inv_m = q->tiles_m > 1 ? (uint32_t)((1ull << 32) / q->tiles_m + 1) : 0;
+    }
+    return (int)(s1 + s2);
+}
+
 template <typename T, int BM, int BN, int KW, int NS, bool A_KC, bool B_KC, int EPI, int ACT>
-static bool launch_mid(GemmArgs p, int E, hipStream_t st) {
+static bool launch_mid(GemmArgs p, int rows, int E, hipStream_t st) {
     typedef MidSmem<T, BM, BN, KW, NS, A_KC, B_KC> SM;
     set_tiles(p, BM, BN, E);
+    const int direct = set_direct(p, nullptr, rows, BM, num_cus() / 8 * SM::OCC);
     const size_t smem = SM::BYTES + WALK_BYTES;
     // a k-contiguous operand whose reduction length is not a multiple of the slab needs the guarded instance
     const bool kg = (A_KC || B_KC) && !p.var_k && p.K % SM::BK != 0;
     static unsigned long long opted[2] = {0, 0};
     auto kern = kg ? mid_gemm_kernel<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, true> : mid_gemm_kernel<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, false>;
     if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
-    kern<<<mid_grid(all_tiles(p), SM::OCC), SM::NT, smem, st>>>(p);
+    kern<<<direct ? 8 * direct : mid_grid(all_tiles(p), SM::OCC), SM::NT, smem, st>>>(p);
     return true;
 }
 
 template <typename T, int BM, int BN, int KW, int NS, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
-static bool launch_mid_pair(GemmArgs p1, GemmArgs p2, int E, hipStream_t st) {
+static bool launch_mid_pair(GemmArgs p1, GemmArgs p2, int rows, int E, hipStream_t st) {
     typedef MidSmem<T, BM, BN, KW, NS, A1, B1> SM;
     set_tiles(p1, BM, BN, E);
     set_tiles(p2, BM, BN, E);
+    const int direct = set_direct(p1, &p2, rows, BM, num_cus() / 8 * SM::OCC);
     const size_t smem = SM::BYTES + WALK_BYTES;
     const bool kg = ((A1 || B1) && !p1.var_k && p1.K % SM::BK != 0) || ((A2 || B2) && !p2.var_k && p2.K % SM::BK != 0);
     static unsigned long long opted[2] = {0, 0};
     auto kern = kg ? mid_gemm_pair_kernel<T, BM, BN, KW, NS, A1, B1, EPI1, A2, B2, EPI2, true> : mid_gemm_pair_kernel<T, BM, BN, KW, NS, A1, B1, EPI1, A2, B2, EPI2, false>;
     if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
-    kern<<<mid_grid(all_tiles(p1) + all_tiles(p2), SM::OCC), SM::NT, smem, st>>>(p1, p2);
+    kern<<<direct ? 8 * direct : mid_grid(all_tiles(p1) + all_tiles(p2), SM::OCC), SM::NT, smem, st>>>(p1, p2);
+    return true;
+}
+
+template <bool A_KC, bool B_KC, int EPI, int ACT>
+static bool launch_thin(GemmArgs p, int rows, int E, hipStream_t st) {
+    set_tiles(p, THIN, THIN, E);
+    const int direct = set_direct(p, nullptr, rows, THIN, num_cus() / 8 * THIN_GRID);
+    const size_t smem = THIN_WAVES * THIN * THIN * 4 + WALK_BYTES;
+    thin_gemm_kernel<A_KC, B_KC, EPI, ACT><<<direct ? 8 * direct : mid_grid(all_tiles(p), THIN_GRID), 64 * THIN_WAVES, smem, st>>>(p);
+    return true;
+}
+
+template <bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
+static bool launch_thin_pair(GemmArgs p1, GemmArgs p2, int rows, int E, hipStream_t st) {
+    set_tiles(p1, THIN, THIN, E);
+    set_tiles(p2, THIN, THIN, E);
+    const int direct = set_direct(p1, &p2, rows, THIN, num_cus() / 8 * THIN_GRID);
+    const size_t smem = THIN_WAVES * THIN * THIN * 4 + WALK_BYTES;
+    thin_gemm_pair_kernel<A1, B1, EPI1, A2, B2, EPI2><<<direct ? 8 * direct : mid_grid(all_tiles(p1) + all_tiles(p2), THIN_GRID), 64 * THIN_WAVES, smem, st>>>(p1, p2);
     return true;
 }
 
@@ -1385,7 +1691,7 @@ static bool launch_big_pair(GemmArgs p1, GemmArgs p2, int E, hipStream_t st) {
 // of the two for the rows of every expert.  With a skewed gate that is more than the mean of what experts hold: those
 // above the capacity drop rows and the others have fewer.  (Six experts, T = 5003, top-2, Zipf gate: 1668 against 1392 on
 // average, so that h W2 with d = 776, f = 3080 gets the large tile where the small one measured faster.)
-enum FfnTile { TILE_64, TILE_128_PAIRED, TILE_128, TILE_256 };      // PAIRED: two wave groups share a tile
+enum FfnTile { TILE_32, TILE_64, TILE_128_PAIRED, TILE_128, TILE_256 };      // PAIRED: two wave groups share a tile
 // Tiles of a given side of one product: `rows` output rows (the expert's, or all M of a weight gradient), N columns.
 static double tiles_expected(int rows, int N, int side, int E) { return (double)E * ceil_div(rows, side) * ceil_div(N, side); }
 // bf16, experts with more than 128 rows: time goes with the number of whole rounds.  The 256 x 256
@@ -1402,13 +1708,21 @@ static bool prefer_mid(double t256, double t128) {
 // rows, d = 136, f = 328: 10 us per product against 17 - 23); 128 x 128 with two wave groups that
 // share a tile's slabs while there are few tiles per CU (248 tiles, f = 2048: 89 us against 124 with
 // one group), with one group otherwise (992 tiles, d = 512: 105 against 117).
+// Where 64 x 64 tiles it is, a product takes 32 x 32 ones if these need no more rounds (three at a time on a CU) than
+// the 64 x 64 ones (one): latency is all there is then.  In us, 64 x 64 against 32 x 32: 28 and 8 tiles 7 and 8 against
+// 5 and 5 (256 tokens, d = 64); 212 and 715 tiles 11.4 and 7.4 (777 tokens, d = 136); 130 and 510 tiles 9.0 and 8.2;
+// 325 and 1170 tiles 19.5 and 15.9; 208 and 832 tiles, K = 320, 10.4 and 13.6.
 // bf16: the same order.  64 x 64 (8 experts of 64 rows, d = 512, f = 2048: 7 and 11 us against 10 and
 // 22 with 128 x 128, 17 and 39 with 256 x 256); with few rows per expert the weights' stream is the
 // bound and two 128 x 128 workgroups per CU keep more of it in flight than one large one (107 experts
 // of 7 rows, d = 1024, f = 4096: 169 us = 5.3 TB/s against 203).
 static FfnTile tile_for(bool f32, int rows, int N, int E) {
     const double cus = num_cus(), t128 = tiles_expected(rows, N, 128, E);
-    if (f32) return t128 <= 0.6 * cus ? TILE_64 : t128 <= 1.5 * cus ? TILE_128_PAIRED : TILE_128;
+    if (f32 && t128 <= 0.6 * cus) {
+        const double t64 = tiles_expected(rows, N, 64, E), t32 = tiles_expected(rows, N, THIN, E);
+        return t32 <= THIN_OCC * cus * fmin(ceil(t64 / cus), 2.0) ? TILE_32 : TILE_64;
+    }
+    if (f32) return t128 <= 1.5 * cus ? TILE_128_PAIRED : TILE_128;
     if (t128 <= (rows <= 128 ? 1.0 : 0.5) * cus) return TILE_64;
     return rows <= 128 || prefer_mid(tiles_expected(rows, N, 256, E), t128) ? TILE_128 : TILE_256;
 }
@@ -1416,10 +1730,13 @@ static FfnTile tile_for(bool f32, int rows, int N, int E) {
 // Two products, `rows` rows by N1 columns and a weight gradient of M2 by N2: the same lines at higher tile
 // counts, because the tiles of both are in the launch (fp32, 248 + 512 tiles: 185 us with two wave groups, 250 with
 // one; 992 + 512: 197 and 179.  bf16, 8 experts of 64 rows, 32 + 512 tiles: 26 us with 64 x 64, 30 with 128 x 128, 41
-// with 256 x 256).
+// with 256 x 256).  32 x 32 tiles up to 4.3 per CU (990 of them 12.6 us against 14.3 with 64 x 64, 1088: 14.0 against
+// 20.8; 720 with reductions of 1600 rows, which four waves share: 21 against 34; 2500: 31 against 27).
 static FfnTile tile_for_pair(bool f32, int rows, int N1, int M2, int N2, int E) {
     const double cus = num_cus(), t128 = tiles_expected(rows, N1, 128, E) + tiles_expected(M2, N2, 128, E);
-    if (f32) return t128 <= 0.75 * cus ? TILE_64 : t128 <= 4.0 * cus ? TILE_128_PAIRED : TILE_128;
+    if (f32 && t128 <= 0.75 * cus)
+        return tiles_expected(rows, N1, THIN, E) + tiles_expected(M2, N2, THIN, E) <= 4.3 * cus ? TILE_32 : TILE_64;
+    if (f32) return t128 <= 4.0 * cus ? TILE_128_PAIRED : TILE_128;
     if (t128 <= (rows <= 128 ? 3.0 : 1.0) * cus) return TILE_64;
     return prefer_mid(tiles_expected(rows, N1, 256, E) + tiles_expected(M2, N2, 256, E), t128) ? TILE_128 : TILE_256;
 }
@@ -1428,12 +1745,13 @@ template <typename T, bool A_KC, bool B_KC, int EPI, int ACT = 0>
 static bool launch_gemm(const GemmArgs& p, int rows, int E, hipStream_t st) {
     const FfnTile t = tile_for(sizeof(T) == 4, rows, p.N, E);
     if constexpr (sizeof(T) == 4) {
-        if (t == TILE_64) return launch_mid<T, 64, 64, 2, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
-        if (t == TILE_128_PAIRED) return launch_mid<T, 128, 128, 2, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
-        return launch_mid<T, 128, 128, 1, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
+        if (t == TILE_32) return launch_thin<A_KC, B_KC, EPI, ACT>(p, rows, E, st);
+        if (t == TILE_64) return launch_mid<T, 64, 64, 2, 2, A_KC, B_KC, EPI, ACT>(p, rows, E, st);
+        if (t == TILE_128_PAIRED) return launch_mid<T, 128, 128, 2, 2, A_KC, B_KC, EPI, ACT>(p, rows, E, st);
+        return launch_mid<T, 128, 128, 1, 2, A_KC, B_KC, EPI, ACT>(p, rows, E, st);
     } else {
-        if (t == TILE_64) return launch_mid<T, 64, 64, 1, 3, A_KC, B_KC, EPI, ACT>(p, E, st);
-        if (t == TILE_128) return launch_mid<T, 128, 128, 1, 2, A_KC, B_KC, EPI, ACT>(p, E, st);
+        if (t == TILE_64) return launch_mid<T, 64, 64, 1, 3, A_KC, B_KC, EPI, ACT>(p, rows, E, st);
+        if (t == TILE_128) return launch_mid<T, 128, 128, 1, 2, A_KC, B_KC, EPI, ACT>(p, rows, E, st);
         return launch_big<A_KC, B_KC, EPI, ACT>(p, E, st);
     }
 }
@@ -1442,12 +1760,13 @@ template <typename T, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
 static bool launch_gemm_pair(const GemmArgs& p1, const GemmArgs& p2, int rows, int E, hipStream_t st) {
     const FfnTile t = tile_for_pair(sizeof(T) == 4, rows, p1.N, p2.M, p2.N, E);
     if constexpr (sizeof(T) == 4) {
-        if (t == TILE_64) return launch_mid_pair<T, 64, 64, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
-        if (t == TILE_128_PAIRED) return launch_mid_pair<T, 128, 128, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
-        return launch_mid_pair<T, 128, 128, 1, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        if (t == TILE_32) return launch_thin_pair<A1, B1, EPI1, A2, B2, EPI2>(p1, p2, rows, E, st);
+        if (t == TILE_64) return launch_mid_pair<T, 64, 64, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, rows, E, st);
+        if (t == TILE_128_PAIRED) return launch_mid_pair<T, 128, 128, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, rows, E, st);
+        return launch_mid_pair<T, 128, 128, 1, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, rows, E, st);
     } else {
-        if (t == TILE_64) return launch_mid_pair<T, 64, 64, 1, 3, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
-        if (t == TILE_128) return launch_mid_pair<T, 128, 128, 1, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
+        if (t == TILE_64) return launch_mid_pair<T, 64, 64, 1, 3, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, rows, E, st);
+        if (t == TILE_128) return launch_mid_pair<T, 128, 128, 1, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, rows, E, st);
         return launch_big_pair<A1, B1, EPI1, A2, B2, EPI2>(p1, p2, E, st);
     }
 }
@@ -1539,16 +1858,35 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     return launch_gemm_pair<T, true, true, EPI_STORE, false, false, EPI_F32>(p, q, rows, E, st);
 }
 
-// measurement aid: the tile of each of the four launches (xd W1, h W2, dz with dW2, dxd with dW1)
-extern "C" int moe_expert_ffn_tiles(const moe_shape* shape, int32_t* side, int32_t* wave_groups) {
+// measurement aids: the tile of each of the four launches (xd W1, h W2, dz with dW2, dxd with dW1), and whether a
+// 64 x 64 fp32 one is computed as 32 x 32 parts
+static int four_tiles(const moe_shape* shape, FfnTile (&t)[4]) {
     int rc = shape_status(shape);
     if (rc || (rc = check_slice_limits(shape))) return rc;
-    if (!side || !wave_groups) return MOE_ERR_NULL;
     const bool f32 = shape->dtype == MOE_F32;
     const int rows = expected_rows(shape), d = shape->d_model, f = shape->d_ff, E = shape->E;
-    const FfnTile t[4] = {tile_for(f32, rows, f, E), tile_for(f32, rows, d, E), tile_for_pair(f32, rows, f, f, d, E), tile_for_pair(f32, rows, d, d, f, E)};
+    t[0] = tile_for(f32, rows, f, E);
+    t[1] = tile_for(f32, rows, d, E);
+    t[2] = tile_for_pair(f32, rows, f, f, d, E);
+    t[3] = tile_for_pair(f32, rows, d, d, f, E);
+    return MOE_OK;
+}
+extern "C" int moe_expert_ffn_parts(const moe_shape* shape, int32_t* parts) {
+    FfnTile t[4];
+    const int rc = four_tiles(shape, t);
+    if (rc) return rc;
+    if (!parts) return MOE_ERR_NULL;
+    for (int i = 0; i < 4; ++i) parts[i] = t[i] == TILE_32;
+    return MOE_OK;
+}
+extern "C" int moe_expert_ffn_tiles(const moe_shape* shape, int32_t* side, int32_t* wave_groups) {
+    FfnTile t[4];
+    const int rc = four_tiles(shape, t);
+    if (rc) return rc;
+    if (!side || !wave_groups) return MOE_ERR_NULL;
+    const bool f32 = shape->dtype == MOE_F32;
     for (int i = 0; i < 4; ++i) {
-        side[i] = t[i] == TILE_64 ? 64 : t[i] == TILE_256 ? 256 : 128;
+        side[i] = t[i] <= TILE_64 ? 64 : t[i] == TILE_256 ? 256 : 128;
         wave_groups[i] = f32 && t[i] != TILE_128 ? 2 : 1;
     }
     return MOE_OK;
