@@ -81,6 +81,7 @@ struct GemmArgs {
     // direct_first on, direct_count tiles in all (0: by the experts' row counts), and t / d is the upper half of t * inv
     int direct_first, direct_count;
     uint32_t inv_expert, inv_m;
+    int lead;         // second product of a launch: its tiles that take as long as one of the first product's (TileWalk::follow)
     // expert dropout in the activation epilogue (drop_thr = 0: off): an element is dropped when its
     // noise word < drop_thr, kept ones are scaled by drop_scale = 1 / (1 - p)
     uint32_t drop_thr;
@@ -361,6 +362,7 @@ struct TileWalk {
     // or barrier is needed (0.9 us less at the start of a launch).
     bool in_regs = false;
     int rn, rt;
+    int ahead = 0, rest = 0;           // rounds that only `rest` of the workgroups take, first
     int t, t_end, step;
     int e, m0, n0, m_lim, k_lim;   // current tile
 
@@ -403,19 +405,35 @@ struct TileWalk {
         tp = reinterpret_cast<const int*>(lds);
         t_end = __builtin_amdgcn_readfirstlane(tp[256]);
         const int S = min((int)(gridDim.x >> 3), (t_end + more + 7) / 8);
-        const int i = (int)(blockIdx.x >> 3);
         step = 8 * S;
-        t = i < S ? (int)(blockIdx.x & 7) * S + i - step : t_end + more;
+        t = place() - step;
+    }
+    // the workgroup's place among the `step` that take turns
+    __device__ __forceinline__ int place() const {
+        const int i = (int)(blockIdx.x >> 3);
+        return i < step >> 3 ? (int)(blockIdx.x & 7) * (step >> 3) + i : 0x3fffffff;
     }
     // The walk over the launch's second product goes on where the first one's ended: `u` is that
     // walk's place after its last next().
-    struct Where { int t, step, total; };
-    __device__ __forceinline__ Where where() const { return {t - t_end, step, t_end}; }
-    __device__ __forceinline__ void resume(Where u, const unsigned char* lds) {
+    struct Where { int step, total; };      // of a walk over a first product: the workgroups that take turns, its tiles
+    __device__ __forceinline__ Where where() const { return {step, t_end}; }
+    __device__ __forceinline__ void resume(const GemmArgs& p, Where u, const unsigned char* lds) {
         tp = reinterpret_cast<const int*>(lds);
         t_end = __builtin_amdgcn_readfirstlane(tp[256]);
         step = u.step;
-        t = u.t - step;
+        follow(u.total, p.lead);
+    }
+    // The second product's tiles (t_end of them), after `total` of the first were dealt one by one.  Workgroups that got
+    // none in the first product's last round take `lead` rounds of the second's before all take turns again: as many as
+    // such a tile lasts, so that a long one (thousands of reduction entries in dxd) does not bring its workgroup a full
+    // share of the others on top.  dxd with dW1 for 7 experts of 470 rows, d = 1720, f = 5520: 258 -> 219 us; 11 of 171,
+    // d = 1560, f = 5168: 259 -> 226; 512 tokens on 8 experts, d = 512, f = 2048 (64 x 64): 24.5 -> 20.2.
+    __device__ __forceinline__ void follow(int total, int lead) {
+        const int late = total - quotient(total, step) * step, at = place();
+        rest = step - late;
+        ahead = late > 0 && at >= late ? lead : 0;
+        // one tile every `rest`, then one every `step`: the step between the two is a whole one
+        t = ahead > 0 ? at - late - rest : (late > 0 ? lead * rest : 0) + at - step;
     }
     __device__ __forceinline__ void count(const GemmArgs& p) {
         in_regs = true;
@@ -428,27 +446,24 @@ struct TileWalk {
     }
     // The workgroup's first tile: as start(), but where the tiles of both products of a launch fit in one round, an XCD
     // has its share of each.  `other` = tiles of the other product, `second`: this is the later one.
-    __device__ __forceinline__ void begin(int other, bool second) {
-        const int x = (int)(blockIdx.x & 7), i = (int)(blockIdx.x >> 3), G = (int)(gridDim.x >> 3);
+    __device__ __forceinline__ void begin(const GemmArgs& p, int other, bool second) {
+        const int xcd = (int)(blockIdx.x & 7), i = (int)(blockIdx.x >> 3), G = (int)(gridDim.x >> 3);
         const int S = (t_end + 7) >> 3, O = (other + 7) >> 3;
         if (S + O <= G) {
             const int j = second ? i - O : i;
             step = 0x3fffffff;
-            t = (j >= 0 && j < S ? x * S + j : t_end) - step;
+            t = (j >= 0 && j < S ? xcd * S + j : t_end) - step;
         } else {
-            const int all = min(G, (t_end + other + 7) >> 3);
-            step = 8 * all;
-            t = (i < all ? x * all + i : t_end + other);
-            if (second) t = t >= other ? t - other : t + (other - t + step - 1) / step * step - other;      // goes on where the first product's walk ended
-            t -= step;
+            step = 8 * min(G, (t_end + other + 7) >> 3);
+            if (second) follow(other, p.lead); else t = place() - step;
         }
     }
     // All tiles that there could be run at once, one per workgroup, and most of them are there: nothing waits for the
     // expert's row count but what needs it (a scalar load).  Each XCD has an eighth of each product's tiles.
     __device__ __forceinline__ bool only(const GemmArgs& p) {
         t = t_end = step = 0;
-        const int x = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3) - p.direct_first;
-        const int S = (p.direct_count + 7) >> 3, i = x * S + j;
+        const int xcd = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3) - p.direct_first;
+        const int S = (p.direct_count + 7) >> 3, i = xcd * S + j;
         if (j < 0 || j >= S || i >= p.direct_count) return false;
         e = p.inv_expert ? (int)__umulhi((uint32_t)i, p.inv_expert) : i;
         const int rem = i - e * p.tiles_m * p.tiles_n, tn = p.inv_m ? (int)__umulhi((uint32_t)rem, p.inv_m) : rem;
@@ -473,7 +488,8 @@ struct TileWalk {
     }
     // moves to the workgroup's next tile; false when the walk is over
     __device__ __forceinline__ bool next(const GemmArgs& p) {
-        t += step;
+        t += ahead > 0 ? rest : step;
+        --ahead;
         if (t >= t_end) return false;
         // the expert that owns tile t: as many experts end at or before it
         int first, n_e;
@@ -547,7 +563,7 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
     unsigned char* walk_lds = smem_raw + SM::BYTES;
     TileWalk<BM, BN>::build(p, walk_lds);
     TileWalk<BM, BN> pw;       // tile whose slabs are being requested
-    if (more < 0) pw.resume(before, walk_lds); else pw.start(p, walk_lds, more);
+    if (more < 0) pw.resume(p, before, walk_lds); else pw.start(p, walk_lds, more);
     bool p_more = pw.next(p);
     int p_kt = 0, p_nk = 0;
     u32x4_t dsA = {0, 0, 0, 0}, dsB = {0, 0, 0, 0};
@@ -602,7 +618,7 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
 
     // ---- consumer ---------------------------------------------------------------
     TileWalk<BM, BN> cw;
-    if (more < 0) cw.resume(before, walk_lds); else cw.start(p, walk_lds, more);
+    if (more < 0) cw.resume(p, before, walk_lds); else cw.start(p, walk_lds, more);
     if (!cw.next(p)) return cw.where();    // nothing to do for this workgroup (uniform)
 #pragma unroll
     for (int s = 0; s < NS; ++s) produce(s);
@@ -883,7 +899,7 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where gemm_body(const Gemm
 
 template <int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI, int ACT, int NWN, bool KG>
 __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_kernel(const GemmArgs p) {   // two waves per SIMD: at most 256 registers
-    gemm_body<BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, KG>(p, 0, {0, 0, 0});
+    gemm_body<BM, BN, BK, A_KC, B_KC, EPI, ACT, NWN, KG>(p, 0, {0, 0});
 }
 
 // Two independent grouped GEMMs in one launch: every workgroup walks its tiles of the
@@ -893,7 +909,7 @@ __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_kernel(const GemmAr
 // workgroups drift apart, which spreads the store bursts of their epilogues.
 template <int BM, int BN, int BK, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2, int NWN, bool KG>
 __global__ __launch_bounds__(128 * NWN, 2) void grouped_gemm_pair_kernel(const GemmArgs p1, const GemmArgs p2) {
-    const typename TileWalk<BM, BN>::Where w = gemm_body<BM, BN, BK, A1, B1, EPI1, 0, NWN, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0, 0});
+    const typename TileWalk<BM, BN>::Where w = gemm_body<BM, BN, BK, A1, B1, EPI1, 0, NWN, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0});
     __syncthreads();      // every wave is done with the ring and the tile table of the first product
     gemm_body<BM, BN, BK, A2, B2, EPI2, 0, NWN, KG>(p2, -1, w);
 }
@@ -1051,10 +1067,10 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
         if (!w.only(p)) return w.where();
     } else if (p.E <= MOE_WAVE) {
         w.count(p);
-        w.begin(more < 0 ? before.total : more, more < 0);
+        w.begin(p, more < 0 ? before.total : more, more < 0);
     } else {
         TileWalk<BM, BN>::build(p, walk_lds);
-        if (more < 0) w.resume(before, walk_lds); else w.start(p, walk_lds, more);
+        if (more < 0) w.resume(p, before, walk_lds); else w.start(p, walk_lds, more);
     }
     for (bool more_tiles = direct || w.next(p); more_tiles; more_tiles = !direct && w.next(p)) {
         // rows that loads may touch: without waiting for the expert's count, all of its buffer's
@@ -1373,11 +1389,11 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
 
 template <typename T, int BM, int BN, int KW, int NS, bool A_KC, bool B_KC, int EPI, int ACT, bool KG>
 __global__ __launch_bounds__(256 * KW, (KW * MidSmem<T, BM, BN, KW, NS, A_KC, B_KC>::OCC)) void mid_gemm_kernel(const GemmArgs p) {
-    mid_body<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, KG>(p, 0, {0, 0, 0});
+    mid_body<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, KG>(p, 0, {0, 0});
 }
 template <typename T, int BM, int BN, int KW, int NS, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2, bool KG>
 __global__ __launch_bounds__(256 * KW, (KW * MidSmem<T, BM, BN, KW, NS, A1, B1>::OCC)) void mid_gemm_pair_kernel(const GemmArgs p1, const GemmArgs p2) {
-    const typename TileWalk<BM, BN>::Where w = mid_body<T, BM, BN, KW, NS, A1, B1, EPI1, 0, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0, 0});
+    const typename TileWalk<BM, BN>::Where w = mid_body<T, BM, BN, KW, NS, A1, B1, EPI1, 0, KG>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0});
     __syncthreads();      // every wave is done with the tile table of the first product
     mid_body<T, BM, BN, KW, NS, A2, B2, EPI2, 0, KG>(p2, -1, w);
 }
@@ -1408,10 +1424,10 @@ __device__ __forceinline__ typename TileWalk<THIN, THIN>::Where thin_body(const 
         if (!w.only(p)) return w.where();
     } else if (p.E <= MOE_WAVE) {
         w.count(p);
-        w.begin(more < 0 ? before.total : more, more < 0);
+        w.begin(p, more < 0 ? before.total : more, more < 0);
     } else {
         TileWalk<THIN, THIN>::build(p, smem_raw + SUMS);
-        if (more < 0) w.resume(before, smem_raw + SUMS); else w.start(p, smem_raw + SUMS, more);
+        if (more < 0) w.resume(p, before, smem_raw + SUMS); else w.start(p, smem_raw + SUMS, more);
     }
     for (bool more_tiles = direct || w.next(p); more_tiles; more_tiles = !direct && w.next(p)) {
         const int m_load = direct ? p.M : w.m_lim;      // rows that loads may touch, without waiting for the expert's count
@@ -1541,11 +1557,11 @@ __device__ __forceinline__ typename TileWalk<THIN, THIN>::Where thin_body(const 
 
 template <bool A_KC, bool B_KC, int EPI, int ACT>
 __global__ __launch_bounds__(64 * THIN_WAVES, THIN_OCC) void thin_gemm_kernel(const GemmArgs p) {
-    thin_body<A_KC, B_KC, EPI, ACT>(p, 0, {0, 0, 0});
+    thin_body<A_KC, B_KC, EPI, ACT>(p, 0, {0, 0});
 }
 template <bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
 __global__ __launch_bounds__(64 * THIN_WAVES, THIN_OCC) void thin_gemm_pair_kernel(const GemmArgs p1, const GemmArgs p2) {
-    const typename TileWalk<THIN, THIN>::Where w = thin_body<A1, B1, EPI1, 0>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0, 0});
+    const typename TileWalk<THIN, THIN>::Where w = thin_body<A1, B1, EPI1, 0>(p1, p2.E * p2.tiles_m * p2.tiles_n, {0, 0});
     __syncthreads();      // every wave is done with the sums and the tile table of the first product
     thin_body<A2, B2, EPI2, 0>(p2, -1, w);
 }
@@ -1732,12 +1748,16 @@ static FfnTile tile_for(bool f32, int rows, int N, int E) {
 // one; 992 + 512: 197 and 179.  bf16, 8 experts of 64 rows, 32 + 512 tiles: 26 us with 64 x 64, 30 with 128 x 128, 41
 // with 256 x 256).  32 x 32 tiles up to 4.3 per CU (990 of them 12.6 us against 14.3 with 64 x 64, 1088: 14.0 against
 // 20.8; 720 with reductions of 1600 rows, which four waves share: 21 against 34; 2500: 31 against 27).
+// bf16, experts of at most 128 rows: the first pair (whose first product's reduction, N2, is the shorter extent) takes
+// 128 x 128 (36 experts of 66 rows, d = 864, f = 2256: 90 us against 127 with 256 x 256; 81 of 11, d = 1064, f = 3368:
+// 365 against 420; 9 of 100, d = 1232, f = 4608: 77 against 96); in the second one either may be the faster.
 static FfnTile tile_for_pair(bool f32, int rows, int N1, int M2, int N2, int E) {
     const double cus = num_cus(), t128 = tiles_expected(rows, N1, 128, E) + tiles_expected(M2, N2, 128, E);
     if (f32 && t128 <= 0.75 * cus)
         return tiles_expected(rows, N1, THIN, E) + tiles_expected(M2, N2, THIN, E) <= 4.3 * cus ? TILE_32 : TILE_64;
     if (f32) return t128 <= 4.0 * cus ? TILE_128_PAIRED : TILE_128;
     if (t128 <= (rows <= 128 ? 3.0 : 1.0) * cus) return TILE_64;
+    if (rows <= 128 && N2 <= N1) return TILE_128;
     return prefer_mid(tiles_expected(rows, N1, 256, E) + tiles_expected(M2, N2, 256, E), t128) ? TILE_128 : TILE_256;
 }
 
@@ -1844,6 +1864,8 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     q.B = dyd; q.ldb = d; q.strideB = (long long)C * d;
     q.out0 = dW2; q.ldo = d; q.strideO = (long long)f * d;
     q.M = f; q.N = d; q.K = C;
+    // a tile's time: its reduction, and about 300 entries' worth of epilogue
+    q.lead = ceil_div(d + 300, rows + 300);
     if (!launch_gemm_pair<T, true, true, EPI_MUL, false, false, EPI_F32>(p, q, rows, E, st)) return false;
     // dxd = dz W1^T:  B(r = n in d, k in f) = W1[n*f + k]
     p.A = dz; p.lda = f; p.strideA = (long long)C * f;
@@ -1855,6 +1877,7 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     q.B = dz; q.ldb = f; q.strideB = (long long)C * f;
     q.out0 = dW1; q.ldo = f; q.strideO = (long long)d * f;
     q.M = d; q.N = f; q.K = C;
+    q.lead = ceil_div(f + 300, rows + 300);
     return launch_gemm_pair<T, true, true, EPI_STORE, false, false, EPI_F32>(p, q, rows, E, st);
 }
 
