@@ -37,8 +37,12 @@ __device__ __forceinline__ void load8<float>(__amdgpu_buffer_rsrc_t rs, uint32_t
 
 // TT = 32-token tiles per workgroup: with more than 32 experts every workgroup reads all of
 // Wg (E * d * 4 bytes, from L2) once, so two token tiles share each of its fragments.
-template <typename T, int NB, bool JIT, int TT>   // JIT: gate jitter on (a separate instance keeps the plain one lean)
-__global__ __launch_bounds__(64 * GLM_KSPLIT, NB == 1 ? 4 : 2) void gate_logits_kernel(
+// JIT: gate jitter on (a separate instance keeps the plain one lean).  Its eight blocks of noise need 251 registers; held to
+// 128 it spilled them: 18.5 µs instead of 15.4 at T = 8192, d = 768, E = 16, and 47 with the noise's 64-bit products.
+// Large grids of narrow rows pay 1-2 % for two waves a SIMD (T = 65536, d = 512: 94 -> 96 µs), wide rows gain
+// (T = 49152, d = 2048: 154 -> 144).
+template <typename T, int NB, bool JIT, int TT>
+__global__ __launch_bounds__(64 * GLM_KSPLIT, NB == 1 && !JIT ? 4 : 2) void gate_logits_kernel(
     int Tn, int d, int E, const T* __restrict__ x, const float* __restrict__ Wg,
     const float* __restrict__ bias, float* __restrict__ logits, float jitter_eps, uint64_t seed) {
     constexpr int GRP = NB <= 2 && TT == 1 ? 8 : 4;   // 16-deep blocks whose loads are in flight together
