@@ -1,7 +1,7 @@
 // moe_layer_fwd / moe_layer_bwd: the entry points of one layer pass in order (host code only).  A call
 // through a foreign-function interface costs several times what issuing a launch does; a 256-token step
 // is ten launches of 2 to 9 us: with eight calls the host needed 70 us for it and set its time, with these two
-// 44 of the 55 us that the GPU takes (replayed from a graph: 57).
+// 44 of the 51 us that the step takes (43 on a faster host).
 #include "moe_common.h"
 
 static int check_args(const moe_shape* s, const moe_layer_options* o, const moe_layer_buffers* b) {

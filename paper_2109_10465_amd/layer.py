@@ -108,8 +108,8 @@ class MoELayer:
         the same tensors: refill x, dy, the weights and the keys in place between replays).  The library
         allocates nothing and clears nothing with memset, so every call of the step is a plain kernel node.
         Replay takes the host out of the loop (18 us of host time instead of 44 for a 256-token step); the time of a
-        step stays the same, since the chain of dependent kernels sets it, not their launch (256 tokens, fp32: 55 us
-        eager, 57 replayed).
+        step stays about the same, since the chain of dependent kernels sets it, not their launch (256 tokens, fp32:
+        51 us eager; 55 eager and 57 replayed when its expert products took 1-2 us longer each).
         The seed of the step's noise draws is a host value and is recorded with the graph."""
         if self.forward_only:
             raise B.MoeError("this layer was built forward-only")
