@@ -474,7 +474,7 @@ struct TileWalk {
         k_lim = p.var_k ? max(0, min(n_e, p.K)) : p.K;
         return true;
     }
-    // only()'s rows, now that the first loads are on their way; does the tile hold any
+    // only()'s rows, now that B's first loads are on their way; does the tile hold any
     __device__ __forceinline__ bool arrived(const GemmArgs& p) {
         asm volatile("" : "+s"(m_lim));
         m_lim = max(0, min(m_lim, p.M));
@@ -1073,8 +1073,6 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
         if (more < 0) w.resume(p, before, walk_lds); else w.start(p, walk_lds, more);
     }
     for (bool more_tiles = direct || w.next(p); more_tiles; more_tiles = !direct && w.next(p)) {
-        // rows that loads may touch: without waiting for the expert's count, all of its buffer's
-        const int m_load = direct ? p.M : w.m_lim;
         const int nk = (w.k_lim + BK - 1) / BK;
         const T* gA = (const T*)p.A + (size_t)w.e * p.strideA;
         const T* gB = (const T*)p.B + (size_t)w.e * p.strideB;
@@ -1103,39 +1101,44 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
 
         bool live;          // does this wave hold any row in use
         if constexpr (!SPLIT) {
-            u32x4_t dsA = TA::desc((const bf16_t*)gA, p.lda, m_load, w.k_lim), dsB = TB::desc((const bf16_t*)gB, p.ldb, p.N, w.k_lim);
-            typename TA::Plan planA;
-            typename TB::Plan planB;
-            TA::plan(planA, p.lda, w.m0, m_load);
-            TB::plan(planB, p.ldb, w.n0, p.N);
-            auto request = [&](int kt, int st) {
+            // one operand's part of slab kt, into ring stage st
+            auto request_one = [&](auto tile, const auto& plan, u32x4_t ds, int ld, int kt, uint32_t base) {
+                typedef decltype(tile) TT;
                 const int k0 = kt < nk ? kt * BK : 0;
-                u32x4_t sa = TA::slab_desc(dsA, TA::slab_shift(p.lda, k0)), sb = TB::slab_desc(dsB, TB::slab_shift(p.ldb, k0));
-                if (kt >= nk) { sa[2] = 0; sb[2] = 0; }      // past the end: zeros, so that every slab counts the same loads
+                u32x4_t sd = TT::slab_desc(ds, TT::slab_shift(ld, k0));
+                if (kt >= nk) sd[2] = 0;      // past the end: zeros, so that every slab counts the same loads
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    sa[i] = __builtin_amdgcn_readfirstlane(sa[i]);
-                    sb[i] = __builtin_amdgcn_readfirstlane(sb[i]);
-                }
-                const uint32_t base = lds0 + st * SM::STAGE;
+                for (int i = 0; i < 4; ++i) sd[i] = __builtin_amdgcn_readfirstlane(sd[i]);
 #pragma unroll
-                for (int i = 0; i < TA::PER_THREAD; ++i) TA::template issue_one<KG>(planA, sa, k0, w.k_lim, base, i);
-#pragma unroll
-                for (int i = 0; i < TB::PER_THREAD; ++i) TB::template issue_one<KG>(planB, sb, k0, w.k_lim, base + TA::BYTES, i);
+                for (int i = 0; i < TT::PER_THREAD; ++i) TT::template issue_one<KG>(plan, sd, k0, w.k_lim, base, i);
             };
-#pragma unroll
-            for (int s = 0; s < NS - 1; ++s) request(s, s);
+            typename TB::Plan planB;
+            TB::plan(planB, p.ldb, w.n0, p.N);
+            const u32x4_t dsB = TB::desc((const bf16_t*)gB, p.ldb, p.N, w.k_lim);
+            auto request_b = [&](int kt, int st) { request_one(TB(), planB, dsB, p.ldb, kt, lds0 + st * SM::STAGE + TA::BYTES); };
+            request_b(0, 0);                  // B first: A is not touched before the rows in use are known
             if (direct && !w.arrived(p)) {
                 wait_vmcnt<0>();
                 continue;
             }
             live = w.m0 + wm * (BM / 2) < w.m_lim;
+            typename TA::Plan planA;
+            TA::plan(planA, p.lda, w.m0, w.m_lim);
+            const u32x4_t dsA = TA::desc((const bf16_t*)gA, p.lda, w.m_lim, w.k_lim);
+            auto request_a = [&](int kt, int st) { request_one(TA(), planA, dsA, p.lda, kt, lds0 + st * SM::STAGE); };
+            request_a(0, 0);
+#pragma unroll
+            for (int s = 1; s < NS - 1; ++s) {
+                request_a(s, s);
+                request_b(s, s);
+            }
             int st = 0;
             for (int kt = 0; kt < nk; ++kt) {
                 wait_vmcnt_lgkm0<(NS - 2) * SM::LOADS>();
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                request(kt + NS - 1, st == 0 ? NS - 1 : st - 1);
+                request_a(kt + NS - 1, st == 0 ? NS - 1 : st - 1);
+                request_b(kt + NS - 1, st == 0 ? NS - 1 : st - 1);
                 if (live) {
                     const unsigned char* a_s = smem_raw + st * SM::STAGE;
                     const unsigned char* b_s = a_s + TA::BYTES;
@@ -1173,25 +1176,35 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
                 }
             };
 #pragma unroll
-            for (int i = 0; i < CA; ++i) geom(TA(), offA[i], dstA[i], kcA[i], i, p.lda, w.m0, m_load);
-#pragma unroll
             for (int i = 0; i < CB; ++i) geom(TB(), offB[i], dstB[i], kcB[i], i, p.ldb, w.n0, p.N);
-            const size_t rangeA = (size_t)(A_KC ? m_load : w.k_lim) * p.lda * 4, rangeB = (size_t)(B_KC ? p.N : w.k_lim) * p.ldb * 4;
+            const size_t rangeB = (size_t)(B_KC ? p.N : w.k_lim) * p.ldb * 4;
             auto load8 = [&](__amdgpu_buffer_rsrc_t rs, uint32_t off, u32x4_t (&r)[2]) {
                 r[0] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
                 r[1] = __builtin_amdgcn_raw_buffer_load_b128(rs, off == BUF_OOB ? BUF_OOB : off + 16, 0, 0);
             };
             // requests slab kt (zeros past the end) into a register set
             struct Slab { u32x4_t a[CA][2], b[CB][2]; };
-            auto fetch = [&](int kt, Slab& r) {
+            auto fetch_b = [&](int kt, Slab& r) {
                 const int k0 = kt < nk ? kt * BK : 0;
-                const size_t shA = (size_t)(A_KC ? k0 : k0 * p.lda) * 4, shB = (size_t)(B_KC ? k0 : k0 * p.ldb) * 4;
-                const __amdgpu_buffer_rsrc_t rsA = buf_rsrc((const char*)gA + shA, kt >= nk ? 0 : (A_KC ? rangeA : (rangeA > shA ? rangeA - shA : 0)));
-                const __amdgpu_buffer_rsrc_t rsB = buf_rsrc((const char*)gB + shB, kt >= nk ? 0 : (B_KC ? rangeB : (rangeB > shB ? rangeB - shB : 0)));
+                const size_t sh = (size_t)(B_KC ? k0 : k0 * p.ldb) * 4;
+                const __amdgpu_buffer_rsrc_t rs = buf_rsrc((const char*)gB + sh, kt >= nk ? 0 : (B_KC ? rangeB : (rangeB > sh ? rangeB - sh : 0)));
 #pragma unroll
-                for (int i = 0; i < CA; ++i) load8(rsA, (A_KC && KG && kcA[i] + k0 >= w.k_lim) ? BUF_OOB : offA[i], r.a[i]);
+                for (int i = 0; i < CB; ++i) load8(rs, (B_KC && KG && kcB[i] + k0 >= w.k_lim) ? BUF_OOB : offB[i], r.b[i]);
+            };
+            Slab s0, s1;
+            fetch_b(0, s0);                  // B first: A is not touched before the rows in use are known
+            fetch_b(1, s1);
+            if (direct && !w.arrived(p)) continue;
+            live = w.m0 + wm * (BM / 2) < w.m_lim;
 #pragma unroll
-                for (int i = 0; i < CB; ++i) load8(rsB, (B_KC && KG && kcB[i] + k0 >= w.k_lim) ? BUF_OOB : offB[i], r.b[i]);
+            for (int i = 0; i < CA; ++i) geom(TA(), offA[i], dstA[i], kcA[i], i, p.lda, w.m0, w.m_lim);
+            const size_t rangeA = (size_t)(A_KC ? w.m_lim : w.k_lim) * p.lda * 4;
+            auto fetch_a = [&](int kt, Slab& r) {
+                const int k0 = kt < nk ? kt * BK : 0;
+                const size_t sh = (size_t)(A_KC ? k0 : k0 * p.lda) * 4;
+                const __amdgpu_buffer_rsrc_t rs = buf_rsrc((const char*)gA + sh, kt >= nk ? 0 : (A_KC ? rangeA : (rangeA > sh ? rangeA - sh : 0)));
+#pragma unroll
+                for (int i = 0; i < CA; ++i) load8(rs, (A_KC && KG && kcA[i] + k0 >= w.k_lim) ? BUF_OOB : offA[i], r.a[i]);
             };
             auto put = [&](unsigned char* st, const Slab& r) {      // a fetched slab, split, into a stage
 #pragma unroll
@@ -1216,7 +1229,8 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
             // pipe for 32 cycles, in which the wave issues up to six vector instructions for nothing).
             auto slab = [&](int kt, Slab& nxt, Slab& spare) {
                 const unsigned char* st = smem_raw + (kt & 1) * SM::STAGE;
-                fetch(kt + 2, spare);
+                fetch_a(kt + 2, spare);
+                fetch_b(kt + 2, spare);
                 bf16x8_t fa[KS][3][TM], fb[KS][3][TN];
 // in the order in which the products below need them
 #pragma unroll
@@ -1255,11 +1269,8 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
                 // LDS writes of this wave are done and the workgroup meets; loads stay in flight
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             };
-            Slab s0, s1;
-            fetch(0, s0);
-            fetch(1, s1);
-            if (direct && !w.arrived(p)) continue;
-            live = w.m0 + wm * (BM / 2) < w.m_lim;
+            fetch_a(0, s0);
+            fetch_a(1, s1);
             put(smem_raw, s0);
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             for (int kt = 0; kt < nk; kt += 2) {
@@ -1430,12 +1441,10 @@ __device__ __forceinline__ typename TileWalk<THIN, THIN>::Where thin_body(const 
         if (more < 0) w.resume(p, before, smem_raw + SUMS); else w.start(p, smem_raw + SUMS, more);
     }
     for (bool more_tiles = direct || w.next(p); more_tiles; more_tiles = !direct && w.next(p)) {
-        const int m_load = direct ? p.M : w.m_lim;      // rows that loads may touch, without waiting for the expert's count
         const int nc = (w.k_lim + 31) >> 5;
         // A chunk's element (r, k0 + 16g + 8s + j) is entry j of k-step s: the order of a reduction is free, and so a
         // lane of a k-contiguous operand reads 64 consecutive bytes and its two lanes a whole line.
         struct Chunk { u32x4_t q[4]; };
-        const __amdgpu_buffer_rsrc_t rsA = buf_rsrc((const float*)p.A + (size_t)w.e * p.strideA, (size_t)(A_KC ? m_load : w.k_lim) * p.lda * 4);
         const __amdgpu_buffer_rsrc_t rsB = buf_rsrc((const float*)p.B + (size_t)w.e * p.strideB, (size_t)(B_KC ? p.N : w.k_lim) * p.ldb * 4);
         const int rA = w.m0 + l32, rB = w.n0 + l32;
         auto load = [&](auto kc, __amdgpu_buffer_rsrc_t rs, int r, int r_lim, int ld, int c) {
@@ -1453,12 +1462,7 @@ __device__ __forceinline__ typename TileWalk<THIN, THIN>::Where thin_body(const 
             return v;
         };
         struct Both { Chunk a, b; };
-        auto fetch = [&](int c) {
-            Both v;
-            v.b = load(std::integral_constant<bool, B_KC>(), rsB, rB, p.N, p.ldb, c);
-            v.a = load(std::integral_constant<bool, A_KC>(), rsA, rA, m_load, p.lda, c);
-            return v;
-        };
+        auto load_b = [&](int c) { return load(std::integral_constant<bool, B_KC>(), rsB, rB, p.N, p.ldb, c); };
         // The products of the leading parts are summed apart from the five corrections (2^-8 of them and less): one
         // rounding at the size of the sum per 16 products instead of six, and two chains of MFMAs instead of one.
         f32x16_t acc, fine;
@@ -1478,16 +1482,30 @@ __device__ __forceinline__ typename TileWalk<THIN, THIN>::Where thin_body(const 
                 for (int q = 0; q < 5; ++q) fine = mma(QA[q], QB[q], fine);
             }
         };
-        // issued in this order and not rearranged: the waits in the loop count on it
-        Both v0 = fetch(wave);
+        // issued in this order and not rearranged: the waits in the loop count on it.  B first: A is not touched before the
+        // rows in use are known.
+        Both v0, v1;
+        v0.b = load_b(wave);
         __builtin_amdgcn_sched_barrier(0);
-        Both v1 = fetch(wave + THIN_WAVES);
+        v1.b = load_b(wave + THIN_WAVES);
+        __builtin_amdgcn_sched_barrier(0);
+        if (direct && !w.arrived(p)) continue;
+        const __amdgpu_buffer_rsrc_t rsA = buf_rsrc((const float*)p.A + (size_t)w.e * p.strideA, (size_t)(A_KC ? w.m_lim : w.k_lim) * p.lda * 4);
+        auto load_a = [&](int c) { return load(std::integral_constant<bool, A_KC>(), rsA, rA, w.m_lim, p.lda, c); };
+        auto fetch = [&](int c) {
+            Both v;
+            v.b = load_b(c);
+            v.a = load_a(c);
+            return v;
+        };
+        v0.a = load_a(wave);
+        __builtin_amdgcn_sched_barrier(0);
+        v1.a = load_a(wave + THIN_WAVES);
         __builtin_amdgcn_sched_barrier(0);
         // this wave's share of the result: row l32, columns 8 wave + 4g + 0..3 of the tile
         const int row = w.m0 + l32, col = w.n0 + 8 * wave + 4 * g;
         const uint32_t off = col < p.N ? (uint32_t)((size_t)row * p.ldo + col) * 4u : BUF_OOB;
         const size_t obase = (size_t)w.e * p.strideO;
-        if (direct && !w.arrived(p)) continue;
         const size_t obytes = (size_t)w.m_lim * p.ldo * 4;       // the expert's rows in use
         float aux[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         if constexpr (EPI == EPI_MUL) BufChunk<float>::load(buf_rsrc((const float*)p.aux + obase, obytes), off, aux);
