@@ -25,6 +25,7 @@ EXPORTS = [
     "moe_gate_route_counted", "moe_layer_fwd", "moe_layer_bwd", "moe_route_launches",
     "moe_gate_logits_token_tiles", "moe_gate_logits_bwd_launches", "moe_gate_logits_bwd_chunks",
     "moe_combine_gate_bwd_launches", "moe_expert_ffn_tiles", "moe_expert_ffn_parts",
+    "moe_expert_ffn_direct",
 ]
 
 
@@ -100,6 +101,7 @@ def lib():
             "moe_gate_logits_token_tiles": [shp],
             "moe_expert_ffn_tiles": [shp, vp, vp],
             "moe_expert_ffn_parts": [shp, vp],
+            "moe_expert_ffn_direct": [shp, vp],
             "moe_combine_gate_bwd_launches": [shp],
             "moe_gate_logits_bwd_chunks": [shp, ctypes.c_float],
             "moe_gate_logits_bwd_launches": [shp, i32, ctypes.c_float],
@@ -300,6 +302,13 @@ def moe_expert_ffn_parts(shape):
     parts = (ctypes.c_int32 * 4)()
     _check(lib().moe_expert_ffn_parts(ctypes.byref(shape), parts), "moe_expert_ffn_parts")
     return [bool(v) for v in parts]
+
+
+def moe_expert_ffn_direct(shape):
+    """Of the same four launches: are the tiles found without the experts' row counts."""
+    direct = (ctypes.c_int32 * 4)()
+    _check(lib().moe_expert_ffn_direct(ctypes.byref(shape), direct), "moe_expert_ffn_direct")
+    return [bool(v) for v in direct]
 
 
 def moe_microbench_mfma_bf16(n_workgroups, iters, random_operands, out, stream=None):

@@ -77,8 +77,8 @@ struct GemmArgs {
     int M, N, K;      // extents; the one bounded by expert_count is an upper limit
     int var_k;        // 0: rows (M) bounded by expert_count; 1: K bounded by it
     int tiles_m, tiles_n, E;
-    // smaller tiles, where all that there could be fit the chip at once: this product's are an XCD's workgroups from
-    // direct_first on, direct_count tiles in all (0: by the experts' row counts), and t / d is the upper half of t * inv
+    // smaller tiles, where each that there could be has a workgroup of its own (set_direct): this product's are an XCD's
+    // workgroups from direct_first on, direct_count tiles in all (0: by the experts' row counts); t / d is the upper half of t * inv
     int direct_first, direct_count;
     uint32_t inv_expert, inv_m;
     int lead;         // second product of a launch: its tiles that take as long as one of the first product's (TileWalk::follow)
@@ -458,8 +458,8 @@ struct TileWalk {
             if (second) follow(other, p.lead); else t = place() - step;
         }
     }
-    // All tiles that there could be run at once, one per workgroup, and most of them are there: nothing waits for the
-    // expert's row count but what needs it (a scalar load).  Each XCD has an eighth of each product's tiles.
+    // One tile per workgroup, as set_direct() numbered them: nothing waits for the expert's row count but what needs it (a
+    // scalar load).  Each XCD has an eighth of each product's tiles.
     __device__ __forceinline__ bool only(const GemmArgs& p) {
         t = t_end = step = 0;
         const int xcd = (int)(blockIdx.x & 7), j = (int)(blockIdx.x >> 3) - p.direct_first;
@@ -1623,12 +1623,17 @@ static void set_tiles(GemmArgs& p, int BM, int BN, int E) {
 }
 static long long all_tiles(const GemmArgs& p) { return (long long)p.E * p.tiles_m * p.tiles_n; }
 
-// One tile per workgroup, addressed without the experts' row counts, where the chip holds all tiles that there could be
-// and at least four of five of them are expected to hold rows (otherwise the others crowd some of the CUs).
-// p2: the launch's second product or null.  Returns the workgroups per XCD, 0 where the tiles are walked instead.
-static int set_direct(GemmArgs& p, GemmArgs* p2, int rows, int side, long long per_xcd) {
+// One tile per workgroup, addressed without the experts' row counts, where at least four of five of all tiles that there
+// could be are expected to hold rows and each has a CU to itself: an expert's tiles are an XCD's, and with a skewed gate the
+// ones in use would share some of the CUs while the others' idle.  Expert FFN forward, addressed so against walked by the
+// counts, Zipf gate: 8 experts of 117 slots, 304 tiles, 24 us and 19; all tokens on one of 5 experts, 1320 tiles of 32 x 32,
+// h W2 44 us and 30; a fifth of the slots empty, 302 tiles, 16.5 and 12.4.  One expert's rows are known: with none of its
+// tiles empty, as many as run at once (`occ` per CU).  p2: the launch's second product or null.  Returns the workgroups per
+// XCD, 0 where the tiles are walked instead.
+static int set_direct(GemmArgs& p, GemmArgs* p2, int rows, int side, int occ) {
     const long long s1 = (all_tiles(p) + 7) / 8, s2 = p2 ? (all_tiles(*p2) + 7) / 8 : 0;
-    if (4 * p.tiles_m > 5 * ceil_div(rows, side) || s1 + s2 > per_xcd) return 0;
+    const int filled = ceil_div(rows, side), per_cu = p.E == 1 && p.tiles_m == filled ? occ : 1;
+    if (4 * p.tiles_m > 5 * filled || s1 + s2 > (long long)num_cus() / 8 * per_cu) return 0;
     for (GemmArgs* q : {&p, p2}) {
         if (!q) continue;
         const int per_e = q->tiles_m * q->tiles_n;
@@ -1644,7 +1649,7 @@ template <typename T, int BM, int BN, int KW, int NS, bool A_KC, bool B_KC, int 
 static bool launch_mid(GemmArgs p, int rows, int E, hipStream_t st) {
     typedef MidSmem<T, BM, BN, KW, NS, A_KC, B_KC> SM;
     set_tiles(p, BM, BN, E);
-    const int direct = set_direct(p, nullptr, rows, BM, num_cus() / 8 * SM::OCC);
+    const int direct = set_direct(p, nullptr, rows, BM, SM::OCC);
     const size_t smem = SM::BYTES + WALK_BYTES;
     // a k-contiguous operand whose reduction length is not a multiple of the slab needs the guarded instance
     const bool kg = (A_KC || B_KC) && !p.var_k && p.K % SM::BK != 0;
@@ -1660,7 +1665,7 @@ static bool launch_mid_pair(GemmArgs p1, GemmArgs p2, int rows, int E, hipStream
     typedef MidSmem<T, BM, BN, KW, NS, A1, B1> SM;
     set_tiles(p1, BM, BN, E);
     set_tiles(p2, BM, BN, E);
-    const int direct = set_direct(p1, &p2, rows, BM, num_cus() / 8 * SM::OCC);
+    const int direct = set_direct(p1, &p2, rows, BM, SM::OCC);
     const size_t smem = SM::BYTES + WALK_BYTES;
     const bool kg = ((A1 || B1) && !p1.var_k && p1.K % SM::BK != 0) || ((A2 || B2) && !p2.var_k && p2.K % SM::BK != 0);
     static unsigned long long opted[2] = {0, 0};
@@ -1673,7 +1678,7 @@ static bool launch_mid_pair(GemmArgs p1, GemmArgs p2, int rows, int E, hipStream
 template <bool A_KC, bool B_KC, int EPI, int ACT>
 static bool launch_thin(GemmArgs p, int rows, int E, hipStream_t st) {
     set_tiles(p, THIN, THIN, E);
-    const int direct = set_direct(p, nullptr, rows, THIN, num_cus() / 8 * THIN_GRID);
+    const int direct = set_direct(p, nullptr, rows, THIN, THIN_GRID);
     const size_t smem = THIN_WAVES * THIN * THIN * 4 + WALK_BYTES;
     thin_gemm_kernel<A_KC, B_KC, EPI, ACT><<<direct ? 8 * direct : mid_grid(all_tiles(p), THIN_GRID), 64 * THIN_WAVES, smem, st>>>(p);
     return true;
@@ -1683,7 +1688,7 @@ template <bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
 static bool launch_thin_pair(GemmArgs p1, GemmArgs p2, int rows, int E, hipStream_t st) {
     set_tiles(p1, THIN, THIN, E);
     set_tiles(p2, THIN, THIN, E);
-    const int direct = set_direct(p1, &p2, rows, THIN, num_cus() / 8 * THIN_GRID);
+    const int direct = set_direct(p1, &p2, rows, THIN, THIN_GRID);
     const size_t smem = THIN_WAVES * THIN * THIN * 4 + WALK_BYTES;
     thin_gemm_pair_kernel<A1, B1, EPI1, A2, B2, EPI2><<<direct ? 8 * direct : mid_grid(all_tiles(p1) + all_tiles(p2), THIN_GRID), 64 * THIN_WAVES, smem, st>>>(p1, p2);
     return true;
@@ -1910,6 +1915,31 @@ static int four_tiles(const moe_shape* shape, FfnTile (&t)[4]) {
     t[1] = tile_for(f32, rows, d, E);
     t[2] = tile_for_pair(f32, rows, f, f, d, E);
     t[3] = tile_for_pair(f32, rows, d, d, f, E);
+    return MOE_OK;
+}
+// and: is every tile of the launch found without the experts' row counts
+extern "C" int moe_expert_ffn_direct(const moe_shape* shape, int32_t* direct) {
+    FfnTile t[4];
+    const int rc = four_tiles(shape, t);
+    if (rc) return rc;
+    if (!direct) return MOE_ERR_NULL;
+    const bool f32 = shape->dtype == MOE_F32;
+    const int d = shape->d_model, f = shape->d_ff;
+    for (int i = 0; i < 4; ++i) {
+        const int side = t[i] == TILE_32 ? THIN : t[i] == TILE_64 ? 64 : 128;
+        const int occ = t[i] == TILE_32 ? THIN_GRID
+            : t[i] == TILE_64 ? (f32 ? MidSmem<float, 64, 64, 2, 2, true, true>::OCC : MidSmem<bf16_t, 64, 64, 1, 3, true, true>::OCC)
+            : t[i] == TILE_128_PAIRED ? MidSmem<float, 128, 128, 2, 2, true, true>::OCC
+            : f32 ? MidSmem<float, 128, 128, 1, 2, true, true>::OCC : MidSmem<bf16_t, 128, 128, 1, 2, true, true>::OCC;
+        GemmArgs p = {}, q = {};
+        p.M = shape->capacity;
+        p.N = i == 1 || i == 3 ? d : f;
+        q.M = i == 2 ? f : d;
+        q.N = i == 2 ? d : f;
+        set_tiles(p, side, side, shape->E);
+        set_tiles(q, side, side, shape->E);
+        direct[i] = t[i] != TILE_256 && set_direct(p, i >= 2 ? &q : nullptr, expected_rows(shape), side, occ) > 0;
+    }
     return MOE_OK;
 }
 extern "C" int moe_expert_ffn_parts(const moe_shape* shape, int32_t* parts) {

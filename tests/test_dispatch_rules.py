@@ -127,3 +127,19 @@ def test_projection_backward_chunks_of_very_wide_tokens_keep_32_bit_offsets(dtyp
             # every chunk but the last is full, so no chunk holds fewer tokens than this
             tokens = -(-T // chunks)
             assert tokens * d * (4 if dtype == I.F32 else 2) < 1 << 31, (T, chunks)
+
+
+@pytest.mark.parametrize("T,d,f,E,k,C,dtype,direct", [
+    # xd W1, h W2, dz with dW2, dxd with dW1: do all tiles that there could be have a CU each and mostly hold rows
+    (256, 64, 256, 4, 1, 64, I.F32, [True] * 4),                # the four launches 18.8 direct, 25 through a table
+    (512, 512, 2048, 8, 1, 64, I.BF16, [True, True, False, False]),
+    (61, 64, 200, 3, 2, 129, I.BF16, [False] * 4),              # mostly empty
+    (372, 1216, 1192, 8, 2, 117, I.BF16, [False] * 4),          # 304 tiles: 24 direct, 19 walked with a Zipf gate
+    (3279, 272, 704, 6, 2, 1093, I.BF16, [False, True, False, False]),     # 324 tiles: 13.4, 12.2 with a hot expert
+    (1746, 368, 1136, 5, 2, 699, I.F32, [False, False, False, True]),      # h W2 44, 30 with one expert taking all
+    (360, 2008, 6312, 6, 1, 75, I.BF16, [False] * 4),           # h W2 48, 37 with one expert taking all
+    (700, 1288, 2056, 1, 1, 700, I.BF16, [True, True, True, False]),       # 363 tiles, three per CU: an expert that has all
+    (15413, 200, 768, 1, 1, 19267, I.BF16, [False, False, False, False]),  # h W2 16.5, 12.4: a fifth of 302 tiles is empty
+])
+def test_tiles_found_without_the_counts(T, d, f, E, k, C, dtype, direct):
+    assert B.moe_expert_ffn_direct(B.make_shape(T, d, f, E, k, C, dtype, I.GELU)) == direct
