@@ -1142,17 +1142,27 @@ __device__ __forceinline__ typename TileWalk<BM, BN>::Where mid_body(const GemmA
                 if (live) {
                     const unsigned char* a_s = smem_raw + st * SM::STAGE;
                     const unsigned char* b_s = a_s + TA::BYTES;
+                    // 64 x 64 has one product per k-step: all of the slab's fragments are asked for before the first one.
+                    // Left to itself the compiler waited for each k-step's in turn, where it saw more waves to be had
+                    // from fewer registers than LDS lets in (h W2, 68 rows, K = 3552: 20.1 us, 18.0 so).
+                    constexpr int STEPS = TM * TN == 1 ? KS : 1;
 #pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
-                        bf16x8_t fa[TM], fb[TN];
+                    for (int k0 = 0; k0 < KS; k0 += STEPS) {
+                        bf16x8_t fa[STEPS][TM], fb[STEPS][TN];
 #pragma unroll
-                        for (int i = 0; i < TM; ++i) fa[i] = TA::frag(a_s, wm * (BM / 2) + i * 32, wk * KS + ks, lane);
+                        for (int ks = 0; ks < STEPS; ++ks) {
 #pragma unroll
-                        for (int j = 0; j < TN; ++j) fb[j] = TB::frag(b_s, wn * (BN / 2) + j * 32, wk * KS + ks, lane);
+                            for (int i = 0; i < TM; ++i) fa[ks][i] = TA::frag(a_s, wm * (BM / 2) + i * 32, wk * KS + k0 + ks, lane);
 #pragma unroll
-                        for (int i = 0; i < TM; ++i)
+                            for (int j = 0; j < TN; ++j) fb[ks][j] = TB::frag(b_s, wn * (BN / 2) + j * 32, wk * KS + k0 + ks, lane);
+                        }
+                        if (STEPS > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int j = 0; j < TN; ++j) acc[i][j] = Mma<bf16_t>::mma(fb[j], fa[i], acc[i][j]);
+                        for (int ks = 0; ks < STEPS; ++ks)
+#pragma unroll
+                            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                                for (int j = 0; j < TN; ++j) acc[i][j] = Mma<bf16_t>::mma(fb[ks][j], fa[ks][i], acc[i][j]);
                     }
                 }
                 st = st == NS - 1 ? 0 : st + 1;
