@@ -1757,24 +1757,38 @@ static bool prefer_mid(double t256, double t128) {
     return ceil(t128 / (2 * cus)) * (cus / 2) / 0.78 < ceil(t256 / cus) * cus;
 }
 
+// fp32, few tiles: 32 x 32 or 64 x 64, by the time (us) that each would take.  n32 and n64 tiles with reductions of k
+// entries, and of the launch's second product m32 and m64 with reductions of l (none: 0).  After its start a launch lasts as
+// long as its longest reduction (64 x 64: 0.016 us per entry; 32 x 32, where four waves share it: 0.0093) or as the most
+// tiles that a CU gets (2.8 + 0.0135 per entry; 1.5 + 0.0048).  Fitted, as the factor on the estimate for 64 x 64 and the
+// limit of 5.5 tiles per CU are, to 885 launches of 8 - 2500 rows, d = 32 - 1500, 1 - 64 experts, balanced and skewed: the form
+// chosen is 2 % (one product) and 4 % (two) slower than the better one on average, where 64 x 64 alone would be 20 % slower.
+// In us, 64 x 64 against 32 x 32, one product: 28 and 8 tiles 7 and 8 against 5 and 5 (256 tokens, d = 64); 150 and 550
+// tiles 9.2 and 7.8 (777 tokens, d = 136); 264 and 990 of K = 176, two rounds against four, 14.9 and 12.0; 240 and 960 of
+// K = 192, one round, 6.8 and 10.6; 504 and 1476 of K = 3864 138 and 159.  Two: 174 and 672 tiles, reductions of 1675
+// rows, 33.6 and 17.5; 304 and 1200, of 2137, 44 and 28; 256 and 992, of 512 and 461, 12.3 and 17.4; 525 and 1845 21 and 62.
+static FfnTile few_tiles(double n32, double n64, int k, double m32, double m64, int l) {
+    const double cus = num_cus(), longest = k > l ? k : l;
+    auto us = [&](double n, double m, double start, double chain, double tile, double entry) {
+        return start + fmax(chain * longest, ceil((n + m) / cus) * (tile + entry * (n * k + m * l) / (n + m)));
+    };
+    const double us32 = us(n32, m32, 0.6, 0.0093, 1.5, 0.0048), us64 = us(n64, m64, 2.8, 0.016, 2.8, 0.0135);
+    return n32 + m32 <= 5.5 * cus && us32 <= (m32 > 0.0 ? 1.25 : 1.15) * us64 ? TILE_32 : TILE_64;
+}
+
 // fp32: 64 x 64 tiles as long as 128 x 128 ones would leave much of the chip idle (five experts of 280
 // rows, d = 136, f = 328: 10 us per product against 17 - 23); 128 x 128 with two wave groups that
 // share a tile's slabs while there are few tiles per CU (248 tiles, f = 2048: 89 us against 124 with
 // one group), with one group otherwise (992 tiles, d = 512: 105 against 117).
-// Where 64 x 64 tiles it is, a product takes 32 x 32 ones if these need no more rounds (three at a time on a CU) than
-// the 64 x 64 ones (one): latency is all there is then.  In us, 64 x 64 against 32 x 32: 28 and 8 tiles 7 and 8 against
-// 5 and 5 (256 tokens, d = 64); 212 and 715 tiles 11.4 and 7.4 (777 tokens, d = 136); 130 and 510 tiles 9.0 and 8.2;
-// 325 and 1170 tiles 19.5 and 15.9; 208 and 832 tiles, K = 320, 10.4 and 13.6.
+// Where 64 x 64 tiles it is, few_tiles() says whether they are computed as 32 x 32 ones.
 // bf16: the same order.  64 x 64 (8 experts of 64 rows, d = 512, f = 2048: 7 and 11 us against 10 and
 // 22 with 128 x 128, 17 and 39 with 256 x 256); with few rows per expert the weights' stream is the
 // bound and two 128 x 128 workgroups per CU keep more of it in flight than one large one (107 experts
 // of 7 rows, d = 1024, f = 4096: 169 us = 5.3 TB/s against 203).
-static FfnTile tile_for(bool f32, int rows, int N, int E) {
+static FfnTile tile_for(bool f32, int rows, int N, int K, int E) {
     const double cus = num_cus(), t128 = tiles_expected(rows, N, 128, E);
-    if (f32 && t128 <= 0.6 * cus) {
-        const double t64 = tiles_expected(rows, N, 64, E), t32 = tiles_expected(rows, N, THIN, E);
-        return t32 <= THIN_OCC * cus * fmin(ceil(t64 / cus), 2.0) ? TILE_32 : TILE_64;
-    }
+    if (f32 && t128 <= 0.6 * cus)
+        return few_tiles(tiles_expected(rows, N, THIN, E), tiles_expected(rows, N, 64, E), K, 0, 0, 0);
     if (f32) return t128 <= 1.5 * cus ? TILE_128_PAIRED : TILE_128;
     if (t128 <= (rows <= 128 ? 1.0 : 0.5) * cus) return TILE_64;
     return rows <= 128 || prefer_mid(tiles_expected(rows, N, 256, E), t128) ? TILE_128 : TILE_256;
@@ -1783,15 +1797,15 @@ static FfnTile tile_for(bool f32, int rows, int N, int E) {
 // Two products, `rows` rows by N1 columns and a weight gradient of M2 by N2: the same lines at higher tile
 // counts, because the tiles of both are in the launch (fp32, 248 + 512 tiles: 185 us with two wave groups, 250 with
 // one; 992 + 512: 197 and 179.  bf16, 8 experts of 64 rows, 32 + 512 tiles: 26 us with 64 x 64, 30 with 128 x 128, 41
-// with 256 x 256).  32 x 32 tiles up to 4.3 per CU (990 of them 12.6 us against 14.3 with 64 x 64, 1088: 14.0 against
-// 20.8; 720 with reductions of 1600 rows, which four waves share: 21 against 34; 2500: 31 against 27).
+// with 256 x 256).  The first product's reduction is N2 long, the second's `rows`.
 // bf16, experts of at most 128 rows: the first pair (whose first product's reduction, N2, is the shorter extent) takes
 // 128 x 128 (36 experts of 66 rows, d = 864, f = 2256: 90 us against 127 with 256 x 256; 81 of 11, d = 1064, f = 3368:
 // 365 against 420; 9 of 100, d = 1232, f = 4608: 77 against 96); in the second one either may be the faster.
 static FfnTile tile_for_pair(bool f32, int rows, int N1, int M2, int N2, int E) {
     const double cus = num_cus(), t128 = tiles_expected(rows, N1, 128, E) + tiles_expected(M2, N2, 128, E);
     if (f32 && t128 <= 0.75 * cus)
-        return tiles_expected(rows, N1, THIN, E) + tiles_expected(M2, N2, THIN, E) <= 4.3 * cus ? TILE_32 : TILE_64;
+        return few_tiles(tiles_expected(rows, N1, THIN, E), tiles_expected(rows, N1, 64, E), N2, tiles_expected(M2, N2, THIN, E),
+                         tiles_expected(M2, N2, 64, E), rows);
     if (f32) return t128 <= 4.0 * cus ? TILE_128_PAIRED : TILE_128;
     if (t128 <= (rows <= 128 ? 3.0 : 1.0) * cus) return TILE_64;
     if (rows <= 128 && N2 <= N1) return TILE_128;
@@ -1800,7 +1814,7 @@ static FfnTile tile_for_pair(bool f32, int rows, int N1, int M2, int N2, int E) 
 
 template <typename T, bool A_KC, bool B_KC, int EPI, int ACT = 0>
 static bool launch_gemm(const GemmArgs& p, int rows, int E, hipStream_t st) {
-    const FfnTile t = tile_for(sizeof(T) == 4, rows, p.N, E);
+    const FfnTile t = tile_for(sizeof(T) == 4, rows, p.N, p.K, E);
     if constexpr (sizeof(T) == 4) {
         if (t == TILE_32) return launch_thin<A_KC, B_KC, EPI, ACT>(p, rows, E, st);
         if (t == TILE_64) return launch_mid<T, 64, 64, 2, 2, A_KC, B_KC, EPI, ACT>(p, rows, E, st);
@@ -1925,8 +1939,8 @@ static int four_tiles(const moe_shape* shape, FfnTile (&t)[4]) {
     if (rc || (rc = check_slice_limits(shape))) return rc;
     const bool f32 = shape->dtype == MOE_F32;
     const int rows = expected_rows(shape), d = shape->d_model, f = shape->d_ff, E = shape->E;
-    t[0] = tile_for(f32, rows, f, E);
-    t[1] = tile_for(f32, rows, d, E);
+    t[0] = tile_for(f32, rows, f, d, E);
+    t[1] = tile_for(f32, rows, d, f, E);
     t[2] = tile_for_pair(f32, rows, f, f, d, E);
     t[3] = tile_for_pair(f32, rows, d, d, f, E);
     return MOE_OK;

@@ -143,3 +143,24 @@ def test_projection_backward_chunks_of_very_wide_tokens_keep_32_bit_offsets(dtyp
 ])
 def test_tiles_found_without_the_counts(T, d, f, E, k, C, dtype, direct):
     assert B.moe_expert_ffn_direct(B.make_shape(T, d, f, E, k, C, dtype, I.GELU)) == direct
+
+
+@pytest.mark.parametrize("rows,d,f,E,parts", [
+    # fp32, few tiles: 32 x 32 in xd W1, h W2, dz with dW2, dxd with dW1
+    (64, 64, 256, 4, [True] * 4),               # 5, 5, 5, 6; 64 x 64: 7, 8, 8, 9
+    (311, 136, 328, 5, [True] * 4),             # one hot expert 7.8, 5.8, 10.8, 8.9; 9.2, 9.8, 11.8, 11.6
+    (1675, 48, 96, 3, [True] * 4),              # long reductions over the rows, Zipf gate 7.0, 4.4, 17.5, 19.0; 7.7, 5.9, 33.6, 34.2
+    (464, 176, 704, 3, [True] * 4),             # 12.0, 13.2, 16.6, 16.6; 14.9, 21.5, 18.7, 13.4
+    (624, 192, 192, 8, [False, False, True, True]),     # full in one round of 64 x 64: 12.7, 10.6, 17.3, 17.2; 9.6, 6.8, 21.4, 20.2
+    (461, 512, 512, 2, [True, True, False, False]),     # 18.2, 17.4; 13.1, 12.3 in the last two
+    (300, 232, 232, 10, [False] * 4),
+])
+def test_fp32_tiles_of_small_products(rows, d, f, E, parts):
+    assert B.moe_expert_ffn_parts(B.make_shape(E * rows, d, f, E, 1, rows, I.F32, I.GELU)) == parts
+
+
+def test_long_reductions_keep_64_x_64_tiles():
+    # h W2 of 12 experts of 85 rows, K = 3864: 64 x 64 138, 32 x 32 159; 32 of 86, K = 2128: 81, 84 (82, 97 with a Zipf gate)
+    for rows, d, f, E in ((85, 1288, 3864, 12), (86, 512, 2128, 32)):
+        s = B.make_shape(E * rows, d, f, E, 1, rows, I.F32, I.GELU)
+        assert B.moe_expert_ffn_tiles(s)[1] == (64, 2) and not B.moe_expert_ffn_parts(s)[1]
