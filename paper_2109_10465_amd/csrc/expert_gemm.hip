@@ -1798,17 +1798,20 @@ static FfnTile tile_for(bool f32, int rows, int N, int K, int E) {
 // counts, because the tiles of both are in the launch (fp32, 248 + 512 tiles: 185 us with two wave groups, 250 with
 // one; 992 + 512: 197 and 179.  bf16, 8 experts of 64 rows, 32 + 512 tiles: 26 us with 64 x 64, 30 with 128 x 128, 41
 // with 256 x 256).  The first product's reduction is N2 long, the second's `rows`.
-// bf16, experts of at most 128 rows: the first pair (whose first product's reduction, N2, is the shorter extent) takes
-// 128 x 128 (36 experts of 66 rows, d = 864, f = 2256: 90 us against 127 with 256 x 256; 81 of 11, d = 1064, f = 3368:
-// 365 against 420; 9 of 100, d = 1232, f = 4608: 77 against 96); in the second one either may be the faster.
-static FfnTile tile_for_pair(bool f32, int rows, int N1, int M2, int N2, int E) {
+// bf16, experts of at most 128 rows: half of a large tile is padding.  dz with dW2 (`first`) takes 128 x 128 (36 experts of
+// 66 rows, d = 864, f = 2256: 90 us against 127 with 256 x 256; 81 of 11, d = 1064, f = 3368: 365 against 420; 24 of 74,
+// d = 1200, f = 600: 25 against 49).  dxd with dW1, where one of the two products' reductions is long, takes it for up to ten
+// tiles per CU (4 of 101, d = 968, f = 3840, 3.9 per CU: 42 against 70; 12 of 17, d = 1376, f = 2056, 9.3: 70 against 79);
+// beyond, the rounds decide as with more rows (36 of 41, d = 1152, f = 4024, 42 per CU: 276 against 252; 64 of 46,
+// d = f = 1512, 36: 235 against 206; 100 of 66, d = 560, f = 1776, 29: 150 against 202).
+static FfnTile tile_for_pair(bool f32, bool first, int rows, int N1, int M2, int N2, int E) {
     const double cus = num_cus(), t128 = tiles_expected(rows, N1, 128, E) + tiles_expected(M2, N2, 128, E);
     if (f32 && t128 <= 0.75 * cus)
         return few_tiles(tiles_expected(rows, N1, THIN, E), tiles_expected(rows, N1, 64, E), N2, tiles_expected(M2, N2, THIN, E),
                          tiles_expected(M2, N2, 64, E), rows);
     if (f32) return t128 <= 4.0 * cus ? TILE_128_PAIRED : TILE_128;
     if (t128 <= (rows <= 128 ? 3.0 : 1.0) * cus) return TILE_64;
-    if (rows <= 128 && N2 <= N1) return TILE_128;
+    if (rows <= 128 && (first || t128 <= 10.0 * cus)) return TILE_128;
     return prefer_mid(tiles_expected(rows, N1, 256, E) + tiles_expected(M2, N2, 256, E), t128) ? TILE_128 : TILE_256;
 }
 
@@ -1829,7 +1832,7 @@ static bool launch_gemm(const GemmArgs& p, int rows, int E, hipStream_t st) {
 
 template <typename T, bool A1, bool B1, int EPI1, bool A2, bool B2, int EPI2>
 static bool launch_gemm_pair(const GemmArgs& p1, const GemmArgs& p2, int rows, int E, hipStream_t st) {
-    const FfnTile t = tile_for_pair(sizeof(T) == 4, rows, p1.N, p2.M, p2.N, E);
+    const FfnTile t = tile_for_pair(sizeof(T) == 4, EPI1 == EPI_MUL, rows, p1.N, p2.M, p2.N, E);
     if constexpr (sizeof(T) == 4) {
         if (t == TILE_32) return launch_thin_pair<A1, B1, EPI1, A2, B2, EPI2>(p1, p2, rows, E, st);
         if (t == TILE_64) return launch_mid_pair<T, 64, 64, 2, 2, A1, B1, EPI1, A2, B2, EPI2>(p1, p2, rows, E, st);
@@ -1941,8 +1944,8 @@ static int four_tiles(const moe_shape* shape, FfnTile (&t)[4]) {
     const int rows = expected_rows(shape), d = shape->d_model, f = shape->d_ff, E = shape->E;
     t[0] = tile_for(f32, rows, f, d, E);
     t[1] = tile_for(f32, rows, d, f, E);
-    t[2] = tile_for_pair(f32, rows, f, f, d, E);
-    t[3] = tile_for_pair(f32, rows, d, d, f, E);
+    t[2] = tile_for_pair(f32, true, rows, f, f, d, E);
+    t[3] = tile_for_pair(f32, false, rows, d, d, f, E);
     return MOE_OK;
 }
 // and: is every tile of the launch found without the experts' row counts

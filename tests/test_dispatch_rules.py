@@ -164,3 +164,21 @@ def test_long_reductions_keep_64_x_64_tiles():
     for rows, d, f, E in ((85, 1288, 3864, 12), (86, 512, 2128, 32)):
         s = B.make_shape(E * rows, d, f, E, 1, rows, I.F32, I.GELU)
         assert B.moe_expert_ffn_tiles(s)[1] == (64, 2) and not B.moe_expert_ffn_parts(s)[1]
+
+
+@pytest.mark.parametrize("rows,d,f,E,first,second", [
+    # bf16, experts of at most 128 rows: tile side of dz with dW2 and of dxd with dW1
+    (66, 864, 2256, 36, 128, 256),      # 90 with 128 x 128 against 127
+    (74, 1200, 600, 24, 128, 128),      # 25, 49; 26, 36: the shorter extent is the other one
+    (61, 1512, 1512, 6, 128, 128),      # 28, 42; 27, 36
+    (46, 1512, 1512, 64, 128, 256),     # 238, 243; 235, 206
+    (102, 1016, 1016, 100, 128, 256),   # 212, 206; 206, 181
+    (74, 1992, 1528, 24, 128, 256),     # 139, 142; 126, 118
+    (101, 968, 3840, 4, 128, 128),      # 26, 37; 42, 70
+    (17, 1376, 2056, 12, 128, 128),     # 59, 74; 70, 79
+    (66, 560, 1776, 100, 128, 128),     # 161, 160; 150, 202: fewer rounds
+    (129, 1512, 1512, 64, 256, 256),
+])
+def test_backward_tiles_of_few_rows(rows, d, f, E, first, second):
+    s = B.make_shape(E * rows, d, f, E, 1, rows, I.BF16, I.GELU)
+    assert [t[0] for t in B.moe_expert_ffn_tiles(s)[2:]] == [first, second]
