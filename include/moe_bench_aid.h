@@ -38,12 +38,12 @@ int moe_gate_logits_bwd_chunks(const moe_shape* shape, float jitter_eps);
 /* Launches of moe_combine_gate_bwd: 1 = one pass over the tokens, 2 = combine, then gate. */
 int moe_combine_gate_bwd_launches(const moe_shape* shape);
 
-/* Tile side (64, 128 or 256) and groups of four waves that share a tile (1 or 2), for each of the
+/* Tile side (32, 64, 128 or 256) and groups of four waves that share a tile (1 or 2), for each of the
  * expert FFN's four launches: xd W1, h W2, dz with dW2, dxd with dW1. */
 int moe_expert_ffn_tiles(const moe_shape* shape, int32_t* side, int32_t* wave_groups);
 
-/* For the same four launches: 1 where fp32's 64 x 64 tiles are computed as 32 x 32 parts, each by a
- * workgroup of its own whose four waves share the reduction, 0 elsewhere. */
+/* For the same four launches: 1 where the tile is fp32's 32 x 32 one, whose reduction a workgroup's four waves share,
+ * 0 elsewhere. */
 int moe_expert_ffn_parts(const moe_shape* shape, int32_t* parts);
 
 /* For the same four launches: 1 where every workgroup takes one tile whose place does not depend on the experts' row

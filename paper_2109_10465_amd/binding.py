@@ -298,7 +298,7 @@ def moe_expert_ffn_tiles(shape):
 
 
 def moe_expert_ffn_parts(shape):
-    """Of the same four launches: are fp32's 64 x 64 tiles computed as 32 x 32 parts."""
+    """Of the same four launches: is the tile fp32's 32 x 32 one."""
     parts = (ctypes.c_int32 * 4)()
     _check(lib().moe_expert_ffn_parts(ctypes.byref(shape), parts), "moe_expert_ffn_parts")
     return [bool(v) for v in parts]

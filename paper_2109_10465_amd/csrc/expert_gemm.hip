@@ -1935,8 +1935,8 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     return launch_gemm_pair<T, true, true, EPI_STORE, false, false, EPI_F32>(p, q, rows, E, st);
 }
 
-// measurement aids: the tile of each of the four launches (xd W1, h W2, dz with dW2, dxd with dW1), and whether a
-// 64 x 64 fp32 one is computed as 32 x 32 parts
+// measurement aids: the tile of each of the four launches (xd W1, h W2, dz with dW2, dxd with dW1), and whether it is the
+// 32 x 32 one
 static int four_tiles(const moe_shape* shape, FfnTile (&t)[4]) {
     int rc = shape_status(shape);
     if (rc || (rc = check_slice_limits(shape))) return rc;
@@ -1988,8 +1988,8 @@ extern "C" int moe_expert_ffn_tiles(const moe_shape* shape, int32_t* side, int32
     if (!side || !wave_groups) return MOE_ERR_NULL;
     const bool f32 = shape->dtype == MOE_F32;
     for (int i = 0; i < 4; ++i) {
-        side[i] = t[i] <= TILE_64 ? 64 : t[i] == TILE_256 ? 256 : 128;
-        wave_groups[i] = f32 && t[i] != TILE_128 ? 2 : 1;
+        side[i] = t[i] == TILE_32 ? THIN : t[i] == TILE_64 ? 64 : t[i] == TILE_256 ? 256 : 128;
+        wave_groups[i] = f32 && (t[i] == TILE_64 || t[i] == TILE_128_PAIRED) ? 2 : 1;
     }
     return MOE_OK;
 }

@@ -156,7 +156,10 @@ def test_tiles_found_without_the_counts(T, d, f, E, k, C, dtype, direct):
     (300, 232, 232, 10, [False] * 4),
 ])
 def test_fp32_tiles_of_small_products(rows, d, f, E, parts):
-    assert B.moe_expert_ffn_parts(B.make_shape(E * rows, d, f, E, 1, rows, I.F32, I.GELU)) == parts
+    s = B.make_shape(E * rows, d, f, E, 1, rows, I.F32, I.GELU)
+    assert B.moe_expert_ffn_parts(s) == parts
+    # and the query of the tiles names the kernel that runs: four waves on 32 x 32, two groups of four on 64 x 64
+    assert B.moe_expert_ffn_tiles(s) == [(32, 1) if p else (64, 2) for p in parts]
 
 
 def test_long_reductions_keep_64_x_64_tiles():

@@ -28,6 +28,7 @@ CASES = [
 ]
 # the activation-only epilogue on the other tiles: name, sizes, tile side and wave groups of xd W1
 TILES = [("eval_bf16_128", 6400, 136, 1032, 64, 1, I.BF16, (128, 1)), ("eval_bf16_256", 2600, 520, 2056, 8, 2, I.BF16, (256, 1)),
+         ("eval_f32_32", 777, 136, 328, 5, 2, I.F32, (32, 1)), ("eval_f32_64", 3084, 232, 232, 12, 1, I.F32, (64, 2)),
          ("eval_f32_128_groups", 1500, 136, 1032, 8, 2, I.F32, (128, 2)), ("eval_f32_128", 2200, 40, 2056, 8, 2, I.F32, (128, 1))]
 TILE_CASES = [(eval_workload(f"{n}_{a}", T, d, f, E, k, dt, act, skew="hot0", skew_param=0.3), tile)
               for n, T, d, f, E, k, dt, tile in TILES for a, act in (("gelu", I.GELU), ("relu", I.RELU))]

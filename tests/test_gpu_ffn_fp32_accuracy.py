@@ -10,8 +10,10 @@ from paper_2109_10465_amd import inputs as I
 import gpu_util as G
 
 #         E    C    d     f  tile (side, wave groups) of xd W1, h W2, dz with dW2, dxd with dW1
-SHAPES = [(2, 70, 72, 136, [(64, 2)] * 4),
-          (8, 380, 136, 1032, [(128, 2), (64, 2), (128, 2), (64, 2)]),
+SHAPES = [(2, 70, 72, 136, [(32, 1)] * 4),
+          (12, 257, 232, 232, [(64, 2)] * 4),
+          (10, 300, 256, 256, [(64, 2)] * 4),           # reductions without a partial slab
+          (8, 380, 136, 1032, [(128, 2), (32, 1), (128, 2), (64, 2)]),
           (8, 380, 904, 1032, [(128, 2)] * 4),
           (32, 520, 264, 1032, [(128, 1)] * 4),
           (32, 520, 272, 1040, [(128, 1)] * 4)]       # reductions without a partial slab

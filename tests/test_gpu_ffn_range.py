@@ -14,8 +14,9 @@ import gpu_util as G
 
 pytestmark = pytest.mark.gpu
 
-#         E    C    d     f: tiles of 64 x 64; of 128 x 128 with two wave groups, with one
-SHAPES = [(2, 70, 72, 136), (8, 380, 136, 1032), (16, 560, 520, 2056)]
+#         E    C    d     f: tiles of 32 x 32; of 64 x 64; of 128 x 128 with two wave groups (in xd W1 and dz with dW2), with one
+SHAPES = [(2, 70, 72, 136), (12, 257, 232, 232), (8, 380, 136, 1032), (16, 560, 520, 2056)]
+TILES = [[(32, 1)] * 4, [(64, 2)] * 4, [(128, 2), (32, 1), (128, 2), (64, 2)], [(128, 1)] * 4]
 
 
 def act64(z, act):
@@ -42,7 +43,7 @@ def same(name, got, want, rel):
 
 @pytest.mark.parametrize("act", [I.RELU, I.GELU], ids=["relu", "gelu"])
 @pytest.mark.parametrize("what", ["inf_row", "inf_weight", "nan", "large", "tiny"])
-@pytest.mark.parametrize("E,C,d,f", SHAPES, ids=["64", "128x2", "128x1"])
+@pytest.mark.parametrize("E,C,d,f", SHAPES, ids=["32", "64", "128x2", "128x1"])
 def test_fp32_operands_outside_the_exact_range(E, C, d, f, what, act):
     rng = np.random.default_rng(E)
     std = 1.0 if what == "tiny" else 0.02
@@ -61,6 +62,8 @@ def test_fp32_operands_outside_the_exact_range(E, C, d, f, what, act):
     else:
         xd *= np.float32(2.0 ** -122)
     s = B.make_shape(E * C, d, f, E, 1, C, I.F32, act)
+    if (E, C, d, f) in SHAPES:
+        assert B.moe_expert_ffn_tiles(s) == TILES[SHAPES.index((E, C, d, f))]
     ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
     new = lambda *sh: torch.zeros(*sh, device="cuda")
     dx, dw1, dw2, ddy = (G.to_dev(a, I.F32) for a in (xd, W1, W2, dyd))

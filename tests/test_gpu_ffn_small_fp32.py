@@ -1,6 +1,7 @@
-"""GPU: the smallest fp32 products, as 32 x 32 tiles whose reduction four waves share and as 64 x 64 ones, in each of the
-three ways in which a workgroup finds its tile: addressed without the experts' row counts (buffers that are mostly
-full), from counts held in registers (half-empty buffers, up to 64 experts) and from the table in LDS (more experts)."""
+"""GPU: the smallest fp32 products, as 32 x 32 tiles whose reduction four waves share, in each of the three ways in which a
+workgroup finds its tile: addressed without the experts' row counts (buffers that are mostly full, a CU for each tile), from
+counts held in registers (half-empty buffers, up to 64 experts) and from the table in LDS (more experts); and as 64 x 64
+ones by the first two (by the table: in the test of every tile)."""
 import numpy as np
 import pytest
 import torch
@@ -30,7 +31,7 @@ SHAPES = [
 @pytest.mark.parametrize("name,T,d,f,E,k,C,parts", SHAPES, ids=[s[0] for s in SHAPES])
 def test_small_fp32_products(name, T, d, f, E, k, C, parts):
     s = B.make_shape(T, d, f, E, k, C, I.F32, I.GELU)
-    assert [t[0] for t in B.moe_expert_ffn_tiles(s)] == [64] * 4 and B.moe_expert_ffn_parts(s) == parts
+    assert [t[0] for t in B.moe_expert_ffn_tiles(s)] == [32 if p else 64 for p in parts] and B.moe_expert_ffn_parts(s) == parts
     w = I.small(name, T, d, f, E, k, C, I.F32, I.GELU, skew="hot0" if E > 2 else "none", skew_param=0.4)
     data = I.make_inputs(w, seed=5)
     _, got = G.run_layer(w, data)

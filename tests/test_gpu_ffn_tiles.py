@@ -12,7 +12,7 @@ import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 F, H = I.F32, I.BF16
-S64, S128, S256, P64, P128 = (64, 1), (128, 1), (256, 1), (64, 2), (128, 2)      # tile side, wave groups
+S32, S64, S128, S256, P64, P128 = (32, 1), (64, 1), (128, 1), (256, 1), (64, 2), (128, 2)      # tile side, wave groups
 #        name          T     d     f   E  k  capacity dtype, tiles of xd W1, h W2, dz with dW2, dxd with dW1
 SHAPES = [
     ("bf16_64_one_row",    3,   72,  136,  3, 1,    1, H, [S64, S64, S64, S64]),       # nearly every row masked
@@ -22,17 +22,24 @@ SHAPES = [
     ("bf16_128_rows",   1500,  776, 2056,  4, 2,  800, H, [S128, S128, S256, S256]),   # the large tile leaves CUs idle
     ("bf16_256_ragged", 2600,  520, 2056,  8, 2,  700, H, [S256, S128, S128, S128]),   # both extents ragged
     ("bf16_256_second", 7168,  520,  328,  8, 2, 1900, H, [S128, S256, S128, S256]),   # h W2 with a partial last slab
-    ("f32_64_edge",      390,   72,  200,  3, 2,  129, F, [P64, P64, P64, P64]),
-    ("f32_64_long_k",    130,  328,  520,  2, 1,   65, F, [P64, P64, P64, P64]),
-    ("f32_128_groups",  1500,  136, 1032,  8, 2,  380, F, [P128, P64, P128, P64]),     # two wave groups per tile
-    ("f32_128_single",  2200,   40, 2056,  8, 2,  560, F, [S128, P64, P128, P64]),
+    ("f32_32_edge",      390,   72,  200,  3, 2,  129, F, [S32, S32, S32, S32]),
+    ("f32_32_long_k",    130,  328,  520,  2, 1,   65, F, [S32, S32, S32, S32]),
+    ("f32_64_edge",     3084,  232,  232, 12, 1,  257, F, [P64, P64, P64, P64]),       # a row past four tiles, 40 columns past three
+    ("f32_64_long_k",   1540,  456,  456,  4, 1,  385, F, [P64, P64, P64, P64]),       # partial last slabs of longer reductions
+    ("f32_64_even",     3000,  256,  256, 10, 1,  300, F, [P64, P64, P64, P64]),       # whole slabs
+    ("f32_64_table_1",  2145,   24,  192, 65, 1,   33, F, [P64, S32, P128, P128]),     # more experts than lanes
+    ("f32_64_table_2",  2145,  192,   24, 65, 1,   33, F, [S32, P64, P128, P128]),
+    ("f32_64_table_3",  6790,   72,   72, 70, 1,   97, F, [S32, S32, P64, P64]),
+    ("f32_64_table_4",  2145,  128,  128, 65, 1,   33, F, [S32, S32, P64, P64]),       # and whole slabs
+    ("f32_128_groups",  1500,  136, 1032,  8, 2,  380, F, [P128, S32, P128, P64]),     # two wave groups per tile
+    ("f32_128_single",  2200,   40, 2056,  8, 2,  560, F, [S128, S32, P128, S32]),
     ("f32_128_one",     8320,  264, 1032, 32, 2,  520, F, [S128, S128, S128, S128]),   # one group, partial last slabs
     ("f32_128_one_even", 8320, 272, 1040, 32, 2,  520, F, [S128, S128, S128, S128]),   # whole slabs
 ]
 
 
 def test_the_shapes_cover_every_tile_of_every_launch():
-    for dtype, tiles in ((H, {S64, S128, S256}), (F, {P64, P128, S128})):
+    for dtype, tiles in ((H, {S64, S128, S256}), (F, {S32, P64, P128, S128})):
         for launch in range(4):
             seen = {s[8][launch] for s in SHAPES if s[7] == dtype}
             # fp32's two-group tile in h W2 and in dxd + dW1: with the accuracy of the fp32 products
@@ -44,7 +51,9 @@ def test_the_shapes_cover_every_tile_of_every_launch():
 def test_ffn_tile(name, T, d, f, E, k, C, dtype, tiles, act):
     assert B.moe_expert_ffn_tiles(B.make_shape(T, d, f, E, k, C, dtype, act)) == tiles
     w = I.small(name, T, d, f, E, k, C, dtype, act, skew="hot0" if E > 2 else "none", skew_param=0.4)
-    data = I.make_inputs(w, seed=3)
+    # ReLU's derivative jumps at 0.  The fp32 products are within 1e-6 of the exact ones (3e-7 measured), relative to their
+    # standard deviation; with seed 5 no sum of the f32_64 shapes is nearer to 0 than 1.4e-6 of it (with seed 3 one is at 4e-8).
+    data = I.make_inputs(w, seed=5 if name.startswith("f32_64") else 3)
     _, got = G.run_layer(w, data)
     G.check_full(w, data, got)
 

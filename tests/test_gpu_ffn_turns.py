@@ -16,7 +16,7 @@ SHAPES = [
     ("128_one_round", 16384, 256, 256, 2, 1, 8300, I.BF16, (128, 128)),     # more tiles than CUs, fewer than run at once
     ("128_table",  6400, 136, 1032,  70, 1, 127, I.BF16, (128, 128)),
     ("64",          600, 512, 2048,  10, 1,  60, I.BF16, (128, 64)),
-    ("f32_64",     8000, 120,  232,   5, 1, 1600, I.F32, (64, 64)),
+    ("f32_64_32",  8000, 120,  232,   5, 1, 1600, I.F32, (64, 32)),
     ("f32_128",    1500, 136, 1032,   8, 2, 380, I.F32, (128, 64)),
 ]
 
