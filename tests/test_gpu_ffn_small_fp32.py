@@ -78,3 +78,38 @@ def test_what_lies_behind_the_rows_in_use_does_not_matter():
     for o in outs[1:]:
         for x, y in zip(outs[0], o):
             assert np.isfinite(x).all() and np.array_equal(x, y)
+
+
+def test_more_tiles_than_workgroups():
+    """A workgroup of the 32 x 32 kernel takes several tiles: row counts far above what the shape lets the rule expect (a
+    routing call never writes such; every index stays inside the buffers).  Its sums in LDS are used again by each tile."""
+    T, E, C, d, f = 64, 4, 1024, 256, 1032
+    s = B.make_shape(T, d, f, E, 1, C, I.F32, I.RELU)
+    assert B.moe_expert_ffn_tiles(s) == [(32, 1)] * 4 and not any(B.moe_expert_ffn_direct(s))
+    cnt = np.array([1024, 1000, 1, 993], np.int32)
+    tiles = sum(-(-int(n) // 32) for n in cnt)
+    assert tiles * -(-f // 32) > 2048       # eight workgroups on each of 256 compute units
+    rng = np.random.default_rng(3)
+    normal = lambda *sh: rng.standard_normal(sh, dtype=np.float32)
+    xd, dyd, hs, da, W1, W2 = normal(E, C, d), normal(E, C, d), normal(E, C, f), normal(E, C, f), normal(E, d, f), normal(E, f, d)
+    dev = [G.to_dev(v, I.F32) for v in (xd, dyd, hs, da, W1, W2)]
+    c = G.to_dev(cnt, None)
+    h, a, yd, dxd, dW1, dW2 = (torch.zeros(E, m, n, device="cuda") for m, n in ((C, f), (C, f), (C, d), (C, d), (d, f), (f, d)))
+    ws = torch.empty(B.moe_workspace_bytes(s), dtype=torch.uint8, device="cuda")
+    print("[gpu] 32 x 32 tiles in several rounds", flush=True)
+    B.moe_expert_ffn_fwd(s, dev[0], c, dev[4], dev[5], h, a, yd)
+    B.moe_expert_ffn_bwd(s, dev[1], dev[0], dev[2], dev[3], c, dev[4], dev[5], dxd, dW1, dW2, ws)
+    dz = ws[:E * C * f * 4].view(torch.float32).view(E, C, f)       # the workspace holds dz
+    torch.cuda.synchronize()
+    got = {n: G.host(t) for n, t in (("h", h), ("yd", yd), ("dz", dz), ("dxd", dxd), ("dW1", dW1), ("dW2", dW2))}
+    for e in range(E):
+        n = cnt[e]
+        x, dy, hh, dd, w1, w2 = (v[e].astype(np.float64) for v in (xd, dyd, hs, da, W1, W2))
+        hg, dzg = got["h"][e][:n].astype(np.float64), got["dz"][e][:n].astype(np.float64)
+        want = {"h": np.maximum(x[:n] @ w1, 0.0), "yd": hg @ w2, "dz": (dy[:n] @ w2.T) * dd[:n], "dxd": dzg @ w1.T,
+                "dW1": x[:n].T @ dzg, "dW2": hh[:n].T @ dy[:n]}
+        for name, w in want.items():
+            g = got[name][e] if "W" in name else got[name][e][:n]
+            # the bound of the fp32 products: any of their six parts that is missing is twice as far off
+            assert G.rel_l2(g, w) <= 1e-6, (name, e, G.rel_l2(g, w))
+            assert float(np.abs(g - w).max()) <= 1e-4 * float(np.abs(w).max()), (name, e)
