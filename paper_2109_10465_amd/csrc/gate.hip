@@ -37,15 +37,16 @@ __device__ __forceinline__ void load8<float>(__amdgpu_buffer_rsrc_t rs, uint32_t
 
 // TT = 32-token tiles per workgroup: with more than 32 experts every workgroup reads all of
 // Wg (E * d * 4 bytes, from L2) once, so two token tiles share each of its fragments.
-// JIT: gate jitter on (a separate instance keeps the plain one lean).  Its eight blocks of noise need 251 registers; held to
-// 128 it spilled them: 18.5 µs instead of 15.4 at T = 8192, d = 768, E = 16, and 47 with the noise's 64-bit products.
-// Large grids of narrow rows pay 1-2 % for two waves a SIMD (T = 65536, d = 512: 94 -> 96 µs), wide rows gain
-// (T = 49152, d = 2048: 154 -> 144).
+// JIT: gate jitter on (a separate instance keeps the plain one lean).  Its groups are four blocks, not eight: eight blocks of
+// noise need 251 registers in bf16 and 173 in fp32, two waves per SIMD, and a wave draws all of a group's noise also for
+// blocks that it has not got.  Four fit in 128, four waves per SIMD.  In us, two waves and eight blocks against this: fp32
+// T = 32768, d = 1024 50 and 40, T = 65536, d = 64 50 and 22; bf16 T = 65536, d = 2048 165 and 140, T = 8192, d = 768 12.4 and 11.4;
+// the slowest against it, bf16 T = 8192, d = 4096, 40.2 and 41.1.
 template <typename T, int NB, bool JIT, int TT>
-__global__ __launch_bounds__(64 * GLM_KSPLIT, NB == 1 && !JIT ? 4 : 2) void gate_logits_kernel(
+__global__ __launch_bounds__(64 * GLM_KSPLIT, NB == 1 ? 4 : 2) void gate_logits_kernel(
     int Tn, int d, int E, const T* __restrict__ x, const float* __restrict__ Wg,
     const float* __restrict__ bias, float* __restrict__ logits, float jitter_eps, uint64_t seed) {
-    constexpr int GRP = NB <= 2 && TT == 1 ? 8 : 4;   // 16-deep blocks whose loads are in flight together
+    constexpr int GRP = NB <= 2 && TT == 1 && !JIT ? 8 : 4;   // 16-deep blocks whose loads are in flight together
     __shared__ float red[GLM_KSPLIT][32][33];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 31, h = lane >> 5;
