@@ -39,14 +39,14 @@ __device__ __forceinline__ void load8<float>(__amdgpu_buffer_rsrc_t rs, uint32_t
 // Wg (E * d * 4 bytes, from L2) once, so two token tiles share each of its fragments.
 // JIT: gate jitter on (a separate instance keeps the plain one lean).  Its groups are four blocks, not eight: eight blocks of
 // noise need 251 registers in bf16 and 173 in fp32, two waves per SIMD, and a wave draws all of a group's noise also for
-// blocks that it has not got.  Four fit in 128, four waves per SIMD.  In us, two waves and eight blocks against this: fp32
-// T = 32768, d = 1024 50 and 40, T = 65536, d = 64 50 and 22; bf16 T = 65536, d = 2048 165 and 140, T = 8192, d = 768 12.4 and 11.4;
-// the slowest against it, bf16 T = 8192, d = 4096, 40.2 and 41.1.
-template <typename T, int NB, bool JIT, int TT>
-__global__ __launch_bounds__(64 * GLM_KSPLIT, NB == 1 ? 4 : 2) void gate_logits_kernel(
+// blocks that it has not got.  Four fit in 128, four waves per SIMD.  In us, eight blocks against four: fp32
+// T = 32768, d = 1024 50 and 39, T = 65536, d = 64 50 and 22; bf16 T = 65536, d = 2048 165 and 140.  EIGHT: eight blocks all
+// the same, where the launch rule below says so.
+template <typename T, int NB, bool JIT, int TT, bool EIGHT = !JIT>
+__global__ __launch_bounds__(64 * GLM_KSPLIT, NB == 1 && (EIGHT != JIT) ? 4 : 2) void gate_logits_kernel(
     int Tn, int d, int E, const T* __restrict__ x, const float* __restrict__ Wg,
     const float* __restrict__ bias, float* __restrict__ logits, float jitter_eps, uint64_t seed) {
-    constexpr int GRP = NB <= 2 && TT == 1 && !JIT ? 8 : 4;   // 16-deep blocks whose loads are in flight together
+    constexpr int GRP = NB <= 2 && TT == 1 && EIGHT ? 8 : 4;   // 16-deep blocks whose loads are in flight together
     __shared__ float red[GLM_KSPLIT][32][33];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 31, h = lane >> 5;
@@ -391,6 +391,13 @@ static bool launch_gate_logits_lds(const moe_shape* s, const void* x, const floa
 // (d = 1024); T = 16384, d = 1024 15.7 against 14.2.  Four tiles: slower.
 static bool two_token_tiles(const moe_shape* s) { return s->d_model <= 512 || ceil_div(s->T, 32) > 256; }
 
+// Up to 32 experts, bf16, with jitter: eight blocks in flight instead of four where a wave has more than four (512
+// columns) and the chip holds no second workgroup per compute unit that four blocks would leave room for.  With x from
+// memory, E = 16, eight against four: T = 8192 12.0 and 12.7 us at d = 768, 43.5 and 45.3 at d = 4096, 11.7 and 7.8 at d = 512;
+// T = 4096, d = 768 12.0 and 12.2; T = 10000, d = 1024 23.6 and 20.7.  fp32: four are the faster ones (T = 8192, d = 2048
+// 29.2 and 25.3).
+static bool eight_jitter_blocks(const moe_shape* s) { return s->d_model > 512 && ceil_div(s->T, 32) <= 256; }
+
 // measurement aid: 32-token tiles per workgroup of the gate projection without jitter, where the rule above decides
 extern "C" int moe_gate_logits_token_tiles(const moe_shape* shape) {
     const int rc = shape_status(shape);
@@ -413,10 +420,16 @@ static bool launch_gate_logits(const moe_shape* s, const void* x, const float* W
         }
     }
     // two token tiles per workgroup on the bf16 matrix path with more than 32 experts
-#define GLM(NB, JIT, TT) gate_logits_kernel<T, NB, JIT, TT><<<ceil_div(s->T, 32 * TT), 64 * GLM_KSPLIT, 0, st>>>( \
+#define GLM(NB, JIT, TT, ...) gate_logits_kernel<T, NB, JIT, TT, ##__VA_ARGS__><<<ceil_div(s->T, 32 * TT), 64 * GLM_KSPLIT, 0, st>>>( \
     s->T, s->d_model, s->E, (const T*)x, Wg, bias, logits, eps, seed)
     constexpr int TT2 = sizeof(T) == 2 ? 2 : 1;
     if (eps != 0.0f) {
+        if constexpr (sizeof(T) == 2) {
+            if (s->E <= 32 && eight_jitter_blocks(s)) {
+                GLM(1, true, 1, true);
+                return true;
+            }
+        }
         if (s->E <= 32) GLM(1, true, 1); else if (s->E <= 64) GLM(2, true, 1);
         else if (s->E <= 128) GLM(4, true, 1); else GLM(8, true, 1);
     } else {

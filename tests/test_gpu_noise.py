@@ -116,3 +116,24 @@ def test_full_size_cfg3_jittered_projection_and_dropout_forward():
         assert G.rel_l2(G.host(h[e, :n])[:, cols], O.act(Z, w.act) * sc) <= G.TOL[w.dtype]
         assert G.rel_l2(G.host(a[e, :n])[:, cols], O.act_grad(Z, w.act) * sc) <= G.TOL[w.dtype]
         assert np.array_equal(G.host(a[e, :n])[:, cols] != 0, sc > 0)
+
+
+@pytest.mark.parametrize("T,d,E,dtype", [
+    (300, 776, 5, I.BF16),          # eight blocks at a time, one of them without data, the last half empty
+    (33, 2056, 32, I.BF16),         # three groups of eight
+    (300, 512, 5, I.BF16),          # four at a time
+    (8200, 520, 3, I.BF16),         # four: more than one workgroup per compute unit
+    (300, 776, 5, I.F32), (33, 2056, 33, I.F32), (70, 136, 64, I.BF16), (70, 776, 100, I.BF16)])
+def test_jittered_projection_in_groups_of_blocks(T, d, E, dtype):
+    rng = np.random.default_rng(T + d)
+    x = rng.standard_normal((T, d)).astype(np.float32)
+    data = {"x": I.round_to_bf16(x) if dtype == I.BF16 else x, "Wg": rng.standard_normal((d, E)).astype(np.float32),
+            "bias": rng.standard_normal(E).astype(np.float32)}
+    lg = torch.full((T, E), float("nan"), device="cuda")
+    print(f"[gpu] jittered projection T={T} d={d} E={E} dtype={dtype}", flush=True)
+    B.moe_gate_logits_jitter(B.make_shape(T, d, 8, E, 1, 4, dtype, I.GELU), G.to_dev(data["x"], dtype), G.to_dev(data["Wg"], I.F32),
+                             G.to_dev(data["bias"], I.F32), 0.05, SEED, lg)
+    torch.cuda.synchronize()
+    ref, _ = G.oracle_logits(data, 0.05, SEED)
+    assert G.rel_l2(G.host(lg), ref) <= 1e-5        # fp32 sums of up to 2056 products
+    G.assert_rows("logits", G.host(lg), ref, 1e-5)
