@@ -82,7 +82,7 @@ struct GemmArgs {
     // workgroups from direct_first on, direct_count tiles in all (0: by the experts' row counts); t / d is the upper half of t * inv
     int direct_first, direct_count;
     uint32_t inv_expert, inv_m;
-    int lead;         // second product of a launch: its tiles that take as long as one of the first product's (TileWalk::follow)
+    int lead;         // second product of a launch: what a tile of the first one lasts, in reduction entries (TileWalk::follow)
     // expert dropout in the activation epilogue (drop_thr = 0: off): an element is dropped when its
     // noise word < drop_thr, kept ones are scaled by drop_scale = 1 / (1 - p)
     uint32_t drop_thr;
@@ -353,6 +353,17 @@ __device__ __forceinline__ int wave_scan(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);    // row_bcast 31: the lower half into the upper
     return v;
 }
+// the largest value of a wave's lanes (0 or more)
+__device__ __forceinline__ int wave_max_scan(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+#define TILE_EPILOGUE 300               // a tile's time: its reduction, and about this many entries' worth of epilogue
 #define WALK_BAND 4                     // row tiles per band of the walk inside an expert
 #define WALK_CNT 260                    // the experts' row counts follow the 257 running tile counts
 #define WALK_BYTES ((WALK_CNT + 256) * 4)
@@ -422,19 +433,24 @@ struct TileWalk {
         tp = reinterpret_cast<const int*>(lds);
         t_end = __builtin_amdgcn_readfirstlane(tp[256]);
         step = u.step;
-        follow(u.total, p.lead);
+        int most = 0;
+        for (int c = 0; c < 256; c += 64) most = max(most, tp[WALK_CNT + c + (threadIdx.x & 63)]);
+        follow(u.total, p.lead, wave_max_scan(most));
     }
     // The second product's tiles (t_end of them), after `total` of the first were dealt one by one.  Workgroups that got
-    // none in the first product's last round take `lead` rounds of the second's before all take turns again: as many as
-    // such a tile lasts, so that a long one (thousands of reduction entries in dxd) does not bring its workgroup a full
-    // share of the others on top.  dxd with dW1 for 7 experts of 470 rows, d = 1720, f = 5520: 258 -> 219 us; 11 of 171,
-    // d = 1560, f = 5168: 259 -> 226; 512 tokens on 8 experts, d = 512, f = 2048 (64 x 64): 24.5 -> 20.2.
-    __device__ __forceinline__ void follow(int total, int lead) {
-        const int late = total - quotient(total, step) * step, at = place();
+    // none in the first product's last round take `rounds` of the second's before all take turns again: as many as such a
+    // tile lasts, so that a long one (thousands of reduction entries in dxd) does not bring its workgroup a full share of
+    // the others on top.  dxd with dW1 for 7 experts of 470 rows, d = 1720, f = 5520: 258 -> 219 us; 11 of 171,
+    // d = 1560, f = 5168: 259 -> 226; 512 tokens on 8 experts, d = 512, f = 2048 (64 x 64): 24.5 -> 20.2.  Counted by the
+    // expert with the most rows (`most`: the longest tiles of the second product): by the rows to be expected, a hot expert's
+    // were dealt two and three to a workgroup (11 experts, 14288 rows, Zipf gate, d = 1920, f = 2264: 631 us dealt evenly, 667).
+    __device__ __forceinline__ void follow(int total, int lead, int most) {
+        const int late = total - quotient(total, step) * step, at = place(), tile = most + TILE_EPILOGUE;
+        const int rounds = quotient(lead + tile - 1, tile);
         rest = step - late;
-        ahead = late > 0 && at >= late ? lead : 0;
+        ahead = late > 0 && at >= late ? rounds : 0;
         // one tile every `rest`, then one every `step`: the step between the two is a whole one
-        t = ahead > 0 ? at - late - rest : (late > 0 ? lead * rest : 0) + at - step;
+        t = ahead > 0 ? at - late - rest : (late > 0 ? rounds * rest : 0) + at - step;
     }
     __device__ __forceinline__ void count(const GemmArgs& p) {
         in_regs = true;
@@ -458,7 +474,7 @@ struct TileWalk {
             t = (j >= 0 && j < S ? xcd * S + j : t_end) - step;
         } else {
             step = 8 * min(G, (t_end + other + 7) >> 3);
-            if (second) follow(other, p.lead); else t = place() - step;
+            if (second) follow(other, p.lead, wave_max_scan(rn)); else t = place() - step;
         }
     }
     // One tile per workgroup, as set_direct() numbered them: nothing waits for the expert's row count but what needs it (a
@@ -1918,8 +1934,7 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     q.B = dyd; q.ldb = d; q.strideB = (long long)C * d;
     q.out0 = dW2; q.ldo = d; q.strideO = (long long)f * d;
     q.M = f; q.N = d; q.K = C;
-    // a tile's time: its reduction, and about 300 entries' worth of epilogue
-    q.lead = ceil_div(d + 300, rows + 300);
+    q.lead = d + TILE_EPILOGUE;
     if (!launch_gemm_pair<T, true, true, EPI_MUL, false, false, EPI_F32>(p, q, rows, E, st)) return false;
     // dxd = dz W1^T:  B(r = n in d, k in f) = W1[n*f + k]
     p.A = dz; p.lda = f; p.strideA = (long long)C * f;
@@ -1931,7 +1946,7 @@ static bool ffn_bwd(const moe_shape* s, const void* dyd, const void* xd, const v
     q.B = dz; q.ldb = f; q.strideB = (long long)C * f;
     q.out0 = dW1; q.ldo = f; q.strideO = (long long)d * f;
     q.M = d; q.N = f; q.K = C;
-    q.lead = ceil_div(f + 300, rows + 300);
+    q.lead = f + TILE_EPILOGUE;
     return launch_gemm_pair<T, true, true, EPI_STORE, false, false, EPI_F32>(p, q, rows, E, st);
 }
 
