@@ -14,8 +14,9 @@
 // either k-contiguous in memory (KC) or r-contiguous (!KC); no transposed copy
 // of any tensor is ever materialised.
 //
-// Two kernels: a large-tile one for bf16 (below) and one with smaller tiles for everything
-// else (its own comment says what for); launch_gemm chooses by the number of tiles.
+// Three kernels: a large-tile one for bf16 (below), one with smaller tiles for everything
+// else and one for fp32's smallest products (their own comments say what for); launch_gemm
+// chooses by the number of tiles.
 //
 // Structure of a large-tile workgroup (8 waves, 2 x 4, two per SIMD; one persistent
 // workgroup per CU):
@@ -23,7 +24,8 @@
 //     tile sequence is dealt block-cyclically, a block of as many consecutive tiles
 //     as an XCD has workgroups going to one XCD (workgroup w runs on XCD w % 8), so
 //     the tiles an XCD works on at one time are neighbours and share operand panels
-//     in its L2, every workgroup gets the same number of tiles up to one, and a
+//     in its L2, every workgroup gets the same number of a product's tiles up to one
+//     (a launch's second product: fewer where the first one's tiles are long), and a
 //     heavily loaded expert is spread over all XCDs.  The slabs of all tiles of a
 //     workgroup form one stream through the LDS ring: the next tile's first slabs
 //     arrive under the current tile's epilogue;
@@ -332,17 +334,6 @@ struct GemmSmem {
     static_assert(BYTES + 4096 <= 160 * 1024, "LDS of one CU (the tile-walk table follows)");
 };
 
-// The walk of one workgroup over its tiles.  Only tiles that hold rows exist:
-// expert e has ceil(n_e / BM) row tiles (all of them if the expert count is the
-// reduction length: an empty expert's weight gradient is still written, as zeros).
-// A table in LDS holds the running number of tiles per expert.  The tile
-// sequence (expert-major) is dealt block-cyclically: with S workgroups per XCD
-// (workgroup w serves XCD w % 8: ids are dealt round-robin to the XCDs), block b
-// of S consecutive tiles goes to XCD b % 8, one tile per workgroup.  The tiles an
-// XCD works on at one time are neighbours and share operand panels in its L2;
-// every workgroup gets the same number of tiles up to one; and the tiles of a
-// heavily loaded expert (long reductions in the weight-gradient GEMMs) are spread
-// over all workgroups instead of piling up on one XCD.
 // inclusive sums over the lanes of a wave, without LDS
 __device__ __forceinline__ int wave_scan(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);     // row_shr 1, 2, 4, 8: inside rows of 16
@@ -363,6 +354,18 @@ __device__ __forceinline__ int wave_max_scan(int v) {
     v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
     return __builtin_amdgcn_readlane(v, 63);
 }
+
+// The walk of one workgroup over its tiles.  Only tiles that hold rows exist:
+// expert e has ceil(n_e / BM) row tiles (all of them if the expert count is the
+// reduction length: an empty expert's weight gradient is still written, as zeros).
+// A table in LDS holds the running number of tiles per expert.  The tile
+// sequence (expert-major) is dealt block-cyclically: with S workgroups per XCD
+// (workgroup w serves XCD w % 8: ids are dealt round-robin to the XCDs), block b
+// of S consecutive tiles goes to XCD b % 8, one tile per workgroup.  The tiles an
+// XCD works on at one time are neighbours and share operand panels in its L2;
+// every workgroup gets the same number of tiles up to one (but for a launch's second
+// product: follow()); and the tiles of a heavily loaded expert (long reductions in the
+// weight-gradient GEMMs) are spread over all workgroups instead of piling up on one XCD.
 #define TILE_EPILOGUE 300               // a tile's time: its reduction, and about this many entries' worth of epilogue
 #define WALK_BAND 4                     // row tiles per band of the walk inside an expert
 #define WALK_CNT 260                    // the experts' row counts follow the 257 running tile counts
@@ -425,9 +428,9 @@ struct TileWalk {
         const int i = (int)(blockIdx.x >> 3);
         return i < step >> 3 ? (int)(blockIdx.x & 7) * (step >> 3) + i : 0x3fffffff;
     }
-    // The walk over the launch's second product goes on where the first one's ended: `u` is that
-    // walk's place after its last next().
-    struct Where { int step, total; };      // of a walk over a first product: the workgroups that take turns, its tiles
+    // The walk over the launch's second product goes on where the first one's ended: it needs the number of workgroups
+    // that take turns and of the first product's tiles.
+    struct Where { int step, total; };
     __device__ __forceinline__ Where where() const { return {step, t_end}; }
     __device__ __forceinline__ void resume(const GemmArgs& p, Where u, const unsigned char* lds) {
         tp = reinterpret_cast<const int*>(lds);
@@ -517,7 +520,7 @@ struct TileWalk {
         m_lim = max(0, min(m_lim, p.M));
         return m0 < m_lim;
     }
-    // a / d for 0 <= a < 2^22: the estimate is at most one off
+    // a / d for a >= 0 and quotients below 2^22: the estimate is at most one off
     __device__ static __forceinline__ int quotient(int a, int d) {
         const int q = __builtin_amdgcn_readfirstlane((int)((float)a * __builtin_amdgcn_rcpf((float)d)));
         const int r = a - q * d;
@@ -1452,9 +1455,10 @@ __global__ __launch_bounds__(256 * KW, (KW * MidSmem<T, BM, BN, KW, NS, A1, B1>:
 // each wave finishes a quarter of the columns.  Every operand element is split by each tile that needs it, so this is
 // for products whose tiles would leave much of the chip idle.  The four launches of 256 tokens, d = 64, f = 256,
 // 4 experts: 7.0, 8.1, 7.7, 9.5 -> 4.8, 5.2, 4.6, 5.8 us; of 777 tokens, d = 136, f = 328, 5 experts, top-2:
-// 12.4, 11.1, 14.3, 12.9 -> 7.4, 6.4, 12.6, 9.0.  Three waves per SIMD: with four (128 registers) 10 - 24 of them spill.
+// 12.4, 11.1, 14.3, 12.9 -> 7.4, 6.4, 12.6, 9.0.  Three waves per SIMD: four of the seven instances then spill 2 - 4
+// registers (12 - 20 bytes a lane) outside of the loop over chunks; with four waves (128 registers) 10 - 24 spill.
 // ---------------------------------------------------------------------------
-enum { THIN = 32, THIN_WAVES = 4, THIN_OCC = 3, THIN_GRID = 8 };      // waves per SIMD; most workgroups per CU of a launch
+enum { THIN = 32, THIN_WAVES = 4, THIN_OCC = 3, THIN_GRID = 8 };      // waves per SIMD = workgroups that a CU holds; most of a launch per CU
 
 template <bool A_KC, bool B_KC, int EPI, int ACT>
 __device__ __forceinline__ typename TileWalk<THIN, THIN>::Where thin_body(const GemmArgs& p, int more, typename TileWalk<THIN, THIN>::Where before) {
@@ -1663,7 +1667,7 @@ static long long all_tiles(const GemmArgs& p) { return (long long)p.E * p.tiles_
 // ones in use would share some of the CUs while the others' idle.  Expert FFN forward, addressed so against walked by the
 // counts, Zipf gate: 8 experts of 117 slots, 304 tiles, 24 us and 19; all tokens on one of 5 experts, 1320 tiles of 32 x 32,
 // h W2 44 us and 30; a fifth of the slots empty, 302 tiles, 16.5 and 12.4.  One expert's rows are known: with none of its
-// tiles empty, as many as run at once (`occ` per CU).  p2: the launch's second product or null.  Returns the workgroups per
+// tiles empty, as many as the launch may have workgroups (`occ` per CU).  p2: the launch's second product or null.  Returns the workgroups per
 // XCD, 0 where the tiles are walked instead.
 static int set_direct(GemmArgs& p, GemmArgs* p2, int rows, int side, int occ) {
     const long long s1 = (all_tiles(p) + 7) / 8, s2 = p2 ? (all_tiles(*p2) + 7) / 8 : 0;
