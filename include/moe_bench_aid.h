@@ -47,8 +47,8 @@ int moe_expert_ffn_tiles(const moe_shape* shape, int32_t* side, int32_t* wave_gr
 int moe_expert_ffn_parts(const moe_shape* shape, int32_t* parts);
 
 /* For the same four launches: 1 where every workgroup takes one tile whose place does not depend on the experts' row
- * counts, 0 where workgroups walk the tiles that the counts leave. */
-int moe_expert_ffn_direct(const moe_shape* shape, int32_t* direct);
+ * counts, 0 where workgroups walk the tiles that the counts leave; and how many workgroups there are. */
+int moe_expert_ffn_direct(const moe_shape* shape, int32_t* direct, int32_t* workgroups);
 
 #ifdef __cplusplus
 }

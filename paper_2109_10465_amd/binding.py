@@ -101,7 +101,7 @@ def lib():
             "moe_gate_logits_token_tiles": [shp],
             "moe_expert_ffn_tiles": [shp, vp, vp],
             "moe_expert_ffn_parts": [shp, vp],
-            "moe_expert_ffn_direct": [shp, vp],
+            "moe_expert_ffn_direct": [shp, vp, vp],
             "moe_combine_gate_bwd_launches": [shp],
             "moe_gate_logits_bwd_chunks": [shp, ctypes.c_float],
             "moe_gate_logits_bwd_launches": [shp, i32, ctypes.c_float],
@@ -306,9 +306,18 @@ def moe_expert_ffn_parts(shape):
 
 def moe_expert_ffn_direct(shape):
     """Of the same four launches: are the tiles found without the experts' row counts."""
-    direct = (ctypes.c_int32 * 4)()
-    _check(lib().moe_expert_ffn_direct(ctypes.byref(shape), direct), "moe_expert_ffn_direct")
-    return [bool(v) for v in direct]
+    return _direct_and_workgroups(shape)[0]
+
+
+def moe_expert_ffn_workgroups(shape):
+    """Of the same four launches: the workgroups."""
+    return _direct_and_workgroups(shape)[1]
+
+
+def _direct_and_workgroups(shape):
+    direct, workgroups = (ctypes.c_int32 * 4)(), (ctypes.c_int32 * 4)()
+    _check(lib().moe_expert_ffn_direct(ctypes.byref(shape), direct, workgroups), "moe_expert_ffn_direct")
+    return [bool(v) for v in direct], list(workgroups)
 
 
 def moe_microbench_mfma_bf16(n_workgroups, iters, random_operands, out, stream=None):

@@ -1646,14 +1646,6 @@ static int gemm_grid(long long tiles) {
     return per_xcd * 8;
 }
 
-static int mid_grid(long long tiles, int occ) {
-    const long long most = (tiles + 7) / 8;
-    long long per_xcd = (long long)num_cus() / 8 * occ;
-    if (per_xcd < 1) per_xcd = 1;
-    if (per_xcd > most) per_xcd = most;
-    return (int)per_xcd * 8;
-}
-
 static void set_tiles(GemmArgs& p, int BM, int BN, int E) {
     p.tiles_m = ceil_div(p.M, BM);
     p.tiles_n = ceil_div(p.N, BN);
@@ -1661,6 +1653,17 @@ static void set_tiles(GemmArgs& p, int BM, int BN, int E) {
     p.xcd_cus = num_cus() / 8;
 }
 static long long all_tiles(const GemmArgs& p) { return (long long)p.E * p.tiles_m * p.tiles_n; }
+
+// smaller tiles: `occ` workgroups per CU.  Of a launch of two products (p2, or null) each has its own eighths of an XCD, as
+// TileWalk::begin() counts them: with one workgroup too few for that the first product's tiles, or the last of the second's,
+// are all one XCD's (fp32, 19 experts of 55 rows, d = 96, f = 384, dxd with dW1, 798 tiles: 800 workgroups 17.2 us, 808 8.2).
+static int mid_grid(const GemmArgs& p, const GemmArgs* p2, int occ) {
+    const long long most = (all_tiles(p) + 7) / 8 + (p2 ? (all_tiles(*p2) + 7) / 8 : 0);
+    long long per_xcd = (long long)num_cus() / 8 * occ;
+    if (per_xcd < 1) per_xcd = 1;
+    if (per_xcd > most) per_xcd = most;
+    return (int)per_xcd * 8;
+}
 
 // One tile per workgroup, addressed without the experts' row counts, where at least four of five of all tiles that there
 // could be are expected to hold rows and each has a CU to itself: an expert's tiles are an XCD's, and with a skewed gate the
@@ -1695,7 +1698,7 @@ static bool launch_mid(GemmArgs p, int rows, int E, hipStream_t st) {
     static unsigned long long opted[2] = {0, 0};
     auto kern = kg ? mid_gemm_kernel<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, true> : mid_gemm_kernel<T, BM, BN, KW, NS, A_KC, B_KC, EPI, ACT, false>;
     if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
-    kern<<<direct ? 8 * direct : mid_grid(all_tiles(p), SM::OCC), SM::NT, smem, st>>>(p);
+    kern<<<direct ? 8 * direct : mid_grid(p, nullptr, SM::OCC), SM::NT, smem, st>>>(p);
     return true;
 }
 
@@ -1710,7 +1713,7 @@ static bool launch_mid_pair(GemmArgs p1, GemmArgs p2, int rows, int E, hipStream
     static unsigned long long opted[2] = {0, 0};
     auto kern = kg ? mid_gemm_pair_kernel<T, BM, BN, KW, NS, A1, B1, EPI1, A2, B2, EPI2, true> : mid_gemm_pair_kernel<T, BM, BN, KW, NS, A1, B1, EPI1, A2, B2, EPI2, false>;
     if (!lds_opt_in((const void*)kern, smem, &opted[kg])) return false;
-    kern<<<direct ? 8 * direct : mid_grid(all_tiles(p1) + all_tiles(p2), SM::OCC), SM::NT, smem, st>>>(p1, p2);
+    kern<<<direct ? 8 * direct : mid_grid(p1, &p2, SM::OCC), SM::NT, smem, st>>>(p1, p2);
     return true;
 }
 
@@ -1719,7 +1722,7 @@ static bool launch_thin(GemmArgs p, int rows, int E, hipStream_t st) {
     set_tiles(p, THIN, THIN, E);
     const int direct = set_direct(p, nullptr, rows, THIN, THIN_GRID);
     const size_t smem = THIN_WAVES * THIN * THIN * 4 + WALK_BYTES;
-    thin_gemm_kernel<A_KC, B_KC, EPI, ACT><<<direct ? 8 * direct : mid_grid(all_tiles(p), THIN_GRID), 64 * THIN_WAVES, smem, st>>>(p);
+    thin_gemm_kernel<A_KC, B_KC, EPI, ACT><<<direct ? 8 * direct : mid_grid(p, nullptr, THIN_GRID), 64 * THIN_WAVES, smem, st>>>(p);
     return true;
 }
 
@@ -1729,7 +1732,7 @@ static bool launch_thin_pair(GemmArgs p1, GemmArgs p2, int rows, int E, hipStrea
     set_tiles(p2, THIN, THIN, E);
     const int direct = set_direct(p1, &p2, rows, THIN, THIN_GRID);
     const size_t smem = THIN_WAVES * THIN * THIN * 4 + WALK_BYTES;
-    thin_gemm_pair_kernel<A1, B1, EPI1, A2, B2, EPI2><<<direct ? 8 * direct : mid_grid(all_tiles(p1) + all_tiles(p2), THIN_GRID), 64 * THIN_WAVES, smem, st>>>(p1, p2);
+    thin_gemm_pair_kernel<A1, B1, EPI1, A2, B2, EPI2><<<direct ? 8 * direct : mid_grid(p1, &p2, THIN_GRID), 64 * THIN_WAVES, smem, st>>>(p1, p2);
     return true;
 }
 
@@ -1972,16 +1975,16 @@ static int four_tiles(const moe_shape* shape, FfnTile (&t)[4]) {
     t[3] = tile_for_pair(f32, false, rows, d, d, f, E);
     return MOE_OK;
 }
-// and: is every tile of the launch found without the experts' row counts
-extern "C" int moe_expert_ffn_direct(const moe_shape* shape, int32_t* direct) {
+// and: is every tile of the launch found without the experts' row counts; its workgroups
+extern "C" int moe_expert_ffn_direct(const moe_shape* shape, int32_t* direct, int32_t* workgroups) {
     FfnTile t[4];
     const int rc = four_tiles(shape, t);
     if (rc) return rc;
-    if (!direct) return MOE_ERR_NULL;
+    if (!direct || !workgroups) return MOE_ERR_NULL;
     const bool f32 = shape->dtype == MOE_F32;
     const int d = shape->d_model, f = shape->d_ff;
     for (int i = 0; i < 4; ++i) {
-        const int side = t[i] == TILE_32 ? THIN : t[i] == TILE_64 ? 64 : 128;
+        const int side = t[i] == TILE_32 ? THIN : t[i] == TILE_64 ? 64 : t[i] == TILE_256 ? BIG_M : 128;
         const int occ = t[i] == TILE_32 ? THIN_GRID
             : t[i] == TILE_64 ? (f32 ? MidSmem<float, 64, 64, 2, 2, true, true>::OCC : MidSmem<bf16_t, 64, 64, 1, 3, true, true>::OCC)
             : t[i] == TILE_128_PAIRED ? MidSmem<float, 128, 128, 2, 2, true, true>::OCC
@@ -1993,7 +1996,10 @@ extern "C" int moe_expert_ffn_direct(const moe_shape* shape, int32_t* direct) {
         q.N = i == 2 ? d : f;
         set_tiles(p, side, side, shape->E);
         set_tiles(q, side, side, shape->E);
-        direct[i] = t[i] != TILE_256 && set_direct(p, i >= 2 ? &q : nullptr, expected_rows(shape), side, occ) > 0;
+        const int per_xcd = t[i] == TILE_256 ? 0 : set_direct(p, i >= 2 ? &q : nullptr, expected_rows(shape), side, occ);
+        direct[i] = per_xcd > 0;
+        workgroups[i] = t[i] == TILE_256 ? gemm_grid(all_tiles(p) + (i >= 2 ? all_tiles(q) : 0))
+            : per_xcd > 0 ? 8 * per_xcd : mid_grid(p, i >= 2 ? &q : nullptr, occ);
     }
     return MOE_OK;
 }

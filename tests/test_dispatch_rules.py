@@ -145,6 +145,22 @@ def test_tiles_found_without_the_counts(T, d, f, E, k, C, dtype, direct):
     assert B.moe_expert_ffn_direct(B.make_shape(T, d, f, E, k, C, dtype, I.GELU)) == direct
 
 
+@pytest.mark.parametrize("T,d,f,E,k,C,dtype", [
+    (521, 96, 384, 19, 2, 55, I.F32),       # dxd with dW1, 114 + 684 tiles of 32 x 32: 800 workgroups 17.2 us, 808 8.2
+    (6044, 88, 88, 5, 1, 1209, I.F32),      # both launches, 570 + 45: 616 16.6, 624 12.9
+    (316, 352, 1408, 4, 2, 198, I.BF16),    # dxd with dW1, 96 + 528 of 64 x 64
+    (1216, 96, 448, 29, 1, 84, I.BF16),
+])
+def test_a_round_of_both_products_has_whole_eighths_of_each(T, d, f, E, k, C, dtype):
+    s = B.make_shape(T, d, f, E, k, C, dtype, I.GELU)
+    up = lambda a, b: -(-a // b)
+    for i, (N, M2, N2) in ((2, (f, f, d)), (3, (d, d, f))):
+        side, groups = B.moe_expert_ffn_tiles(s)[i]
+        first, second = E * up(C, side) * up(N, side), E * up(M2, side) * up(N2, side)
+        most = 32 * (8 if side == 32 else {(I.BF16, 64): 3, (I.BF16, 128): 2, (I.F32, 64): 1, (I.F32, 128): 3 - groups}[dtype, side])
+        assert side < 256 and B.moe_expert_ffn_workgroups(s)[i] == 8 * min(most, up(first, 8) + up(second, 8))
+
+
 @pytest.mark.parametrize("rows,d,f,E,parts", [
     # fp32, few tiles: 32 x 32 in xd W1, h W2, dz with dW2, dxd with dW1
     (64, 64, 256, 4, [True] * 4),               # 5, 5, 5, 6; 64 x 64: 7, 8, 8, 9

@@ -29,21 +29,18 @@ SHAPES = [
     ("f32_32_table", 260,  64,   64, 65, 1,   4, I.F32, (32, 32), (2, 2)),
     ("64_hot",     1936, 384,  816,  16, 1, 968, I.BF16, (64, 64), (1, 2)),       # 2 and 3 by the rows to be expected
 ]
-# workgroups of a kernel that run on a compute unit at once: by element type, tile side and wave groups
-AT_ONCE = {(I.BF16, 64, 1): 3, (I.BF16, 128, 1): 2, (I.BF16, 256, 1): 1, (I.F32, 32, 1): 8, (I.F32, 64, 2): 1,
-           (I.F32, 128, 2): 1, (I.F32, 128, 1): 2}
 
 
 def rounds_first(s, launch, count, cus=256):
     """What the walk makes of these row counts, as the dealing is described beside it."""
-    side, groups = B.moe_expert_ffn_tiles(s)[launch]
+    side, _ = B.moe_expert_ffn_tiles(s)[launch]
     if B.moe_expert_ffn_direct(s)[launch]:
         return 0
     d, f, E = s.d_model, s.d_ff, s.E
     N, L = (f, d) if launch == 2 else (d, f)
     c = lambda x: -(-int(x) // side)
     first, second = sum(c(n) for n in count) * c(N), E * c(f) * c(d)
-    per_xcd = min(cus // 8 * AT_ONCE[s.dtype, side, groups], -(-(E * c(s.capacity) * c(N) + second) // 8))
+    per_xcd = B.moe_expert_ffn_workgroups(s)[launch] // 8
     by_table = E > 64 or side == 256
     if not by_table and -(-first // 8) - (-second // 8) <= (per_xcd if side == 32 else min(per_xcd, cus // 8)):
         return 0
