@@ -79,7 +79,6 @@ struct GemmArgs {
     int M, N, K;      // extents; the one bounded by expert_count is an upper limit
     int var_k;        // 0: rows (M) bounded by expert_count; 1: K bounded by it
     int tiles_m, tiles_n, E;
-    int xcd_cus;      // compute units of an XCD
     // smaller tiles, where each that there could be has a workgroup of its own (set_direct): this product's are an XCD's
     // workgroups from direct_first on, direct_count tiles in all (0: by the experts' row counts); t / d is the upper half of t * inv
     int direct_first, direct_count;
@@ -465,13 +464,15 @@ struct TileWalk {
         t_end = __builtin_amdgcn_readlane(rt, 63);
     }
     // The workgroup's first tile: as start(), but where the tiles of both products of a launch fit in one round, an XCD
-    // has its share of each.  `other` = tiles of the other product, `second`: this is the later one.  64 x 64 and larger
-    // tiles: with a CU for each of them; else the second product's, the longer ones where rows are many, would share CUs
-    // with the first's from the start (15702 rows, Zipf gate, d = f = 256, 274 tiles: 63.9 us, 60.8 one product after the other).
+    // has its share of each.  `other` = tiles of the other product, `second`: this is the later one.  Also where there are
+    // more tiles than CUs: one product after the other, the first one's are some XCDs' alone (13 experts of 62 rows, d = 376,
+    // f = 504, 728 tiles of 64 x 64: both launches 22.1 us, 14.4 side by side; 5 of 232, d = 504, f = 2016 43.9 and 39.0).  Where
+    // the second product's tiles last many times as long and share CUs with the first's, it can cost (15702 rows, Zipf gate,
+    // d = f = 256, 274 tiles: one launch 61 us in a row, 64 side by side).
     __device__ __forceinline__ void begin(const GemmArgs& p, int other, bool second) {
         const int xcd = (int)(blockIdx.x & 7), i = (int)(blockIdx.x >> 3), G = (int)(gridDim.x >> 3);
         const int S = (t_end + 7) >> 3, O = (other + 7) >> 3;
-        if (S + O <= (BM > 32 ? min(G, p.xcd_cus) : G)) {
+        if (S + O <= G) {
             const int j = second ? i - O : i;
             step = 0x3fffffff;
             t = (j >= 0 && j < S ? xcd * S + j : t_end) - step;
@@ -1650,7 +1651,6 @@ static void set_tiles(GemmArgs& p, int BM, int BN, int E) {
     p.tiles_m = ceil_div(p.M, BM);
     p.tiles_n = ceil_div(p.N, BN);
     p.E = E;
-    p.xcd_cus = num_cus() / 8;
 }
 static long long all_tiles(const GemmArgs& p) { return (long long)p.E * p.tiles_m * p.tiles_n; }
 

@@ -16,7 +16,7 @@ SHAPES = [
     ("large",     30000, 256, 1024, 120, 1, 256, I.BF16, (256, 256), (1, 3)),
     ("128_regs",   6400, 136, 1032,  64, 1, 127, I.BF16, (128, 128), (2, 4)),
     ("128_table",  6400, 136, 1032,  70, 1, 127, I.BF16, (128, 128), (2, 4)),
-    ("128_one_round", 16384, 256, 256, 2, 1, 8300, I.BF16, (128, 128), (1, 1)),     # more tiles than CUs, fewer than run at once
+    ("128_one_round", 16384, 256, 256, 2, 1, 8300, I.BF16, (128, 128), (0, 0)),     # more tiles than CUs, fewer than run at once
     ("64",          600, 512, 2048,  10, 1,  60, I.BF16, (128, 64), (3, 7)),
     ("64_table",   1300, 136,  264,  65, 1,  20, I.BF16, (64, 64), (2, 2)),
     ("f32_64",      320, 264,  264,  16, 1,  20, I.F32, (64, 64), (2, 2)),
@@ -31,7 +31,7 @@ SHAPES = [
 ]
 
 
-def rounds_first(s, launch, count, cus=256):
+def rounds_first(s, launch, count):
     """What the walk makes of these row counts, as the dealing is described beside it."""
     side, _ = B.moe_expert_ffn_tiles(s)[launch]
     if B.moe_expert_ffn_direct(s)[launch]:
@@ -42,7 +42,7 @@ def rounds_first(s, launch, count, cus=256):
     first, second = sum(c(n) for n in count) * c(N), E * c(f) * c(d)
     per_xcd = B.moe_expert_ffn_workgroups(s)[launch] // 8
     by_table = E > 64 or side == 256
-    if not by_table and -(-first // 8) - (-second // 8) <= (per_xcd if side == 32 else min(per_xcd, cus // 8)):
+    if not by_table and -(-first // 8) - (-second // 8) <= per_xcd:
         return 0
     step = 8 * min(per_xcd, -(-(first + second) // 8))
     if first % step == 0:
