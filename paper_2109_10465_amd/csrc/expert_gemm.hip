@@ -445,10 +445,13 @@ struct TileWalk {
     // the others on top.  dxd with dW1 for 7 experts of 470 rows, d = 1720, f = 5520: 258 -> 219 us; 11 of 171,
     // d = 1560, f = 5168: 259 -> 226; 512 tokens on 8 experts, d = 512, f = 2048 (64 x 64): 24.5 -> 20.2.  Counted by the
     // expert with the most rows (`most`: the longest tiles of the second product): by the rows to be expected, a hot expert's
-    // were dealt two and three to a workgroup (11 experts, 14288 rows, Zipf gate, d = 1920, f = 2264: 631 us dealt evenly, 667).
+    // were dealt two and three to a workgroup (11 experts, 14288 rows, Zipf gate, d = 1920, f = 2264: 631 us dealt evenly, 667).  The other
+    // experts' are shorter, so an eighth of a tile over a whole number counts as one more (14 experts of 14 rows, one of them
+    // 48, d = 368, f = 1424, 1.92 tiles: backward 85.7 us with two rounds, 81.0 with three; 41 experts, Zipf gate, 250 rows,
+    // d = 664, f = 768 194.9 and 187.3; 29 of 538, d = 304, f = 448 42.0 and 43.6).
     __device__ __forceinline__ void follow(int total, int lead, int most) {
         const int late = total - quotient(total, step) * step, at = place(), tile = most + TILE_EPILOGUE;
-        const int rounds = quotient(lead + tile - 1, tile);
+        const int rounds = quotient(lead + tile + (tile >> 3) - 1, tile);
         rest = step - late;
         ahead = late > 0 && at >= late ? rounds : 0;
         // one tile every `rest`, then one every `step`: the step between the two is a whole one

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 # the second's before all take turns; 0 where no such turns are taken (one round holds all), 1 = evenly dealt
 # name            T      d     f    E  k  capacity dtype   tile side of dz with dW2, of dxd with dW1   rounds
 SHAPES = [
-    ("large",     30000, 256, 1024, 120, 1, 256, I.BF16, (256, 256), (1, 3)),
+    ("large",     30000, 256, 1024, 120, 1, 256, I.BF16, (256, 256), (2, 3)),
     ("128_regs",   6400, 136, 1032,  64, 1, 127, I.BF16, (128, 128), (2, 4)),
     ("128_table",  6400, 136, 1032,  70, 1, 127, I.BF16, (128, 128), (2, 4)),
     ("128_one_round", 16384, 256, 256, 2, 1, 8300, I.BF16, (128, 128), (0, 0)),     # more tiles than CUs, fewer than run at once
@@ -21,13 +21,14 @@ SHAPES = [
     ("64_table",   1300, 136,  264,  65, 1,  20, I.BF16, (64, 64), (2, 2)),
     ("f32_64",      320, 264,  264,  16, 1,  20, I.F32, (64, 64), (2, 2)),
     ("f32_64_32",  8000, 120,  232,   5, 1, 1600, I.F32, (64, 32), (1, 0)),
-    ("f32_128_64", 1500, 136, 1032,   8, 2, 380, I.F32, (128, 64), (1, 2)),
+    ("f32_128_64", 1500, 136, 1032,   8, 2, 380, I.F32, (128, 64), (1, 3)),
     ("f32_128_groups", 320, 136, 1032, 16, 1, 20, I.F32, (128, 128), (2, 5)),
     ("f32_128_groups_table", 1300, 136, 136, 65, 1, 20, I.F32, (128, 128), (2, 2)),
     ("f32_128",     480, 136, 2056,  24, 1,  20, I.F32, (128, 128), (2, 8)),
     ("f32_128_table", 1400, 136, 520, 70, 1, 20, I.F32, (128, 128), (2, 3)),
     ("f32_32_table", 260,  64,   64, 65, 1,   4, I.F32, (32, 32), (2, 2)),
-    ("64_hot",     1936, 384,  816,  16, 1, 968, I.BF16, (64, 64), (1, 2)),       # 2 and 3 by the rows to be expected
+    ("64_hot",     1936, 384,  816,  16, 1, 968, I.BF16, (64, 64), (2, 2)),       # 2 and 3 by the rows to be expected
+    ("f32_128_eighth", 330, 368, 1424, 14, 1, 48, I.F32, (128, 128), (3, 6)),     # 1.92 and 4.95 tiles
 ]
 
 
@@ -47,7 +48,8 @@ def rounds_first(s, launch, count):
     step = 8 * min(per_xcd, -(-(first + second) // 8))
     if first % step == 0:
         return 1
-    return -(-(L + 300) // (int(max(count)) + 300))         # the expert with the most rows has the longest tiles
+    tile = int(max(count)) + 300            # the expert with the most rows has the longest tiles: an eighth more counts
+    return (L + 300 + tile + tile // 8 - 1) // tile
 
 
 @pytest.mark.parametrize("name,T,d,f,E,k,C,dtype,sides,rounds", SHAPES, ids=[s[0] for s in SHAPES])
